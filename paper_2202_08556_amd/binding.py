@@ -16,6 +16,10 @@ _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdaspmm.
 if not os.path.exists(_LIB_PATH):
     raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2202_08556_amd.build`")
 _lib = ctypes.CDLL(_LIB_PATH)
+try:
+    from . import _native    # the hot calls without ctypes, on the same libdaspmm.so
+except ImportError as _exc:
+    raise ImportError(f"{__package__}._native: {_exc}: build it with `python -m paper_2202_08556_amd.build`") from _exc
 
 DA_OK, DA_ERR_INVALID_ARG, DA_ERR_BAD_ALGO, DA_ERR_UNSUPPORTED, DA_ERR_HIP = range(5)
 (DA_RB_RM_SR, DA_RB_RM_PR, DA_RB_CM_SR, DA_RB_CM_PR,
@@ -98,11 +102,8 @@ def da_spmm_status(m, k, N, rowptr, colind, vals, B, C, algo, stream=None) -> in
                             _ptr(B), _ptr(C), int(algo), _stream(stream)))
 
 
-def da_spmm(m, k, N, rowptr, colind, vals, B, C, algo, stream=None) -> None:
-    """C = A.B on the device; arguments as in include/da_spmm.h (torch CUDA tensors or addresses)."""
-    st = da_spmm_status(m, k, N, rowptr, colind, vals, B, C, algo, stream)
-    if st != DA_OK:
-        raise DaSpmmError(st, da_spmm_last_error())
+_native.setup(DaSpmmError, torch.cuda.current_stream)
+da_spmm = _native.da_spmm
 
 
 def da_spmm_ex_status(m, k, N, rowptr, colind, vals, B, ldb, layout_b, C, ldc, layout_c, algo, stream=None) -> int:
@@ -110,11 +111,7 @@ def da_spmm_ex_status(m, k, N, rowptr, colind, vals, B, ldb, layout_b, C, ldc, l
                                int(layout_b), _ptr(C), int(ldc), int(layout_c), int(algo), _stream(stream)))
 
 
-def da_spmm_ex(m, k, N, rowptr, colind, vals, B, ldb, layout_b, C, ldc, layout_c, algo, stream=None) -> None:
-    """C = A.B with explicit storage order (DA_ROW_MAJOR / DA_COL_MAJOR) and leading dimensions."""
-    st = da_spmm_ex_status(m, k, N, rowptr, colind, vals, B, ldb, layout_b, C, ldc, layout_c, algo, stream)
-    if st != DA_OK:
-        raise DaSpmmError(st, da_spmm_last_error())
+da_spmm_ex = _native.da_spmm_ex
 
 
 class PreparedSpmm:
@@ -183,14 +180,7 @@ def da_csr_transpose_status(m, k, nnz, rowptr, colind, vals, t_rowptr, t_colind,
                                      int(workspace_bytes), _stream(stream)))
 
 
-def da_csr_transpose(m, k, nnz, rowptr, colind, vals, t_rowptr, t_colind, t_vals, workspace, workspace_bytes,
-                     stream=None) -> None:
-    """CSR arrays of A^T on the device; arguments as in include/da_spmm.h."""
-    st = da_csr_transpose_status(m, k, nnz, rowptr, colind, vals, t_rowptr, t_colind, t_vals, workspace,
-                                 workspace_bytes, stream)
-    if st != DA_OK:
-        raise DaSpmmError(st, da_spmm_last_error())
-
+da_csr_transpose = _native.da_csr_transpose
 
 DA_NOALLOC_SCRATCH_BYTES = 32 << 20
 

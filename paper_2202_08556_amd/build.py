@@ -1,4 +1,5 @@
-"""Compile libdaspmm.so (HIP kernels + C ABI) for gfx950, in-tree, with hipcc."""
+"""Compile libdaspmm.so (HIP kernels + C ABI) for gfx950 and the Python module _native on top of it, in-tree,
+with hipcc."""
 from __future__ import annotations
 
 import os
@@ -37,7 +38,34 @@ def build_hip(verbose: bool = False) -> str:
     if verbose and out.strip():
         print(out)
     os.replace(tmp, LIB)
+    build_native(verbose)
     return LIB
+
+
+NATIVE = os.path.join(PKG, "_native.so")
+
+
+def build_native(verbose: bool = False) -> str:
+    """The Python module _native (host code only), linked against libdaspmm.so beside it and the
+    torch libraries of the running interpreter."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(os.path.abspath(torch.__file__))
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = [hipcc(), "--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1",
+           "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
+           "-I" + os.path.join(tdir, "include"), "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           os.path.join(CSRC, "native.cpp"), "-o", tmp,
+           "-L" + PKG, "-ldaspmm", "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(tdir, "lib")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("hipcc failed:\n" + res.stdout)
+    os.replace(tmp, NATIVE)
+    return NATIVE
 
 
 CALIB = os.path.join(PKG, "calib_copy")
