@@ -408,6 +408,48 @@ TransposePlan plan_transpose(int64_t k, int64_t nnz) {
     return t;
 }
 
+// Plan of the transpose in one or two passes (transpose_* kernels), for k <= 2^20 when the row number
+// and the second digit fit one word.  Tiles of 1024 entries while that leaves a chip of 256 CUs less than
+// full, of 2048 beyond (1024 ... 4096 measured within 7 %).  Groups of up to 8 tiles, at least 512 of them where
+// there are as many tiles.
+struct TransposeFast {
+    bool usable;
+    int passes, bits[2], row_bits, tile, ntiles, group, ngroups;
+    size_t off_mid, off_vals, off_hist, off_group, off_total, off_rows, bytes;
+};
+
+int bits_for(int64_t values) {                            // smallest b with 2^b >= values, at least 1
+    int b = 1;
+    while (b < 31 && (int64_t(1) << b) < values) ++b;
+    return b;
+}
+
+TransposeFast plan_transpose_fast(int64_t m, int64_t k, int64_t nnz) {
+    TransposeFast t{};
+    const int bits = bits_for(k);
+    t.row_bits = bits_for(m);
+    t.passes = bits <= kDigitBitsMax ? 1 : 2;
+    t.bits[0] = t.passes == 1 ? bits : (bits + 1) / 2;
+    t.bits[1] = t.passes == 1 ? 0 : bits - t.bits[0];
+    t.usable = t.bits[0] <= kDigitBitsMax && t.row_bits + t.bits[1] <= 32;
+    for (int i = 0; i < t.passes; ++i) if (t.bits[i] < 4) t.bits[i] = 4;     // transpose_scan_kernel takes 16 digits a block
+    t.tile = kSortBlock * (nnz < 1024 * 1024 ? 4 : 8);
+    t.ntiles = (int)((nnz + t.tile - 1) / t.tile);
+    t.group = t.ntiles <= 512 ? 1 : (t.ntiles >= kGroupMax * 512 ? kGroupMax : t.ntiles / 512);
+    t.ngroups = (t.ntiles + t.group - 1) / t.group;
+    size_t off = 0;
+    const size_t per = align256((size_t)nnz * 4);
+    const int widest = t.bits[0] > t.bits[1] ? t.bits[0] : t.bits[1];
+    t.off_mid = off; off += per;
+    t.off_vals = off; off += per;
+    t.off_hist = off; off += align256(((size_t)t.ntiles << widest) * sizeof(int));
+    t.off_group = off; off += align256(((size_t)t.ngroups << widest) * sizeof(int));
+    t.off_total = off; off += align256(2 * kDigitBinsMax * sizeof(int));
+    t.off_rows = off; off += align256(((size_t)t.ntiles + 1) * sizeof(int));
+    t.bytes = off;
+    return t;
+}
+
 // One schedule to build: da_eb_schedule's outputs, and optionally the row of every chunk's first
 // entry in schedule order (first_rows[u] belongs to chunk order[u]) and indexed by chunk number
 // (rows_by_unit); all device pointers, the last three may be null
@@ -423,6 +465,12 @@ int check_transpose_args(int64_t m, int64_t k, int64_t nnz, const int32_t* rowpt
 int enqueue_transpose(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
                       const float* vals, int32_t* t_rowptr, int32_t* t_colind, float* t_vals,
                       void* workspace, size_t workspace_bytes, void* stream);
+
+// The size every transpose asks for, whichever way it then goes
+size_t transpose_workspace_bytes(int64_t m, int64_t k, int64_t nnz) {
+    const size_t a = plan_transpose(k, nnz).bytes, b = plan_transpose_fast(m, k, nnz).bytes;
+    return a > b ? a : b;
+}
 
 // Scratch memory of the entry point that allocates nothing (da_csr_transpose_noalloc): a static
 // device array, one copy per GPU, held from the moment the library is loaded on that GPU until the
@@ -597,7 +645,7 @@ int da_csr_transpose_workspace(int64_t m, int64_t k, int64_t nnz, size_t* bytes)
     if (m < 0 || k < 0 || nnz < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
     if (m > 0x7ffffffeLL || k > 0x7ffffffeLL || nnz > 0x7fffffffLL)
         return fail(DA_ERR_INVALID_ARG, "size beyond the int32 index range%s");
-    *bytes = plan_transpose(k, nnz).bytes;
+    *bytes = transpose_workspace_bytes(m, k, nnz);
     return DA_OK;
 }
 
@@ -619,7 +667,7 @@ int da_csr_transpose_noalloc(int64_t m, int64_t k, int64_t nnz, const int32_t* r
 {
     const int st = check_transpose_args(m, k, nnz, rowptr, colind, vals, t_rowptr, t_colind, t_vals);
     if (st != DA_OK) return st;
-    if (plan_transpose(k, nnz).bytes > kScratchBytes)
+    if (transpose_workspace_bytes(m, k, nnz) > kScratchBytes)
         return fail(DA_ERR_UNSUPPORTED,
                     "da_csr_transpose_noalloc: the sort needs more than the library's 32 MiB static scratch "
                     "(about 24 bytes per stored entry); use da_csr_transpose with a workspace%s");
@@ -646,18 +694,70 @@ int check_transpose_args(int64_t m, int64_t k, int64_t nnz, const int32_t* rowpt
     return DA_OK;
 }
 
+template <int ROUNDS>
+void launch_transpose_passes(const TransposeFast& t, TransposePass P, int64_t k, int32_t* t_rowptr, float* t_vals,
+                             char* ws, hipStream_t s) {
+    const dim3 grid((unsigned)(8 * ((t.ntiles + 7) / 8))), block(kSortBlock);
+    unsigned* mid = reinterpret_cast<unsigned*>(ws + t.off_mid);
+    float* mid_vals = reinterpret_cast<float*>(ws + t.off_vals);
+    int* totals = reinterpret_cast<int*>(ws + t.off_total);
+    P.hist = reinterpret_cast<int*>(ws + t.off_hist);
+    P.tile_row = reinterpret_cast<int*>(ws + t.off_rows);
+    P.group_hist = reinterpret_cast<int*>(ws + t.off_group);
+    P.ntiles = t.ntiles; P.group = t.group;
+    const float* vals = P.vals_in;
+    for (int p = 0; p < t.passes; ++p) {
+        const bool last = p == t.passes - 1;
+        const int bins = 1 << t.bits[p];
+        const size_t lds = transpose_scatter_lds<ROUNDS>(bins);
+        P.bits = t.bits[p];
+        P.total = totals + p * kDigitBinsMax;
+        P.mid_in = mid;
+        P.mid_out = mid;
+        P.vals_in = p == 0 ? vals : mid_vals;
+        P.vals_out = last ? t_vals : mid_vals;
+        if (p == 0) hipLaunchKernelGGL((transpose_count_kernel<ROUNDS, true>), dim3((unsigned)t.ngroups), dim3(1024), 0, s, P);
+        else hipLaunchKernelGGL((transpose_count_kernel<ROUNDS, false>), dim3((unsigned)t.ngroups), dim3(1024), 0, s, P);
+        hipLaunchKernelGGL(transpose_scan_kernel, dim3((unsigned)(bins / kScanDigits)), dim3(1024), 0, s, P.group_hist, t.ngroups, bins,
+                           P.total);
+        if (p == 0 && last) hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, true, true>), grid, block, lds, s, P);
+        else if (p == 0) hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, true, false>), grid, block, lds, s, P);
+        else hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, false, true>), grid, block, lds, s, P);
+    }
+    if (t.passes == 1)
+        hipLaunchKernelGGL(transpose_rowptr_one_kernel, dim3(1), dim3(256), 0, s, totals, 1 << t.bits[0], P.n, (int)k, t_rowptr);
+    else
+        hipLaunchKernelGGL((transpose_rowptr_kernel<kSortBlock * ROUNDS>), dim3(1u << t.bits[0]), dim3(256), 0, s, mid, P.n, (int)k, t.row_bits,
+                           t.bits[0], t.bits[1], totals, P.hist, P.group_hist, totals + kDigitBinsMax, t.ntiles, t.group, t_rowptr);
+}
+
 // The radix passes of the transpose on the given scratch memory.  Every part of the scratch that
-// a kernel reads was written earlier in the same call (keys / rows / values of the ping-pong, the
-// whole histogram, every chunk sum), so stale contents of a reused buffer are never seen.
+// a kernel reads was written earlier in the same call (entries between the passes, the whole
+// histogram, totals or chunk sums), so stale contents of a reused buffer are never seen.
 int enqueue_transpose(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, const int32_t* colind,
                       const float* vals, int32_t* t_rowptr, int32_t* t_colind, float* t_vals,
                       void* workspace, size_t workspace_bytes, void* stream)
 {
-    const TransposePlan t = plan_transpose(k, nnz);
-    if (nnz > 0 && (!workspace || workspace_bytes < t.bytes))
+    if (nnz > 0 && (!workspace || workspace_bytes < transpose_workspace_bytes(m, k, nnz)))
         return fail(DA_ERR_INVALID_ARG, "workspace missing or smaller than da_csr_transpose_workspace reports%s");
     if (nnz > 0 && reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
         return fail(DA_ERR_INVALID_ARG, "workspace is not 256-byte aligned%s");
+    if (nnz > 0) {
+        const TransposeFast f = plan_transpose_fast(m, k, nnz);
+        if (f.usable) {
+            TransposePass P{};
+            P.colind = colind; P.rowptr = rowptr; P.vals_in = vals; P.t_colind = t_colind;
+            P.m = (int)m; P.n = (int)nnz; P.row_bits = f.row_bits;
+            char* ws = static_cast<char*>(workspace);
+            hipStream_t s = (hipStream_t)stream;
+            if (f.tile == kSortBlock * 4) launch_transpose_passes<4>(f, P, k, t_rowptr, t_vals, ws, s);
+            else launch_transpose_passes<8>(f, P, k, t_rowptr, t_vals, ws, s);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return hip_fail(e, "da_csr_transpose launch");
+            return DA_OK;
+        }
+    }
+    const TransposePlan t = plan_transpose(k, nnz);
     hipStream_t s = (hipStream_t)stream;
     const int n = (int)nnz;
     char* ws = static_cast<char*>(workspace);

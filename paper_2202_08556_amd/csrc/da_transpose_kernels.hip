@@ -4,21 +4,31 @@
 //
 // Row j of A^T lists the stored entries of column j of A with ascending row numbers.  CSR stores
 // entries row after row, so a STABLE sort of the entries by column index is exactly that order,
-// and it is deterministic (no atomic cursors on global memory).  The sort is a least-significant-
-// digit radix sort of (column, row, value) triples with digits of at most 8 bits; one pass is
-//     radix_count_kernel    per-block digit histogram                       -> hist[digit][block]
-//     scan_*_kernel         exclusive prefix sum over hist in that order    (three small kernels)
-//     radix_scatter_kernel  stable scatter: position = scanned hist entry + number of earlier
-//                           entries of the block with the same digit
-// Inside a block each wave owns a contiguous run of entries and walks it 64 entries at a time; the
-// lanes that hold the same digit find each other with one ballot per digit bit, so the rank of an
-// entry among its peers is a population count and only one lane per distinct digit touches the
-// wave's running counter in LDS.  The block first orders its tile by digit in LDS and then copies
-// it out, so that entries with the same digit leave as contiguous runs (coalesced stores) rather
-// than as single 4-byte stores.
-// The first pass reads colind / vals and derives the row number of every entry from rowptr; the
-// last pass writes straight into the arrays of A^T (row numbers become its column indices) plus
-// the sorted keys, from which the new row pointers follow by one lower-bound search per row.
+// and it is deterministic (no atomic cursors on global memory).
+//
+// Two radix sorts live here.
+//
+// (1) The transpose proper (transpose_* kernels): least-significant-digit radix sort in one or two
+//     passes of at most 10 bits, for k <= 2^20.  What bounds it is memory traffic, so it moves as little
+//     as possible: the first pass drops the digit it has sorted by and packs the rest of the column
+//     index with the row number into one word, the second pass unpacks it, so an entry is 8 bytes
+//     between the passes and full column indices are never written.  One pass is
+//         transpose_count_kernel    digit histograms of a group of tiles, as prefixes inside the group
+//         transpose_scan_kernel     exclusive prefix over the groups, per digit, and digit totals
+//         transpose_scatter_kernel  stable placement of a tile
+//     and transpose_rowptr_kernel derives the row pointers of A^T from the histograms: after the first
+//     pass the entries are ordered by the low digit, so row pointer (high, low) is the position at which
+//     the second pass puts the first entry at or behind the start of `low` with digit `high`.
+// (2) A general sort of (key, id, payload) triples with digits of at most 8 bits (radix_* kernels), used
+//     for the EB schedules, and for the transpose when k > 2^20 or when row number and high digit do
+//     not fit one word together.
+//
+// In both, each wave owns a contiguous run of entries and walks it 64 entries at a time; the lanes
+// that hold the same digit find each other with one ballot per digit bit, so the rank of an entry
+// among its peers is a population count and only one lane per distinct digit touches the wave's
+// running counter in LDS.  The block first orders its tile by digit in LDS and then copies it out, so
+// that entries with the same digit leave as contiguous runs (coalesced stores) rather than as single
+// 4-byte stores.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -419,6 +429,423 @@ __global__ __launch_bounds__(kSortBlock) void rowptr_from_sorted_kernel(const in
         if (keys[mid] < c) lo = mid + 1; else hi = mid;
     }
     t_rowptr[c] = lo;
+}
+
+// ------------------------------------------------------------------------------------------
+// the transpose in one or two passes
+// ------------------------------------------------------------------------------------------
+constexpr int kDigitBitsMax = 10;
+constexpr int kDigitBinsMax = 1 << kDigitBitsMax;
+constexpr int kGroupMax = 8;                             // tiles counted by one block
+constexpr int kScanDigits = 16;                          // digits per block of transpose_scan_kernel
+
+// One pass.  Entries come from the matrix (colind, vals, row numbers from rowptr) in the first pass and
+// from (mid_in, vals_in) in the second.  mid = row | (column >> low digit's bits) << row_bits.
+struct TransposePass {
+    const int* colind;
+    const int* rowptr;
+    const unsigned* mid_in;
+    const float* vals_in;
+    unsigned* mid_out;
+    int* t_colind;
+    float* vals_out;
+    int* hist;               // [tile][digit]: entries of the digit in the earlier tiles of the group
+    int* group_hist;         // [group][digit]: entries of the digit in the group, then in the groups before it
+    int* total;              // [digit]
+    int* tile_row;           // [tile]: row of the tile's first entry, and behind the last tile the last entry's
+    int m, n, ntiles;
+    int group;               // tiles per group
+    int bits;                // width of this pass's digit
+    int row_bits;
+};
+
+// Tiles are dealt to the XCDs in contiguous groups: the runs that neighbouring tiles write for one
+// digit are neighbours in memory, and the L2 of one XCD merges them into whole lines.
+__device__ __forceinline__ int tile_of_block(int ntiles) {
+    const int per = (ntiles + 7) >> 3;
+    return (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+}
+
+template <bool FIRST>
+__device__ __forceinline__ unsigned pass_digit(unsigned key, const TransposePass& P) {
+    return FIRST ? key & ((1u << P.bits) - 1u) : key >> P.row_bits;
+}
+
+// The row that owns entry q, found by the 64 lanes of a wave together (64 probes per step).
+__device__ __forceinline__ int owner_row_wave(const int* __restrict__ rowptr, int lo, int hi, int q, int lane) {
+    while (lo < hi) {
+        const long len = hi - lo;
+        const int r = lo + (int)((len * (lane + 1)) / 65);
+        const int low = 64 - __popcll(__ballot(rowptr[r + 1] > q));   // probes 0 .. low-1 lie before the owner
+        const int nlo = low == 0 ? lo : lo + (int)((len * low) / 65) + 1;
+        hi = low == 64 ? hi : lo + (int)((len * (low + 1)) / 65);
+        lo = nlo;
+    }
+    return lo;
+}
+
+// cnt[d] += 1 for every valid lane.  The lanes that agree with the first valid one are added at once: the
+// entries of a popular column lie together after the first pass, and 64 additions to one LDS word take
+// 64 turns (count of the second pass 33 -> 18 us on a power-law matrix of 13 M entries).
+__device__ __forceinline__ void count_digit(int* cnt, unsigned d, bool valid) {
+    if (!valid) return;
+    const unsigned d0 = (unsigned)__builtin_amdgcn_readfirstlane((int)d);
+    const unsigned long long same = __ballot(d == d0);
+    const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+    if (d != d0) atomicAdd(&cnt[d], 1);
+    else if (below == 0) atomicAdd(&cnt[d], __popcll(same));
+}
+
+// A block counts the tiles of one group one after another, so that what remains to be scanned is one row
+// of counts per group (one row per tile took as long to scan as the tiles take to count).  All keys of
+// the group are requested before the first one is counted.
+template <int ROUNDS, bool FIRST>
+__global__ __launch_bounds__(1024) void transpose_count_kernel(TransposePass P)
+{
+    constexpr int THREADS = 1024, T = kSortBlock * ROUNDS, PER = T / THREADS;
+    static_assert(PER * THREADS == T && kGroupMax <= THREADS / 64, "whole rounds per tile, one wave per tile's row search");
+    __shared__ int cnt[kDigitBinsMax];
+    const int bins = 1 << P.bits;
+    const int tile0 = blockIdx.x * P.group, tiles = min(P.group, P.ntiles - tile0);
+    const long base = (long)tile0 * T;
+    const int count = (int)min((long)tiles * T, (long)P.n - base);
+    const unsigned* __restrict__ keys = (FIRST ? reinterpret_cast<const unsigned*>(P.colind) : P.mid_in) + base;
+    unsigned key[kGroupMax * PER];
+#pragma unroll
+    for (int r = 0; r < kGroupMax * PER; ++r) {
+        const int e = r * THREADS + (int)threadIdx.x;
+        key[r] = e < count ? keys[e] : 0u;
+    }
+    if ((int)threadIdx.x < bins) cnt[threadIdx.x] = 0;
+    if constexpr (FIRST) {                                // the scatter kernel starts its row walk from here
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        if (w < tiles) {
+            const int tile = tile0 + w;
+            const int r = owner_row_wave(P.rowptr, 0, P.m - 1, (int)((long)tile * T), lane);
+            if (lane == 0) P.tile_row[tile] = r;
+            if (tile == P.ntiles - 1) {
+                const int l = owner_row_wave(P.rowptr, r, P.m - 1, P.n - 1, lane);
+                if (lane == 0) P.tile_row[P.ntiles] = l;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kGroupMax; ++g) {
+        if (g < tiles) {
+            if ((int)threadIdx.x < bins) P.hist[(long)(tile0 + g) * bins + threadIdx.x] = cnt[threadIdx.x];
+            __syncthreads();
+#pragma unroll
+            for (int r = g * PER; r < (g + 1) * PER; ++r)
+                count_digit(cnt, pass_digit<FIRST>(key[r], P), r * THREADS + (int)threadIdx.x < count);
+            __syncthreads();
+        }
+    }
+    if ((int)threadIdx.x < bins) P.group_hist[(long)blockIdx.x * bins + threadIdx.x] = cnt[threadIdx.x];
+}
+
+// Exclusive prefix over the groups for every digit, in place, and the digit totals.  A block owns 16
+// digits (64-byte pieces of the rows) and cuts the groups into 64 stretches, one per thread and digit.
+__global__ __launch_bounds__(1024) void transpose_scan_kernel(int* __restrict__ hist, int rows, int bins, int* __restrict__ total)
+{
+    constexpr int U = 8;
+    __shared__ int part[64][kScanDigits + 1];
+    const int dl = threadIdx.x & (kScanDigits - 1), ch = threadIdx.x / kScanDigits;
+    const int per = (rows + 63) >> 6;
+    const int t0 = min(ch * per, rows), t1 = min(t0 + per, rows);
+    int* __restrict__ h = hist + blockIdx.x * kScanDigits + dl;
+    int sum = 0;
+    for (int t = t0; t < t1; t += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) sum += t + u < t1 ? h[(long)(t + u) * bins] : 0;
+    }
+    part[ch][dl] = sum;
+    __syncthreads();
+    {
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;      // wave w scans the stretches of digit w
+        const int v = part[lane][w];
+        const int inc = wave_inclusive_scan_dpp(v);
+        part[lane][w] = inc - v;
+        if (lane == 63) total[blockIdx.x * kScanDigits + w] = inc;
+    }
+    __syncthreads();
+    int run = part[ch][dl];
+    for (int t = t0; t < t1; t += U) {
+        int v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = t + u < t1 ? h[(long)(t + u) * bins] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t + u < t1) h[(long)(t + u) * bins] = run;
+            run += v[u];
+        }
+    }
+}
+
+// Exclusive prefix sums over 1024 values spread 4 to a thread in order (value i of thread t belongs to
+// index 4 t + i) of a block of 256.  sh: 4 ints.  All threads must call it.
+__device__ __forceinline__ void block_scan_bins(int (&v)[4], int* sh) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { const int x = v[i]; v[i] = sum; sum += x; }
+    const int inc = wave_inclusive_scan_dpp(sum);
+    __syncthreads();
+    if (lane == 63) sh[wave] = inc;
+    __syncthreads();
+    const int s0 = sh[0], s1 = sh[1], s2 = sh[2];
+    const int off = inc - sum + (wave > 0 ? s0 : 0) + (wave > 1 ? s1 : 0) + (wave > 2 ? s2 : 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] += off;
+}
+
+// Values 4 t ... 4 t + 3 of p for thread t, zeros at and behind `bins` (p is read inside its bins only).
+__device__ __forceinline__ void load_bins(const int* __restrict__ p, int bins, int (&v)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int d = (int)threadIdx.x * 4 + i, x = p[min(d, bins - 1)];
+        v[i] = d < bins ? x : 0;
+    }
+}
+
+// Lanes of the wave that hold the same digit of `bits` bits, among the lanes of `valid`.
+__device__ __forceinline__ unsigned long long digit_peers_of(unsigned d, int bits, unsigned long long valid) {
+    unsigned lo = (unsigned)valid, hi = (unsigned)(valid >> 32);
+#pragma unroll
+    for (int b = 0; b < kDigitBitsMax; ++b)
+        if (b < bits) {
+            const int m = (int)(d << (31 - b)) >> 31;                 // all ones when the bit is set
+            const unsigned long long vote = __ballot(m < 0);
+            lo &= ~((unsigned)vote ^ (unsigned)m);
+            hi &= ~((unsigned)(vote >> 32) ^ (unsigned)m);
+        }
+    return (unsigned long long)hi << 32 | lo;
+}
+
+// LDS of a scatter block in bytes: tile (key, value, digit), digit offsets, 16-bit counters per wave.
+template <int ROUNDS>
+constexpr size_t transpose_scatter_lds(int bins) {
+    return (size_t)kSortBlock * ROUNDS * 10 + (size_t)bins * 4 + (size_t)bins * 2 * kSortWaves + kSortWaves * 4;
+}
+
+// Stable placement of one tile.  FIRST: input is the matrix; LAST: output is the arrays of A^T.
+//
+// Row numbers (FIRST): the rows that begin inside the tile leave a mark at their first entry, in a
+// coalesced walk over their row pointers, and an entry's row is the last mark at or before it.  (A binary
+// search per entry took as long as the rest of the pass: 175 against 82 us at 13 M entries.)  A tile that
+// spans very many rows without entries searches after all.
+//
+// What bounds a pass: memory (8 bytes in and out per entry, and partly filled lines: a tile holds only a
+// few entries per digit) and, close behind, the vector instructions of the ranking; small tiles keep
+// enough waves resident to overlap the two.
+template <int ROUNDS, bool FIRST, bool LAST>
+__global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(TransposePass P)
+{
+    constexpr int THREADS = kSortBlock, T = THREADS * ROUNDS, WAVES = kSortWaves, RUN = ROUNDS * 64;
+    static_assert(THREADS == 256 && kDigitBinsMax == 1024 && T <= 0xffff, "4 digits a thread, counters of 16 bits");
+    extern __shared__ __align__(16) int lds[];
+    const int tile = tile_of_block(P.ntiles);
+    if (tile >= P.ntiles) return;
+    const int bins = 1 << P.bits;
+    int* skey = lds;                                      // [T]
+    float* sval = reinterpret_cast<float*>(lds + T);      // [T]
+    int* gofs = lds + 2 * T;                              // [bins]: global position minus tile slot, per digit
+    unsigned* wcnt = reinterpret_cast<unsigned*>(gofs + bins);                       // [WAVES][bins / 2]: count, then first slot
+    unsigned short* sdig = reinterpret_cast<unsigned short*>(wcnt + WAVES * (bins / 2));   // [T]
+    int* sh = reinterpret_cast<int*>(sdig + T);           // [WAVES]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long base = (long)tile * T;
+    const int count = (int)min((long)T, (long)P.n - base);
+    const int own = wave * RUN + lane;                    // the lane's first entry
+    const unsigned* __restrict__ keys = (FIRST ? reinterpret_cast<const unsigned*>(P.colind) : P.mid_in) + base;
+    const float* __restrict__ vals = P.vals_in + base;
+    unsigned key[ROUNDS];
+    float val[ROUNDS];
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        const unsigned e = (unsigned)min(own + q * 64, count - 1);
+        key[q] = keys[e];
+        val[q] = vals[e];
+    }
+    // thread t owns digits 4 t ... 4 t + 3: the global position of the tile's first entry of the digit
+    const bool owner = (int)threadIdx.x * 4 < bins;
+    int gpos[4], before[4], in_group[4];
+    load_bins(P.total, bins, gpos);
+    load_bins(P.group_hist + (long)(tile / P.group) * bins, bins, before);
+    load_bins(P.hist + (long)tile * bins, bins, in_group);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) before[i] += in_group[i];
+    if (owner) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) *reinterpret_cast<uint2*>(&wcnt[w * (bins / 2) + 2 * threadIdx.x]) = make_uint2(0u, 0u);
+    }
+    int row[ROUNDS];
+    if constexpr (FIRST) {
+        const int* __restrict__ rowptr = P.rowptr;
+        const int row_lo = P.tile_row[tile], row_hi = P.tile_row[tile + 1];
+        if (row_hi - row_lo <= 8 * T) {
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) skey[q * THREADS + threadIdx.x] = 0;
+            __syncthreads();
+            for (int r = row_lo + 1 + (int)threadIdx.x; r <= row_hi; r += THREADS) {
+                const int p = rowptr[r] - (int)base;      // row_hi may begin with the next tile
+                if (p < count) atomicMax(&skey[p], r - row_lo);
+            }
+            __syncthreads();
+            int last = 0;                                 // the last mark of the wave's run
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) {
+                row[q] = skey[own + q * 64];
+                const unsigned long long some = __ballot(row[q] != 0);
+                if (some) last = __builtin_amdgcn_readlane(row[q], 63 - __clzll((long long)some));
+            }
+            if (lane == 0) sh[wave] = last;
+            __syncthreads();
+            int carry = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) { const int x = sh[w]; if (w < wave && x != 0) carry = x; }
+            const unsigned long long upto = ~0ull >> (63 - lane);
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) {
+                const unsigned long long some = __ballot(row[q] != 0), mine = some & upto;
+                const int v = __shfl(row[q], mine ? 63 - __clzll((long long)mine) : 0);
+                const int next = some ? __builtin_amdgcn_readlane(row[q], 63 - __clzll((long long)some)) : carry;
+                row[q] = row_lo + (mine ? v : carry);
+                carry = next;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) row[q] = owner_row(rowptr, row_lo, row_hi, (int)base + min(own + q * 64, count - 1));
+            __syncthreads();
+        }
+    } else {
+        __syncthreads();
+    }
+    // rank of every entry among the wave's entries of the same digit
+    unsigned* counter = wcnt + wave * (bins / 2);
+    unsigned rank[ROUNDS];
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        const bool valid = own + q * 64 < count;
+        const unsigned d = pass_digit<FIRST>(key[q], P);
+        const unsigned long long peers = digit_peers_of(d, P.bits, __ballot(valid));
+        const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(peers >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)peers, 0u));
+        const int leader = (__ffsll((long long)peers) - 1) & 63;
+        const int sft = (int)(d & 1u) * 16;
+        unsigned old = 0;
+        if (valid && below == 0) old = atomicAdd(&counter[d >> 1], (unsigned)__popcll(peers) << sft);
+        rank[q] = ((__shfl(old, leader) >> sft) & 0xffffu) + below;
+        __builtin_amdgcn_sched_barrier(0);                // keep the ballots of one round together
+    }
+    block_scan_bins(gpos, sh);                            // digit totals -> first positions (synchronises)
+    {
+        // two digits to a word: no sum of a tile's counts leaves 16 bits
+        uint2 c[WAVES], sum = make_uint2(0u, 0u);
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            c[w] = owner ? *reinterpret_cast<const uint2*>(&wcnt[w * (bins / 2) + 2 * threadIdx.x]) : make_uint2(0u, 0u);
+            sum.x += c[w].x;
+            sum.y += c[w].y;
+        }
+        int slot[4] = {(int)(sum.x & 0xffffu), (int)(sum.x >> 16), (int)(sum.y & 0xffffu), (int)(sum.y >> 16)};
+        block_scan_bins(slot, sh);
+        if (owner) {
+            *reinterpret_cast<int4*>(&gofs[4 * threadIdx.x]) =
+                make_int4(gpos[0] + before[0] - slot[0], gpos[1] + before[1] - slot[1], gpos[2] + before[2] - slot[2],
+                          gpos[3] + before[3] - slot[3]);
+            uint2 run = make_uint2((unsigned)slot[0] | (unsigned)slot[1] << 16, (unsigned)slot[2] | (unsigned)slot[3] << 16);
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                *reinterpret_cast<uint2*>(&wcnt[w * (bins / 2) + 2 * threadIdx.x]) = run;
+                run.x += c[w].x;
+                run.y += c[w].y;
+            }
+        }
+    }
+    __syncthreads();
+    const unsigned short* first_slot = reinterpret_cast<const unsigned short*>(counter);
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        if (own + q * 64 < count) {
+            const unsigned d = pass_digit<FIRST>(key[q], P);
+            const unsigned slot = first_slot[d] + rank[q];
+            unsigned out = key[q];
+            if constexpr (FIRST) out = LAST ? (unsigned)row[q] : (unsigned)row[q] | (key[q] >> P.bits) << P.row_bits;
+            skey[slot] = (int)out;
+            sval[slot] = val[q];
+            if constexpr (FIRST) sdig[slot] = (unsigned short)d;
+        }
+    }
+    __syncthreads();
+    // copy out: neighbouring tile slots of one digit are neighbouring global positions
+    const unsigned row_mask = (1u << P.row_bits) - 1u;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < count; i += THREADS) {
+        const unsigned x = (unsigned)skey[i];
+        const int d = FIRST ? (int)sdig[i] : (int)(x >> P.row_bits);
+        const int pos = gofs[d] + i;
+        if constexpr (LAST) P.t_colind[pos] = (int)(FIRST ? x : x & row_mask);
+        else P.mid_out[pos] = x;
+        P.vals_out[pos] = sval[i];
+    }
+}
+
+// Row pointers of A^T after two passes.  Block `low` finds where the first pass's output begins to hold
+// that low digit and counts the high digits between the beginning of that tile of the second pass and
+// there; what lies before the tile is in the second pass's prefixes.
+template <int T>
+__global__ __launch_bounds__(256) void transpose_rowptr_kernel(
+    const unsigned* __restrict__ mid, int n, int k, int row_bits, int low_bits, int high_bits,
+    const int* __restrict__ low_total, const int* __restrict__ hist, const int* __restrict__ group_hist,
+    const int* __restrict__ high_total, int ntiles, int group, int* __restrict__ t_rowptr)
+{
+    __shared__ int cnt[kDigitBinsMax];
+    __shared__ int sh[4];
+    __shared__ int start;
+    const int low = blockIdx.x, low_bins = 1 << low_bits, high_bins = 1 << high_bits;
+    int first[4], lows[4];
+    load_bins(high_total, high_bins, first);
+    load_bins(low_total, low_bins, lows);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cnt[threadIdx.x * 4 + i] = 0;
+    block_scan_bins(lows, sh);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) if ((int)threadIdx.x * 4 + i == low) start = lows[i];
+    block_scan_bins(first, sh);
+    __syncthreads();
+    const int pos = start;                                // entries with a smaller low digit
+    const int tile = min(pos / T, ntiles - 1);            // pos == n: the last tile is counted whole
+    const int count = pos - tile * T;                     // 0 ... T
+    const unsigned* __restrict__ keys = mid + (long)tile * T;
+#pragma unroll
+    for (int r = 0; r < T / 256; ++r) {
+        const int e = r * 256 + (int)threadIdx.x;
+        count_digit(cnt, e < count ? keys[e] >> row_bits : 0u, e < count);
+    }
+    __syncthreads();
+    int before[4], in_group[4];
+    load_bins(group_hist + (long)(tile / group) * high_bins, high_bins, before);
+    load_bins(hist + (long)tile * high_bins, high_bins, in_group);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int d = threadIdx.x * 4 + i;
+        const long c = ((long)d << low_bits) | low;
+        if (d < high_bins && c < k) t_rowptr[c] = first[i] + before[i] + in_group[i] + cnt[d];
+    }
+    if (low == 0 && threadIdx.x == 0) t_rowptr[k] = n;
+}
+
+// Row pointers of A^T after one pass: the digits' places themselves.
+__global__ __launch_bounds__(256) void transpose_rowptr_one_kernel(const int* __restrict__ total, int bins, int n, int k,
+                                                                   int* __restrict__ t_rowptr)
+{
+    __shared__ int sh[4];
+    int first[4];
+    load_bins(total, bins, first);
+    block_scan_bins(first, sh);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { const int d = threadIdx.x * 4 + i; if (d < k) t_rowptr[d] = first[i]; }
+    if (threadIdx.x == 0) t_rowptr[k] = n;
 }
 
 }  // namespace daspmm
