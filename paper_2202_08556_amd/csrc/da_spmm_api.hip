@@ -12,6 +12,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <vector>
 
 namespace {
 
@@ -500,6 +501,54 @@ int scratch_address(void** out) {
     return DA_OK;
 }
 
+// Device scratch and pinned host memory of da_spmm_features, kept between calls (allocating, clearing,
+// copying and freeing them took ten times as long as the reduction).  A call owns one slot from start to
+// end, so calls of several threads and streams do not meet; at most kFeatureSlots idle ones are kept per
+// device, the rest is freed when the call returns.
+constexpr size_t kFeatureSlots = 8;
+struct FeatureSlot {
+    FeatureScratch* scratch = nullptr;
+    FeatureResult* result = nullptr;
+    unsigned long long ticket = 0;
+};
+std::mutex g_feature_mu;
+std::vector<FeatureSlot> g_feature_slots[kMaxDevices];
+
+void free_slot(const FeatureSlot& s) {
+    if (s.scratch) (void)hipFree(s.scratch);
+    if (s.result) (void)hipHostFree(s.result);
+}
+
+hipError_t take_slot(int dev, FeatureSlot* out) {
+    {
+        std::lock_guard<std::mutex> lk(g_feature_mu);
+        auto& pool = g_feature_slots[dev];
+        if (!pool.empty()) {
+            *out = pool.back();
+            pool.pop_back();
+            return hipSuccess;
+        }
+    }
+    FeatureSlot s;
+    hipError_t e = hipMalloc(&s.scratch, sizeof(FeatureScratch));
+    if (e == hipSuccess) e = hipMemset(s.scratch, 0, sizeof(FeatureScratch));
+    if (e == hipSuccess) e = hipHostMalloc(&s.result, sizeof(FeatureResult), hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipDeviceSynchronize();          // the clearing is done before any stream uses it
+    if (e != hipSuccess) { free_slot(s); return e; }
+    s.result->ticket = 0;
+    *out = s;
+    return hipSuccess;
+}
+
+void give_slot(int dev, const FeatureSlot& s) {
+    {
+        std::lock_guard<std::mutex> lk(g_feature_mu);
+        auto& pool = g_feature_slots[dev];
+        if (pool.size() < kFeatureSlots) { pool.push_back(s); return; }
+    }
+    free_slot(s);
+}
+
 // DA_SPMM_DEBUG_VALIDATE=1 makes da_spmm / da_spmm_ex / da_csr_transpose check the CSR arrays on
 // the device before they launch anything (this synchronises the stream)
 bool debug_validate() {
@@ -608,21 +657,35 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t* rowptr, void* stream, 
     if (m == 0) return DA_OK;
     if (!rowptr) return fail(DA_ERR_INVALID_ARG, "null rowptr%s");
     hipStream_t st = (hipStream_t)stream;
-    unsigned long long* dbuf = nullptr;
-    hipError_t e = hipMalloc(&dbuf, 3 * sizeof(unsigned long long));
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
-    unsigned long long h[3] = {0, 0, 0};
-    e = hipMemsetAsync(dbuf, 0, sizeof h, st);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    if (dev < 0 || dev >= kMaxDevices) return fail(DA_ERR_UNSUPPORTED, "device ordinal beyond 63%s");
+    FeatureSlot slot;
+    e = take_slot(dev, &slot);
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_features: scratch");
+    ++slot.ticket;
+    // 8 row pointers a thread: enough blocks to hide their latency, few enough for the shared counters
+    long blocks = (m + 8 * kBlock - 1) / (8 * kBlock);
+    const long cap = (long)cu_count() * 4;
+    if (blocks > cap) blocks = cap;
+    hipLaunchKernelGGL(features_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, (int)m, rowptr, slot.scratch, slot.result,
+                       slot.ticket);
+    e = hipGetLastError();
     if (e == hipSuccess) {
-        long blocks = (m + kBlock - 1) / kBlock;
-        const long cap = (long)cu_count() * 8;
-        if (blocks > cap) blocks = cap;
-        hipLaunchKernelGGL(features_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, (int)m, rowptr, dbuf);
-        e = hipGetLastError();
+        // The result arrives in host memory: look for it a while (a stream that is idle answers within
+        // microseconds), then wait for the stream.
+        bool here = false;
+        for (int i = 0; i < 20000 && !here; ++i) {
+            here = __atomic_load_n(&slot.result->ticket, __ATOMIC_ACQUIRE) == slot.ticket;
+            if (!here) __builtin_ia32_pause();
+        }
+        if (!here) e = hipStreamSynchronize(st);
+        if (e == hipSuccess && __atomic_load_n(&slot.result->ticket, __ATOMIC_ACQUIRE) != slot.ticket) e = hipErrorUnknown;
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(h, dbuf, sizeof h, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(dbuf);
+    const unsigned long long h[3] = {slot.result->sq, slot.result->mx, slot.result->nnz};
+    if (e == hipSuccess) give_slot(dev, slot);
+    else free_slot(slot);
     if (e != hipSuccess) return hip_fail(e, "da_spmm_features");
     // population variance = (m * sum len^2 - nnz^2) / m^2, formed exactly in 128-bit integers
     const unsigned __int128 num = (unsigned __int128)(unsigned long long)m * h[0]

@@ -1013,18 +1013,36 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
 
 // ------------------------------------------------------------------------------------------
 // Input characteristics (Sec. 5.1, Table 2): sum of squared row lengths and the longest row,
-// reduced exactly in integers.  out[0] += sum len^2, out[1] = max len, out[2] = nnz.
+// reduced exactly in integers.  The block that finishes last writes them and nnz straight into pinned
+// host memory, followed by `ticket`, and leaves the device scratch (sum, longest, finished blocks) zero
+// for the next call: no allocation, clearing or copy around the kernel.
 // ------------------------------------------------------------------------------------------
+struct FeatureScratch { unsigned long long sq, mx, done; };
+struct FeatureResult { unsigned long long sq, mx, nnz, ticket; };
+
 __global__ __launch_bounds__(kBlock) void features_kernel(
-    int m, const int* __restrict__ rowptr, unsigned long long* __restrict__ out)
+    int m, const int* __restrict__ rowptr, FeatureScratch* __restrict__ scratch, FeatureResult* __restrict__ result,
+    unsigned long long ticket)
 {
+    constexpr int U = 8;
     __shared__ unsigned long long s_sq[kWavesPerBlock];
     __shared__ unsigned long long s_mx[kWavesPerBlock];
     unsigned long long sq = 0, mx = 0;
-    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < m; i += (long)gridDim.x * kBlock) {
-        const unsigned long long len = (unsigned long long)(rowptr[i + 1] - rowptr[i]);
-        sq += len * len;
-        mx = len > mx ? len : mx;
+    const long stride = (long)gridDim.x * kBlock;
+    for (long i = (long)blockIdx.x * kBlock + threadIdx.x; i < m; i += U * stride) {
+        int a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                     // all loads in flight together
+            const long r = i + u * stride < m ? i + u * stride : m - 1;
+            a[u] = rowptr[r];
+            b[u] = rowptr[r + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned long long len = i + u * stride < m ? (unsigned long long)(b[u] - a[u]) : 0ull;
+            sq += len * len;
+            mx = len > mx ? len : mx;
+        }
     }
 #pragma unroll
     for (int d = kWave / 2; d >= 1; d >>= 1) {
@@ -1037,9 +1055,21 @@ __global__ __launch_bounds__(kBlock) void features_kernel(
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < kWavesPerBlock; ++w) { sq += s_sq[w]; mx = s_mx[w] > mx ? s_mx[w] : mx; }
-        atomicAdd(out + 0, sq);
-        atomicMax(out + 1, mx);
-        if (blockIdx.x == 0) out[2] = (unsigned long long)rowptr[m];
+        if (gridDim.x > 1) {
+            atomicAdd(&scratch->sq, sq);
+            atomicMax(&scratch->mx, mx);
+            __threadfence();
+            if (atomicAdd(&scratch->done, 1ull) != gridDim.x - 1) return;
+            __threadfence();
+            sq = atomicExch(&scratch->sq, 0ull);
+            mx = atomicExch(&scratch->mx, 0ull);
+            atomicExch(&scratch->done, 0ull);
+        }
+        result->sq = sq;
+        result->mx = mx;
+        result->nnz = (unsigned long long)rowptr[m];
+        __threadfence_system();
+        __hip_atomic_store(&result->ticket, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

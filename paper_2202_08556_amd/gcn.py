@@ -21,8 +21,9 @@ class SparseGraph:
     """CSR matrix A (m x k) resident on the device, with its selector features, the algorithm
     chosen per feature length, and (built on first use) A^T.
 
-    The first product prepares the matrix (da_spmm_prepare: EB chunk order and row hints).  The
-    library keeps the plans of the 16 most recently prepared matrices; a program that holds more
+    The matrix is prepared (da_spmm_prepare: EB chunk order and row hints) before the second product
+    with an EB algorithm: the preparation costs as much as a product or more and RB algorithms do not use
+    it, so a graph that is used once, a sampled mini-batch say, goes without.  The library keeps the plans of the 16 most recently prepared matrices; a program that holds more
     graphs than that (a graph and its transpose count as two) loses the oldest plans silently, which
     costs the EB algorithms their chunk order (speed), never the result."""
 
@@ -39,6 +40,7 @@ class SparseGraph:
         self._algo = {}
         self._t = None
         self._prepared = False
+        self._eb_products = 0
 
     @classmethod
     def from_numpy(cls, a, device="cuda:0") -> "SparseGraph":
@@ -90,12 +92,17 @@ class SparseGraph:
             raise ValueError("X must be a float32 k x N tensor")
         X = X.contiguous()
         N = int(X.shape[1])
-        if not self._prepared:                      # one-off: chunk order for the EB algorithms
-            da.da_spmm_prepare(self.m, self.k, self.nnz, self.rowptr, self.colind)
-            self._prepared = True
+        if algo is None:
+            algo = self.algo_for(N)
+        if algo >= da.DA_EB_RM_SR and not self._prepared:
+            if self._eb_products:                   # one-off: chunk order for the EB algorithms
+                da.da_spmm_prepare(self.m, self.k, self.nnz, self.rowptr, self.colind)
+                self._prepared = True
+            elif self._features is None:            # EB grids want nnz known
+                self.features(N)
+            self._eb_products += 1
         C = torch.empty((self.m, N), dtype=torch.float32, device=X.device)
-        da.da_spmm(self.m, self.k, N, self.rowptr, self.colind, self.vals, X, C,
-                   self.algo_for(N) if algo is None else algo)
+        da.da_spmm(self.m, self.k, N, self.rowptr, self.colind, self.vals, X, C, algo)
         return C
 
 
