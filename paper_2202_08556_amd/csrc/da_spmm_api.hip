@@ -114,7 +114,9 @@ int64_t lookup_nnz(const void* rowptr, int64_t m) {
 // a product call copies the reference under the mutex, launches outside it and drops the reference
 // after the launch, so that a concurrent release / re-prepare / eviction can free the memory only
 // once no call is between its lookup and its launch (hipFree itself waits for launched kernels).
-constexpr int kPlanUnits[4] = {64, 128, 256, 512};
+constexpr int kPlans = 5;
+constexpr int kPlanUnits[kPlans] = {32, 64, 128, 256, 512};     // plan_info reads number 3, 256
+constexpr int64_t kSmallPlanMaxNnz = 4 << 20;   // beyond, launches never take the smallest chunks: no order for them
 struct DeviceBlock {
     void* p = nullptr;
     ~DeviceBlock() { if (p) (void)hipFree(p); }
@@ -123,11 +125,11 @@ struct Plan {
     const void* rowptr = nullptr;
     const void* colind = nullptr;
     int64_t m = 0, nnz = 0;
-    int* order[4] = {nullptr, nullptr, nullptr, nullptr};
-    int* first_row[4] = {nullptr, nullptr, nullptr, nullptr};   // per schedule position: row of the chunk's first entry (hint)
-    int* row_by_chunk[4] = {nullptr, nullptr, nullptr, nullptr}; // the same rows indexed by chunk number
-    int units[4] = {0, 0, 0, 0};
-    int first_units[4] = {0, 0, 0, 0};   // chunks of the first schedule segment (multi-row chunks)
+    int* order[kPlans] = {};
+    int* first_row[kPlans] = {};   // per schedule position: row of the chunk's first entry (hint)
+    int* row_by_chunk[kPlans] = {}; // the same rows indexed by chunk number
+    int units[kPlans] = {};
+    int first_units[kPlans] = {};   // chunks of the first schedule segment (multi-row chunks)
     std::shared_ptr<DeviceBlock> block;
     bool captured = false;               // a stream capture recorded a kernel that reads the orders
 };
@@ -135,11 +137,16 @@ std::mutex g_plan_mu;
 Plan g_plans[16];
 int g_plan_next = 0;
 
-bool has_plan(const void* rowptr, const void* colind, int64_t m) {
+// What the launch geometry wants to know of a matrix's plan: whether there is one, and the share of the
+// entries that lie in chunks of 256 inside one row (rows much longer than a chunk).
+struct PlanInfo { bool found; double long_rows; };
+
+PlanInfo plan_info(const void* rowptr, const void* colind, int64_t m) {
     std::lock_guard<std::mutex> lk(g_plan_mu);
     for (const auto& pl : g_plans)
-        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m) return true;
-    return false;
+        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m)
+            return PlanInfo{true, 1.0 - (double)pl.first_units[3] / (double)pl.units[3]};
+    return PlanInfo{false, 0.0};
 }
 
 // Schedule of a prepared matrix for this chunk size; split holds the CHUNKS of the first segment
@@ -152,8 +159,8 @@ Schedule lookup_schedule(const void* rowptr, const void* colind, int64_t m, int 
     std::lock_guard<std::mutex> lk(g_plan_mu);
     for (auto& pl : g_plans)
         if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m)
-            for (int i = 0; i < 4; ++i)
-                if (kPlanUnits[i] == chunk) {
+            for (int i = 0; i < kPlans; ++i)
+                if (kPlanUnits[i] == chunk && pl.order[i]) {
                     *keep = pl.block;
                     if (capturing) pl.captured = true;
                     return Schedule{pl.order[i], pl.units[i], (int)pl.nnz, 0, pl.first_units[i], 0, 0, 0, 3, pl.first_row[i], pl.row_by_chunk[i]};
@@ -161,16 +168,16 @@ Schedule lookup_schedule(const void* rowptr, const void* colind, int64_t m, int 
     return Schedule{nullptr, 0, 0, 0, 0, 0, 0, 0, 3, nullptr, nullptr};
 }
 
-// Default geometry per algorithm family and N.  Measured on MI355X: 16-byte and 4-byte gathers
-// run at full rate, 8-byte gathers at about half, and narrow rows (N < 32) gather fastest with one
-// column per lane.  Setting DA_SPMM_TUNE=1 lets DA_SPMM_V / _G / _NV / _CHUNK override the choice
-// (for tuning runs only; invalid combinations are rejected).
-int pick_geometry(bool cm, bool pr, bool eb, int64_t N, const void* B, const void* C, const Strides& sd,
-                  int64_t known_nnz, bool prepared, Geometry* out) {
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C);
-    // 16-byte accesses need unit column strides and rows that start on 16-byte boundaries
-    const bool vec4_ok = (N % 4 == 0) && (addr % 16 == 0) && sd.cb == 1 && sd.cc == 1 &&
-                         sd.rb % 4 == 0 && sd.rc % 4 == 0;
+// Default geometry per algorithm family and N.  Measured on MI355X: 16-byte and 4-byte gathers run at
+// full rate, 8-byte gathers at about half.  SR narrows to one column per lane for N <= 16: lane groups of
+// 4 lanes or fewer walk 16 or more rows or chunks per wave and wait for the longest (power-law N = 8,
+// EB+RM+SR: 110 us with 8 lanes of one column, 176 with 2 lanes of 4).  PR has no such spread, its slots
+// share a row: there 16-byte gathers win at any width (power-law N = 16, RB+RM+PR: 159 us against 265).
+// Setting DA_SPMM_TUNE=1 lets DA_SPMM_V / _G / _NV / _CHUNK override the choice (for tuning runs only;
+// invalid combinations are rejected).
+int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides& sd,
+                  int64_t known_nnz, const PlanInfo& plan, Geometry* out) {
+    const bool vec4_ok = N >= 4 && sd.cb == 1 && sd.cc == 1;      // 16-byte accesses, at any alignment
     Geometry g{1, 1, 1, 0, false, kSweepStripe};
     if (cm) {
         g.V = vec4_ok ? 4 : 1;
@@ -178,7 +185,7 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t N, const void* B, const voi
         g.NV = vecs >= 4 ? 4 : pow2_ceil(vecs);
         g.G = 1;
     } else {
-        g.V = (vec4_ok && N >= 32) ? 4 : 1;
+        g.V = (vec4_ok && (pr || N > 16)) ? 4 : 1;
         g.G = pow2_ceil((N + g.V - 1) / g.V);
         // SR: at most 128 columns per tile (32 lanes of 4): at N = 256 two passes over 512-byte row
         // segments keep more rows of B in L2 than one pass over 1 KB rows and were never slower
@@ -203,10 +210,22 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t N, const void* B, const voi
     }
     if (eb) {
         if (pr) g.chunk = kEntriesPerWavePR;
-        // with a chunk schedule (prepared matrix) groups of 8 lanes do better on half-size chunks:
-        // twice as many waves pass through the machine and the sweep has a time axis
-        else g.chunk = g.G >= 16 ? 256 : (g.G == 8 ? (prepared ? 128 : 256) : (g.G == 4 ? 128 : 64));
-        if (known_nnz >= 0) {
+        else g.chunk = g.G >= 8 ? 256 : (g.G == 4 ? 128 : 64);
+        if (known_nnz >= 0 && plan.found && pr) {
+            // a chunk size the plan has row hints for, and about 5 waves per SIMD
+            while (g.chunk > 64 && g.chunk > known_nnz / ((long)cu_count() * 20)) g.chunk /= 2;
+        } else if (known_nnz >= 0 && plan.found && g.G >= 8) {
+            // With the plan's row hints a chunk is cheap to begin and with coalesced atomic additions cheap
+            // to end, so small chunks win: the workers are closer together in the sweep over B and in their
+            // progress (power-law N = 128: 449 us at 256 entries, 409 at 64; rows of 175 entries, N = 64:
+            // 523 and 381).  Smaller still while 64 leaves too few workers.  Larger where most entries are
+            // in long rows, whose chunks all add to the same few lines of C (rows of 60 000 entries, N = 32:
+            // 306 us at 64, 278 at 128).
+            const int64_t chunks = known_nnz / 64;
+            g.chunk = 64;
+            if (chunks < (g.G == 8 ? 48 : 28) * 1024 && known_nnz <= kSmallPlanMaxNnz) g.chunk = 32;
+            else if (N >= 32 && plan.long_rows > (g.G == 8 ? 0.2 : 0.5)) g.chunk = 128;
+        } else if (known_nnz >= 0) {
             // Small matrices: shrink the chunks until there are about four waves of workers per
             // SIMD, so that the chunk walk, a chain of dependent memory round trips, does not set
             // the run time.  Lane-sized workers (G < 8) keep their chunk: their search cost per
@@ -634,8 +653,8 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     const bool cm = (algo & 2) != 0;
     const bool pr = (algo & 1) != 0;
     Geometry g;
-    const int st = pick_geometry(cm, pr, eb, N, B, C, sd, eb ? lookup_nnz(rowptr, m) : -1,
-                                 eb && has_plan(rowptr, colind, m), &g);
+    const int st = pick_geometry(cm, pr, eb, m, N, sd, eb ? lookup_nnz(rowptr, m) : -1,
+                                 eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
     const Family fam = eb ? (pr ? EB_PR : EB_SR) : (pr ? RB_PR : RB_SR);
     return dispatch(fam, g, p);
@@ -1006,11 +1025,12 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     if (k > (1LL << 30)) { remember_nnz(rowptr, m, nnz); return DA_OK; }    // no schedule for such widths
     Plan pl;
     pl.rowptr = rowptr; pl.colind = colind; pl.m = m; pl.nnz = nnz;
-    size_t ints = 64, ws_bytes = 0, ws_off[4];             // the first 4 ints receive the segment sizes
-    for (int i = 0; i < 4; ++i) {
+    size_t ints = 64, ws_bytes = 0, ws_off[kPlans];        // the first ints receive the segment sizes
+    const int first_plan = nnz > kSmallPlanMaxNnz ? 1 : 0;
+    for (int i = first_plan; i < kPlans; ++i) {
         pl.units[i] = (int)((nnz + kPlanUnits[i] - 1) / kPlanUnits[i]);
         ints += 3 * (size_t)((pl.units[i] + 63) & ~63);     // the order and, twice, the first rows of the chunks
-        ws_off[i] = ws_bytes;                               // the four sorts run side by side, each in its own part
+        ws_off[i] = ws_bytes;                               // the sorts run side by side, each in its own part
         ws_bytes += align256(plan_transpose(2 * k, pl.units[i]).bytes);
     }
     pl.block = std::make_shared<DeviceBlock>();
@@ -1021,8 +1041,8 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     if (e != hipSuccess) return hip_fail(e, "hipMalloc");
     size_t off = 64;
     int* seg = static_cast<int*>(pl.block->p);
-    ScheduleJob jobs[4];
-    for (int i = 0; i < 4; ++i) {
+    ScheduleJob jobs[kPlans];
+    for (int i = first_plan; i < kPlans; ++i) {
         pl.order[i] = seg + off;
         off += (size_t)((pl.units[i] + 63) & ~63);
         pl.first_row[i] = seg + off;
@@ -1032,7 +1052,7 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
         jobs[i] = ScheduleJob{kPlanUnits[i], pl.order[i], seg + i, pl.first_row[i], pl.row_by_chunk[i],
                               static_cast<char*>(ws.p) + ws_off[i], ws_bytes - ws_off[i]};
     }
-    int status = enqueue_schedules(m, k, nnz, rowptr, colind, jobs, 4, stream);
+    int status = enqueue_schedules(m, k, nnz, rowptr, colind, jobs + first_plan, kPlans - first_plan, stream);
     e = hipSuccess;
     if (status == DA_OK)
         e = hipMemcpyAsync(pl.first_units, seg, sizeof pl.first_units, hipMemcpyDeviceToHost, (hipStream_t)stream);

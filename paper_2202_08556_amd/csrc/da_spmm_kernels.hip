@@ -11,8 +11,8 @@
 //       the B row it points to.  RM mapping: G > 1 (a lane group reads one contiguous B row
 //       segment, coalesced).  CM mapping: G = 1 (neighbouring lanes hold different rows / entries).
 //   V   consecutive columns a lane loads at once (the float2/float4 technique of Sec. 4): 1 or 4.
-//   NV  vectors of V columns a lane walks one after another (CM: the lane's own strip of columns;
-//       RM uses NV = 1).
+//   NV  vectors of V columns a lane walks one after another, G*V columns apart (CM: the lane's own
+//       strip of columns; RM uses NV = 1).
 // A lane group covers G*V*NV columns; further column tiles are further blocks (see block_map).
 // B and C are row-major in memory in every case.
 //
@@ -35,7 +35,8 @@ constexpr int kU = 8;                       // gathers in flight per lane (4 ...
 
 // Element strides of the dense operands: B(r, n) is at B[r*rb + n*cb], C(i, n) at C[i*rc + n*cc].
 // Row-major storage has cb = cc = 1 and rb, rc = leading dimension; column-major storage has
-// rb = rc = 1 and cb, cc = leading dimension.  Vector loads / stores (V = 4) need cb = cc = 1.
+// rb = rc = 1 and cb, cc = leading dimension.  Vector loads / stores (V = 4) need cb = cc = 1 and N >= 4,
+// no alignment: the hardware takes 16-byte accesses at any multiple of 4 bytes.
 struct Strides {
     long rb, cb, rc, cc;
 };
@@ -81,18 +82,18 @@ __device__ __forceinline__ int hinted_row(const int* __restrict__ rowptr, int m,
 // ------------------------------------------------------------------------------------------
 // small helpers
 // ------------------------------------------------------------------------------------------
+typedef float floatx4 __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int V>
 __device__ __forceinline__ void load_vec(const float* __restrict__ p, float (&x)[V]) {
     if constexpr (V == 4) {
-        const float4 t = *reinterpret_cast<const float4*>(p);
+        const floatx4 t = *reinterpret_cast<const floatx4*>(p);
         x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
     } else {
         static_assert(V == 1, "V is 1 or 4");
         x[0] = *p;
     }
 }
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // C is written once and never read back by the kernels: its stores are marked non-temporal so
 // that they do not push B rows out of L2.
@@ -107,20 +108,51 @@ __device__ __forceinline__ void store_vec(float* __restrict__ p, const float (&x
 }
 
 // Rows shared between workers are combined with hardware fp32 atomic adds (Sec. 4: "atomic_add"
-// for rows assigned to different workers); the return value is not used.
+// for rows assigned to different workers); the return value is not used.  The first `skip` components
+// belong to another lane as well (Cols): harmless to store twice, not to add twice.
 template <int V>
-__device__ __forceinline__ void emit_vec(float* __restrict__ p, const float (&x)[V], bool atomic) {
+__device__ __forceinline__ void emit_vec(float* __restrict__ p, const float (&x)[V], bool atomic, int skip) {
     if (atomic) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) unsafeAtomicAdd(p + v, x[v]);
+        for (int v = 0; v < V; ++v)
+            if (V == 1 || v >= skip) unsafeAtomicAdd(p + v, x[v]);
     } else {
         store_vec<V>(p, x);
     }
 }
 
-// A lane's accumulators: NV vectors of V columns, vector i at column offset i*V from the lane's n0.
-template <int V, int NV>
+// The columns of a lane: nvec vectors of V columns, vector i at column n0 + i*G*V.  When N is not a
+// multiple of V = 4 the last vector of the row is moved left by `shift` columns so that it ends with
+// the row; its first `shift` columns are then also its left neighbour's, who computes the same values.
+// (One column per lane instead, as before, issues four times the loads: N = 41 took twice as long on
+// matrices that fit the caches.)
+template <int V, int G, int NV>
+struct Cols {
+    int n0, nvec, shift;
+    __device__ __forceinline__ Cols(int tile, int j, int N) {
+        n0 = (tile * NV * G + j) * V;
+        const int left = N - n0;
+        nvec = left <= 0 ? 0 : min(NV, (left - 1) / (G * V) + 1);
+        shift = 0;
+        if constexpr (V > 1) {
+            if (nvec > 0) shift = max(0, n0 + (nvec - 1) * G * V + V - N);
+            if constexpr (NV == 1) n0 -= shift;
+        }
+    }
+    // column offset of vector i from n0; vectors past nvec repeat the first one (valid memory)
+    __device__ __forceinline__ int offset(int i) const {
+        if constexpr (NV == 1) return 0;
+        if constexpr (V == 1) return (i < nvec ? i : 0) * G * V;
+        const int moved = i == nvec - 1 ? shift : 0;
+        return i < nvec ? i * G * V - moved : (nvec == 1 ? -shift : 0);
+    }
+    __device__ __forceinline__ int skip(int i) const { return i == nvec - 1 ? shift : 0; }
+};
+
+// A lane's accumulators, laid out like its columns.
+template <int V, int G, int NV>
 struct Acc {
+    typedef Cols<V, G, NV> C;
     float a[NV][V];
     __device__ __forceinline__ void clear() {
 #pragma unroll
@@ -128,11 +160,11 @@ struct Acc {
 #pragma unroll
             for (int v = 0; v < V; ++v) a[i][v] = 0.f;
     }
-    // Branch-free gather of the lane's vectors of one B row (nvalid >= 1).  Vectors past nvalid
-    // re-read vector 0 (valid memory); their values are never written out.  cs = column stride.
-    __device__ __forceinline__ void load(const float* __restrict__ p, int nvalid, long cs) {
+    // Branch-free gather of the lane's vectors of one B row (c.nvec >= 1).  Values of vectors past nvec
+    // are never written out.  cs = column stride.
+    __device__ __forceinline__ void load(const float* __restrict__ p, const C& c, long cs) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) load_vec<V>(p + (i < nvalid ? i : 0) * V * cs, a[i]);
+        for (int i = 0; i < NV; ++i) load_vec<V>(p + (V == 1 ? c.offset(i) * cs : c.offset(i)), a[i]);
     }
     __device__ __forceinline__ void fma(float s, const Acc& b) {
 #pragma unroll
@@ -152,18 +184,47 @@ struct Acc {
 #pragma unroll
             for (int v = 0; v < V; ++v) a[i][v] += b.a[i][v];
     }
-    __device__ __forceinline__ void emit(float* __restrict__ p, int nvalid, bool atomic, long cs) const {
+    __device__ __forceinline__ void emit(float* __restrict__ p, const C& c, bool atomic, long cs) const {
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            if (i < nvalid) emit_vec<V>(p + i * V * cs, a[i], atomic);
+            if (i < c.nvec) emit_vec<V>(p + (V == 1 ? c.offset(i) * cs : c.offset(i)), a[i], atomic, c.skip(i));
     }
 };
 
-// number of valid V-vectors of a lane whose first column is n0
-template <int V, int NV>
-__device__ __forceinline__ int valid_vectors(int n0, int N) {
-    const int left = (N - n0 + V - 1) / V;          // V == 4 implies N % 4 == 0
-    return left < 0 ? 0 : (left > NV ? NV : left);
+// Orders LDS traffic of the lanes of one wave: the LDS unit serves one wave's requests in issue
+// order, so only the compiler has to be kept from moving accesses across this point.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A lane group adds its sums of one row of C atomically.  With 16-byte vectors the four additions of a lane
+// would each touch every fourth element of the row, four requests to a line where one does: the group's
+// sums pass through LDS (`turn`, 4*G floats of the group's own) so that each addition of the G lanes covers
+// G neighbouring elements.  (On a matrix with rows of 40 000 entries EB+RM+SR at N = 64 went from 164 to
+// 84 us, and to the rate of the mapping with one column per lane.)  Every lane of the group must call it;
+// crow = first column of the group's tile in the row, left = columns of B from there on.
+template <int V, int G, int NV>
+__device__ __forceinline__ void add_row(float* __restrict__ crow, const Acc<V, G, NV>& x, const Cols<V, G, NV>& c, int j,
+                                        int left, long cs, float* turn) {
+    if constexpr (V == 4 && G >= 4 && NV == 1) {
+        const int at = j * V - c.shift;
+        if (c.nvec > 0) {
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (at + v >= 0) turn[at + v] = x.a[0][v];  // the row's last vector may begin before the tile
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int n = v * G + j;
+            if (n < left) unsafeAtomicAdd(crow + n, turn[n]);
+        }
+        wave_lds_sync();
+    } else {
+        if (c.nvec > 0) x.emit(crow + (long)(j * V - (NV == 1 ? c.shift : 0)) * cs, c, true, cs);
+    }
 }
 
 // Address of the lane's first column in a row of B.  The gather address is the only per-entry
@@ -195,14 +256,6 @@ struct BRows {
         }
     }
 };
-
-// Orders LDS traffic of the lanes of one wave: the LDS unit serves one wave's requests in issue
-// order, so only the compiler has to be kept from moving accesses across this point.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Sum over the lanes of a wave that share lane % G (the slots of a PR kernel); every lane ends up
 // with the total.  Butterfly steps at distance 32 and 16 use the gfx950 lane-swap instructions,
@@ -409,11 +462,11 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
     const int g = lane / G, j = lane % G;
     const BlockMap bm = block_map(pin_tiles);
     const long row = (bm.bx * kWavesPerBlock + wave) * RPW + g;
-    const int n0 = (bm.tile * G + j) * V * NV;
-    const int nvec = valid_vectors<V, NV>(n0, N);
+    const Cols<V, G, NV> cols(bm.tile, j, N);
+    const int n0 = cols.n0, nvec = cols.nvec;
     int start = 0, end = 0;
     if (row < m) { start = rowptr[row]; end = rowptr[row + 1]; }
-    Acc<V, NV> acc;
+    Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);
 
@@ -424,11 +477,11 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
                 const int p0 = start + t;
                 int c[UU];
                 float a[UU];
-                Acc<V, NV> b[UU];
+                Acc<V, G, NV> b[UU];
 #pragma unroll
                 for (int u = 0; u < UU; ++u) { c[u] = colind[p0 + u]; a[u] = vals[p0 + u]; }
 #pragma unroll
-                for (int u = 0; u < UU; ++u) b[u].load(brow.row(c[u]), nvec, sd.cb);
+                for (int u = 0; u < UU; ++u) b[u].load(brow.row(c[u]), cols, sd.cb);
 #pragma unroll
                 for (int u = 0; u < UU; ++u) acc.fma(a[u], b[u]);
             });
@@ -445,11 +498,11 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
                 for_blocks<UL>(min(SB, end - p0), [&](auto uc, int t) {
                     constexpr int UU = decltype(uc)::value;
                     int2 e[UU];
-                    Acc<V, NV> b[UU];
+                    Acc<V, G, NV> b[UU];
 #pragma unroll
                     for (int u = 0; u < UU; ++u) e[u] = st[t + u];
 #pragma unroll
-                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), nvec, sd.cb);
+                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), cols, sd.cb);
 #pragma unroll
                     for (int u = 0; u < UU; ++u) acc.fma(__int_as_float(e[u].y), b[u]);
                 });
@@ -457,7 +510,7 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
             wave_lds_sync();
         }
     }
-    if (row < m && nvec > 0) acc.emit(C + row * sd.rc + (long)n0 * sd.cc, nvec, false, sd.cc);
+    if (row < m && nvec > 0) acc.emit(C + row * sd.rc + (long)n0 * sd.cc, cols, false, sd.cc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -480,10 +533,10 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     const BlockMap bm = block_map(pin_tiles);
     const long row = bm.bx * kWavesPerBlock + wave;
     if (row >= m) return;                                 // whole wave leaves together
-    const int n0 = (bm.tile * G + j) * V * NV;
-    const int nvec = valid_vectors<V, NV>(n0, N);
+    const Cols<V, G, NV> cols(bm.tile, j, N);
+    const int n0 = cols.n0, nvec = cols.nvec;
     const int start = rowptr[row], end = rowptr[row + 1];
-    Acc<V, NV> acc;
+    Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);
 
@@ -496,18 +549,18 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
                 const int p0 = start + t * kWave + lane;
                 int c[UU];
                 float a[UU];
-                Acc<V, NV> b[UU];
+                Acc<V, G, NV> b[UU];
 #pragma unroll
                 for (int u = 0; u < UU; ++u) { c[u] = colind[p0 + u * kWave]; a[u] = vals[p0 + u * kWave]; }
 #pragma unroll
-                for (int u = 0; u < UU; ++u) b[u].load(brow.row(c[u]), nvec, sd.cb);
+                for (int u = 0; u < UU; ++u) b[u].load(brow.row(c[u]), cols, sd.cb);
 #pragma unroll
                 for (int u = 0; u < UU; ++u) acc.fma(a[u], b[u]);
             });
             const int p = start + (len / kWave) * kWave + lane;
             if (p < end) {
-                Acc<V, NV> b;
-                b.load(brow.row(colind[p]), nvec, sd.cb);
+                Acc<V, G, NV> b;
+                b.load(brow.row(colind[p]), cols, sd.cb);
                 acc.fma(vals[p], b);
             }
         }
@@ -524,19 +577,19 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
                 for_blocks<UL>(cnt / S, [&](auto uc, int t) {
                     constexpr int UU = decltype(uc)::value;
                     int2 ee[UU];
-                    Acc<V, NV> b[UU];
+                    Acc<V, G, NV> b[UU];
 #pragma unroll
                     for (int u = 0; u < UU; ++u) ee[u] = st[(t + u) * S + s];
 #pragma unroll
-                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(ee[u].x), nvec, sd.cb);
+                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(ee[u].x), cols, sd.cb);
 #pragma unroll
                     for (int u = 0; u < UU; ++u) acc.fma(__int_as_float(ee[u].y), b[u]);
                 });
                 const int t = (cnt / S) * S + s;              // ragged last step
                 if (t < cnt) {
                     const int2 ee = st[t];
-                    Acc<V, NV> b;
-                    b.load(brow.row(ee.x), nvec, sd.cb);
+                    Acc<V, G, NV> b;
+                    b.load(brow.row(ee.x), cols, sd.cb);
                     acc.fma(__int_as_float(ee.y), b);
                 }
             }
@@ -548,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     for (int i = 0; i < NV; ++i)
 #pragma unroll
         for (int v = 0; v < V; ++v) acc.a[i][v] = slot_allreduce<G>(acc.a[i][v]);
-    if (s == 0 && nvec > 0) acc.emit(C + row * sd.rc + (long)n0 * sd.cc, nvec, false, sd.cc);
+    if (s == 0 && nvec > 0) acc.emit(C + row * sd.rc + (long)n0 * sd.cc, cols, false, sd.cc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -585,7 +638,7 @@ __global__ __launch_bounds__(kBlock) void eb_zero_kernel(
             const int r = __ffsll((long long)mask) - 1;
             mask &= mask - 1;
             float* __restrict__ crow = C + (base + r) * sd.rc;
-            for (int n0 = lane * V; n0 < N; n0 += kWave * V) store_vec<V>(crow + (long)n0 * sd.cc, z);
+            for (int n0 = lane * V; n0 < N; n0 += kWave * V) store_vec<V>(crow + (long)min(n0, N - V) * sd.cc, z);
         }
     } else {
         // short rows of C: T lanes per row, 64/T flagged rows per store instruction.  The flagged
@@ -599,7 +652,7 @@ __global__ __launch_bounds__(kBlock) void eb_zero_kernel(
         const int n0 = (lane & (T - 1)) * V;
         for (int s = lane / T; s < count; s += kWave / T) {
             const int r = listed[wave][s];
-            if (n0 < N) store_vec<V>(C + (base + r) * sd.rc + (long)n0 * sd.cc, z);
+            if (n0 < N) store_vec<V>(C + (base + r) * sd.rc + (long)min(n0, N - V) * sd.cc, z);
         }
     }
 }
@@ -621,7 +674,7 @@ __global__ __launch_bounds__(kBlock) void eb_zero_kernel(
 template <int G> constexpr bool kOwnShortRows = G >= 16;
 
 template <int V, int G, int NV, bool WIDE>
-__global__ __launch_bounds__(kBlock) void eb_sr_kernel(
+__global__ __launch_bounds__(kBlock, 6) void eb_sr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
     const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int chunk,
     int pin_tiles, Schedule sch, int own_short)
@@ -630,13 +683,16 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
     constexpr int SB = StageBatch<G>::value;
     constexpr int UL = G == 1 ? kU / NV : kU;             // entries whose gathers are issued together
     __shared__ int2 stage[G > 1 ? kWavesPerBlock * GPW * SB : 1];
+    __shared__ float turns[V == 4 && G >= 4 ? kBlock * V : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane / G, j = lane % G;
     const BlockMap bm = block_map(pin_tiles);
-    const int n0 = (bm.tile * G + j) * V * NV;
-    const int nvec = valid_vectors<V, NV>(n0, N);
+    const Cols<V, G, NV> cols(bm.tile, j, N);
+    const int n0 = cols.n0, nvec = cols.nvec;
     const BRows<WIDE> brow(B, n0, sd);
-    float* __restrict__ Cn = C + (long)n0 * sd.cc;
+    const int tile0 = bm.tile * G * V * NV;                // first column of the tile
+    float* __restrict__ Ct = C + (long)tile0 * sd.cc;
+    float* turn = turns + (V == 4 && G >= 4 ? (wave * GPW + g) * G * V : 0);
     const int nnz = rowptr[m];
     int2* st = stage + (G > 1 ? (wave * GPW + g) * SB : 0);
 
@@ -698,7 +754,7 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
         }
         if (lo >= hi) continue;
         bool shared_with_prev = row_start < lo;            // only the worker's first row can be
-        Acc<V, NV> acc;
+        Acc<V, G, NV> acc;
         acc.clear();
 
         int q0 = c0, skip = lo - c0;                       // entries of the first batch that are not ours
@@ -716,7 +772,7 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
             for_blocks<UL>(skip, min(SB, hi - q0), [&](auto uc, int t) {
                 constexpr int UU = decltype(uc)::value;
                 int2 e[UU];
-                Acc<V, NV> b[UU];
+                Acc<V, G, NV> b[UU];
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {
                     if constexpr (G > 1) e[u] = st[t + u];
@@ -724,7 +780,7 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
                 }
                 if (nvec > 0) {
 #pragma unroll
-                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), nvec, sd.cb);
+                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), cols, sd.cb);
                 }
                 if (row_end > q0 + t + UU) {
                     // the common case: the whole block lies inside the current row
@@ -746,7 +802,8 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
                         if (nvec > 0) acc.add(b[u]);
                         const int next = q0 + t + u + 1;
                         if (next == row_end) {                 // the row is complete
-                            if (nvec > 0) acc.emit(Cn + (long)row * sd.rc, nvec, shared_with_prev, sd.cc);
+                            if (shared_with_prev) add_row(Ct + (long)row * sd.rc, acc, cols, j, N - tile0, sd.cc, turn);
+                            else if (nvec > 0) acc.emit(Ct + (long)row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
                             acc.clear();
                             shared_with_prev = false;
                             if (next < hi) {
@@ -766,8 +823,8 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
             });
             if constexpr (G > 1) wave_lds_sync();
         }
-        if (row_end > hi && nvec > 0)                      // last row continues with the next worker
-            acc.emit(Cn + (long)row * sd.rc, nvec, true, sd.cc);
+        if (row_end > hi)                                  // last row continues with the next worker
+            add_row(Ct + (long)row * sd.rc, acc, cols, j, N - tile0, sd.cc, turn);
     }
 }
 
@@ -791,7 +848,7 @@ __global__ __launch_bounds__(kBlock) void eb_sr_kernel(
 // neighbouring chunks, are combined with atomic adds.
 // ------------------------------------------------------------------------------------------
 template <int V, int G, int NV>
-__device__ __forceinline__ Acc<V, NV> slots_allreduce(Acc<V, NV> x) {
+__device__ __forceinline__ Acc<V, G, NV> slots_allreduce(Acc<V, G, NV> x) {
 #pragma unroll
     for (int i = 0; i < NV; ++i)
 #pragma unroll
@@ -824,13 +881,16 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
     constexpr int UU = G < 4 ? G : 4;                     // steps whose gathers are issued together (8 measured slower)
     __shared__ int4 stage[G > 1 ? kBlock : 1];
     __shared__ int starts[kWavesPerBlock][kStagedChunk + 2];
+    __shared__ float turns[V == 4 && G >= 4 ? kBlock * V : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int s = lane / G, j = lane % G;
     const BlockMap bm = block_map(pin_tiles);
-    const int n0 = (bm.tile * G + j) * V * NV;
-    const int nvec = valid_vectors<V, NV>(n0, N);
+    const Cols<V, G, NV> cols(bm.tile, j, N);
+    const int n0 = cols.n0, nvec = cols.nvec;
     const BRows<WIDE> brow(B, n0, sd);
-    float* __restrict__ Cn = C + (long)n0 * sd.cc;
+    const int tile0 = bm.tile * G * V * NV;                // first column of the tile
+    float* __restrict__ Ct = C + (long)tile0 * sd.cc;
+    float* turn = turns + (V == 4 && G >= 4 ? (wave * kWave + s * G) * V : 0);
     const int nnz = rowptr[m];
     int4* st = stage + (G > 1 ? wave * kWave : 0);
     int* cnt = starts[wave];
@@ -850,7 +910,7 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
         int row_lo = (scheduled && sch.first_row != nullptr) ? hinted_row(rowptr, m, sch.first_row[u], c0, &hint_start, &hint_end) : -1;
         if (row_lo < 0) row_lo = row_of_entry_group<kWave>(rowptr, 0, m - 1, c0, lane, 0);
         const int row_hi = row_of_entry_group<kWave>(rowptr, row_lo, m - 1, c1 - 1, lane, 0);
-        Acc<V, NV> acc;                                    // per-slot partial sums of row `cur`
+        Acc<V, G, NV> acc;                                    // per-slot partial sums of row `cur`
         acc.clear();
         int cur = -1;                                      // row being accumulated (wave-uniform)
         bool cur_started = false;                          // its first entry lies in this chunk
@@ -913,7 +973,7 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
 
             for (int tb = 0; tb * S < cnt; tb += UU) {
                 int4 e[UU];
-                Acc<V, NV> b[UU];
+                Acc<V, G, NV> b[UU];
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {
                     if constexpr (G > 1) e[u] = st[((tb + u) * S + s) & (kWave - 1)]; else e[u] = mine;
@@ -922,7 +982,7 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                 // branch-free gathers: slots past the end of the chunk hold column 0
                 if (nvec > 0) {
 #pragma unroll
-                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), nvec, sd.cb);
+                    for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), cols, sd.cb);
                 }
                 // all products first: no store or atomic is issued while a gather is outstanding
                 // (stores share the in-order memory counter with loads)
@@ -952,15 +1012,18 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                         if (cur < 0) { cur = first_row; cur_started = (first_flags & 1) != 0; }
                         acc.add(b[u]);
                         if (last_flags & 2) {                           // the row ends here
-                            const Acc<V, NV> total = slots_allreduce<V, G, NV>(acc);
-                            if (s == 0 && nvec > 0) total.emit(Cn + (long)cur * sd.rc, nvec, !cur_started, sd.cc);
+                            const Acc<V, G, NV> total = slots_allreduce<V, G, NV>(acc);
+                            if (s == 0) {
+                                if (!cur_started) add_row(Ct + (long)cur * sd.rc, total, cols, j, N - tile0, sd.cc, turn);
+                                else if (nvec > 0) total.emit(Ct + (long)cur * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                            }
                             acc.clear();
                             cur = -1;
                         }
                     } else {
                         // a row boundary inside the step: conditional reduction
-                        const Acc<V, NV> p = b[u];                      // this slot's product
-                        Acc<V, NV> x = p;
+                        const Acc<V, G, NV> p = b[u];                      // this slot's product
+                        Acc<V, G, NV> x = p;
                         // run heads: a slot whose entry is the first of its row (entries are stored
                         // row after row, so its left neighbour then holds another row); the first
                         // slot past the valid ones counts as a head so that the last run ends there
@@ -979,15 +1042,17 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                         // the run that starts the step continues the row accumulated so far
                         bool started = true;                            // runs that begin inside the step
                         if (cur >= 0) {
-                            const Acc<V, NV> total = slots_allreduce<V, G, NV>(acc);
+                            const Acc<V, G, NV> total = slots_allreduce<V, G, NV>(acc);
                             if (s == 0) { x.add(total); started = cur_started; }
                         } else if (s == 0) {
                             started = (first_flags & 1) != 0;
                         }
                         const bool last_ended = (last_flags & 2) != 0;
                         const bool in_last_run = evalid && er == last_row;
-                        if (head && evalid && nvec > 0 && (!in_last_run || last_ended))
-                            x.emit(Cn + (long)er * sd.rc, nvec, !started, sd.cc);
+                        if (head && evalid && (!in_last_run || last_ended)) {
+                            if (!started) add_row(Ct + (long)er * sd.rc, x, cols, j, N - tile0, sd.cc, turn);
+                            else if (nvec > 0) x.emit(Ct + (long)er * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                        }
                         if (last_ended) {
                             acc.clear();
                             cur = -1;
@@ -1005,8 +1070,8 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
             if constexpr (G > 1) wave_lds_sync();
         }
         if (cur >= 0) {                                       // row continues in the next chunk
-            const Acc<V, NV> total = slots_allreduce<V, G, NV>(acc);
-            if (s == 0 && nvec > 0) total.emit(Cn + (long)cur * sd.rc, nvec, true, sd.cc);
+            const Acc<V, G, NV> total = slots_allreduce<V, G, NV>(acc);
+            if (s == 0) add_row(Ct + (long)cur * sd.rc, total, cols, j, N - tile0, sd.cc, turn);
         }
     }
 }

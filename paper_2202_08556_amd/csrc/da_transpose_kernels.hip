@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kSortBlock) void radix_scatter_kernel(
 // Several schedules (one per chunk size) are built side by side: every kernel of the pipeline takes
 // up to kMaxSortJobs jobs and blockIdx.y selects the job, so that the orders for all chunk sizes of
 // a matrix cost the launches of one.
-constexpr int kMaxSortJobs = 4;
+constexpr int kMaxSortJobs = 5;
 
 struct SortJob {                       // one radix pass of one job (pointers change from pass to pass)
     const int* keys_in; const int* rows_in; const float* vals_in;
