@@ -28,7 +28,9 @@ DA_NUM_ALGOS = 8
 DA_ROW_MAJOR, DA_COL_MAJOR = 0, 1
 EXPORTS = ("da_spmm", "da_spmm_ex", "da_spmm_select", "da_spmm_features", "da_csr_transpose_workspace",
            "da_csr_transpose", "da_csr_transpose_noalloc", "da_csr_validate", "da_spmm_prepare", "da_spmm_release",
-           "da_eb_schedule_workspace", "da_eb_schedule", "da_spmm_algo_name", "da_spmm_last_error")
+           "da_eb_schedule_workspace", "da_eb_schedule", "da_spmm_weight_grad_workspace", "da_spmm_weight_grad", "da_spmm_column_sums_workspace",
+           "da_spmm_column_sums", "da_spmm_bias_relu", "da_spmm_dense",
+           "da_spmm_algo_name", "da_spmm_last_error")
 
 
 class da_features(ctypes.Structure):
@@ -63,6 +65,18 @@ _lib.da_eb_schedule_workspace.argtypes = [_i64, _i64, ctypes.c_int, ctypes.POINT
 _lib.da_eb_schedule_workspace.restype = ctypes.c_int
 _lib.da_eb_schedule.argtypes = [_i64, _i64, _i64, _vp, _vp, ctypes.c_int, _vp, _vp, _vp, ctypes.c_size_t, _vp]
 _lib.da_eb_schedule.restype = ctypes.c_int
+_lib.da_spmm_weight_grad_workspace.argtypes = [_i64, _i64, _i64, ctypes.POINTER(ctypes.c_size_t)]
+_lib.da_spmm_weight_grad_workspace.restype = ctypes.c_int
+_lib.da_spmm_weight_grad.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _vp, ctypes.c_size_t, _vp]
+_lib.da_spmm_column_sums_workspace.argtypes = [_i64, _i64, ctypes.POINTER(ctypes.c_size_t)]
+_lib.da_spmm_column_sums_workspace.restype = ctypes.c_int
+_lib.da_spmm_column_sums.argtypes = [_i64, _i64, _vp, _i64, _vp, _vp, ctypes.c_size_t, _vp]
+_lib.da_spmm_column_sums.restype = ctypes.c_int
+_lib.da_spmm_bias_relu.argtypes = [_i64, _i64, _vp, _vp, ctypes.c_int, _vp]
+_lib.da_spmm_bias_relu.restype = ctypes.c_int
+_lib.da_spmm_weight_grad.restype = ctypes.c_int
+_lib.da_spmm_dense.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _i64, _vp, _i64, _vp]
+_lib.da_spmm_dense.restype = ctypes.c_int
 _lib.da_spmm_algo_name.argtypes = [ctypes.c_int]
 _lib.da_spmm_algo_name.restype = ctypes.c_char_p
 _lib.da_spmm_last_error.argtypes = []
@@ -237,6 +251,39 @@ def da_eb_schedule(m, k, nnz, rowptr, colind, unit, order, first_segment, worksp
                    stream=None) -> None:
     _check(da_eb_schedule_status(m, k, nnz, rowptr, colind, unit, order, first_segment, workspace, workspace_bytes,
                                  stream))
+
+
+def da_spmm_weight_grad_workspace(rows, fin, fout) -> int:
+    out = ctypes.c_size_t(0)
+    _check(int(_lib.da_spmm_weight_grad_workspace(int(rows), int(fin), int(fout), ctypes.byref(out))))
+    return int(out.value)
+
+
+def da_spmm_weight_grad(rows, fin, fout, X, ldx, G, ldg, dW, workspace, workspace_bytes, stream=None) -> None:
+    """dW = X^T . G; see include/da_spmm.h."""
+    _check(int(_lib.da_spmm_weight_grad(int(rows), int(fin), int(fout), _ptr(X), int(ldx), _ptr(G), int(ldg), _ptr(dW),
+                                        _ptr(workspace), int(workspace_bytes), _stream(stream))))
+
+
+def da_spmm_column_sums_workspace(rows, n) -> int:
+    out = ctypes.c_size_t(0)
+    _check(int(_lib.da_spmm_column_sums_workspace(int(rows), int(n), ctypes.byref(out))))
+    return int(out.value)
+
+
+def da_spmm_column_sums(rows, n, G, ldg, sums, workspace, workspace_bytes, stream=None) -> None:
+    _check(int(_lib.da_spmm_column_sums(int(rows), int(n), _ptr(G), int(ldg), _ptr(sums), _ptr(workspace),
+                                        int(workspace_bytes), _stream(stream))))
+
+
+def da_spmm_bias_relu(rows, n, Z, bias, relu, stream=None) -> None:
+    _check(int(_lib.da_spmm_bias_relu(int(rows), int(n), _ptr(Z), _ptr(bias), int(bool(relu)), _stream(stream))))
+
+
+def da_spmm_dense(rows, k, n, A, lda, W, wk, wn, C, ldc, stream=None) -> None:
+    """C = A . W for a tall A and a small W with element strides (wk, wn); see include/da_spmm.h."""
+    _check(int(_lib.da_spmm_dense(int(rows), int(k), int(n), _ptr(A), int(lda), _ptr(W), int(wk), int(wn), _ptr(C), int(ldc),
+                                  _stream(stream))))
 
 
 def da_spmm_algo_name(algo: int):

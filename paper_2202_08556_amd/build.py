@@ -53,12 +53,14 @@ def build_native(verbose: bool = False) -> str:
     import torch
     tdir = os.path.dirname(os.path.abspath(torch.__file__))
     tmp = NATIVE + ".tmp%d" % os.getpid()
-    cmd = [hipcc(), "--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1",
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    cmd = [hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+           "-isystem", os.path.join(rocm, "include"), "-DTORCH_EXTENSION_NAME=_native",
            "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
-           "-I" + os.path.join(tdir, "include"), "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(tdir, "include"), "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
            os.path.join(CSRC, "native.cpp"), "-o", tmp,
-           "-L" + PKG, "-ldaspmm", "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
-           "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(tdir, "lib")]
+           "-L" + PKG, "-ldaspmm", "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu",
+           "-ltorch_hip", "-lc10", "-lc10_hip", "-lamdhip64", "-L" + os.path.join(rocm, "lib"), "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + os.path.join(tdir, "lib")]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

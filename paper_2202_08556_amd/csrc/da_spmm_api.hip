@@ -4,7 +4,9 @@
 #include "da_spmm.h"
 #include "da_spmm_kernels.hip"
 #include "da_transpose_kernels.hip"
+#include "da_dense_kernels.hip"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -1085,6 +1087,155 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
         old = std::move(slot->block);
         *slot = pl;
     }
+    return DA_OK;
+}
+
+namespace {
+constexpr int kDenseMaxLds = 144 << 10;
+
+// Row blocks of the weight gradient: two blocks to a CU over all tiles, and no fewer than 64 rows each.
+int weight_grad_blocks(int64_t rows, int64_t tiles) {
+    int64_t nb = 2 * cu_count() / tiles;
+    const int64_t most = (rows + 63) / 64;
+    if (nb > most) nb = most;
+    return (int)(nb < 1 ? 1 : nb);
+}
+int64_t weight_grad_tiles(int64_t fin, int64_t fout) {
+    return ((fin + kWgTile - 1) / kWgTile) * ((fout + kWgTile - 1) / kWgTile);
+}
+}  // namespace
+
+int da_spmm_weight_grad_workspace(int64_t rows, int64_t fin, int64_t fout, size_t* bytes)
+{
+    if (!bytes) return fail(DA_ERR_INVALID_ARG, "null bytes%s");
+    if (rows < 0 || fin < 0 || fout < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
+    if (rows > 0x7fffffffLL || fin > (1 << 20) || fout > (1 << 20)) return fail(DA_ERR_INVALID_ARG, "size too large%s");
+    const int64_t tiles = weight_grad_tiles(fin, fout);
+    *bytes = tiles == 0 ? 0 : (size_t)tiles * weight_grad_blocks(rows, tiles) * kWgPart * sizeof(float);
+    return DA_OK;
+}
+
+int da_spmm_weight_grad(int64_t rows, int64_t fin, int64_t fout, const float* X, int64_t ldx, const float* G, int64_t ldg,
+                        float* dW, void* workspace, size_t workspace_bytes, void* stream)
+{
+    size_t need = 0;
+    const int st = da_spmm_weight_grad_workspace(rows, fin, fout, &need);
+    if (st != DA_OK) return st;
+    if (fin < 4 || fout < 4) return fail(DA_ERR_UNSUPPORTED, "fewer than 4 columns%s");
+    if (rows < 1) return fail(DA_ERR_UNSUPPORTED, "no rows%s");
+    if (ldx < fin || ldg < fout) return fail(DA_ERR_INVALID_ARG, "leading dimension smaller than the extent it strides over%s");
+    if (!X || !G || !dW) return fail(DA_ERR_INVALID_ARG, "null X, G or dW%s");
+    if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
+        return fail(DA_ERR_INVALID_ARG, "workspace missing, misaligned or smaller than da_spmm_weight_grad_workspace reports%s");
+    const int64_t tiles = weight_grad_tiles(fin, fout);
+    if (tiles > kMaxGridY) return fail(DA_ERR_UNSUPPORTED, "more than 65535 tiles%s");
+    const int nb = weight_grad_blocks(rows, tiles);
+    const int64_t per = ((rows + nb - 1) / nb + 15) / 16 * 16;      // whole turns of a wave, 16 rows
+    hipStream_t s = (hipStream_t)stream;
+    float* part = static_cast<float*>(workspace);
+    hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)nb, (unsigned)tiles), dim3(kWgBlock), 0, s, (int)rows, (int)fin,
+                       (int)fout, X, (long)ldx, G, (long)ldg, (int)per, part);
+    hipLaunchKernelGGL(weight_grad_sum_kernel, dim3(kWgTile, (unsigned)tiles), dim3(1024), 0, s, part, nb, (int)fin,
+                       (int)fout, dW);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_weight_grad launch");
+    return DA_OK;
+}
+
+// Row blocks of the column sums, and columns per block
+static int column_sums_blocks(int64_t rows) {
+    int64_t nb = 2 * cu_count();
+    const int64_t most = (rows + 63) / 64;
+    if (nb > most) nb = most;
+    return (int)(nb < 1 ? 1 : nb);
+}
+
+int da_spmm_column_sums_workspace(int64_t rows, int64_t n, size_t* bytes)
+{
+    if (!bytes) return fail(DA_ERR_INVALID_ARG, "null bytes%s");
+    if (rows < 0 || n < 0 || rows > 0x7fffffffLL || n > (1 << 22)) return fail(DA_ERR_INVALID_ARG, "bad size%s");
+    *bytes = (size_t)column_sums_blocks(rows) * (size_t)n * sizeof(float);
+    return DA_OK;
+}
+
+int da_spmm_column_sums(int64_t rows, int64_t n, const float* G, int64_t ldg, float* sums, void* workspace,
+                        size_t workspace_bytes, void* stream)
+{
+    size_t need = 0;
+    const int st = da_spmm_column_sums_workspace(rows, n, &need);
+    if (st != DA_OK) return st;
+    if (n == 0) return DA_OK;
+    if (ldg < n) return fail(DA_ERR_INVALID_ARG, "leading dimension smaller than the extent it strides over%s");
+    if ((rows > 0 && !G) || !sums) return fail(DA_ERR_INVALID_ARG, "null G or sums%s");
+    if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
+        return fail(DA_ERR_INVALID_ARG, "workspace missing, misaligned or smaller than da_spmm_column_sums_workspace reports%s");
+    const int nb = column_sums_blocks(rows), lanes = n >= kCsBlock ? kCsBlock : pow2_ceil(n);
+    const int64_t ny = (n + lanes - 1) / lanes;
+    if (ny > kMaxGridY) return fail(DA_ERR_UNSUPPORTED, "too many columns%s");
+    const int per = (int)((rows + nb - 1) / nb);
+    hipStream_t s = (hipStream_t)stream;
+    float* part = static_cast<float*>(workspace);
+    hipLaunchKernelGGL(column_sums_kernel, dim3((unsigned)nb, (unsigned)ny), dim3(kCsBlock), 0, s, (int)rows, (int)n, lanes, G,
+                       (long)ldg, per, part);
+    hipLaunchKernelGGL(column_sums_sum_kernel, dim3((unsigned)((n + 63) / 64)), dim3(1024), 0, s, part, nb, (int)n, sums);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_column_sums launch");
+    return DA_OK;
+}
+
+int da_spmm_bias_relu(int64_t rows, int64_t n, float* Z, const float* bias, int relu, void* stream)
+{
+    if (rows < 0 || n < 0 || n > 0x7fffffffLL) return fail(DA_ERR_INVALID_ARG, "bad size%s");
+    if (rows == 0 || n == 0 || (!bias && !relu)) return DA_OK;
+    if (!Z) return fail(DA_ERR_INVALID_ARG, "null Z%s");
+    long blocks = (rows * n / 4 + 255) / 256;
+    const long most = (long)cu_count() * 16;
+    if (blocks > most) blocks = most;
+    if (blocks < 1) blocks = 1;
+    hipLaunchKernelGGL(bias_relu_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, (long)rows, (int)n, Z, bias, relu);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_bias_relu launch");
+    return DA_OK;
+}
+
+int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float* A, int64_t lda, const float* W, int64_t wk, int64_t wn,
+                  float* C, int64_t ldc, void* stream)
+{
+    if (rows < 0 || k < 0 || n < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
+    if (rows > 0x7fffffffLL || k > (1 << 20) || n > (1 << 20)) return fail(DA_ERR_INVALID_ARG, "size too large%s");
+    if (rows == 0 || n == 0) return DA_OK;
+    if (k < 1) return fail(DA_ERR_UNSUPPORTED, "no columns in A%s");
+    if (lda < k || ldc < n || wk < 1 || wn < 1) return fail(DA_ERR_INVALID_ARG, "leading dimension smaller than the extent it strides over%s");
+    if (!A || !W || !C) return fail(DA_ERR_INVALID_ARG, "null A, W or C%s");
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t widest = n <= 128 ? (n + 15) / 16 * 16 : 128;
+    if (k > 256 || (size_t)widest * dense_pitch((int)k) * sizeof(float) > (size_t)kDenseMaxLds)
+        return fail(DA_ERR_UNSUPPORTED, "weight matrix beyond what a block keeps in LDS%s");
+    auto go = [&](auto nt, auto kmax) {
+        constexpr int NT = decltype(nt)::value, KS = decltype(kmax)::value;
+        const size_t lds = dense_lds<NT>((int)k);
+        // blocks that are resident together (LDS, and 3 of 4 waves per SIMD by registers), each wave with
+        // several sets of rows if there are as many
+        const int64_t resident = (int64_t)cu_count() * std::min<int64_t>(3, (160 << 10) / (int64_t)lds);
+        const int64_t ny = (n + 16 * NT - 1) / (16 * NT);
+        int64_t nx = (rows + 63) / 64;
+        if (nx * ny > resident) nx = std::max<int64_t>(1, resident / ny);
+        hipLaunchKernelGGL((dense_product_kernel<NT, KS>), dim3((unsigned)nx, (unsigned)ny), dim3(kDpBlock), lds, s, (int)rows,
+                           (int)n, (int)k, A, (long)lda, W, (long)wk, (long)wn, C, (long)ldc);
+    };
+    auto by_k = [&](auto nt) {
+        if (k <= 64) go(nt, Count<4>{});
+        else if (k <= 128) go(nt, Count<8>{});
+        else go(nt, Count<16>{});
+    };
+    if (n <= 16) by_k(Count<1>{});
+    else if (n <= 32) by_k(Count<2>{});
+    else if (n <= 48) by_k(Count<3>{});
+    else if (n <= 64) by_k(Count<4>{});
+    else if (n <= 96) by_k(Count<6>{});
+    else by_k(Count<8>{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_dense launch");
     return DA_OK;
 }
 

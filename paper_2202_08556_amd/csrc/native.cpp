@@ -1,16 +1,35 @@
-// Python module `_native`: the product and transpose calls of the C ABI for a Python program, without
-// ctypes.  A small product takes 3 to 5 us on the device; marshalling its ten arguments in Python
-// (int(), data_ptr(), current_stream(), ctypes conversions) took longer than the product itself, so
-// the host set the pace: da_spmm on a 4096-row matrix with N = 8 ran at 7.8 us a call.  Here a call is
-// one C function that unpacks the arguments in place; everything else (checks, geometry, launch) is
-// behind the C ABI as before.  No device code.
+// Python module `_native`: what a Python program does for every call, in C++.
+//
+// (1) The product and transpose calls of the C ABI without ctypes.  A small product takes 3 to 5 us on the
+// device; marshalling its ten arguments in Python (int(), data_ptr(), current_stream(), ctypes
+// conversions) took longer than the product itself, so the host set the pace: da_spmm on a 4096-row matrix
+// with N = 8 ran at 7.8 us a call.
+//
+// (2) Graphs and graph-convolution layers (gcn.py holds their Python side): the matrix with what is known
+// of it, the aggregation A . X with gradient A^T . dY, and the layer relu(A . (X . W) + b), each forward
+// and backward one C++ function with one autograd node.  On graphs of a few thousand nodes the device
+// needs 20 to 60 us for a layer; separate operations, each with its own Python call and node, took 80 to
+// 190 us of host time.
+//
+// No device code here; all work goes through the C ABI (and, for large dense products, the GEMM library).
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <ATen/ATen.h>
+#include <ATen/autocast_mode.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/utils/pybind.h>
 
 #include <exception>
+#include <memory>
+#include <mutex>
+#include <vector>
 
 #include "da_spmm.h"
 
@@ -194,6 +213,334 @@ PyObject* py_setup(PyObject*, PyObject* args) {
     Py_RETURN_NONE;
 }
 
+// ------------------------------------------------------------------------------------------
+// graphs
+// ------------------------------------------------------------------------------------------
+using at::Tensor;
+
+// A failed call of the C ABI, to be raised as binding.DaSpmmError
+struct DaError : std::exception {
+    int status;
+    std::string text;
+    explicit DaError(int st) : status(st), text(da_spmm_last_error()) {}
+    const char* what() const noexcept override { return text.c_str(); }
+};
+
+void check(int status) {
+    if (status != DA_OK) throw DaError(status);
+}
+
+void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+
+template <class T> T* data(const Tensor& t) { return t.defined() ? static_cast<T*>(t.data_ptr()) : nullptr; }
+
+// Distance between the rows of a dense operand that this module lays out itself.  A row that is not whole
+// 64-byte pieces touches one cache line more on average: with N = 41 a gathered row of B costs 2.3 lines of
+// 128 bytes at a distance of 41 and 2 at 48 (power-law graph of 262 144 nodes: 245 and 219 us).
+int64_t row_pitch(int64_t n) {
+    if (n <= 4) return n;
+    if (n <= 8) return 8;
+    return (n + 15) / 16 * 16;
+}
+
+struct Graph : std::enable_shared_from_this<Graph> {
+    int64_t m, k, nnz;
+    Tensor rowptr, colind, vals;
+    std::recursive_mutex mu;                  // what follows is filled in by the first calls that need it
+    bool have_features = false, prepared = false;
+    int eb_products = 0;
+    da_features features{};
+    std::vector<std::pair<int64_t, int>> algo;
+    std::shared_ptr<Graph> t;
+    std::weak_ptr<Graph> t_of;
+
+    Graph(int64_t m_, int64_t k_, Tensor rp, Tensor ci, Tensor va)
+        : m(m_), k(k_), nnz(ci.numel()), rowptr(rp.contiguous()), colind(ci.contiguous()), vals(va.contiguous()) {}
+    ~Graph() {
+        if (prepared) da_spmm_release(data<int32_t>(rowptr));
+    }
+
+    const da_features& known() {
+        std::lock_guard<std::recursive_mutex> lk(mu);
+        if (!have_features) {                 // one device reduction per graph
+            c10::DeviceGuard guard(rowptr.device());
+            check(da_spmm_features(m, 1, data<int32_t>(rowptr), stream_of(rowptr), &features));
+            have_features = true;
+        }
+        return features;
+    }
+
+    int algo_for(int64_t N) {
+        std::lock_guard<std::recursive_mutex> lk(mu);
+        for (const auto& a : algo)
+            if (a.first == N) return a.second;
+        da_features f = known();
+        f.N = N;
+        const int id = da_spmm_select(&f);
+        if (id < 0) throw DaError(-id);
+        algo.emplace_back(N, id);
+        return id;
+    }
+
+    void prepare() {
+        std::lock_guard<std::recursive_mutex> lk(mu);
+        if (prepared) return;
+        check(da_spmm_prepare(m, k, nnz, data<int32_t>(rowptr), data<int32_t>(colind), stream_of(rowptr)));
+        prepared = true;
+    }
+
+    std::shared_ptr<Graph> transposed() {
+        std::lock_guard<std::recursive_mutex> lk(mu);
+        if (auto back = t_of.lock()) return back;
+        if (!t) {
+            c10::DeviceGuard guard(rowptr.device());
+            Tensor trp = at::empty({k + 1}, rowptr.options()), tci = at::empty({nnz}, colind.options()),
+                   tva = at::empty({nnz}, vals.options());
+            size_t bytes = 0;
+            check(da_csr_transpose_workspace(m, k, nnz, &bytes));
+            // scratch of the call; torch allocations are 512-byte aligned and the caching allocator keeps the
+            // block alive for work already queued on this stream
+            Tensor ws = at::empty({(int64_t)bytes}, rowptr.options().dtype(at::kByte));
+            check(da_csr_transpose(m, k, nnz, data<int32_t>(rowptr), data<int32_t>(colind), data<float>(vals),
+                                   data<int32_t>(trp), data<int32_t>(tci), data<float>(tva), data<void>(ws), bytes,
+                                   stream_of(rowptr)));
+            t = std::make_shared<Graph>(k, m, trp, tci, tva);
+            t->t_of = weak_from_this();
+        }
+        return t;
+    }
+
+    // A . X for X with unit column stride.  The matrix is prepared (chunk order of the EB algorithms) before the
+    // second product with an EB algorithm that the selector chose, and before the first one the caller chose.
+    Tensor product(const Tensor& X, int64_t N, int id) {
+        c10::DeviceGuard guard(rowptr.device());
+        const bool chosen = id < 0;
+        if (chosen) id = algo_for(N);
+        if (id >= DA_EB_RM_SR && !prepared) {
+            std::lock_guard<std::recursive_mutex> lk(mu);
+            if (!chosen || eb_products > 0) prepare();
+            ++eb_products;
+        }
+        Tensor C = at::empty({m, N}, vals.options());
+        check(da_spmm_ex(m, k, N, data<int32_t>(rowptr), data<int32_t>(colind), data<float>(vals), data<float>(X),
+                         X.stride(0), DA_ROW_MAJOR, data<float>(C), N, DA_ROW_MAJOR, id, stream_of(rowptr)));
+        return C;
+    }
+};
+using GraphPtr = std::shared_ptr<Graph>;
+
+GraphPtr make_graph(int64_t m, int64_t k, const Tensor& rowptr, const Tensor& colind, const Tensor& vals) {
+    if (rowptr.scalar_type() != at::kInt || colind.scalar_type() != at::kInt || vals.scalar_type() != at::kFloat)
+        throw py::type_error("rowptr / colind must be int32 and vals float32");
+    if (!(rowptr.is_cuda() && colind.is_cuda() && vals.is_cuda())) throw py::value_error("CSR arrays must live on the GPU");
+    if (rowptr.numel() != m + 1 || colind.numel() != vals.numel()) throw py::value_error("CSR array sizes do not match");
+    return std::make_shared<Graph>(m, k, rowptr, colind, vals);
+}
+
+// X as the product takes it: float32, k rows, neighbouring columns
+Tensor operand(const Graph& g, const Tensor& X) {
+    if (X.scalar_type() != at::kFloat || X.dim() != 2 || X.size(0) != g.k) throw py::value_error("X must be a float32 k x N tensor");
+    return X.contiguous();
+}
+
+struct AggregateBackward : torch::autograd::Node {
+    GraphPtr graph;
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        if (!grads[0].defined() || !task_should_compute_output(0)) return {Tensor()};
+        at::AutoDispatchBelowADInplaceOrView below;
+        const auto t = graph->transposed();
+        const Tensor dY = operand(*t, grads[0].detach());
+        return {t->product(dY, dY.size(1), -1)};
+    }
+    std::string name() const override { return "AggregateBackward"; }
+};
+
+bool wants_grad(const Tensor& t) { return t.defined() && t.requires_grad(); }
+
+Tensor aggregate(const GraphPtr& g, const Tensor& X, int id) {
+    const Tensor x = operand(*g, X);
+    Tensor Y;
+    {
+        at::AutoDispatchBelowADInplaceOrView below;
+        Y = g->product(x, x.size(1), id);
+    }
+    if (at::GradMode::is_enabled() && wants_grad(X)) {
+        auto node = std::shared_ptr<AggregateBackward>(new AggregateBackward(), torch::autograd::deleteNode);
+        node->graph = g;
+        node->set_next_edges(torch::autograd::collect_next_edges(X));
+        torch::autograd::set_history(Y, node);
+    }
+    return Y;
+}
+
+// A . W, into `out` (unit column stride).  The own kernel keeps W in LDS: it wins while the inner dimension is
+// at most 128 and, whatever the size, where the GEMM library's 18 us of host time are the larger part.
+void dense_product(const Tensor& A, const Tensor& W, bool transpose_w, Tensor& out) {
+    const int64_t rows = A.size(0), k = A.size(1), n = out.size(1);
+    if (k >= 1 && (k <= 128 || (k <= 256 && rows * k * n <= 300000000)) && A.stride(1) == 1 && W.is_contiguous()) {
+        const int st = da_spmm_dense(rows, k, n, data<float>(A), A.stride(0), data<float>(W), transpose_w ? 1 : n,
+                                     transpose_w ? k : 1, data<float>(out), out.stride(0), stream_of(A));
+        if (st != DA_ERR_UNSUPPORTED) return check(st);
+    }
+    at::mm_out(out, A, transpose_w ? W.t() : W);
+}
+
+Tensor weight_gradient(const Tensor& X, const Tensor& G) {
+    const int64_t rows = X.size(0), fin = X.size(1), fout = G.size(1);
+    if (rows >= 1 && fin >= 4 && fout >= 4 && X.stride(1) == 1 && G.stride(1) == 1) {
+        size_t bytes = 0;
+        check(da_spmm_weight_grad_workspace(rows, fin, fout, &bytes));
+        Tensor dW = at::empty({fin, fout}, X.options());
+        Tensor ws = at::empty({(int64_t)bytes}, X.options().dtype(at::kByte));
+        check(da_spmm_weight_grad(rows, fin, fout, data<float>(X), X.stride(0), data<float>(G), G.stride(0), data<float>(dW),
+                                  data<void>(ws), bytes, stream_of(X)));
+        return dW;
+    }
+    return at::mm(X.t(), G);
+}
+
+Tensor column_sums(const Tensor& G) {
+    size_t bytes = 0;
+    check(da_spmm_column_sums_workspace(G.size(0), G.size(1), &bytes));
+    Tensor sums = at::empty({G.size(1)}, G.options());
+    Tensor ws = at::empty({(int64_t)bytes}, G.options().dtype(at::kByte));
+    check(da_spmm_column_sums(G.size(0), G.size(1), data<float>(G), G.stride(0), data<float>(sums), data<void>(ws), bytes,
+                              stream_of(G)));
+    return sums;
+}
+
+// Z = A . (X . W) + b, out = relu(Z):  dZ = dY where out > 0;  db = column sums of dZ;  dH = A^T . dZ;
+// dW = X^T . dH;  dX = dH . W^T
+struct GraphConvBackward : torch::autograd::Node {
+    GraphPtr graph;
+    torch::autograd::SavedVariable x, w, out;
+    bool relu = false;
+
+    void release_variables() override {
+        std::lock_guard<std::mutex> lk(mutex_);
+        x.reset_data();
+        w.reset_data();
+        out.reset_data();
+    }
+
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        torch::autograd::variable_list result(3);
+        if (!grads[0].defined()) return result;
+        Tensor X, W, Y;
+        {
+            std::lock_guard<std::mutex> lk(mutex_);
+            X = x.unpack();
+            W = w.unpack();
+            if (relu) Y = out.unpack(shared_from_this());
+        }
+        c10::DeviceGuard guard(graph->rowptr.device());
+        const bool again = at::GradMode::is_enabled();       // gradients of gradients: dense parts differentiable
+        Tensor dZ = relu ? at::threshold_backward(grads[0], Y, 0) : grads[0];
+        if (task_should_compute_output(2)) {
+            if (again) result[2] = dZ.sum(0);
+            else { at::AutoDispatchBelowADInplaceOrView below; result[2] = column_sums(dZ.contiguous()); }
+        }
+        if (!task_should_compute_output(0) && !task_should_compute_output(1)) return result;
+        Tensor dH;
+        {
+            at::AutoDispatchBelowADInplaceOrView below;
+            const auto t = graph->transposed();
+            dH = t->product(operand(*t, dZ.detach()), dZ.size(1), -1);
+        }
+        if (again) {
+            if (task_should_compute_output(1)) result[1] = at::mm(X.t(), dH);
+            if (task_should_compute_output(0)) result[0] = at::mm(dH, W.t());
+            return result;
+        }
+        at::AutoDispatchBelowADInplaceOrView below;
+        if (task_should_compute_output(1)) result[1] = weight_gradient(X, dH);
+        if (task_should_compute_output(0)) {
+            result[0] = at::empty({X.size(0), X.size(1)}, X.options());
+            dense_product(dH, W, true, result[0]);
+        }
+        return result;
+    }
+    std::string name() const override { return "GraphConvBackward"; }
+};
+
+Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std::optional<Tensor>& bias, bool relu) {
+    const Tensor b = bias.value_or(Tensor());
+    Tensor Z;
+    const int64_t n = W.size(1);
+    {
+        at::AutoDispatchBelowADInplaceOrView below;
+        c10::DeviceGuard guard(g->rowptr.device());
+        Tensor H = at::empty({X.size(0), row_pitch(n)}, X.options()).narrow(1, 0, n);
+        dense_product(X, W, false, H);
+        Z = g->product(H, n, -1);
+        check(da_spmm_bias_relu(g->m, n, data<float>(Z), data<float>(b), relu ? 1 : 0, stream_of(Z)));
+    }
+    if (at::GradMode::is_enabled() && (wants_grad(X) || wants_grad(W) || wants_grad(b))) {
+        auto node = std::shared_ptr<GraphConvBackward>(new GraphConvBackward(), torch::autograd::deleteNode);
+        node->graph = g;
+        node->relu = relu;
+        node->x = torch::autograd::SavedVariable(X, false);
+        node->w = torch::autograd::SavedVariable(W, false);
+        node->set_next_edges(torch::autograd::collect_next_edges(X, W, b));
+        torch::autograd::set_history(Z, node);
+        if (relu) node->out = torch::autograd::SavedVariable(Z, true);
+    }
+    return Z;
+}
+
+// Whether graph_conv takes these operands as they are (anything else goes the way of separate operations)
+bool graph_conv_takes(const GraphPtr& g, const Tensor& X, const Tensor& W, const std::optional<Tensor>& bias) {
+    auto plain = [&](const Tensor& t, int64_t dim) {
+        return t.scalar_type() == at::kFloat && t.dim() == dim && t.is_contiguous() && t.layout() == at::kStrided &&
+               t.device() == g->rowptr.device() && !t.is_neg() && !t.unsafeGetTensorImpl()->is_python_dispatch();
+    };
+    if (at::autocast::is_autocast_enabled(at::kCUDA)) return false;
+    return plain(X, 2) && plain(W, 2) && X.size(0) == g->k && X.size(1) == W.size(0) && W.size(1) >= 1 && X.size(1) >= 1 &&
+           g->m >= 1 && (!bias || (plain(*bias, 1) && bias->size(0) == W.size(1)));
+}
+
+void bind_graphs(py::module_& mod) {
+    py::register_exception_translator([](std::exception_ptr p) {
+        try {
+            if (p) std::rethrow_exception(p);
+        } catch (const DaError& e) {
+            py::object err = py::reinterpret_borrow<py::object>(g_error)(e.status, e.text);
+            PyErr_SetObject(g_error, err.ptr());
+        }
+    });
+    using release = py::call_guard<py::gil_scoped_release>;
+    py::class_<Graph, GraphPtr>(mod, "Graph")
+        .def(py::init(&make_graph))
+        .def_readonly("m", &Graph::m)
+        .def_readonly("k", &Graph::k)
+        .def_readonly("nnz", &Graph::nnz)
+        .def_readonly("rowptr", &Graph::rowptr)
+        .def_readonly("colind", &Graph::colind)
+        .def_readonly("vals", &Graph::vals)
+        .def_readonly("prepared", &Graph::prepared)
+        .def("features", [](Graph& g) {
+            da_features f;
+            { py::gil_scoped_release r; f = g.known(); }
+            return py::make_tuple(f.rows, f.nnz, f.row_nnz_mean, f.row_nnz_std, f.row_nnz_max);
+        })
+        .def("algo_for", &Graph::algo_for, release())
+        .def("prepare", &Graph::prepare, release())
+        .def("transposed", &Graph::transposed, release())
+        .def("spmm", [](Graph& g, const Tensor& X, int id) {
+            const Tensor x = operand(g, X);
+            py::gil_scoped_release r;
+            at::AutoDispatchBelowADInplaceOrView below;
+            return g.product(x, x.size(1), id);
+        });
+    mod.def("aggregate", [](const GraphPtr& g, const Tensor& X) {
+        const Tensor x = operand(*g, X);      // errors are Python exceptions: raised with the lock held
+        py::gil_scoped_release r;
+        return aggregate(g, X, -1);
+    });
+    mod.def("graph_conv", &graph_conv, release());
+    mod.def("graph_conv_takes", &graph_conv_takes);
+}
+
 PyMethodDef kMethods[] = {
     {"setup", py_setup, METH_VARARGS, nullptr},
     {"da_spmm", (PyCFunction)(void (*)(void))py_spmm, METH_FASTCALL | METH_KEYWORDS,
@@ -213,4 +560,16 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_native", "Calls of the da_spmm C
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__native(void) { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit__native(void) {
+    PyObject* m = PyModule_Create(&kModule);
+    if (!m) return nullptr;
+    try {
+        auto mod = py::reinterpret_borrow<py::module_>(m);
+        bind_graphs(mod);
+    } catch (const std::exception& e) {
+        Py_DECREF(m);
+        PyErr_SetString(PyExc_ImportError, e.what());
+        return nullptr;
+    }
+    return m;
+}
