@@ -237,8 +237,8 @@ int da_csr_transpose(int64_t m, int64_t k, int64_t nnz,
  * (32 MiB) that every GPU the library is loaded on holds until the process ends.  The call
  * allocates and frees nothing and does not synchronise; it skips the DA_SPMM_DEBUG_VALIDATE check
  * (which allocates).
- * Limit: da_csr_transpose_workspace(m, k, nnz) must not exceed DA_NOALLOC_SCRATCH_BYTES (about
- * 1.39 million stored entries); beyond it the call returns DA_ERR_UNSUPPORTED, enqueues nothing
+ * Limit: the general sort's scratch must not exceed DA_NOALLOC_SCRATCH_BYTES (24 bytes per stored
+ * entry and its histograms, about 1.39 million entries); beyond it the call returns DA_ERR_UNSUPPORTED, enqueues nothing
  * and the last-error text says so.
  * All calls on one GPU share that GPU's array: calls whose execution can overlap on one GPU
  * (different streams, different host threads) race on it -- order them on one stream or with

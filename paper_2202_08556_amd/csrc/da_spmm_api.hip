@@ -488,10 +488,12 @@ int enqueue_transpose(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, 
                       const float* vals, int32_t* t_rowptr, int32_t* t_colind, float* t_vals,
                       void* workspace, size_t workspace_bytes, void* stream);
 
-// The size every transpose asks for, whichever way it then goes
+// The size a transpose asks for.  The general sort's size is all that it needs: where the packed passes
+// would take more and are not given it, they leave the call to the general sort.
 size_t transpose_workspace_bytes(int64_t m, int64_t k, int64_t nnz) {
-    const size_t a = plan_transpose(k, nnz).bytes, b = plan_transpose_fast(m, k, nnz).bytes;
-    return a > b ? a : b;
+    const size_t a = plan_transpose(k, nnz).bytes;
+    const TransposeFast f = plan_transpose_fast(m, k, nnz);
+    return f.usable && f.bytes > a ? f.bytes : a;
 }
 
 // Scratch memory of the entry point that allocates nothing (da_csr_transpose_noalloc): a static
@@ -751,7 +753,7 @@ int da_csr_transpose_noalloc(int64_t m, int64_t k, int64_t nnz, const int32_t* r
 {
     const int st = check_transpose_args(m, k, nnz, rowptr, colind, vals, t_rowptr, t_colind, t_vals);
     if (st != DA_OK) return st;
-    if (transpose_workspace_bytes(m, k, nnz) > kScratchBytes)
+    if (plan_transpose(k, nnz).bytes > kScratchBytes)
         return fail(DA_ERR_UNSUPPORTED,
                     "da_csr_transpose_noalloc: the sort needs more than the library's 32 MiB static scratch "
                     "(about 24 bytes per stored entry); use da_csr_transpose with a workspace%s");
@@ -822,13 +824,13 @@ int enqueue_transpose(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, 
                       const float* vals, int32_t* t_rowptr, int32_t* t_colind, float* t_vals,
                       void* workspace, size_t workspace_bytes, void* stream)
 {
-    if (nnz > 0 && (!workspace || workspace_bytes < transpose_workspace_bytes(m, k, nnz)))
+    if (nnz > 0 && (!workspace || workspace_bytes < plan_transpose(k, nnz).bytes))
         return fail(DA_ERR_INVALID_ARG, "workspace missing or smaller than da_csr_transpose_workspace reports%s");
     if (nnz > 0 && reinterpret_cast<uintptr_t>(workspace) % 256 != 0)
         return fail(DA_ERR_INVALID_ARG, "workspace is not 256-byte aligned%s");
     if (nnz > 0) {
         const TransposeFast f = plan_transpose_fast(m, k, nnz);
-        if (f.usable) {
+        if (f.usable && f.bytes <= workspace_bytes) {
             TransposePass P{};
             P.colind = colind; P.rowptr = rowptr; P.vals_in = vals; P.t_colind = t_colind;
             P.m = (int)m; P.n = (int)nnz; P.row_bits = f.row_bits;

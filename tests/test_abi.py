@@ -53,6 +53,13 @@ def test_argument_errors_without_device_work():
         da.da_spmm(4, 4, 4, None, None, None, None, None, 0, stream=0)
 
 
+@pytest.mark.parametrize("m,k,nnz", [(5878, 102439736, 272761), (435, 194910804, 365377), (919930, 69790531, 434425)])
+def test_wide_transposes_fit_the_static_scratch(m, k, nnz):
+    """Matrices too wide for the packed passes take the general sort and need no more than its 24 bytes an entry
+    and histograms: these fit the scratch array of da_csr_transpose_noalloc."""
+    assert 24 * nnz <= da.da_csr_transpose_workspace(m, k, nnz) <= 32 << 20
+
+
 def test_transpose_argument_errors_without_device_work():
     assert da.da_csr_transpose_workspace(10, 10, 0) >= 0
     big = da.da_csr_transpose_workspace(1 << 20, 1 << 20, 1 << 24)
