@@ -16,14 +16,17 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/autocast_mode.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/csrc/utils/pybind.h>
 
 #include <exception>
@@ -340,8 +343,27 @@ GraphPtr make_graph(int64_t m, int64_t k, const Tensor& rowptr, const Tensor& co
 // X as the product takes it: float32, k rows, neighbouring columns
 Tensor operand(const Graph& g, const Tensor& X) {
     if (X.scalar_type() != at::kFloat || X.dim() != 2 || X.size(0) != g.k) throw py::value_error("X must be a float32 k x N tensor");
-    return X.contiguous();
+    return X.resolve_neg().contiguous();
 }
+
+// Whether torch does nothing around an operation but differentiate backwards: no tracer that records, no mode
+// and no function transform that intercepts
+bool ordinary_context() {
+    return !torch::jit::tracer::isTracing() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
+           !at::impl::torch_function_mode_enabled() &&
+           !c10::impl::tls_is_dispatch_key_included(c10::DispatchKey::FuncTorchDynamicLayerFrontMode);
+}
+
+// Whether a tensor is its memory and nothing else: no wrapper, no lazy negation, no tangent
+bool ordinary(const Tensor& t) {
+    constexpr c10::DispatchKeySet wrapped(
+        {c10::DispatchKey::Python, c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::FuncTorchGradWrapper,
+         c10::DispatchKey::Functionalize, c10::DispatchKey::Negative, c10::DispatchKey::Conjugate, c10::DispatchKey::ZeroTensor});
+    return t.layout() == at::kStrided && !t.key_set().has_any(wrapped) && !t._fw_grad(0).defined();
+}
+
+// ... and its Python object is a Tensor or Parameter, no subclass that overrides operations
+bool ordinary(py::handle x) { return THPVariable_CheckExact(x.ptr()) && ordinary(THPVariable_Unpack(x.ptr())); }
 
 struct AggregateBackward : torch::autograd::Node {
     GraphPtr graph;
@@ -426,6 +448,7 @@ struct GraphConvBackward : torch::autograd::Node {
     torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
         torch::autograd::variable_list result(3);
         if (!grads[0].defined()) return result;
+        const Tensor dY = grads[0].resolve_neg();
         Tensor X, W, Y;
         {
             std::lock_guard<std::mutex> lk(mutex_);
@@ -435,7 +458,7 @@ struct GraphConvBackward : torch::autograd::Node {
         }
         c10::DeviceGuard guard(graph->rowptr.device());
         const bool again = at::GradMode::is_enabled();       // gradients of gradients: dense parts differentiable
-        Tensor dZ = relu ? at::threshold_backward(grads[0], Y, 0) : grads[0];
+        Tensor dZ = relu ? at::threshold_backward(dY, Y, 0) : dY;
         if (task_should_compute_output(2)) {
             if (again) result[2] = dZ.sum(0);
             else { at::AutoDispatchBelowADInplaceOrView below; result[2] = column_sums(dZ.contiguous()); }
@@ -489,14 +512,16 @@ Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std
 }
 
 // Whether graph_conv takes these operands as they are (anything else goes the way of separate operations)
-bool graph_conv_takes(const GraphPtr& g, const Tensor& X, const Tensor& W, const std::optional<Tensor>& bias) {
+bool graph_conv_takes(const GraphPtr& g, py::handle x, py::handle w, py::handle bias) {
+    if (!ordinary_context() || at::autocast::is_autocast_enabled(at::kCUDA)) return false;
+    if (!ordinary(x) || !ordinary(w) || !(bias.is_none() || ordinary(bias))) return false;
     auto plain = [&](const Tensor& t, int64_t dim) {
-        return t.scalar_type() == at::kFloat && t.dim() == dim && t.is_contiguous() && t.layout() == at::kStrided &&
-               t.device() == g->rowptr.device() && !t.is_neg() && !t.unsafeGetTensorImpl()->is_python_dispatch();
+        return t.scalar_type() == at::kFloat && t.dim() == dim && t.is_contiguous() && t.device() == g->rowptr.device();
     };
-    if (at::autocast::is_autocast_enabled(at::kCUDA)) return false;
+    const Tensor &X = THPVariable_Unpack(x.ptr()), &W = THPVariable_Unpack(w.ptr());
     return plain(X, 2) && plain(W, 2) && X.size(0) == g->k && X.size(1) == W.size(0) && W.size(1) >= 1 && X.size(1) >= 1 &&
-           g->m >= 1 && (!bias || (plain(*bias, 1) && bias->size(0) == W.size(1)));
+           g->m >= 1 && (bias.is_none() || (plain(THPVariable_Unpack(bias.ptr()), 1) &&
+                                            THPVariable_Unpack(bias.ptr()).size(0) == W.size(1)));
 }
 
 void bind_graphs(py::module_& mod) {
@@ -511,12 +536,12 @@ void bind_graphs(py::module_& mod) {
     using release = py::call_guard<py::gil_scoped_release>;
     py::class_<Graph, GraphPtr>(mod, "Graph")
         .def(py::init(&make_graph))
-        .def_readonly("m", &Graph::m)
-        .def_readonly("k", &Graph::k)
-        .def_readonly("nnz", &Graph::nnz)
-        .def_readonly("rowptr", &Graph::rowptr)
-        .def_readonly("colind", &Graph::colind)
-        .def_readonly("vals", &Graph::vals)
+        .def_readwrite("m", &Graph::m)
+        .def_readwrite("k", &Graph::k)
+        .def_readwrite("nnz", &Graph::nnz)
+        .def_readwrite("rowptr", &Graph::rowptr)
+        .def_readwrite("colind", &Graph::colind)
+        .def_readwrite("vals", &Graph::vals)
         .def_readonly("prepared", &Graph::prepared)
         .def("features", [](Graph& g) {
             da_features f;
@@ -537,6 +562,7 @@ void bind_graphs(py::module_& mod) {
         py::gil_scoped_release r;
         return aggregate(g, X, -1);
     });
+    mod.def("aggregate_takes", [](py::handle X) { return ordinary_context() && ordinary(X); });
     mod.def("graph_conv", &graph_conv, release());
     mod.def("graph_conv_takes", &graph_conv_takes);
 }

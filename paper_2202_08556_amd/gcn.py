@@ -32,13 +32,11 @@ class SparseGraph:
     order (speed), never the result."""
 
     def __init__(self, m: int, k: int, rowptr: torch.Tensor, colind: torch.Tensor, vals: torch.Tensor):
-        self._bind(_native.Graph(m, k, rowptr, colind, vals))
-
-    def _bind(self, g):
-        self._g = g
-        self.m, self.k, self.nnz = g.m, g.k, g.nnz
-        self.rowptr, self.colind, self.vals = g.rowptr, g.colind, g.vals
+        self._g = _native.Graph(m, k, rowptr, colind, vals)
         self._t = None
+
+    def __reduce__(self):
+        return type(self), (self.m, self.k, self.rowptr, self.colind, self.vals)
 
     @classmethod
     def from_numpy(cls, a, device="cuda:0") -> "SparseGraph":
@@ -63,7 +61,7 @@ class SparseGraph:
         """A^T as a SparseGraph (k x m); built once by da_csr_transpose."""
         if self._t is None:
             t = SparseGraph.__new__(SparseGraph)
-            t._bind(self._g.transposed())
+            t._g = self._g.transposed()
             t._t = self
             self._t = t
         return self._t
@@ -73,9 +71,39 @@ class SparseGraph:
         return self._g.spmm(X, -1 if algo is None else int(algo))
 
 
+def _field(name):
+    def get(self):
+        return getattr(self._g, name)
+
+    def put(self, value):
+        setattr(self._g, name, value)
+
+    return property(get, put)
+
+
+for _name in ("m", "k", "nnz", "rowptr", "colind", "vals"):
+    setattr(SparseGraph, _name, _field(_name))
+
+
+class _Aggregate(torch.autograd.Function):
+    """The aggregation where torch has more to do than backward differentiation (tracing, function
+    transforms, tangents, tensor subclasses, modes): the Function supports or refuses each of them."""
+
+    @staticmethod
+    def forward(ctx, X, graph):
+        ctx.graph = graph
+        return graph.spmm(X)
+
+    @staticmethod
+    def backward(ctx, dY):
+        return ctx.graph.transposed().spmm(dY), None
+
+
 def aggregate(graph: SparseGraph, X: torch.Tensor) -> torch.Tensor:
     """A . X with gradient A^T . dY with respect to X (A itself is a constant of the graph)."""
-    return _native.aggregate(graph._g, X)
+    if _native.aggregate_takes(X):
+        return _native.aggregate(graph._g, X)
+    return _Aggregate.apply(X, graph)
 
 
 class GraphConv(torch.nn.Module):
