@@ -213,20 +213,26 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides
     if (eb) {
         if (pr) g.chunk = kEntriesPerWavePR;
         else g.chunk = g.G >= 8 ? 256 : (g.G == 4 ? 128 : 64);
-        if (known_nnz >= 0 && plan.found && pr) {
+        if (known_nnz > kSmallPlanMaxNnz && plan.found && !pr && g.G >= 8 && plan.long_rows > 0.5) {
+            // Most entries lie in rows much longer than a chunk: every chunk is one more fp32 addition to the
+            // same few rows of C, and rounding errors grow with their number (33 M entries, rows of 60 000,
+            // N = 8: 4.5e-7 of the result at 128 entries, 5.8e-7 at 64, and 181 against 168 us; N = 64:
+            // 4.0e-7 at 256, 4.5e-7 at 128, both 462 us).  Small matrices need the workers instead: 1.2 M
+            // entries in rows of 12 000, N = 32: 65 us at 64 entries, 32 us at 32.
+            g.chunk = N <= 8 ? 128 : 256;
+        } else if (known_nnz >= 0 && plan.found && pr) {
             // a chunk size the plan has row hints for, and about 5 waves per SIMD
             while (g.chunk > 64 && g.chunk > known_nnz / ((long)cu_count() * 20)) g.chunk /= 2;
         } else if (known_nnz >= 0 && plan.found && g.G >= 8) {
             // With the plan's row hints a chunk is cheap to begin and with coalesced atomic additions cheap
             // to end, so small chunks win: the workers are closer together in the sweep over B and in their
             // progress (power-law N = 128: 449 us at 256 entries, 409 at 64; rows of 175 entries, N = 64:
-            // 523 and 381).  Smaller still while 64 leaves too few workers.  Larger where most entries are
-            // in long rows, whose chunks all add to the same few lines of C (rows of 60 000 entries, N = 32:
-            // 306 us at 64, 278 at 128).
+            // 523 and 381).  Smaller still while 64 leaves too few workers.  Larger for lane groups of 8 where
+            // more than a fifth of the entries are in long rows, whose chunks all add to the same few lines of C.
             const int64_t chunks = known_nnz / 64;
             g.chunk = 64;
             if (chunks < (g.G == 8 ? 48 : 28) * 1024 && known_nnz <= kSmallPlanMaxNnz) g.chunk = 32;
-            else if (N >= 32 && plan.long_rows > (g.G == 8 ? 0.2 : 0.5)) g.chunk = 128;
+            else if (N >= 32 && g.G == 8 && plan.long_rows > 0.2) g.chunk = 128;
         } else if (known_nnz >= 0) {
             // Small matrices: shrink the chunks until there are about four waves of workers per
             // SIMD, so that the chunk walk, a chain of dependent memory round trips, does not set
