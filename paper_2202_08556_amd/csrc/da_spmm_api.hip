@@ -494,13 +494,9 @@ int enqueue_transpose(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, 
                       const float* vals, int32_t* t_rowptr, int32_t* t_colind, float* t_vals,
                       void* workspace, size_t workspace_bytes, void* stream);
 
-// The size a transpose asks for.  The general sort's size is all that it needs: where the packed passes
-// would take more and are not given it, they leave the call to the general sort.
-size_t transpose_workspace_bytes(int64_t m, int64_t k, int64_t nnz) {
-    const size_t a = plan_transpose(k, nnz).bytes;
-    const TransposeFast f = plan_transpose_fast(m, k, nnz);
-    return f.usable && f.bytes > a ? f.bytes : a;
-}
+// The size a transpose asks for and needs: the general sort's.  The packed passes run where their scratch fits
+// into it, which it does from about a thousand entries on (about 16 B per entry at most against 24).
+size_t transpose_workspace_bytes(int64_t k, int64_t nnz) { return plan_transpose(k, nnz).bytes; }
 
 // Scratch memory of the entry point that allocates nothing (da_csr_transpose_noalloc): a static
 // device array, one copy per GPU, held from the moment the library is loaded on that GPU until the
@@ -737,7 +733,7 @@ int da_csr_transpose_workspace(int64_t m, int64_t k, int64_t nnz, size_t* bytes)
     if (m < 0 || k < 0 || nnz < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
     if (m > 0x7ffffffeLL || k > 0x7ffffffeLL || nnz > 0x7fffffffLL)
         return fail(DA_ERR_INVALID_ARG, "size beyond the int32 index range%s");
-    *bytes = transpose_workspace_bytes(m, k, nnz);
+    *bytes = transpose_workspace_bytes(k, nnz);
     return DA_OK;
 }
 
