@@ -151,7 +151,7 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, 
  * da_spmm_prepare builds those orders for the chunk sizes the EB kernels use, together with the row
  * that owns each chunk's first entry (a hint the kernels check against the row pointers before they
  * use it), and keeps them, keyed by (rowptr, colind, m), in library-owned device memory (about
- * nnz/11 ints) until da_spmm_release
+ * nnz/11 ints, nnz/5.5 up to 4 M entries) until da_spmm_release
  * (rowptr == NULL releases every matrix) or until 16 other matrices have been prepared.  Later
  * da_spmm / da_spmm_ex calls with the same rowptr, colind and m and an EB algorithm id pick the
  * order up by themselves; results are the same up to fp32 rounding order.  It also records nnz
