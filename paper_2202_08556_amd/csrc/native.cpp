@@ -96,11 +96,13 @@ bool attribute_address(PyObject* x, const char* name, bool call, void** out) {
     return !(!*out && PyErr_Occurred());
 }
 
-// device address of a tensor; an int or None passes through
+// Device address of a tensor, the one its data_ptr() gives: memory that it shares as a lazy copy becomes its
+// own first, so that an output is never written into the tensor it was copied from.  A subclass answers for
+// itself; an int or None passes through.
 bool to_address(PyObject* x, void** out) {
     if (x == Py_None) { *out = nullptr; return true; }
-    if (THPVariable_Check(x)) {
-        *out = const_cast<void*>(THPVariable_Unpack(x).const_data_ptr());
+    if (THPVariable_CheckExact(x)) {
+        *out = THPVariable_Unpack(x).mutable_data_ptr();
         return true;
     }
     if (PyLong_Check(x)) { *out = PyLong_AsVoidPtr(x); return !(!*out && PyErr_Occurred()); }

@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_2202_08556_amd", "libdaspmm.so")
@@ -135,3 +136,34 @@ def test_features_argument_errors():
     assert da._lib.da_spmm_features(4, 8, None, None, None) == da.DA_ERR_INVALID_ARG
     assert da._lib.da_spmm_features(0, 8, None, None, ctypes.byref(out)) == da.DA_OK
     assert out.rows == 0 and out.nnz == 0 and out.N == 8
+
+
+class _Addressed(torch.Tensor):
+    """A tensor that says itself where its data is."""
+    asked = 0
+
+    def data_ptr(self):
+        type(self).asked += 1
+        return super().data_ptr()
+
+
+@pytest.mark.parametrize("call", ["spmm", "ex", "transpose"])
+def test_addresses_are_those_of_data_ptr(call):
+    """Outputs that are lazy copies get memory of their own before their address is taken, and a subclass is asked for
+    its address.  Sizes of zero: the calls return before they would look at the memory."""
+    base = torch.ones(64)
+    outs = [torch._lazy_clone(base) for _ in range(3)] + [torch.ones(64).as_subclass(_Addressed)]
+    assert all(torch._C._is_cow_tensor(o) for o in outs[:3])
+    _Addressed.asked = 0
+    for out in outs[2:]:
+        if call == "spmm":
+            da.da_spmm(0, 4, 4, None, None, None, None, out, 0, stream=0)
+        elif call == "ex":
+            da.da_spmm_ex(0, 4, 4, None, None, None, None, 4, da.DA_ROW_MAJOR, out, 4, da.DA_ROW_MAJOR, 0, stream=0)
+    if call == "transpose":                                   # refused for its size, after the addresses were taken
+        for a in (outs[:3], [outs[3]] * 3):
+            with pytest.raises(da.DaSpmmError):
+                da.da_csr_transpose(-1, 4, 4, None, None, None, *a, None, 0, stream=0)
+        assert not any(torch._C._is_cow_tensor(o) for o in outs[:3])
+    assert not torch._C._is_cow_tensor(outs[2])
+    assert _Addressed.asked >= 1
