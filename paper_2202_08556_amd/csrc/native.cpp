@@ -239,6 +239,10 @@ void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device
 
 template <class T> T* data(const Tensor& t) { return t.defined() ? static_cast<T*>(t.data_ptr()) : nullptr; }
 
+// Distance between the rows of a contiguous matrix or of one with unit column stride.  A matrix of one row may
+// have any row stride there (a transposed column, an expanded sum): its width does.
+int64_t leading(const Tensor& t) { return t.size(0) > 1 ? t.stride(0) : t.size(1); }
+
 // Distance between the rows of a dense operand that this module lays out itself.  A row that is not whole
 // 64-byte pieces touches one cache line more on average: with N = 41 a gathered row of B costs 2.3 lines of
 // 128 bytes at a distance of 41 and 2 at 48 (power-law graph of 262 144 nodes: 245 and 219 us).
@@ -328,7 +332,7 @@ struct Graph : std::enable_shared_from_this<Graph> {
         }
         Tensor C = at::empty({m, N}, vals.options());
         check(da_spmm_ex(m, k, N, data<int32_t>(rowptr), data<int32_t>(colind), data<float>(vals), data<float>(X),
-                         X.stride(0), DA_ROW_MAJOR, data<float>(C), N, DA_ROW_MAJOR, id, stream_of(rowptr)));
+                         leading(X), DA_ROW_MAJOR, data<float>(C), N, DA_ROW_MAJOR, id, stream_of(rowptr)));
         return C;
     }
 };
@@ -402,8 +406,8 @@ Tensor aggregate(const GraphPtr& g, const Tensor& X, int id) {
 void dense_product(const Tensor& A, const Tensor& W, bool transpose_w, Tensor& out) {
     const int64_t rows = A.size(0), k = A.size(1), n = out.size(1);
     if (k >= 1 && (k <= 128 || (k <= 256 && rows * k * n <= 300000000)) && A.stride(1) == 1 && W.is_contiguous()) {
-        const int st = da_spmm_dense(rows, k, n, data<float>(A), A.stride(0), data<float>(W), transpose_w ? 1 : n,
-                                     transpose_w ? k : 1, data<float>(out), out.stride(0), stream_of(A));
+        const int st = da_spmm_dense(rows, k, n, data<float>(A), leading(A), data<float>(W), transpose_w ? 1 : n,
+                                     transpose_w ? k : 1, data<float>(out), leading(out), stream_of(A));
         if (st != DA_ERR_UNSUPPORTED) return check(st);
     }
     at::mm_out(out, A, transpose_w ? W.t() : W);
@@ -416,7 +420,7 @@ Tensor weight_gradient(const Tensor& X, const Tensor& G) {
         check(da_spmm_weight_grad_workspace(rows, fin, fout, &bytes));
         Tensor dW = at::empty({fin, fout}, X.options());
         Tensor ws = at::empty({(int64_t)bytes}, X.options().dtype(at::kByte));
-        check(da_spmm_weight_grad(rows, fin, fout, data<float>(X), X.stride(0), data<float>(G), G.stride(0), data<float>(dW),
+        check(da_spmm_weight_grad(rows, fin, fout, data<float>(X), leading(X), data<float>(G), leading(G), data<float>(dW),
                                   data<void>(ws), bytes, stream_of(X)));
         return dW;
     }
@@ -428,7 +432,7 @@ Tensor column_sums(const Tensor& G) {
     check(da_spmm_column_sums_workspace(G.size(0), G.size(1), &bytes));
     Tensor sums = at::empty({G.size(1)}, G.options());
     Tensor ws = at::empty({(int64_t)bytes}, G.options().dtype(at::kByte));
-    check(da_spmm_column_sums(G.size(0), G.size(1), data<float>(G), G.stride(0), data<float>(sums), data<void>(ws), bytes,
+    check(da_spmm_column_sums(G.size(0), G.size(1), data<float>(G), leading(G), data<float>(sums), data<void>(ws), bytes,
                               stream_of(G)));
     return sums;
 }

@@ -1,0 +1,73 @@
+"""Graphs and layers at the edges of what a caller may do with them: one row, sizes beyond the own kernels, operands
+changed or dropped between forward and backward, graphs that are not plain, threads, captures, copies, errors."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2202_08556_amd import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+
+def graph_of(a):
+    from paper_2202_08556_amd import gcn
+    return gcn.SparseGraph.from_numpy(a)
+
+
+def dense(a):
+    d = torch.zeros((a.m, a.k), dtype=torch.float64)
+    for i in range(a.m):
+        for p in range(a.rowptr[i], a.rowptr[i + 1]):
+            d[i, a.colind[p]] += float(a.vals[p])
+    return d
+
+
+def matrix(m, k, seed=1):
+    """A small matrix without empty rows."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(1, max(2, k // 2), size=m)
+    rowptr, colind = gen.csr_from_lens(rng, lens, k)
+    return gen.CSR(m, k, rowptr.astype(np.int32), colind.astype(np.int32),
+                   rng.uniform(-1, 1, colind.size).astype(np.float32), "small", seed)
+
+
+def near(got, want):
+    """Sums of a few hundred fp32 products against float64: 1e-5 of the largest value is a hundred roundings."""
+    want = want.double().cpu()
+    return got.shape == want.shape and bool((got.detach().double().cpu() - want).abs().max() <= 1e-5 * max(1.0, float(want.abs().max())))
+
+
+def layer_of(fin, fout, **kw):
+    from paper_2202_08556_amd import gcn
+    torch.manual_seed(fin * 1000 + fout)
+    layer = gcn.GraphConv(fin, fout, **kw).cuda()
+    if layer.bias is not None:
+        with torch.no_grad():
+            layer.bias.uniform_(-0.5, 0.5)
+    return layer
+
+
+# ---- one row --------------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("m,k", [(7, 1), (1, 9), (1, 1)])
+@pytest.mark.parametrize("n", [1, 5, 40])
+def test_operands_of_one_row(m, k, n):
+    """torch gives a contiguous tensor of one row any row stride: a transposed column, the gradient of a sum."""
+    from paper_2202_08556_amd import gcn
+    a = matrix(m, k)
+    A, graph = dense(a), graph_of(a)
+    col = torch.randn((n, k), device="cuda")
+    X = col.t().requires_grad_(True)                          # k x n, strides (1, k)
+    for dY in (None, torch.randn((n, m), device="cuda").t()):
+        Y = gcn.aggregate(graph, X)
+        gx, = torch.autograd.grad(Y.sum() if dY is None else Y, X, dY)
+        assert near(Y, A @ X.detach().double().cpu())
+        assert near(gx, A.t() @ (torch.ones((m, n)) if dY is None else dY).double().cpu())
+    layer = layer_of(6, n, relu=False)
+    x = torch.randn((6, k), device="cuda").t().requires_grad_(True)
+    W, b = layer.weight.detach().double().cpu(), layer.bias.detach().double().cpu()
+    for dY in (None, torch.randn((n, m), device="cuda").t()):
+        Y = layer(graph, x)
+        assert near(Y, A @ (x.detach().double().cpu() @ W) + b)
+        gx, gw, gb = torch.autograd.grad(Y.sum() if dY is None else Y, (x, layer.weight, layer.bias), dY)
+        d = (torch.ones((m, n)) if dY is None else dY).double().cpu()
+        assert near(gx, (A.t() @ d) @ W.t()) and near(gw, x.detach().double().cpu().t() @ (A.t() @ d)) and near(gb, d.sum(0))
