@@ -438,7 +438,8 @@ Tensor column_sums(const Tensor& G) {
 }
 
 // Z = A . (X . W) + b, out = relu(Z):  dZ = dY where out > 0;  db = column sums of dZ;  dH = A^T . dZ;
-// dW = X^T . dH;  dX = dH . W^T
+// dW = X^T . dH;  dX = dH . W^T.  X is kept for dW only and W for dX only: the caller may change or drop what no
+// gradient needs.
 struct GraphConvBackward : torch::autograd::Node {
     GraphPtr graph;
     torch::autograd::SavedVariable x, w, out;
@@ -458,8 +459,8 @@ struct GraphConvBackward : torch::autograd::Node {
         Tensor X, W, Y;
         {
             std::lock_guard<std::mutex> lk(mutex_);
-            X = x.unpack();
-            W = w.unpack();
+            if (task_should_compute_output(1)) X = x.unpack();
+            if (task_should_compute_output(0)) W = w.unpack();
             if (relu) Y = out.unpack(shared_from_this());
         }
         c10::DeviceGuard guard(graph->rowptr.device());
@@ -484,7 +485,7 @@ struct GraphConvBackward : torch::autograd::Node {
         at::AutoDispatchBelowADInplaceOrView below;
         if (task_should_compute_output(1)) result[1] = weight_gradient(X, dH);
         if (task_should_compute_output(0)) {
-            result[0] = at::empty({X.size(0), X.size(1)}, X.options());
+            result[0] = at::empty({dH.size(0), W.size(0)}, dH.options());
             dense_product(dH, W, true, result[0]);
         }
         return result;
@@ -508,8 +509,8 @@ Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std
         auto node = std::shared_ptr<GraphConvBackward>(new GraphConvBackward(), torch::autograd::deleteNode);
         node->graph = g;
         node->relu = relu;
-        node->x = torch::autograd::SavedVariable(X, false);
-        node->w = torch::autograd::SavedVariable(W, false);
+        if (wants_grad(W)) node->x = torch::autograd::SavedVariable(X, false);
+        if (wants_grad(X)) node->w = torch::autograd::SavedVariable(W, false);
         node->set_next_edges(torch::autograd::collect_next_edges(X, W, b));
         torch::autograd::set_history(Z, node);
         if (relu) node->out = torch::autograd::SavedVariable(Z, true);

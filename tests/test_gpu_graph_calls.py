@@ -71,3 +71,54 @@ def test_operands_of_one_row(m, k, n):
         gx, gw, gb = torch.autograd.grad(Y.sum() if dY is None else Y, (x, layer.weight, layer.bias), dY)
         d = (torch.ones((m, n)) if dY is None else dY).double().cpu()
         assert near(gx, (A.t() @ d) @ W.t()) and near(gw, x.detach().double().cpu().t() @ (A.t() @ d)) and near(gb, d.sum(0))
+
+
+# ---- what a layer keeps for its backward pass ------------------------------------------------------------------------
+def test_layer_keeps_only_what_its_gradients_need():
+    a = gen.powerlaw_csr(m=1500, seed=3)
+    graph, layer = graph_of(a), layer_of(24, 16)
+    X = torch.randn((a.m, 24), device="cuda")
+    dY = torch.randn((a.m, 16), device="cuda")
+    params = (layer.weight, layer.bias)
+    want = torch.autograd.grad(layer(graph, X), params, dY)
+    Y = layer(graph, X)                                       # W changes, and its gradient does not need it
+    with torch.no_grad():
+        layer.weight.mul_(1.25)
+    for g, w in zip(torch.autograd.grad(Y, params, dY), want):
+        assert torch.allclose(g, w, rtol=1e-5, atol=1e-5)
+    layer.weight.requires_grad_(False)
+    leaf = X.clone().requires_grad_(True)
+    want, = torch.autograd.grad(layer(graph, leaf), leaf, dY)
+    middle = leaf * 1.0
+    Y = layer(graph, middle)                                  # X changes, and its gradient does not need it
+    with torch.no_grad():
+        middle.zero_()
+    got, = torch.autograd.grad(Y, leaf, dY)
+    assert torch.allclose(got, want, rtol=1e-5, atol=1e-5)
+    with torch.inference_mode():
+        frozen = X * 1.0
+    Y = layer(graph, frozen)                                  # only the bias is trained
+    torch.autograd.grad(Y, layer.bias, dY)
+    torch.cuda.synchronize()
+    big = torch.randn((a.m, 24), device="cuda")
+    Y = layer(graph, big)
+    before = torch.cuda.memory_allocated()
+    del big
+    assert before - torch.cuda.memory_allocated() >= a.m * 24 * 4
+    torch.autograd.grad(Y, layer.bias, dY)
+
+
+def test_changes_that_a_gradient_depends_on_are_refused():
+    a = gen.powerlaw_csr(m=600, seed=4)
+    graph, layer = graph_of(a), layer_of(8, 8)
+    X = torch.randn((a.m, 8), device="cuda", requires_grad=True)
+    dY = torch.randn((a.m, 8), device="cuda")
+    Y = layer(graph, X)
+    with torch.no_grad():
+        layer.weight.mul_(1.25)
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        torch.autograd.grad(Y, X, dY)
+    Y = layer(graph, X)
+    torch.autograd.grad(Y, X, dY)
+    with pytest.raises(RuntimeError, match="second time"):
+        torch.autograd.grad(Y, X, dY)
