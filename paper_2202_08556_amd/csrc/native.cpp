@@ -29,9 +29,11 @@
 #include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/csrc/utils/pybind.h>
 
+#include <atomic>
 #include <exception>
 #include <memory>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "da_spmm.h"
@@ -252,28 +254,52 @@ int64_t row_pitch(int64_t n) {
     return (n + 15) / 16 * 16;
 }
 
-struct Graph : std::enable_shared_from_this<Graph> {
+// The matrix of a graph.  Python may replace its fields while another thread's product runs without the
+// interpreter lock, so a graph holds them behind a pointer: a call reads one state of all fields and keeps its
+// arrays alive, a change makes a new state.
+struct Arrays {
     int64_t m, k, nnz;
     Tensor rowptr, colind, vals;
+};
+using ArraysPtr = std::shared_ptr<const Arrays>;
+
+struct Graph : std::enable_shared_from_this<Graph> {
+    std::mutex arrays_mu;                     // held for a copy of the pointer only
+    ArraysPtr arrays;
+    std::atomic<bool> prepared{false};
     std::recursive_mutex mu;                  // what follows is filled in by the first calls that need it
-    bool have_features = false, prepared = false;
+    bool have_features = false;
     int eb_products = 0;
     da_features features{};
     std::vector<std::pair<int64_t, int>> algo;
     std::shared_ptr<Graph> t;
     std::weak_ptr<Graph> t_of;
 
-    Graph(int64_t m_, int64_t k_, Tensor rp, Tensor ci, Tensor va)
-        : m(m_), k(k_), nnz(ci.numel()), rowptr(rp.contiguous()), colind(ci.contiguous()), vals(va.contiguous()) {}
+    Graph(int64_t m, int64_t k, const Tensor& rp, const Tensor& ci, const Tensor& va)
+        : arrays(std::make_shared<Arrays>(Arrays{m, k, ci.numel(), rp.contiguous(), ci.contiguous(), va.contiguous()})) {}
     ~Graph() {
-        if (prepared) da_spmm_release(data<int32_t>(rowptr));
+        if (prepared) da_spmm_release(data<int32_t>(arrays->rowptr));
+    }
+
+    ArraysPtr now() {
+        std::lock_guard<std::mutex> lk(arrays_mu);
+        return arrays;
+    }
+
+    template <class T> void change(T Arrays::*field, const T& value) {
+        ArraysPtr old;                        // freed after the lock
+        std::lock_guard<std::mutex> lk(arrays_mu);
+        auto next = std::make_shared<Arrays>(*arrays);
+        (*next).*field = value;
+        old = std::exchange(arrays, std::move(next));
     }
 
     const da_features& known() {
         std::lock_guard<std::recursive_mutex> lk(mu);
         if (!have_features) {                 // one device reduction per graph
-            c10::DeviceGuard guard(rowptr.device());
-            check(da_spmm_features(m, 1, data<int32_t>(rowptr), stream_of(rowptr), &features));
+            const ArraysPtr a = now();
+            c10::DeviceGuard guard(a->rowptr.device());
+            check(da_spmm_features(a->m, 1, data<int32_t>(a->rowptr), stream_of(a->rowptr), &features));
             have_features = true;
         }
         return features;
@@ -291,10 +317,11 @@ struct Graph : std::enable_shared_from_this<Graph> {
         return id;
     }
 
-    void prepare() {
+    void prepare() { prepare(*now()); }
+    void prepare(const Arrays& a) {
         std::lock_guard<std::recursive_mutex> lk(mu);
         if (prepared) return;
-        check(da_spmm_prepare(m, k, nnz, data<int32_t>(rowptr), data<int32_t>(colind), stream_of(rowptr)));
+        check(da_spmm_prepare(a.m, a.k, a.nnz, data<int32_t>(a.rowptr), data<int32_t>(a.colind), stream_of(a.rowptr)));
         prepared = true;
     }
 
@@ -302,37 +329,39 @@ struct Graph : std::enable_shared_from_this<Graph> {
         std::lock_guard<std::recursive_mutex> lk(mu);
         if (auto back = t_of.lock()) return back;
         if (!t) {
-            c10::DeviceGuard guard(rowptr.device());
-            Tensor trp = at::empty({k + 1}, rowptr.options()), tci = at::empty({nnz}, colind.options()),
-                   tva = at::empty({nnz}, vals.options());
+            const ArraysPtr a = now();
+            c10::DeviceGuard guard(a->rowptr.device());
+            Tensor trp = at::empty({a->k + 1}, a->rowptr.options()), tci = at::empty({a->nnz}, a->colind.options()),
+                   tva = at::empty({a->nnz}, a->vals.options());
             size_t bytes = 0;
-            check(da_csr_transpose_workspace(m, k, nnz, &bytes));
+            check(da_csr_transpose_workspace(a->m, a->k, a->nnz, &bytes));
             // scratch of the call; torch allocations are 512-byte aligned and the caching allocator keeps the
             // block alive for work already queued on this stream
-            Tensor ws = at::empty({(int64_t)bytes}, rowptr.options().dtype(at::kByte));
-            check(da_csr_transpose(m, k, nnz, data<int32_t>(rowptr), data<int32_t>(colind), data<float>(vals),
+            Tensor ws = at::empty({(int64_t)bytes}, a->rowptr.options().dtype(at::kByte));
+            check(da_csr_transpose(a->m, a->k, a->nnz, data<int32_t>(a->rowptr), data<int32_t>(a->colind), data<float>(a->vals),
                                    data<int32_t>(trp), data<int32_t>(tci), data<float>(tva), data<void>(ws), bytes,
-                                   stream_of(rowptr)));
-            t = std::make_shared<Graph>(k, m, trp, tci, tva);
+                                   stream_of(a->rowptr)));
+            t = std::make_shared<Graph>(a->k, a->m, trp, tci, tva);
             t->t_of = weak_from_this();
         }
         return t;
     }
 
-    // A . X for X with unit column stride.  The matrix is prepared (chunk order of the EB algorithms) before the
-    // second product with an EB algorithm that the selector chose, and before the first one the caller chose.
-    Tensor product(const Tensor& X, int64_t N, int id) {
-        c10::DeviceGuard guard(rowptr.device());
+    // a . X for X with unit column stride, a = this graph's arrays.  The matrix is prepared (chunk order of the EB
+    // algorithms) before the second product with an EB algorithm that the selector chose, and before the first one
+    // the caller chose.
+    Tensor product(const Arrays& a, const Tensor& X, int64_t N, int id) {
+        c10::DeviceGuard guard(a.rowptr.device());
         const bool chosen = id < 0;
         if (chosen) id = algo_for(N);
         if (id >= DA_EB_RM_SR && !prepared) {
             std::lock_guard<std::recursive_mutex> lk(mu);
-            if (!chosen || eb_products > 0) prepare();
+            if (!chosen || eb_products > 0) prepare(a);
             ++eb_products;
         }
-        Tensor C = at::empty({m, N}, vals.options());
-        check(da_spmm_ex(m, k, N, data<int32_t>(rowptr), data<int32_t>(colind), data<float>(vals), data<float>(X),
-                         leading(X), DA_ROW_MAJOR, data<float>(C), N, DA_ROW_MAJOR, id, stream_of(rowptr)));
+        Tensor C = at::empty({a.m, N}, a.vals.options());
+        check(da_spmm_ex(a.m, a.k, N, data<int32_t>(a.rowptr), data<int32_t>(a.colind), data<float>(a.vals), data<float>(X),
+                         leading(X), DA_ROW_MAJOR, data<float>(C), N, DA_ROW_MAJOR, id, stream_of(a.rowptr)));
         return C;
     }
 };
@@ -347,8 +376,8 @@ GraphPtr make_graph(int64_t m, int64_t k, const Tensor& rowptr, const Tensor& co
 }
 
 // X as the product takes it: float32, k rows, neighbouring columns
-Tensor operand(const Graph& g, const Tensor& X) {
-    if (X.scalar_type() != at::kFloat || X.dim() != 2 || X.size(0) != g.k) throw py::value_error("X must be a float32 k x N tensor");
+Tensor operand(const Arrays& a, const Tensor& X) {
+    if (X.scalar_type() != at::kFloat || X.dim() != 2 || X.size(0) != a.k) throw py::value_error("X must be a float32 k x N tensor");
     return X.resolve_neg().contiguous();
 }
 
@@ -377,8 +406,9 @@ struct AggregateBackward : torch::autograd::Node {
         if (!grads[0].defined() || !task_should_compute_output(0)) return {Tensor()};
         at::AutoDispatchBelowADInplaceOrView below;
         const auto t = graph->transposed();
-        const Tensor dY = operand(*t, grads[0].detach());
-        return {t->product(dY, dY.size(1), -1)};
+        const ArraysPtr at_now = t->now();
+        const Tensor dY = operand(*at_now, grads[0].detach());
+        return {t->product(*at_now, dY, dY.size(1), -1)};
     }
     std::string name() const override { return "AggregateBackward"; }
 };
@@ -386,11 +416,12 @@ struct AggregateBackward : torch::autograd::Node {
 bool wants_grad(const Tensor& t) { return t.defined() && t.requires_grad(); }
 
 Tensor aggregate(const GraphPtr& g, const Tensor& X, int id) {
-    const Tensor x = operand(*g, X);
+    const ArraysPtr a = g->now();
+    const Tensor x = operand(*a, X);
     Tensor Y;
     {
         at::AutoDispatchBelowADInplaceOrView below;
-        Y = g->product(x, x.size(1), id);
+        Y = g->product(*a, x, x.size(1), id);
     }
     if (at::GradMode::is_enabled() && wants_grad(X)) {
         auto node = std::shared_ptr<AggregateBackward>(new AggregateBackward(), torch::autograd::deleteNode);
@@ -463,7 +494,7 @@ struct GraphConvBackward : torch::autograd::Node {
             if (task_should_compute_output(0)) W = w.unpack();
             if (relu) Y = out.unpack(shared_from_this());
         }
-        c10::DeviceGuard guard(graph->rowptr.device());
+        c10::DeviceGuard guard(graph->now()->rowptr.device());
         const bool again = at::GradMode::is_enabled();       // gradients of gradients: dense parts differentiable
         Tensor dZ = relu ? at::threshold_backward(dY, Y, 0) : dY;
         if (task_should_compute_output(2)) {
@@ -475,7 +506,8 @@ struct GraphConvBackward : torch::autograd::Node {
         {
             at::AutoDispatchBelowADInplaceOrView below;
             const auto t = graph->transposed();
-            dH = t->product(operand(*t, dZ.detach()), dZ.size(1), -1);
+            const ArraysPtr at_now = t->now();
+            dH = t->product(*at_now, operand(*at_now, dZ.detach()), dZ.size(1), -1);
         }
         if (again) {
             if (task_should_compute_output(1)) result[1] = at::mm(X.t(), dH);
@@ -497,13 +529,15 @@ Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std
     const Tensor b = bias.value_or(Tensor());
     Tensor Z;
     const int64_t n = W.size(1);
+    const ArraysPtr a = g->now();
+    if (X.size(0) != a->k) throw py::value_error("X must be a float32 k x N tensor");
     {
         at::AutoDispatchBelowADInplaceOrView below;
-        c10::DeviceGuard guard(g->rowptr.device());
+        c10::DeviceGuard guard(a->rowptr.device());
         Tensor H = at::empty({X.size(0), row_pitch(n)}, X.options()).narrow(1, 0, n);
         dense_product(X, W, false, H);
-        Z = g->product(H, n, -1);
-        check(da_spmm_bias_relu(g->m, n, data<float>(Z), data<float>(b), relu ? 1 : 0, stream_of(Z)));
+        Z = g->product(*a, H, n, -1);
+        check(da_spmm_bias_relu(a->m, n, data<float>(Z), data<float>(b), relu ? 1 : 0, stream_of(Z)));
     }
     if (at::GradMode::is_enabled() && (wants_grad(X) || wants_grad(W) || wants_grad(b))) {
         auto node = std::shared_ptr<GraphConvBackward>(new GraphConvBackward(), torch::autograd::deleteNode);
@@ -522,12 +556,13 @@ Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std
 bool graph_conv_takes(const GraphPtr& g, py::handle x, py::handle w, py::handle bias) {
     if (!ordinary_context() || at::autocast::is_autocast_enabled(at::kCUDA)) return false;
     if (!ordinary(x) || !ordinary(w) || !(bias.is_none() || ordinary(bias))) return false;
+    const ArraysPtr a = g->now();
     auto plain = [&](const Tensor& t, int64_t dim) {
-        return t.scalar_type() == at::kFloat && t.dim() == dim && t.is_contiguous() && t.device() == g->rowptr.device();
+        return t.scalar_type() == at::kFloat && t.dim() == dim && t.is_contiguous() && t.device() == a->rowptr.device();
     };
     const Tensor &X = THPVariable_Unpack(x.ptr()), &W = THPVariable_Unpack(w.ptr());
-    return plain(X, 2) && plain(W, 2) && X.size(0) == g->k && X.size(1) == W.size(0) && W.size(1) >= 1 && X.size(1) >= 1 &&
-           g->m >= 1 && (bias.is_none() || (plain(THPVariable_Unpack(bias.ptr()), 1) &&
+    return plain(X, 2) && plain(W, 2) && X.size(0) == a->k && X.size(1) == W.size(0) && W.size(1) >= 1 && X.size(1) >= 1 &&
+           a->m >= 1 && (bias.is_none() || (plain(THPVariable_Unpack(bias.ptr()), 1) &&
                                             THPVariable_Unpack(bias.ptr()).size(0) == W.size(1)));
 }
 
@@ -541,31 +576,34 @@ void bind_graphs(py::module_& mod) {
         }
     });
     using release = py::call_guard<py::gil_scoped_release>;
+    auto get = [](auto field) { return [field](Graph& g) { return (*g.now()).*field; }; };
+    auto put = [](auto field) { return [field](Graph& g, decltype(Arrays{}.*field) value) { g.change(field, value); }; };
     py::class_<Graph, GraphPtr>(mod, "Graph")
         .def(py::init(&make_graph))
-        .def_readwrite("m", &Graph::m)
-        .def_readwrite("k", &Graph::k)
-        .def_readwrite("nnz", &Graph::nnz)
-        .def_readwrite("rowptr", &Graph::rowptr)
-        .def_readwrite("colind", &Graph::colind)
-        .def_readwrite("vals", &Graph::vals)
-        .def_readonly("prepared", &Graph::prepared)
+        .def_property("m", get(&Arrays::m), put(&Arrays::m))
+        .def_property("k", get(&Arrays::k), put(&Arrays::k))
+        .def_property("nnz", get(&Arrays::nnz), put(&Arrays::nnz))
+        .def_property("rowptr", get(&Arrays::rowptr), put(&Arrays::rowptr))
+        .def_property("colind", get(&Arrays::colind), put(&Arrays::colind))
+        .def_property("vals", get(&Arrays::vals), put(&Arrays::vals))
+        .def_property_readonly("prepared", [](Graph& g) { return g.prepared.load(); })
         .def("features", [](Graph& g) {
             da_features f;
             { py::gil_scoped_release r; f = g.known(); }
             return py::make_tuple(f.rows, f.nnz, f.row_nnz_mean, f.row_nnz_std, f.row_nnz_max);
         })
         .def("algo_for", &Graph::algo_for, release())
-        .def("prepare", &Graph::prepare, release())
+        .def("prepare", [](Graph& g) { g.prepare(); }, release())
         .def("transposed", &Graph::transposed, release())
         .def("spmm", [](Graph& g, const Tensor& X, int id) {
-            const Tensor x = operand(g, X);
+            const ArraysPtr a = g.now();
+            const Tensor x = operand(*a, X);
             py::gil_scoped_release r;
             at::AutoDispatchBelowADInplaceOrView below;
-            return g.product(x, x.size(1), id);
+            return g.product(*a, x, x.size(1), id);
         });
     mod.def("aggregate", [](const GraphPtr& g, const Tensor& X) {
-        const Tensor x = operand(*g, X);      // errors are Python exceptions: raised with the lock held
+        const Tensor x = operand(*g->now(), X);      // errors are Python exceptions: raised with the lock held
         py::gil_scoped_release r;
         return aggregate(g, X, -1);
     });

@@ -122,3 +122,38 @@ def test_changes_that_a_gradient_depends_on_are_refused():
     torch.autograd.grad(Y, X, dY)
     with pytest.raises(RuntimeError, match="second time"):
         torch.autograd.grad(Y, X, dY)
+
+
+# ---- threads ---------------------------------------------------------------------------------------------------------
+def test_arrays_replaced_while_another_thread_multiplies():
+    """A product sees the arrays of one moment and keeps them alive: each result is that of the old or the new values."""
+    import threading
+
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=900, seed=6)
+    graph = graph_of(a)
+    vals = graph.vals.clone()
+    X = torch.randn((a.m, 32), device="cuda")
+    want = gcn.aggregate(graph, X)
+    done, results, errors = threading.Event(), [], []
+
+    def multiply():
+        try:
+            for _ in range(200):
+                results.append(gcn.aggregate(graph, X))
+        except BaseException as exc:
+            errors.append(exc)
+        finally:
+            done.set()
+
+    worker = threading.Thread(target=multiply)
+    worker.start()
+    i = 0
+    while not done.is_set():
+        graph.vals = vals * (1 + i % 2)                       # the array set before is dropped here
+        assert graph.vals.shape == vals.shape and graph.nnz == a.nnz
+        i += 1
+    worker.join()
+    assert not errors and len(results) == 200
+    for Y in results:
+        assert torch.allclose(Y, want, rtol=1e-4, atol=1e-5) or torch.allclose(Y, 2 * want, rtol=1e-4, atol=1e-5)
