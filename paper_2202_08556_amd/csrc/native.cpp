@@ -28,6 +28,7 @@
 #include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/csrc/utils/pybind.h>
+#include <hip/hip_runtime.h>
 
 #include <atomic>
 #include <exception>
@@ -239,6 +240,13 @@ void check(int status) {
 
 void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
 
+bool capturing(const Tensor& t) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing((hipStream_t)stream_of(t), &status);
+    if (e != hipSuccess) (void)hipGetLastError();            // the default stream beside another one's capture
+    return e != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 template <class T> T* data(const Tensor& t) { return t.defined() ? static_cast<T*>(t.data_ptr()) : nullptr; }
 
 // Distance between the rows of a contiguous matrix or of one with unit column stride.  A matrix of one row may
@@ -349,12 +357,13 @@ struct Graph : std::enable_shared_from_this<Graph> {
 
     // a . X for X with unit column stride, a = this graph's arrays.  The matrix is prepared (chunk order of the EB
     // algorithms) before the second product with an EB algorithm that the selector chose, and before the first one
-    // the caller chose.
+    // the caller chose, unless the stream is being captured: preparing allocates and waits, and its orders only
+    // cost speed where they are missing.
     Tensor product(const Arrays& a, const Tensor& X, int64_t N, int id) {
         c10::DeviceGuard guard(a.rowptr.device());
         const bool chosen = id < 0;
         if (chosen) id = algo_for(N);
-        if (id >= DA_EB_RM_SR && !prepared) {
+        if (id >= DA_EB_RM_SR && !prepared && !capturing(a.rowptr)) {
             std::lock_guard<std::recursive_mutex> lk(mu);
             if (!chosen || eb_products > 0) prepare(a);
             ++eb_products;

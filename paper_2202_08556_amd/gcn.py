@@ -26,7 +26,9 @@ class SparseGraph:
 
     The matrix is prepared (da_spmm_prepare: EB chunk order and row hints) before the second product
     with an EB algorithm: the preparation costs as much as a product or more and RB algorithms do not use
-    it, so a graph that is used once, a sampled mini-batch say, goes without.  The library keeps the plans
+    it, so a graph that is used once, a sampled mini-batch say, goes without.  It is not prepared while a HIP
+    graph is captured: call prepare() (also of transposed()) or make two passes before the capture, or the
+    captured products run without the chunk order.  The library keeps the plans
     of the 16 most recently prepared matrices; a program that holds more graphs than that (a graph and its
     transpose count as two) loses the oldest plans silently, which costs the EB algorithms their chunk
     order (speed), never the result."""

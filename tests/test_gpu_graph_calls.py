@@ -157,3 +157,43 @@ def test_arrays_replaced_while_another_thread_multiplies():
     assert not errors and len(results) == 200
     for Y in results:
         assert torch.allclose(Y, want, rtol=1e-4, atol=1e-5) or torch.allclose(Y, 2 * want, rtol=1e-4, atol=1e-5)
+
+
+# ---- captures --------------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("given", [None, 4])
+def test_capture_after_one_pass(given):
+    """The second EB product of a graph prepares it, which a capture must not: it goes without."""
+    from paper_2202_08556_amd import gcn
+    a = gen.skewed_csr(m=16384, heavy_lo=3000, heavy_hi=9000, seed=4001)
+    graph, layer = graph_of(a), layer_of(12, 24)
+    X = torch.randn((a.m, 24), device="cuda")
+    x = torch.randn((a.m, 12), device="cuda", requires_grad=True)
+    dY = torch.randn((a.m, 24), device="cuda")
+    assert graph.algo_for(24) >= 4
+
+    def passes():
+        if given is not None:
+            return [graph.spmm(X, given)]
+        Y = layer(graph, x)
+        return [Y.detach(), *torch.autograd.grad(Y, (x, layer.weight, layer.bias), dY)]
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        if given is None:
+            passes()
+    side.synchronize()
+    held = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(held, stream=side):
+        outs = passes()
+    assert not graph._g.prepared
+    for _ in range(3):
+        for o in outs:
+            o.fill_(float("nan"))
+        want = passes()                                       # eager work between the replays, which prepares
+        torch.cuda.synchronize()
+        held.replay()
+        torch.cuda.synchronize()
+        for o, w in zip(outs, want):
+            assert torch.allclose(o, w, rtol=1e-3, atol=1e-5 * float(w.abs().max()))
+    assert graph._g.prepared
