@@ -131,7 +131,10 @@ int da_spmm_select(const da_features *f);
 /*
  * Extract the selector's input characteristics (Sec. 5.1, Table 2) from the row pointers with one
  * device reduction.  rowptr is a device pointer (int32[m+1]); `out` is a HOST pointer.  Blocks
- * until the result is on the host (synchronises `stream`).  m == 0 gives all-zero features.
+ * until its own result is on the host, which need not be the end of all work on `stream`; refused
+ * (DA_ERR_HIP) while `stream` is being captured.  m == 0 gives all-zero features.  A call takes a
+ * slot of device scratch and pinned memory from a pool that it creates as needed and that keeps at
+ * most 8 idle slots per device.
  * Side effect: the library remembers nnz for this (rowptr, m) pair in a small host table and
  * later da_spmm calls on the same matrix use it to size the grids of the EB algorithms (a
  * missing or stale entry only costs speed: EB kernels read nnz on the device and cover every
@@ -167,8 +170,8 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, 
  * later prepares; a re-prepare of the same matrix keeps it): only da_spmm_release frees it, which
  * the caller must not do while the graph is still replayed.  da_spmm_release(NULL) also frees plans
  * that a re-prepare with another nnz has set aside.
- * These two host tables (nnz hints, plans) are the library's only mutable global state; both only
- * steer launch geometry and chunk order, never the result.
+ * These two host tables (nnz hints, plans) and the slots of da_spmm_features are the library's only
+ * mutable global state; the tables only steer launch geometry and chunk order, never the result.
  *
  * da_eb_schedule is the building block: order[u], u = 0 .. ceil(nnz/unit)-1, lists the chunk
  * numbers (chunk c = stored entries [c*unit, (c+1)*unit)) sorted by a key in [0, 2k), ties in

@@ -544,7 +544,8 @@ void free_slot(const FeatureSlot& s) {
     if (s.result) (void)hipHostFree(s.result);
 }
 
-hipError_t take_slot(int dev, FeatureSlot* out) {
+// A new slot is cleared on the stream of the call that takes it, whose kernel follows; nothing waits for other streams.
+hipError_t take_slot(int dev, hipStream_t stream, FeatureSlot* out) {
     {
         std::lock_guard<std::mutex> lk(g_feature_mu);
         auto& pool = g_feature_slots[dev];
@@ -556,9 +557,8 @@ hipError_t take_slot(int dev, FeatureSlot* out) {
     }
     FeatureSlot s;
     hipError_t e = hipMalloc(&s.scratch, sizeof(FeatureScratch));
-    if (e == hipSuccess) e = hipMemset(s.scratch, 0, sizeof(FeatureScratch));
+    if (e == hipSuccess) e = hipMemsetAsync(s.scratch, 0, sizeof(FeatureScratch), stream);
     if (e == hipSuccess) e = hipHostMalloc(&s.result, sizeof(FeatureResult), hipHostMallocMapped | hipHostMallocCoherent);
-    if (e == hipSuccess) e = hipDeviceSynchronize();          // the clearing is done before any stream uses it
     if (e != hipSuccess) { free_slot(s); return e; }
     s.result->ticket = 0;
     *out = s;
@@ -686,8 +686,12 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t* rowptr, void* stream, 
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     if (dev < 0 || dev >= kMaxDevices) return fail(DA_ERR_UNSUPPORTED, "device ordinal beyond 63%s");
+    // the call waits for its result, which a recorded kernel would not deliver
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusNone; }
+    if (capture != hipStreamCaptureStatusNone) return hip_fail(hipErrorStreamCaptureUnsupported, "da_spmm_features");
     FeatureSlot slot;
-    e = take_slot(dev, &slot);
+    e = take_slot(dev, st, &slot);
     if (e != hipSuccess) return hip_fail(e, "da_spmm_features: scratch");
     ++slot.ticket;
     // 8 row pointers a thread: enough blocks to hide their latency, few enough for the shared counters

@@ -197,3 +197,35 @@ def test_capture_after_one_pass(given):
         for o, w in zip(outs, want):
             assert torch.allclose(o, w, rtol=1e-3, atol=1e-5 * float(w.abs().max()))
     assert graph._g.prepared
+
+
+def test_features_are_refused_in_a_capture_and_wait_for_no_other_stream():
+    """Nothing is recorded for them, and new scratch is cleared on the stream of its call."""
+    from concurrent.futures import ThreadPoolExecutor
+
+    from oracle import reference as orc
+    from paper_2202_08556_amd import binding as da
+    a = gen.powerlaw_csr(m=5000, seed=8)
+    rp = torch.from_numpy(a.rowptr).cuda()
+    want = orc.features(a.rowptr, 4)
+    side = torch.cuda.Stream()
+    out = torch.zeros(4, device="cuda")
+    held = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(held, stream=side):
+        out.add_(1)
+        with pytest.raises(da.DaSpmmError):
+            da.da_spmm_features(a.m, 4, rp)
+        out.add_(1)
+    for _ in range(3):
+        held.replay()
+    torch.cuda.synchronize()
+    assert out.tolist() == [6.0] * 4
+
+    def some(i):                                              # more calls at once than idle slots are kept
+        with torch.cuda.stream(torch.cuda.Stream()):
+            return [da.da_spmm_features(a.m, 4, rp) for _ in range(20)]
+
+    with ThreadPoolExecutor(12) as pool:
+        for got in (f for fs in pool.map(some, range(12)) for f in fs):
+            assert got["nnz"] == want["nnz"] and got["row_nnz_max"] == want["row_nnz_max"]
+            assert got["row_nnz_std"] == pytest.approx(want["row_nnz_std"], rel=1e-9)
