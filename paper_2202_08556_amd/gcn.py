@@ -53,7 +53,12 @@ class SparseGraph:
 
     def algo_for(self, N: int) -> int:
         """Algorithm id the selector picks for this matrix and feature length (cached)."""
-        return self._g.algo_for(int(N))
+        if _as_written(self):
+            return self._g.algo_for(int(N))
+        cached = self.__dict__.setdefault("_algo", {})
+        if N not in cached:
+            cached[N] = da.da_spmm_select(self.features(N))
+        return cached[N]
 
     def prepare(self) -> None:
         """Build the chunk orders of the EB algorithms now (da_spmm_prepare); released with the graph."""
@@ -70,7 +75,22 @@ class SparseGraph:
 
     def spmm(self, X: torch.Tensor, algo: int | None = None) -> torch.Tensor:
         """A . X for a row-major fp32 k x N tensor on the same device; returns a new m x N tensor."""
+        if algo is None and not _as_written(self):
+            algo = self.algo_for(int(X.shape[1])) if X.dim() == 2 else 0
         return self._g.spmm(X, -1 if algo is None else int(algo))
+
+
+_METHODS = frozenset(("spmm", "transposed", "algo_for", "features"))
+
+
+def _as_written(graph) -> bool:
+    """Whether products of `graph` may be made below its Python methods: it is a SparseGraph and neither its class
+    nor the object has replaced one of them."""
+    t = type(graph)
+    if t is not SparseGraph and not (isinstance(graph, SparseGraph) and
+                                     all(getattr(t, name) is getattr(SparseGraph, name) for name in _METHODS)):
+        return False
+    return _METHODS.isdisjoint(graph.__dict__)
 
 
 def _field(name):
@@ -89,7 +109,8 @@ for _name in ("m", "k", "nnz", "rowptr", "colind", "vals"):
 
 class _Aggregate(torch.autograd.Function):
     """The aggregation where torch has more to do than backward differentiation (tracing, function
-    transforms, tangents, tensor subclasses, modes): the Function supports or refuses each of them."""
+    transforms, tangents, tensor subclasses, modes) and for graphs with products of their own (any object with
+    spmm and transposed): the Function supports or refuses each of them."""
 
     @staticmethod
     def forward(ctx, X, graph):
@@ -103,7 +124,7 @@ class _Aggregate(torch.autograd.Function):
 
 def aggregate(graph: SparseGraph, X: torch.Tensor) -> torch.Tensor:
     """A . X with gradient A^T . dY with respect to X (A itself is a constant of the graph)."""
-    if _native.aggregate_takes(X):
+    if _as_written(graph) and _native.aggregate_takes(X):
         return _native.aggregate(graph._g, X)
     return _Aggregate.apply(X, graph)
 
@@ -119,7 +140,7 @@ class GraphConv(torch.nn.Module):
         torch.nn.init.xavier_uniform_(self.weight)
 
     def forward(self, graph: SparseGraph, X: torch.Tensor) -> torch.Tensor:
-        if _native.graph_conv_takes(graph._g, X, self.weight, self.bias):
+        if _as_written(graph) and _native.graph_conv_takes(graph._g, X, self.weight, self.bias):
             return _native.graph_conv(graph._g, X, self.weight, self.bias, self.relu)
         Z = aggregate(graph, X @ self.weight)
         if self.bias is not None:

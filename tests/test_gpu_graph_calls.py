@@ -229,3 +229,49 @@ def test_features_are_refused_in_a_capture_and_wait_for_no_other_stream():
         for got in (f for fs in pool.map(some, range(12)) for f in fs):
             assert got["nnz"] == want["nnz"] and got["row_nnz_max"] == want["row_nnz_max"]
             assert got["row_nnz_std"] == pytest.approx(want["row_nnz_std"], rel=1e-9)
+
+
+# ---- graphs with methods of their own --------------------------------------------------------------------------------
+@pytest.mark.parametrize("kind", ["spmm", "transposed", "algo_for", "features", "object", "instance"])
+def test_graphs_with_methods_of_their_own(kind):
+    """aggregate and GraphConv go through spmm and transposed of the graph they are given, spmm through algo_for and
+    algo_for through features, where a subclass or an object brings its own."""
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=800, seed=9)
+    plain = graph_of(a)
+    seen = []
+
+    class Own(gcn.SparseGraph):
+        pass
+
+    class Other:
+        def spmm(self, X, algo=None):
+            seen.append("object")
+            return plain.spmm(X, algo)
+
+        def transposed(self):
+            return plain.transposed()
+
+    def noting(name):
+        def method(self, *args):
+            seen.append(name)
+            return getattr(gcn.SparseGraph, name)(self, *args)
+        return method
+
+    if kind == "object":
+        graph = Other()
+    else:
+        graph = Own(a.m, a.k, plain.rowptr, plain.colind, plain.vals) if kind != "instance" else graph_of(a)
+        if kind == "instance":
+            graph.spmm = lambda X, algo=None: (seen.append(kind), gcn.SparseGraph.spmm(graph, X, algo))[1]
+        else:
+            setattr(Own, kind, noting(kind))
+    layer = layer_of(16, 8)
+    X = torch.randn((a.m, 16), device="cuda", requires_grad=True)
+    dY = torch.randn((a.m, 16), device="cuda")
+    for f, d in ((lambda g: gcn.aggregate(g, X), dY), (lambda g: layer(g, X), dY[:, :8])):
+        del seen[:]
+        got, want = f(graph), f(plain)
+        g_got, g_want = torch.autograd.grad(got, X, d), torch.autograd.grad(want, X, d)
+        assert kind in seen
+        assert torch.allclose(got, want, rtol=1e-4, atol=1e-5) and torch.allclose(g_got[0], g_want[0], rtol=1e-4, atol=1e-5)
