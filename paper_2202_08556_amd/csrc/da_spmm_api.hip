@@ -1100,6 +1100,8 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
 
 namespace {
 constexpr int kDenseMaxLds = 144 << 10;
+constexpr int64_t kDenseMaxRows = 0x7fffffffLL;
+constexpr int64_t kDenseMaxCols = 1 << 20, kSumsMaxCols = 1 << 22;
 
 // Row blocks of the weight gradient: two blocks to a CU over all tiles, and no fewer than 64 rows each.
 int weight_grad_blocks(int64_t rows, int64_t tiles) {
@@ -1117,8 +1119,9 @@ int da_spmm_weight_grad_workspace(int64_t rows, int64_t fin, int64_t fout, size_
 {
     if (!bytes) return fail(DA_ERR_INVALID_ARG, "null bytes%s");
     if (rows < 0 || fin < 0 || fout < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
-    if (rows > 0x7fffffffLL || fin > (1 << 20) || fout > (1 << 20)) return fail(DA_ERR_INVALID_ARG, "size too large%s");
+    if (rows > kDenseMaxRows || fin > kDenseMaxCols || fout > kDenseMaxCols) return fail(DA_ERR_UNSUPPORTED, "size too large%s");
     const int64_t tiles = weight_grad_tiles(fin, fout);
+    if (tiles > kMaxGridY) return fail(DA_ERR_UNSUPPORTED, "more than 65535 tiles%s");
     *bytes = tiles == 0 ? 0 : (size_t)tiles * weight_grad_blocks(rows, tiles) * kWgPart * sizeof(float);
     return DA_OK;
 }
@@ -1136,7 +1139,6 @@ int da_spmm_weight_grad(int64_t rows, int64_t fin, int64_t fout, const float* X,
     if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
         return fail(DA_ERR_INVALID_ARG, "workspace missing, misaligned or smaller than da_spmm_weight_grad_workspace reports%s");
     const int64_t tiles = weight_grad_tiles(fin, fout);
-    if (tiles > kMaxGridY) return fail(DA_ERR_UNSUPPORTED, "more than 65535 tiles%s");
     const int nb = weight_grad_blocks(rows, tiles);
     const int64_t per = ((rows + nb - 1) / nb + 15) / 16 * 16;      // whole turns of a wave, 16 rows
     hipStream_t s = (hipStream_t)stream;
@@ -1161,7 +1163,8 @@ static int column_sums_blocks(int64_t rows) {
 int da_spmm_column_sums_workspace(int64_t rows, int64_t n, size_t* bytes)
 {
     if (!bytes) return fail(DA_ERR_INVALID_ARG, "null bytes%s");
-    if (rows < 0 || n < 0 || rows > 0x7fffffffLL || n > (1 << 22)) return fail(DA_ERR_INVALID_ARG, "bad size%s");
+    if (rows < 0 || n < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
+    if (rows > kDenseMaxRows || n > kSumsMaxCols) return fail(DA_ERR_UNSUPPORTED, "size too large%s");
     *bytes = (size_t)column_sums_blocks(rows) * (size_t)n * sizeof(float);
     return DA_OK;
 }
@@ -1179,7 +1182,6 @@ int da_spmm_column_sums(int64_t rows, int64_t n, const float* G, int64_t ldg, fl
         return fail(DA_ERR_INVALID_ARG, "workspace missing, misaligned or smaller than da_spmm_column_sums_workspace reports%s");
     const int nb = column_sums_blocks(rows), lanes = n >= kCsBlock ? kCsBlock : pow2_ceil(n);
     const int64_t ny = (n + lanes - 1) / lanes;
-    if (ny > kMaxGridY) return fail(DA_ERR_UNSUPPORTED, "too many columns%s");
     const int per = (int)((rows + nb - 1) / nb);
     hipStream_t s = (hipStream_t)stream;
     float* part = static_cast<float*>(workspace);
@@ -1210,7 +1212,7 @@ int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float* A, int64_t ld
                   float* C, int64_t ldc, void* stream)
 {
     if (rows < 0 || k < 0 || n < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
-    if (rows > 0x7fffffffLL || k > (1 << 20) || n > (1 << 20)) return fail(DA_ERR_INVALID_ARG, "size too large%s");
+    if (rows > kDenseMaxRows || n > kDenseMaxCols) return fail(DA_ERR_UNSUPPORTED, "size too large%s");
     if (rows == 0 || n == 0) return DA_OK;
     if (k < 1) return fail(DA_ERR_UNSUPPORTED, "no columns in A%s");
     if (lda < k || ldc < n || wk < 1 || wn < 1) return fail(DA_ERR_INVALID_ARG, "leading dimension smaller than the extent it strides over%s");

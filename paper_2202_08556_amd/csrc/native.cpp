@@ -453,23 +453,29 @@ void dense_product(const Tensor& A, const Tensor& W, bool transpose_w, Tensor& o
     at::mm_out(out, A, transpose_w ? W.t() : W);
 }
 
+// The kernels refuse sizes that their grids or counters do not hold; the library takes those.
 Tensor weight_gradient(const Tensor& X, const Tensor& G) {
     const int64_t rows = X.size(0), fin = X.size(1), fout = G.size(1);
+    size_t bytes = 0;
     if (rows >= 1 && fin >= 4 && fout >= 4 && X.stride(1) == 1 && G.stride(1) == 1) {
-        size_t bytes = 0;
-        check(da_spmm_weight_grad_workspace(rows, fin, fout, &bytes));
-        Tensor dW = at::empty({fin, fout}, X.options());
-        Tensor ws = at::empty({(int64_t)bytes}, X.options().dtype(at::kByte));
-        check(da_spmm_weight_grad(rows, fin, fout, data<float>(X), leading(X), data<float>(G), leading(G), data<float>(dW),
-                                  data<void>(ws), bytes, stream_of(X)));
-        return dW;
+        const int st = da_spmm_weight_grad_workspace(rows, fin, fout, &bytes);
+        if (st != DA_ERR_UNSUPPORTED) {
+            check(st);
+            Tensor dW = at::empty({fin, fout}, X.options());
+            Tensor ws = at::empty({(int64_t)bytes}, X.options().dtype(at::kByte));
+            check(da_spmm_weight_grad(rows, fin, fout, data<float>(X), leading(X), data<float>(G), leading(G), data<float>(dW),
+                                      data<void>(ws), bytes, stream_of(X)));
+            return dW;
+        }
     }
     return at::mm(X.t(), G);
 }
 
 Tensor column_sums(const Tensor& G) {
     size_t bytes = 0;
-    check(da_spmm_column_sums_workspace(G.size(0), G.size(1), &bytes));
+    const int st = da_spmm_column_sums_workspace(G.size(0), G.size(1), &bytes);
+    if (st == DA_ERR_UNSUPPORTED) return G.sum(0);
+    check(st);
     Tensor sums = at::empty({G.size(1)}, G.options());
     Tensor ws = at::empty({(int64_t)bytes}, G.options().dtype(at::kByte));
     check(da_spmm_column_sums(G.size(0), G.size(1), data<float>(G), leading(G), data<float>(sums), data<void>(ws), bytes,

@@ -167,3 +167,15 @@ def test_addresses_are_those_of_data_ptr(call):
         assert not any(torch._C._is_cow_tensor(o) for o in outs[:3])
     assert not torch._C._is_cow_tensor(outs[2])
     assert _Addressed.asked >= 1
+
+
+def test_dense_parts_say_unsupported_where_the_library_is_to_take_over():
+    p, big = 1 << 20, 1 << 62
+    lib = da._lib
+    size = ctypes.c_size_t(0)
+    assert lib.da_spmm_dense(4, 8, 2 ** 20 + 1, p, 8, p, 2 ** 20 + 1, 1, p, 2 ** 20 + 1, None) == da.DA_ERR_UNSUPPORTED
+    for fin, fout in ((2 ** 20 + 1, 8), (8, 2 ** 20 + 1), (65600, 4160)):
+        assert lib.da_spmm_weight_grad_workspace(4, fin, fout, ctypes.byref(size)) == da.DA_ERR_UNSUPPORTED
+        assert lib.da_spmm_weight_grad(4, fin, fout, p, fin, p, fout, p, p, big, None) == da.DA_ERR_UNSUPPORTED
+    assert lib.da_spmm_column_sums_workspace(4, 2 ** 22 + 1, ctypes.byref(size)) == da.DA_ERR_UNSUPPORTED
+    assert lib.da_spmm_column_sums(4, 2 ** 22 + 1, p, 2 ** 22 + 1, p, p, big, None) == da.DA_ERR_UNSUPPORTED

@@ -275,3 +275,20 @@ def test_graphs_with_methods_of_their_own(kind):
         g_got, g_want = torch.autograd.grad(got, X, d), torch.autograd.grad(want, X, d)
         assert kind in seen
         assert torch.allclose(got, want, rtol=1e-4, atol=1e-5) and torch.allclose(g_got[0], g_want[0], rtol=1e-4, atol=1e-5)
+
+
+# ---- sizes beyond the own dense kernels ------------------------------------------------------------------------------
+@pytest.mark.parametrize("fin,fout", [(4, 2 ** 22 + 3), (65600, 4160)], ids=["columns", "tiles"])
+def test_layers_beyond_the_own_dense_kernels(fin, fout):
+    """More columns than the kernels take, more tiles of a weight gradient than a grid holds: the library's."""
+    a = matrix(5, 6)
+    A, graph, layer = dense(a).float().cuda(), graph_of(a), layer_of(fin, fout, relu=False)
+    X = torch.randn((a.k, fin), device="cuda", requires_grad=True)
+    Y = layer(graph, X)
+    dY = torch.randn((a.m, fout), device="cuda")
+    gx, gw, gb = torch.autograd.grad(Y, (X, layer.weight, layer.bias), dY)
+    with torch.no_grad():
+        dH = A.t() @ dY
+        for got, want in ((Y, A @ (X @ layer.weight) + layer.bias), (gx, dH @ layer.weight.t()), (gw, X.t() @ dH), (gb, dY.sum(0))):
+            # fp32 on both sides: sums of up to 2^22 products of either sign, a hundred roundings of the largest
+            assert got.shape == want.shape and float((got - want).abs().max()) <= 1e-5 * float(want.abs().max())
