@@ -262,7 +262,7 @@ int da_csr_transpose_noalloc(int64_t m, int64_t k, int64_t nnz,
  *   X  fp32[rows x fin], leading dimension ldx >= fin;  G  fp32[rows x fout], ldg >= fout
  *   dW fp32[fin x fout], dense
  *   workspace  device scratch of the size da_spmm_weight_grad_workspace reports, 16-byte aligned
- *   4 <= fin, fout <= 2^20, rows >= 1 and at most 65535 tiles of 64 x 64 (DA_ERR_UNSUPPORTED otherwise)
+ *   4 <= fin, fout <= 2^20, 1 <= rows <= 2^30 and at most 65535 tiles of 64 x 64 (DA_ERR_UNSUPPORTED otherwise)
  */
 int da_spmm_weight_grad_workspace(int64_t rows, int64_t fin, int64_t fout, size_t *bytes /* host, out */);
 int da_spmm_weight_grad(int64_t rows, int64_t fin, int64_t fout, const float *X, int64_t ldx,
@@ -270,7 +270,7 @@ int da_spmm_weight_grad(int64_t rows, int64_t fin, int64_t fout, const float *X,
                         void *workspace, size_t workspace_bytes, void *stream);
 
 /* sums[c] = sum over the rows of G (rows x n, leading dimension ldg >= n), c < n; workspace as above.
- * n <= 2^22 (DA_ERR_UNSUPPORTED beyond). */
+ * n <= 2^22, rows <= 2^30 (DA_ERR_UNSUPPORTED beyond). */
 int da_spmm_column_sums_workspace(int64_t rows, int64_t n, size_t *bytes /* host, out */);
 int da_spmm_column_sums(int64_t rows, int64_t n, const float *G, int64_t ldg, float *sums,
                         void *workspace, size_t workspace_bytes, void *stream);
@@ -282,7 +282,7 @@ int da_spmm_bias_relu(int64_t rows, int64_t n, float *Z, const float *bias, int 
  * C = A . W on the fp32 matrix cores: A fp32[rows x k] row-major (lda >= k), element (p, q) of W at
  * W[p*wk + q*wn] (wk = n, wn = 1 for a row-major k x n matrix; wk = 1, wn = k for the transpose of a row-major
  * n x k matrix), C fp32[rows x n] row-major (ldc >= n), overwritten.  1 <= k <= 256 and at most 144 KiB of W
- * per 128 columns (a block keeps them in LDS), n <= 2^20; DA_ERR_UNSUPPORTED beyond.
+ * per 128 columns (a block keeps them in LDS), n <= 2^20, rows <= 2^30; DA_ERR_UNSUPPORTED beyond.
  */
 int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float *A, int64_t lda, const float *W, int64_t wk, int64_t wn,
                   float *C, int64_t ldc, void *stream);

@@ -1100,7 +1100,7 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
 
 namespace {
 constexpr int kDenseMaxLds = 144 << 10;
-constexpr int64_t kDenseMaxRows = 0x7fffffffLL;
+constexpr int64_t kDenseMaxRows = 1 << 30;         // the kernels count rows, and a block's rows past the end, in 32 bits
 constexpr int64_t kDenseMaxCols = 1 << 20, kSumsMaxCols = 1 << 22;
 
 // Row blocks of the weight gradient: two blocks to a CU over all tiles, and no fewer than 64 rows each.

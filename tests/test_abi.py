@@ -169,6 +169,20 @@ def test_addresses_are_those_of_data_ptr(call):
     assert _Addressed.asked >= 1
 
 
+@pytest.mark.parametrize("rows", [2 ** 30 + 1, 2 ** 31 - 1])
+def test_dense_parts_refuse_more_rows_than_their_kernels_count(rows):
+    """The last rows of a block's range must not leave 32 bits; refused before anything is launched (the addresses
+    are never used)."""
+    p, big = 1 << 20, 1 << 62
+    lib = da._lib
+    size = ctypes.c_size_t(0)
+    assert lib.da_spmm_dense(rows, 8, 8, p, 8, p, 8, 1, p, 8, None) == da.DA_ERR_UNSUPPORTED
+    assert lib.da_spmm_weight_grad(rows, 8, 8, p, 8, p, 8, p, p, big, None) == da.DA_ERR_UNSUPPORTED
+    assert lib.da_spmm_weight_grad_workspace(rows, 8, 8, ctypes.byref(size)) == da.DA_ERR_UNSUPPORTED
+    assert lib.da_spmm_column_sums(rows, 8, p, 8, p, p, big, None) == da.DA_ERR_UNSUPPORTED
+    assert lib.da_spmm_column_sums_workspace(rows, 8, ctypes.byref(size)) == da.DA_ERR_UNSUPPORTED
+
+
 def test_dense_parts_say_unsupported_where_the_library_is_to_take_over():
     p, big = 1 << 20, 1 << 62
     lib = da._lib
