@@ -424,13 +424,12 @@ struct AggregateBackward : torch::autograd::Node {
 
 bool wants_grad(const Tensor& t) { return t.defined() && t.requires_grad(); }
 
-Tensor aggregate(const GraphPtr& g, const Tensor& X, int id) {
-    const ArraysPtr a = g->now();
-    const Tensor x = operand(*a, X);
+// x: X as operand() gives it
+Tensor aggregate(const GraphPtr& g, const Arrays& a, const Tensor& X, const Tensor& x) {
     Tensor Y;
     {
         at::AutoDispatchBelowADInplaceOrView below;
-        Y = g->product(*a, x, x.size(1), id);
+        Y = g->product(a, x, x.size(1), -1);
     }
     if (at::GradMode::is_enabled() && wants_grad(X)) {
         auto node = std::shared_ptr<AggregateBackward>(new AggregateBackward(), torch::autograd::deleteNode);
@@ -512,9 +511,10 @@ struct GraphConvBackward : torch::autograd::Node {
         c10::DeviceGuard guard(graph->now()->rowptr.device());
         const bool again = at::GradMode::is_enabled();       // gradients of gradients: dense parts differentiable
         Tensor dZ = relu ? at::threshold_backward(dY, Y, 0) : dY;
+        if (!again) dZ = dZ.contiguous();                    // once for all that read it
         if (task_should_compute_output(2)) {
             if (again) result[2] = dZ.sum(0);
-            else { at::AutoDispatchBelowADInplaceOrView below; result[2] = column_sums(dZ.contiguous()); }
+            else { at::AutoDispatchBelowADInplaceOrView below; result[2] = column_sums(dZ); }
         }
         if (!task_should_compute_output(0) && !task_should_compute_output(1)) return result;
         Tensor dH;
@@ -618,9 +618,10 @@ void bind_graphs(py::module_& mod) {
             return g.product(*a, x, x.size(1), id);
         });
     mod.def("aggregate", [](const GraphPtr& g, const Tensor& X) {
-        const Tensor x = operand(*g->now(), X);      // errors are Python exceptions: raised with the lock held
+        const ArraysPtr a = g->now();
+        const Tensor x = operand(*a, X);      // errors are Python exceptions: raised with the lock held
         py::gil_scoped_release r;
-        return aggregate(g, X, -1);
+        return aggregate(g, *a, X, x);
     });
     mod.def("aggregate_takes", [](py::handle X) { return ordinary_context() && ordinary(X); });
     mod.def("graph_conv", &graph_conv, release());

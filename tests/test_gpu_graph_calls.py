@@ -292,3 +292,35 @@ def test_layers_beyond_the_own_dense_kernels(fin, fout):
         for got, want in ((Y, A @ (X @ layer.weight) + layer.bias), (gx, dH @ layer.weight.t()), (gw, X.t() @ dH), (gb, dY.sum(0))):
             # fp32 on both sides: sums of up to 2^22 products of either sign, a hundred roundings of the largest
             assert got.shape == want.shape and float((got - want).abs().max()) <= 1e-5 * float(want.abs().max())
+
+
+# ---- copies ----------------------------------------------------------------------------------------------------------
+def test_operands_are_laid_out_once():
+    """A non-contiguous X or gradient costs one contiguous copy, also where several products read it."""
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=1024, seed=11)
+    graph, layer = graph_of(a), layer_of(32, 32, relu=False)
+    wide = torch.randn((32, a.m), device="cuda").t()
+    dense_x = wide.contiguous()
+    ones = torch.ones((1, 1), device="cuda").expand(a.m, 32)
+    dense_g = ones.contiguous()
+    size = a.m * 32 * 4
+
+    def allocated(f):
+        f()                                                   # plans and scratch of the first calls
+        f()
+        before = torch.cuda.memory_stats()["allocated_bytes.all.allocated"]
+        f()
+        return torch.cuda.memory_stats()["allocated_bytes.all.allocated"] - before
+
+    def aggregated(x, g):
+        x = x.detach().requires_grad_(True)
+        return torch.autograd.grad(gcn.aggregate(graph, x), x, g)
+
+    def layered(x, g):
+        return torch.autograd.grad(layer(graph, dense_x.requires_grad_(True)), (dense_x, layer.weight, layer.bias), g)
+
+    both = allocated(lambda: aggregated(dense_x, dense_g))
+    assert allocated(lambda: aggregated(wide, dense_g)) == both + size
+    assert allocated(lambda: aggregated(dense_x, ones)) == both + size
+    assert allocated(lambda: layered(dense_x, ones)) == allocated(lambda: layered(dense_x, dense_g)) + size
