@@ -34,6 +34,7 @@
 #include <exception>
 #include <memory>
 #include <mutex>
+#include <optional>
 #include <utility>
 #include <vector>
 
@@ -359,13 +360,12 @@ struct Graph : std::enable_shared_from_this<Graph> {
     // algorithms) before the second product with an EB algorithm that the selector chose, and before the first one
     // the caller chose, unless the stream is being captured: preparing allocates and waits, and its orders only
     // cost speed where they are missing.
-    Tensor product(const Arrays& a, const Tensor& X, int64_t N, int id) {
+    Tensor product(const Arrays& a, const Tensor& X, int64_t N, std::optional<int> given = std::nullopt) {
         c10::DeviceGuard guard(a.rowptr.device());
-        const bool chosen = id < 0;
-        if (chosen) id = algo_for(N);
+        const int id = given ? *given : algo_for(N);
         if (id >= DA_EB_RM_SR && !prepared && !capturing(a.rowptr)) {
             std::lock_guard<std::recursive_mutex> lk(mu);
-            if (!chosen || eb_products > 0) prepare(a);
+            if (given || eb_products > 0) prepare(a);
             ++eb_products;
         }
         Tensor C = at::empty({a.m, N}, a.vals.options());
@@ -417,7 +417,7 @@ struct AggregateBackward : torch::autograd::Node {
         const auto t = graph->transposed();
         const ArraysPtr at_now = t->now();
         const Tensor dY = operand(*at_now, grads[0].detach());
-        return {t->product(*at_now, dY, dY.size(1), -1)};
+        return {t->product(*at_now, dY, dY.size(1))};
     }
     std::string name() const override { return "AggregateBackward"; }
 };
@@ -429,7 +429,7 @@ Tensor aggregate(const GraphPtr& g, const Arrays& a, const Tensor& X, const Tens
     Tensor Y;
     {
         at::AutoDispatchBelowADInplaceOrView below;
-        Y = g->product(a, x, x.size(1), -1);
+        Y = g->product(a, x, x.size(1));
     }
     if (at::GradMode::is_enabled() && wants_grad(X)) {
         auto node = std::shared_ptr<AggregateBackward>(new AggregateBackward(), torch::autograd::deleteNode);
@@ -522,7 +522,7 @@ struct GraphConvBackward : torch::autograd::Node {
             at::AutoDispatchBelowADInplaceOrView below;
             const auto t = graph->transposed();
             const ArraysPtr at_now = t->now();
-            dH = t->product(*at_now, operand(*at_now, dZ.detach()), dZ.size(1), -1);
+            dH = t->product(*at_now, operand(*at_now, dZ.detach()), dZ.size(1));
         }
         if (again) {
             if (task_should_compute_output(1)) result[1] = at::mm(X.t(), dH);
@@ -551,7 +551,7 @@ Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std
         c10::DeviceGuard guard(a->rowptr.device());
         Tensor H = at::empty({X.size(0), row_pitch(n)}, X.options()).narrow(1, 0, n);
         dense_product(X, W, false, H);
-        Z = g->product(*a, H, n, -1);
+        Z = g->product(*a, H, n);
         check(da_spmm_bias_relu(a->m, n, data<float>(Z), data<float>(b), relu ? 1 : 0, stream_of(Z)));
     }
     if (at::GradMode::is_enabled() && (wants_grad(X) || wants_grad(W) || wants_grad(b))) {
@@ -610,7 +610,7 @@ void bind_graphs(py::module_& mod) {
         .def("algo_for", &Graph::algo_for, release())
         .def("prepare", [](Graph& g) { g.prepare(); }, release())
         .def("transposed", &Graph::transposed, release())
-        .def("spmm", [](Graph& g, const Tensor& X, int id) {
+        .def("spmm", [](Graph& g, const Tensor& X, std::optional<int> id) {
             const ArraysPtr a = g.now();
             const Tensor x = operand(*a, X);
             py::gil_scoped_release r;

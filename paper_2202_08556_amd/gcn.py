@@ -77,7 +77,7 @@ class SparseGraph:
         """A . X for a row-major fp32 k x N tensor on the same device; returns a new m x N tensor."""
         if algo is None and not _as_written(self):
             algo = self.algo_for(int(X.shape[1])) if X.dim() == 2 else 0
-        return self._g.spmm(X, -1 if algo is None else int(algo))
+        return self._g.spmm(X, None if algo is None else int(algo))
 
 
 _METHODS = frozenset(("spmm", "transposed", "algo_for", "features"))

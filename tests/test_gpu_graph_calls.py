@@ -324,3 +324,14 @@ def test_operands_are_laid_out_once():
     assert allocated(lambda: aggregated(wide, dense_g)) == both + size
     assert allocated(lambda: aggregated(dense_x, ones)) == both + size
     assert allocated(lambda: layered(dense_x, ones)) == allocated(lambda: layered(dense_x, dense_g)) + size
+
+
+# ---- errors ----------------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("algo", [-1, -7, 8])
+def test_algorithm_ids_outside_the_table_are_refused(algo):
+    from paper_2202_08556_amd import binding as da
+    a = gen.powerlaw_csr(m=300, seed=12)
+    graph = graph_of(a)
+    with pytest.raises(da.DaSpmmError) as err:
+        graph.spmm(torch.ones((a.m, 4), device="cuda"), algo)
+    assert err.value.status == da.DA_ERR_BAD_ALGO
