@@ -22,6 +22,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
 #include <torch/csrc/autograd/functions/utils.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -35,6 +36,7 @@
 #include <memory>
 #include <mutex>
 #include <optional>
+#include <stdexcept>
 #include <utility>
 #include <vector>
 
@@ -239,6 +241,32 @@ void check(int status) {
     if (status != DA_OK) throw DaError(status);
 }
 
+void set_error(const DaError& e) {                // the interpreter lock is held
+    const py::object err = py::reinterpret_borrow<py::object>(g_error)(e.status, e.text);
+    PyErr_SetObject(g_error, err.ptr());
+}
+
+// Runs a step of a backward pass.  The autograd engine hands Python exceptions on and makes a plain RuntimeError of
+// all others, so errors become Python exceptions here.
+template <class F>
+auto in_backward(F&& f) {
+    auto raise = [](const auto& set) {
+        py::gil_scoped_acquire gil;
+        set();
+        python_error err;
+        err.persist();
+        throw err;
+    };
+    try {
+        return f();
+    } catch (const DaError& e) {
+        raise([&] { set_error(e); });
+    } catch (const py::builtin_exception& e) {
+        raise([&] { e.set_error(); });
+    }
+    throw std::logic_error("not reached");
+}
+
 void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
 
 bool capturing(const Tensor& t) {
@@ -412,6 +440,9 @@ bool ordinary(py::handle x) { return THPVariable_CheckExact(x.ptr()) && ordinary
 struct AggregateBackward : torch::autograd::Node {
     GraphPtr graph;
     torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        return in_backward([&] { return gradients(grads); });
+    }
+    torch::autograd::variable_list gradients(const torch::autograd::variable_list& grads) {
         if (!grads[0].defined() || !task_should_compute_output(0)) return {Tensor()};
         at::AutoDispatchBelowADInplaceOrView below;
         const auto t = graph->transposed();
@@ -498,6 +529,9 @@ struct GraphConvBackward : torch::autograd::Node {
     }
 
     torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        return in_backward([&] { return gradients(grads); });
+    }
+    torch::autograd::variable_list gradients(const torch::autograd::variable_list& grads) {
         torch::autograd::variable_list result(3);
         if (!grads[0].defined()) return result;
         const Tensor dY = grads[0].resolve_neg();
@@ -586,8 +620,7 @@ void bind_graphs(py::module_& mod) {
         try {
             if (p) std::rethrow_exception(p);
         } catch (const DaError& e) {
-            py::object err = py::reinterpret_borrow<py::object>(g_error)(e.status, e.text);
-            PyErr_SetObject(g_error, err.ptr());
+            set_error(e);
         }
     });
     using release = py::call_guard<py::gil_scoped_release>;

@@ -335,3 +335,18 @@ def test_algorithm_ids_outside_the_table_are_refused(algo):
     with pytest.raises(da.DaSpmmError) as err:
         graph.spmm(torch.ones((a.m, 4), device="cuda"), algo)
     assert err.value.status == da.DA_ERR_BAD_ALGO
+
+
+@pytest.mark.parametrize("call", ["aggregate", "layer"])
+def test_errors_of_a_backward_pass_are_the_library_s(call):
+    """The transpose of a graph whose row count was spoilt after the forward pass is refused on the host."""
+    from paper_2202_08556_amd import binding as da
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=300, seed=13)
+    graph, layer = graph_of(a), layer_of(4, 4)
+    X = torch.randn((a.m, 4), device="cuda", requires_grad=True)
+    Y = gcn.aggregate(graph, X) if call == "aggregate" else layer(graph, X)
+    graph.m = -1
+    with pytest.raises(da.DaSpmmError) as err:
+        torch.autograd.grad(Y, X, torch.ones_like(Y))
+    assert err.value.status == da.DA_ERR_INVALID_ARG
