@@ -415,6 +415,7 @@ GraphPtr make_graph(int64_t m, int64_t k, const Tensor& rowptr, const Tensor& co
 // X as the product takes it: float32, k rows, neighbouring columns
 Tensor operand(const Arrays& a, const Tensor& X) {
     if (X.scalar_type() != at::kFloat || X.dim() != 2 || X.size(0) != a.k) throw py::value_error("X must be a float32 k x N tensor");
+    if (X.device() != a.rowptr.device()) throw py::value_error("X must be on the device of the graph");
     return X.resolve_neg().contiguous();
 }
 

@@ -350,3 +350,14 @@ def test_errors_of_a_backward_pass_are_the_library_s(call):
     with pytest.raises(da.DaSpmmError) as err:
         torch.autograd.grad(Y, X, torch.ones_like(Y))
     assert err.value.status == da.DA_ERR_INVALID_ARG
+
+
+def test_operands_on_the_host_are_refused():
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=300, seed=14)
+    graph, X = graph_of(a), torch.ones((a.m, 4))
+    for call in (graph.spmm, lambda x: gcn.aggregate(graph, x), lambda x: gcn._Aggregate.apply(x, graph)):
+        with pytest.raises(ValueError, match="device"):
+            call(X)
+    with pytest.raises((ValueError, RuntimeError)):
+        gcn.GraphConv(4, 4)(graph, X)                         # weights on the host too
