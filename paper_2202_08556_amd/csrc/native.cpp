@@ -404,7 +404,8 @@ struct Graph : std::enable_shared_from_this<Graph> {
 };
 using GraphPtr = std::shared_ptr<Graph>;
 
-GraphPtr make_graph(int64_t m, int64_t k, const Tensor& rowptr, const Tensor& colind, const Tensor& vals) {
+GraphPtr make_graph(int64_t m, int64_t k, const Tensor& rowptr, const Tensor& colind, const Tensor& vals, bool restored) {
+    if (restored) return std::make_shared<Graph>(m, k, rowptr, colind, vals);   // from a copy or file, wherever that left them
     if (rowptr.scalar_type() != at::kInt || colind.scalar_type() != at::kInt || vals.scalar_type() != at::kFloat)
         throw py::type_error("rowptr / colind must be int32 and vals float32");
     if (!(rowptr.is_cuda() && colind.is_cuda() && vals.is_cuda())) throw py::value_error("CSR arrays must live on the GPU");
@@ -628,7 +629,8 @@ void bind_graphs(py::module_& mod) {
     auto get = [](auto field) { return [field](Graph& g) { return (*g.now()).*field; }; };
     auto put = [](auto field) { return [field](Graph& g, decltype(Arrays{}.*field) value) { g.change(field, value); }; };
     py::class_<Graph, GraphPtr>(mod, "Graph")
-        .def(py::init(&make_graph))
+        .def(py::init(&make_graph), py::arg("m"), py::arg("k"), py::arg("rowptr"), py::arg("colind"), py::arg("vals"),
+             py::arg("restored") = false)
         .def_property("m", get(&Arrays::m), put(&Arrays::m))
         .def_property("k", get(&Arrays::k), put(&Arrays::k))
         .def_property("nnz", get(&Arrays::nnz), put(&Arrays::nnz))

@@ -37,8 +37,21 @@ class SparseGraph:
         self._g = _native.Graph(m, k, rowptr, colind, vals)
         self._t = None
 
-    def __reduce__(self):
-        return type(self), (self.m, self.k, self.rowptr, self.colind, self.vals)
+    def __getstate__(self):
+        """What copies and files hold: the matrix and whatever attributes a program has added."""
+        state = {name: value for name, value in self.__dict__.items() if name not in ("_g", "_t", "_algo")}
+        state.update((name, getattr(self, name)) for name in ("m", "k", "nnz", "rowptr", "colind", "vals"))
+        return state
+
+    def __setstate__(self, state):
+        state = dict(state)
+        m, k, nnz, *arrays = (state.pop(name) for name in ("m", "k", "nnz", "rowptr", "colind", "vals"))
+        for name in ("_features", "_algo", "_prepared", "_t"):       # in files of earlier versions; found again when needed
+            state.pop(name, None)
+        self.__dict__.update(state)
+        self._g = _native.Graph(m, k, *arrays, restored=True)
+        self._g.nnz = nnz
+        self._t = None
 
     @classmethod
     def from_numpy(cls, a, device="cuda:0") -> "SparseGraph":

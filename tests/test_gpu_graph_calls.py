@@ -361,3 +361,36 @@ def test_operands_on_the_host_are_refused():
             call(X)
     with pytest.raises((ValueError, RuntimeError)):
         gcn.GraphConv(4, 4)(graph, X)                         # weights on the host too
+
+
+# ---- copies of graphs ----------------------------------------------------------------------------------------
+def test_copies_keep_added_attributes_and_files_of_earlier_versions_load():
+    import copy
+    import io
+    import pickle
+
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=400, seed=15)
+    graph = graph_of(a)
+    X = torch.randn((a.m, 8), device="cuda", requires_grad=True)
+    want = gcn.aggregate(graph, X)
+    graph.label = "train"
+    graph.transposed()
+    twins = [copy.copy(graph), copy.deepcopy(graph), pickle.loads(pickle.dumps(graph))]
+    old = gcn.SparseGraph.__new__(gcn.SparseGraph)            # the attributes that an instance used to consist of
+    old.__setstate__(dict(m=a.m, k=a.k, nnz=a.nnz, rowptr=graph.rowptr, colind=graph.colind, vals=graph.vals, label="train",
+                          _features=dict(rows=a.m), _algo={8: 3}, _t=None, _prepared=True))
+    file = io.BytesIO()
+    torch.save(graph, file)
+    file.seek(0)
+    host = torch.load(file, map_location="cpu", weights_only=False)
+    assert not host.vals.is_cuda
+    for name in ("rowptr", "colind", "vals"):
+        setattr(host, name, getattr(host, name).cuda())
+    for twin in twins + [old, host]:
+        Y = gcn.aggregate(twin, X)
+        assert twin.label == "train" and torch.allclose(Y, want, rtol=1e-4, atol=1e-6)
+        g, w = torch.autograd.grad(Y.sum(), X)[0], torch.autograd.grad(want.sum(), X, retain_graph=True)[0]
+        assert torch.allclose(g, w, rtol=1e-4, atol=1e-5)
+    assert twins[0].vals is graph.vals or twins[0].vals.data_ptr() == graph.vals.data_ptr()
+    assert twins[1].vals.data_ptr() != graph.vals.data_ptr()
