@@ -34,7 +34,9 @@ class SparseGraph:
     order (speed), never the result."""
 
     def __init__(self, m: int, k: int, rowptr: torch.Tensor, colind: torch.Tensor, vals: torch.Tensor):
-        self._g = _native.Graph(m, k, rowptr, colind, vals)
+        if int(m) != m:                             # before the arrays' lengths are compared with whole numbers
+            raise ValueError("CSR array sizes do not match")
+        self._g = _native.Graph(int(m), int(k), rowptr, colind, vals)
         self._t = None
 
     def __getstate__(self):

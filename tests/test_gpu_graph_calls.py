@@ -363,7 +363,7 @@ def test_operands_on_the_host_are_refused():
         gcn.GraphConv(4, 4)(graph, X)                         # weights on the host too
 
 
-# ---- copies of graphs ----------------------------------------------------------------------------------------
+# ---- copies of graphs and sizes ----------------------------------------------------------------------------------------
 def test_copies_keep_added_attributes_and_files_of_earlier_versions_load():
     import copy
     import io
@@ -394,3 +394,13 @@ def test_copies_keep_added_attributes_and_files_of_earlier_versions_load():
         assert torch.allclose(g, w, rtol=1e-4, atol=1e-5)
     assert twins[0].vals is graph.vals or twins[0].vals.data_ptr() == graph.vals.data_ptr()
     assert twins[1].vals.data_ptr() != graph.vals.data_ptr()
+
+
+def test_sizes_given_as_floats():
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=300, seed=16)
+    arrays = graph_of(a)
+    graph = gcn.SparseGraph(float(a.m), np.float64(a.k), arrays.rowptr, arrays.colind, arrays.vals)
+    assert (graph.m, graph.k) == (a.m, a.k) and isinstance(graph.m, int)
+    with pytest.raises(ValueError):
+        gcn.SparseGraph(a.m + 0.5, a.k, arrays.rowptr, arrays.colind, arrays.vals)
