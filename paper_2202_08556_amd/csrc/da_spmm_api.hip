@@ -88,27 +88,28 @@ int env_int(const char* name, int fallback) {
 
 bool is_pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 
-// nnz of matrices whose features were extracted, keyed by (rowptr address, m).  da_spmm uses it
-// only to size EB grids; EB kernels stride over all chunks whatever the grid size, so a stale or
-// missing hint costs speed, never correctness.
-struct NnzHint { const void* rowptr; int64_t m; int64_t nnz; };
+// What is known of matrices whose features were extracted or that were prepared, keyed by (rowptr address,
+// m): nnz, and the length of the row that an average entry lies in (sum of squared row lengths over nnz;
+// 0 = unknown).  da_spmm uses both only for the launch geometry; the EB kernels stride over all chunks
+// whatever the grid size, so a stale or missing hint costs speed, never correctness.
+struct MatrixHint { const void* rowptr; int64_t m; int64_t nnz; double seen_len; };
 std::mutex g_hint_mu;
-NnzHint g_hints[16];
+MatrixHint g_hints[16];
 int g_hint_next = 0;
 
-void remember_nnz(const void* rowptr, int64_t m, int64_t nnz) {
+void remember_matrix(const void* rowptr, int64_t m, int64_t nnz, double seen_len) {
     std::lock_guard<std::mutex> lk(g_hint_mu);
     for (auto& h : g_hints)
-        if (h.rowptr == rowptr && h.m == m) { h.nnz = nnz; return; }
-    g_hints[g_hint_next] = NnzHint{rowptr, m, nnz};
+        if (h.rowptr == rowptr && h.m == m) { h.nnz = nnz; h.seen_len = seen_len; return; }
+    g_hints[g_hint_next] = MatrixHint{rowptr, m, nnz, seen_len};
     g_hint_next = (g_hint_next + 1) % 16;
 }
 
-int64_t lookup_nnz(const void* rowptr, int64_t m) {
+MatrixHint lookup_matrix(const void* rowptr, int64_t m) {
     std::lock_guard<std::mutex> lk(g_hint_mu);
     for (const auto& h : g_hints)
-        if (h.rowptr == rowptr && h.m == m) return h.nnz;
-    return -1;
+        if (h.rowptr == rowptr && h.m == m) return h;
+    return MatrixHint{nullptr, 0, -1, 0.0};
 }
 
 // Chunk schedules of matrices prepared with da_spmm_prepare, keyed like the nnz hints.  The
@@ -170,15 +171,41 @@ Schedule lookup_schedule(const void* rowptr, const void* colind, int64_t m, int 
     return Schedule{nullptr, 0, 0, 0, 0, 0, 0, 0, 3, nullptr, nullptr};
 }
 
+// SR from 17 columns, where rows of B and C are not whole 16-byte pieces: whether a wave is better off with 8, 4 or 2
+// workers of 16-byte lanes than with 2 or 1 of one column per lane.
+// RB: a wave waits for its longest row.  Where rows are short and of one length the loads decide (27-point
+// stencil, N = 24: 19 us against 27; 12 entries a row, N = 17: 20 and 25; 15 +- 7: 21 and 23), beyond that the
+// waiting does (25 +- 12: 24 and 23; 40 +- 20: 36 and 31; lognormal rows of 23, coefficient 1.3: 61 and 47;
+// power-law: 198 and 131), at any width up to 63 (power-law N = 63: 202 and 167).  Above 64 columns one column per
+// lane takes a second pass over the row (N = 65, lognormal: 92 and 108), which pays only where one row of very many
+// entries sets the time (N = 65, rows of 1000: 118 and 99; power-law A^T: 974 and 797).
+// EB: without a plan a chunk begins with a search that a wave's workers make one after another (power-law
+// N = 24: 202 and 186; skewed: 887 and 835).  With one the loads decide (power-law N = 24: 145 and 161, N = 41:
+// 210 and 242), unless the matrix has too few entries for that many workers (105 000: 19 and 13), or so many in
+// long rows that the workers end their chunks with additions to the same lines (A^T of a power-law graph with 1.2 M
+// entries, N = 17: 44 and 31) -- which 12 waves per SIMD hide (33 M entries in rows of 60 000, N = 24: 316 and
+// 354; 13 M: 152 and 134).  From 25 columns the one-column lanes are nearly all in use, and rows of B that
+// begin anywhere cost 16-byte lanes more lines (power-law A^T with 4.5 M entries, N = 31: 100 and 72).
+bool wide_lanes_pay(bool eb, int64_t N, const MatrixHint& hint, const PlanInfo& plan) {
+    if (N > 64) return eb || hint.seen_len < 800.0;
+    if (!eb) return hint.seen_len > 0.0 && hint.seen_len < 28.0;
+    if (!plan.found || hint.nnz < 0 || (N >= 25 && N <= 32)) return false;
+    const int64_t waves = hint.nnz / 256 / (N <= 32 ? 8 : 4);
+    return waves >= (int64_t)cu_count() * 4 * 12 || (hint.nnz >= 600000 && hint.seen_len >= 16.0 && hint.seen_len <= 1500.0);
+}
+
 // Default geometry per algorithm family and N.  Measured on MI355X: 16-byte and 4-byte gathers run at
 // full rate, 8-byte gathers at about half.  SR narrows to one column per lane for N <= 16: lane groups of
 // 4 lanes or fewer walk 16 or more rows or chunks per wave and wait for the longest (power-law N = 8,
 // EB+RM+SR: 110 us with 8 lanes of one column, 176 with 2 lanes of 4).  PR has no such spread, its slots
 // share a row: there 16-byte gathers win at any width (power-law N = 16, RB+RM+PR: 159 us against 265).
+// Between (17 ... 31 columns, and up to 63 where rows of B are not whole 16-byte pieces) 16-byte gathers
+// issue fewer loads but put 8 or 4 workers on a wave instead of 2 or 1, see wide_lanes_pay.
 // Setting DA_SPMM_TUNE=1 lets DA_SPMM_V / _G / _NV / _CHUNK override the choice (for tuning runs only;
 // invalid combinations are rejected).
-int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides& sd,
-                  int64_t known_nnz, const PlanInfo& plan, Geometry* out) {
+int pick_geometry(bool cm, bool pr, bool eb, int64_t N, const Strides& sd, bool aligned,
+                  const MatrixHint& hint, const PlanInfo& plan, Geometry* out) {
+    const int64_t known_nnz = hint.nnz;
     const bool vec4_ok = N >= 4 && sd.cb == 1 && sd.cc == 1;      // 16-byte accesses, at any alignment
     Geometry g{1, 1, 1, 0, false, kSweepStripe};
     if (cm) {
@@ -187,7 +214,8 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides
         g.NV = vecs >= 4 ? 4 : pow2_ceil(vecs);
         g.G = 1;
     } else {
-        g.V = (vec4_ok && (pr || N > 16)) ? 4 : 1;
+        const bool whole = aligned && N >= 32 && N % 4 == 0;
+        g.V = (vec4_ok && (pr || whole || (N > 16 && wide_lanes_pay(eb, N, hint, plan)))) ? 4 : 1;
         g.G = pow2_ceil((N + g.V - 1) / g.V);
         // SR: at most 128 columns per tile (32 lanes of 4): at N = 256 two passes over 512-byte row
         // segments keep more rows of B in L2 than one pass over 1 KB rows and were never slower
@@ -290,7 +318,7 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         // device and the grid is sized for a few waves of blocks over the whole machine, bounded
         // by what the matrix could hold at most.
         long blocks;
-        const int64_t known = lookup_nnz(p.rowptr, p.m);
+        const int64_t known = lookup_matrix(p.rowptr, p.m).nnz;
         if (known >= 0) {
             blocks = (known + entries_per_block - 1) / entries_per_block;
             if (blocks > (1L << 20)) blocks = 1L << 20;
@@ -574,6 +602,25 @@ void give_slot(int dev, const FeatureSlot& s) {
     free_slot(s);
 }
 
+// Enqueues the reduction over the row pointers; its result is in slot->result once the ticket is there.  The slot is
+// the caller's to give back, or to free after an error.
+hipError_t start_features(int64_t m, const int32_t* rowptr, hipStream_t stream, int* dev, FeatureSlot* slot) {
+    hipError_t e = hipGetDevice(dev);
+    if (e == hipSuccess && (*dev < 0 || *dev >= kMaxDevices)) e = hipErrorInvalidDevice;
+    if (e == hipSuccess) e = take_slot(*dev, stream, slot);
+    if (e != hipSuccess) return e;
+    ++slot->ticket;
+    // 8 row pointers a thread: enough blocks to hide their latency, few enough for the shared counters
+    long blocks = (m + 8 * kBlock - 1) / (8 * kBlock);
+    const long cap = (long)cu_count() * 4;
+    if (blocks > cap) blocks = cap;
+    hipLaunchKernelGGL(features_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, (int)m, rowptr, slot->scratch, slot->result,
+                       slot->ticket);
+    return hipGetLastError();
+}
+
+bool arrived(const FeatureSlot& s) { return __atomic_load_n(&s.result->ticket, __ATOMIC_ACQUIRE) == s.ticket; }
+
 // DA_SPMM_DEBUG_VALIDATE=1 makes da_spmm / da_spmm_ex / da_csr_transpose check the CSR arrays on
 // the device before they launch anything (this synchronises the stream)
 bool debug_validate() {
@@ -659,7 +706,9 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     const bool cm = (algo & 2) != 0;
     const bool pr = (algo & 1) != 0;
     Geometry g;
-    const int st = pick_geometry(cm, pr, eb, m, N, sd, eb ? lookup_nnz(rowptr, m) : -1,
+    const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
+    const bool ask = eb || (!cm && !pr && N > 16);
+    const int st = pick_geometry(cm, pr, eb, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
     const Family fam = eb ? (pr ? EB_PR : EB_SR) : (pr ? RB_PR : RB_SR);
@@ -682,40 +731,28 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t* rowptr, void* stream, 
     if (m == 0) return DA_OK;
     if (!rowptr) return fail(DA_ERR_INVALID_ARG, "null rowptr%s");
     hipStream_t st = (hipStream_t)stream;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-    if (dev < 0 || dev >= kMaxDevices) return fail(DA_ERR_UNSUPPORTED, "device ordinal beyond 63%s");
     // the call waits for its result, which a recorded kernel would not deliver
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &capture) != hipSuccess) { (void)hipGetLastError(); capture = hipStreamCaptureStatusNone; }
     if (capture != hipStreamCaptureStatusNone) return hip_fail(hipErrorStreamCaptureUnsupported, "da_spmm_features");
+    int dev = 0;
     FeatureSlot slot;
-    e = take_slot(dev, st, &slot);
-    if (e != hipSuccess) return hip_fail(e, "da_spmm_features: scratch");
-    ++slot.ticket;
-    // 8 row pointers a thread: enough blocks to hide their latency, few enough for the shared counters
-    long blocks = (m + 8 * kBlock - 1) / (8 * kBlock);
-    const long cap = (long)cu_count() * 4;
-    if (blocks > cap) blocks = cap;
-    hipLaunchKernelGGL(features_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, (int)m, rowptr, slot.scratch, slot.result,
-                       slot.ticket);
-    e = hipGetLastError();
+    hipError_t e = start_features(m, rowptr, st, &dev, &slot);
+    if (e == hipErrorInvalidDevice) return fail(DA_ERR_UNSUPPORTED, "device ordinal beyond 63%s");
     if (e == hipSuccess) {
         // The result arrives in host memory: look for it a while (a stream that is idle answers within
         // microseconds), then wait for the stream.
         bool here = false;
         for (int i = 0; i < 20000 && !here; ++i) {
-            here = __atomic_load_n(&slot.result->ticket, __ATOMIC_ACQUIRE) == slot.ticket;
+            here = arrived(slot);
             if (!here) __builtin_ia32_pause();
         }
         if (!here) e = hipStreamSynchronize(st);
-        if (e == hipSuccess && __atomic_load_n(&slot.result->ticket, __ATOMIC_ACQUIRE) != slot.ticket) e = hipErrorUnknown;
+        if (e == hipSuccess && !arrived(slot)) e = hipErrorUnknown;
     }
+    if (e != hipSuccess) { free_slot(slot); return hip_fail(e, "da_spmm_features"); }
     const unsigned long long h[3] = {slot.result->sq, slot.result->mx, slot.result->nnz};
-    if (e == hipSuccess) give_slot(dev, slot);
-    else free_slot(slot);
-    if (e != hipSuccess) return hip_fail(e, "da_spmm_features");
+    give_slot(dev, slot);
     // population variance = (m * sum len^2 - nnz^2) / m^2, formed exactly in 128-bit integers
     const unsigned __int128 num = (unsigned __int128)(unsigned long long)m * h[0]
                                   - (unsigned __int128)h[2] * h[2];
@@ -724,7 +761,7 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t* rowptr, void* stream, 
     const double var = (double)num / (md * md);
     out->rows = m;
     out->nnz = (int64_t)h[2];
-    remember_nnz(rowptr, m, out->nnz);
+    remember_matrix(rowptr, m, out->nnz, h[2] ? (double)h[0] / (double)h[2] : 0.0);
     out->row_nnz_mean = mean;
     out->row_nnz_std = std::sqrt(var);
     out->row_nnz_max = (double)h[1];
@@ -1032,7 +1069,7 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
         const int v = da_csr_validate(m, k, nnz, rowptr, colind, stream);
         if (v != DA_OK) return v;
     }
-    if (k > (1LL << 30)) { remember_nnz(rowptr, m, nnz); return DA_OK; }    // no schedule for such widths
+    if (k > (1LL << 30)) { remember_matrix(rowptr, m, nnz, 0.0); return DA_OK; }    // no schedule for such widths
     Plan pl;
     pl.rowptr = rowptr; pl.colind = colind; pl.m = m; pl.nnz = nnz;
     size_t ints = 64, ws_bytes = 0, ws_off[kPlans];        // the first ints receive the segment sizes
@@ -1064,12 +1101,20 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     }
     int status = enqueue_schedules(m, k, nnz, rowptr, colind, jobs + first_plan, kPlans - first_plan, stream);
     e = hipSuccess;
-    if (status == DA_OK)
+    int dev = 0;
+    FeatureSlot sums;                                      // row lengths, for the launch geometry
+    if (status == DA_OK) e = start_features(m, rowptr, (hipStream_t)stream, &dev, &sums);
+    const bool summed = e == hipSuccess && status == DA_OK;
+    if (e == hipErrorInvalidDevice) e = hipSuccess;        // no slots for that many devices: lengths stay unknown
+    if (status == DA_OK && e == hipSuccess)
         e = hipMemcpyAsync(pl.first_units, seg, sizeof pl.first_units, hipMemcpyDeviceToHost, (hipStream_t)stream);
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
     if (status == DA_OK && e != hipSuccess) status = hip_fail(e, "da_spmm_prepare");
+    double seen_len = 0.0;
+    if (status == DA_OK && summed && arrived(sums)) seen_len = (double)sums.result->sq / (double)nnz;
+    if (status == DA_OK && summed) give_slot(dev, sums); else free_slot(sums);
     if (status != DA_OK) return status;
-    remember_nnz(rowptr, m, nnz);
+    remember_matrix(rowptr, m, nnz, seen_len);
     std::shared_ptr<DeviceBlock> old;                      // freed after the mutex is released
     {
         std::lock_guard<std::mutex> lk(g_plan_mu);
