@@ -519,6 +519,10 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
 // lanes load V consecutive columns at once (technique 2), the wave's entries are fetched once and
 // shared through LDS (technique 3), and the slots are combined by a reduction tree (Sec. 3.4 K2).
 // In a batch of 64 staged entries slot s takes entries s, s+S, s+2S, ...
+// With 4 slots (groups of 16 lanes) a slot adds four products to each other before it adds them to its sum, which then
+// takes fewer additions than with 8 slots (N = 41, rows of 400: error 1.9e-7 with one addition an entry, 1.4e-7 with 8
+// slots, 1.1e-7 now).  Two sums instead, of the even and the odd entries, cost registers: 27-point stencil, N = 41:
+// 45 -> 54 us.
 // ------------------------------------------------------------------------------------------
 template <int V, int G, int NV, bool WIDE>
 __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
@@ -583,7 +587,16 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
 #pragma unroll
                     for (int u = 0; u < UU; ++u) b[u].load(brow.row(ee[u].x), cols, sd.cb);
 #pragma unroll
-                    for (int u = 0; u < UU; ++u) acc.fma(__int_as_float(ee[u].y), b[u]);
+                    for (int u = 0; u < UU; ++u) {
+                        if (S > 4 || UU == 1) {
+                            acc.fma(__int_as_float(ee[u].y), b[u]);
+                        } else if (u % 2 == 0) {           // UU is a power of two
+                            b[u].scale(__int_as_float(ee[u].y));
+                            b[u].fma(__int_as_float(ee[(u + 1) % UU].y), b[(u + 1) % UU]);
+                            if (UU < 4) acc.add(b[u]);
+                            else if (u % 4 == 2) { b[u].add(b[(u + UU - 2) % UU]); acc.add(b[u]); }
+                        }
+                    }
                 });
                 const int t = (cnt / S) * S + s;              // ragged last step
                 if (t < cnt) {
@@ -994,6 +1007,21 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                     for (int i = 0; i < NV; ++i)
 #pragma unroll
                         for (int v = 0; v < V; ++v) b[u].a[i][v] = ok ? a * b[u].a[i][v] : 0.f;
+                }
+                // all steps in one row that does not end here: their products are added to each other first, so that
+                // a slot's sum takes one addition for four entries and no step looks for row boundaries (N = 65, rows of
+                // 400: error 2.3e-7 with an addition each, 1.3e-7 now, as with 8 slots; 296 -> 182 us)
+                if constexpr (UU == 4) {
+                    const int row0 = __builtin_amdgcn_readfirstlane(e[0].z);
+                    if ((tb + UU) * S <= cnt && row0 == __builtin_amdgcn_readlane(e[UU - 1].z, (S - 1) * G) &&
+                        (__builtin_amdgcn_readlane(e[UU - 1].w, (S - 1) * G) & 2) == 0) {
+                        if (cur < 0) { cur = row0; cur_started = (__builtin_amdgcn_readfirstlane(e[0].w) & 1) != 0; }
+                        b[0].add(b[1]);
+                        b[2].add(b[3]);
+                        b[0].add(b[2]);
+                        acc.add(b[0]);
+                        continue;
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {

@@ -47,3 +47,19 @@ def test_sr_ids_at_every_lane_mapping(name, known):
                 got = np.lib.stride_tricks.as_strided(flat, (ai.m, N), ((N + 3) * 4, 4))
                 assert orc.bit_mismatches(np.ascontiguousarray(got), want) == 0, (name, known, N, algo)
         da.da_spmm_release(prob.rowptr)
+
+
+@pytest.mark.parametrize("algo", [1, 5])
+@pytest.mark.parametrize("N", [41, 64, 65, 128])
+def test_pr_sums_are_as_exact_with_wide_lane_groups(algo, N):
+    """PR with 4 or 2 slots along a row adds as few terms one after another as with 8.  A sum of L products of random
+    sign, one after another, is off by about 2^-24 sqrt(L/6) of its size: 1.7e-7 for the L = 50 of 8 slots on
+    rows of 400 entries, 2.4e-7 and 3.5e-7 for 4 and 2; measured were 1.4e-7, 1.9e-7 and 2.3e-7."""
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import DeviceProblem
+    a = gen.lognormal_csr(4000, 400.0, 0.2, seed=41)
+    B = np.random.default_rng(42).standard_normal((a.k, N)).astype(np.float32)
+    prob = DeviceProblem(a, B)
+    want, _ = orc.spmm(a.rowptr, a.colind, a.vals, B)
+    got = prob.run(algo).astype(np.float64)
+    assert np.linalg.norm(got - want) <= 1.55e-7 * np.linalg.norm(want)
