@@ -519,10 +519,11 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
 // lanes load V consecutive columns at once (technique 2), the wave's entries are fetched once and
 // shared through LDS (technique 3), and the slots are combined by a reduction tree (Sec. 3.4 K2).
 // In a batch of 64 staged entries slot s takes entries s, s+S, s+2S, ...
-// With 4 slots (groups of 16 lanes) a slot adds four products to each other before it adds them to its sum, which then
+// With 4 slots (groups of 16 lanes) and N no multiple of four, which ran with 8 slots of one-column lanes before it took
+// 16-byte lanes, a slot adds four products to each other before it adds them to its sum, which then
 // takes fewer additions than with 8 slots (N = 41, rows of 400: error 1.9e-7 with one addition an entry, 1.4e-7 with 8
 // slots, 1.1e-7 now).  Two sums instead, of the even and the odd entries, cost registers: 27-point stencil, N = 41:
-// 45 -> 54 us.
+// 45 -> 54 us; multiples of four keep one addition an entry (rows of 1000, N = 36: 46 us, 49 with groups).
 // ------------------------------------------------------------------------------------------
 template <int V, int G, int NV, bool WIDE>
 __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
@@ -543,6 +544,7 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);
+    const bool grouped = S <= 4 && N % 4 != 0;
 
     if constexpr (G == 1) {
         if (nvec > 0) {
@@ -588,7 +590,7 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
                     for (int u = 0; u < UU; ++u) b[u].load(brow.row(ee[u].x), cols, sd.cb);
 #pragma unroll
                     for (int u = 0; u < UU; ++u) {
-                        if (S > 4 || UU == 1) {
+                        if (S > 4 || UU == 1 || !grouped) {
                             acc.fma(__int_as_float(ee[u].y), b[u]);
                         } else if (u % 2 == 0) {           // UU is a power of two
                             b[u].scale(__int_as_float(ee[u].y));

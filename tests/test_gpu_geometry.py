@@ -50,7 +50,7 @@ def test_sr_ids_at_every_lane_mapping(name, known):
 
 
 @pytest.mark.parametrize("algo", [1, 5])
-@pytest.mark.parametrize("N", [41, 64, 65, 128])
+@pytest.mark.parametrize("N", [41, 65, 127])
 def test_pr_sums_are_as_exact_with_wide_lane_groups(algo, N):
     """PR with 4 or 2 slots along a row adds as few terms one after another as with 8.  A sum of L products of random
     sign, one after another, is off by about 2^-24 sqrt(L/6) of its size: 1.7e-7 for the L = 50 of 8 slots on
