@@ -180,8 +180,9 @@ Schedule lookup_schedule(const void* rowptr, const void* colind, int64_t m, int 
 // lane takes a second pass over the row (N = 65, lognormal: 92 and 108), which pays only where one row of very many
 // entries sets the time (N = 65, rows of 1000: 118 and 99; power-law A^T: 974 and 797).
 // EB: without a plan a chunk begins with a search that a wave's workers make one after another (power-law
-// N = 24: 202 and 186; skewed: 887 and 835).  With one the loads decide (power-law N = 24: 145 and 161, N = 41:
-// 210 and 242), unless the matrix has too few entries for that many workers (105 000: 19 and 13), or so many in
+// N = 24: 202 and 186; skewed: 887 and 835), which some million entries in rows of some hundred pay back with smaller
+// chunks (4.5 M in rows of 616, N = 24: 72 and 80; 3.6 M of 914: 65 and 74; 2 M of 1090, N = 50: 41 and 47).  With
+// one the loads decide (power-law N = 24: 145 and 161, N = 41: 210 and 242), unless the matrix has too few entries for that many workers (105 000: 19 and 13), or so many in
 // long rows that the workers end their chunks with additions to the same lines (A^T of a power-law graph with 1.2 M
 // entries, N = 17: 44 and 31) -- which 12 waves per SIMD hide (33 M entries in rows of 60 000, N = 24: 316 and
 // 354; 13 M: 152 and 134).  From 25 columns the one-column lanes are nearly all in use, and rows of B that
@@ -189,9 +190,67 @@ Schedule lookup_schedule(const void* rowptr, const void* colind, int64_t m, int 
 bool wide_lanes_pay(bool eb, int64_t N, const MatrixHint& hint, const PlanInfo& plan) {
     if (N > 64) return eb || hint.seen_len < 800.0;
     if (!eb) return hint.seen_len > 0.0 && hint.seen_len < 28.0;
-    if (!plan.found || hint.nnz < 0 || (N >= 25 && N <= 32)) return false;
+    if (hint.nnz < 0 || (N >= 25 && N <= 32)) return false;
+    if (!plan.found) return hint.nnz >= 1500000 && hint.nnz <= 6000000 && hint.seen_len >= 200.0 && hint.seen_len <= 1500.0;
     const int64_t waves = hint.nnz / 256 / (N <= 32 ? 8 : 4);
     return waves >= (int64_t)cu_count() * 4 * 12 || (hint.nnz >= 600000 && hint.seen_len >= 16.0 && hint.seen_len <= 1500.0);
+}
+
+// Rounding error of a row of n entries that is summed in chunks of c entries, relative to n: every chunk is summed
+// one entry after another by each of `chains` partial sums, and the chunks are added one after another.  For
+// products of random sign the errors of a sum of c terms grow with c, for products of one sign with c^2.
+double random_error(double c, double chains, double n) { return c / chains + n / c; }
+double one_sign_error(double c, double chains, double n) { return c * c / (chains * chains) + n * n / c; }
+
+// Stored entries per worker of the EB ids.
+//
+// Without a plan: 256 entries for SR lane groups of 16 or more and fewer for narrow ones, whose search costs more per
+// entry; 512 for the waves of PR.  Small matrices: shrunk until there are about four waves of workers per SIMD, so
+// that the chunk walk, a chain of dependent memory round trips, does not set the run time.  PR, and SR above 64
+// columns, count the lanes of one column there where rows of B are not whole 16-byte pieces.
+//
+// With a plan a chunk is cheap to begin (row hints) and with coalesced atomic additions cheap to end, and the orders
+// exist for powers of two only.  SR: 64 entries keep the workers closer together in the sweep over B (power-law
+// N = 128: 449 us at 256, 399 at 64; rows of 175 entries, N = 64: 350 and 167), 32 where 64 leaves too few workers
+// (1.2 M entries in rows of 40, N = 64: 37 and 29), 128 up to 64 columns where more than a fifth of the entries are
+// in rows much longer than a chunk, whose chunks all add to the same few lines of C, and 128 still makes 12 waves
+// per SIMD (power-law, 13 M entries, N = 24: 145 at 64, 141 at 128; N = 32: 118 and 110; N = 64: 205 and 198; with
+// 4.5 M entries, N = 24: 59 and 67).  One column per lane in groups of 16 and more: 128, 256 on rows of more than
+// 16 000 entries, 64 up to 4 M entries, and not more than the size without a plan (power-law N = 16: 120 at 64, 111
+// at 128; rows of 30 000, N = 41: 120 at 256, 130 at 128; 1.4 M entries, N = 16: 32 us at 32, 28 at 64, 29 at 88).
+// PR: the size without a plan, rounded down (0.64 M entries, N = 32: 34 us at 64, 30 at 128; 1.9 M in rows of 16 000,
+// N = 32: 39 at 256, 65 at 512).
+//
+// Smaller chunks split a row into more parts.  Rows of up to some thousand entries lose nothing by that, a chunk
+// of 256 being the longer sum; the error of longer ones grows with the number of chunks (1.9 M entries in rows of
+// 16 000, N = 17: 3.0e-7 of the result at 232, 4.2e-7 at 64).  So the size is doubled while the row length that
+// an average entry sees makes the error for random signs larger than at the size without a plan (a twentieth of it is
+// less than the order of the atomic additions changes from run to run), or that for one sign by more than 1.4.
+int chunk_size(bool cm, bool pr, int64_t N, bool whole, const Geometry& g, const MatrixHint& hint, const PlanInfo& plan) {
+    const int64_t cols = whole ? (N + 3) / 4 : N;
+    const int lanes = cm ? 1 : (!plan.found && !pr && N < 64 ? g.G : std::min(pow2_ceil(cols), whole ? 32 : (pr ? kDefaultGroupPR : kWave)));
+    const int most = pr ? kEntriesPerWavePR : (lanes >= 16 ? 256 : (lanes == 8 ? (plan.found ? 128 : 256) : (lanes == 4 ? 128 : 64)));
+    if (hint.nnz < 0) return most;
+    const int least = pr ? 64 : (lanes >= 8 ? 32 : most);
+    const int64_t workers = (int64_t)cu_count() * 16 * (pr ? 1 : kWave / lanes);
+    const int64_t spread = (hint.nnz / workers + 7) / 8 * 8;
+    const int plain = (int)std::min<int64_t>(most, std::max<int64_t>(least, spread));
+    if (!plan.found || (!pr && (cm || lanes < 8))) return plain;
+
+    int near = 32;                                                    // plain rounded down to a power of two
+    while (near * 2 <= plain) near *= 2;
+    int c;
+    if (pr) c = std::min(kEntriesPerWavePR, std::max(64, near));
+    else if (g.V == 1 && g.G >= 16) c = std::min(hint.nnz <= kSmallPlanMaxNnz ? 64 : (hint.seen_len <= 16384.0 ? 128 : 256), near);
+    else if (hint.nnz > kSmallPlanMaxNnz)
+        c = g.V == 4 && N <= 64 && plan.long_rows > 0.2 && hint.nnz / 128 / (kWave / g.G) >= (int64_t)cu_count() * 4 * 12 ? 128 : 64;
+    else c = hint.nnz / 64 < (g.G == 8 ? 48 : 28) * 1024 ? 32 : 64;
+    // partial sums of a chunk, now and in lanes of one column; PR adds its products four at a time in groups of 4 and more
+    const double n = hint.seen_len, ours = pr ? (g.G >= 4 ? 4.0 : 1.0) * (kWave / g.G) : 1.0, theirs = pr ? (double)(kWave / lanes) : 1.0;
+    while (c < plain && (random_error(c, ours, n) > 1.12 * random_error(plain, theirs, n) ||
+                         one_sign_error(c, ours, n) > 2.0 * one_sign_error(plain, theirs, n)))
+        c *= 2;
+    return c;
 }
 
 // Default geometry per algorithm family and N.  Measured on MI355X: 16-byte and 4-byte gathers run at
@@ -239,40 +298,8 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t N, const Strides& sd, bool 
             return fail(DA_ERR_UNSUPPORTED, "DA_SPMM_V/_G/_NV override is not a supported combination%s");
     }
     if (eb) {
-        if (pr) g.chunk = kEntriesPerWavePR;
-        else g.chunk = g.G >= 8 ? 256 : (g.G == 4 ? 128 : 64);
-        if (known_nnz > kSmallPlanMaxNnz && plan.found && !pr && g.G >= 8 && plan.long_rows > 0.5) {
-            // Most entries lie in rows much longer than a chunk: every chunk is one more fp32 addition to the
-            // same few rows of C, and rounding errors grow with their number (33 M entries, rows of 60 000,
-            // N = 8: 4.5e-7 of the result at 128 entries, 5.8e-7 at 64, and 181 against 168 us; N = 64:
-            // 4.0e-7 at 256, 4.5e-7 at 128, both 462 us).  Small matrices need the workers instead: 1.2 M
-            // entries in rows of 12 000, N = 32: 65 us at 64 entries, 32 us at 32.
-            g.chunk = N <= 8 ? 128 : 256;
-        } else if (known_nnz >= 0 && plan.found && pr) {
-            // a chunk size the plan has row hints for, and about 5 waves per SIMD
-            while (g.chunk > 64 && g.chunk > known_nnz / ((long)cu_count() * 20)) g.chunk /= 2;
-        } else if (known_nnz >= 0 && plan.found && g.G >= 8) {
-            // With the plan's row hints a chunk is cheap to begin and with coalesced atomic additions cheap
-            // to end, so small chunks win: the workers are closer together in the sweep over B and in their
-            // progress (power-law N = 128: 449 us at 256 entries, 409 at 64; rows of 175 entries, N = 64:
-            // 523 and 381).  Smaller still while 64 leaves too few workers.  Larger for lane groups of 8 where
-            // more than a fifth of the entries are in long rows, whose chunks all add to the same few lines of C.
-            const int64_t chunks = known_nnz / 64;
-            g.chunk = 64;
-            if (chunks < (g.G == 8 ? 48 : 28) * 1024 && known_nnz <= kSmallPlanMaxNnz) g.chunk = 32;
-            else if (N >= 32 && g.G == 8 && plan.long_rows > 0.2) g.chunk = 128;
-        } else if (known_nnz >= 0) {
-            // Small matrices: shrink the chunks until there are about four waves of workers per
-            // SIMD, so that the chunk walk, a chain of dependent memory round trips, does not set
-            // the run time.  Lane-sized workers (G < 8) keep their chunk: their search cost per
-            // entry is already high.
-            const long workers = (long)cu_count() * 16 * (pr ? 1 : kWave / g.G);
-            const int floor_ = pr ? 64 : (g.G >= 8 ? 32 : g.chunk);
-            long want = known_nnz / workers;
-            want = (want + 7) / 8 * 8;
-            if (want < floor_) want = floor_;
-            if (want < g.chunk) g.chunk = (int)want;
-        }
+        const bool whole = vec4_ok && aligned && N >= 32 && N % 4 == 0;
+        g.chunk = chunk_size(cm, pr, N, whole, g, hint, plan);
         if (tune) g.chunk = env_int("DA_SPMM_CHUNK", g.chunk);
         if (g.chunk < 8 || g.chunk > (1 << 20)) return fail(DA_ERR_UNSUPPORTED, "bad DA_SPMM_CHUNK%s");
     }
