@@ -330,8 +330,12 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     }
     case RB_PR: {
         if constexpr (G <= kMaxGroupPR) {
-            hipLaunchKernelGGL((rb_pr_kernel<V, G, NV, WIDE>), grid_for((p.m + kWavesPerBlock - 1) / kWavesPerBlock),
-                               block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin);
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid_for((p.m + kWavesPerBlock - 1) / kWavesPerBlock),
+                                   block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin);
+            };
+            if (V == 4 && G >= 16 && p.N % 4 != 0) go(rb_pr_kernel<V, G, NV, WIDE, V == 4 && G >= 16>);
+            else go(rb_pr_kernel<V, G, NV, WIDE, false>);
         }
         break;
     }

@@ -523,9 +523,10 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
 // 16-byte lanes, a slot adds four products to each other before it adds them to its sum, which then
 // takes fewer additions than with 8 slots (N = 41, rows of 400: error 1.9e-7 with one addition an entry, 1.4e-7 with 8
 // slots, 1.1e-7 now).  Two sums instead, of the even and the odd entries, cost registers: 27-point stencil, N = 41:
-// 45 -> 54 us; multiples of four keep one addition an entry (rows of 1000, N = 36: 46 us, 49 with groups).
+// 45 -> 54 us; multiples of four keep one addition an entry (GROUPED = false; rows of 1000, N = 36: 46 us, 49 with
+// groups, and as many with the choice made at run time).
 // ------------------------------------------------------------------------------------------
-template <int V, int G, int NV, bool WIDE>
+template <int V, int G, int NV, bool WIDE, bool GROUPED>
 __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
     const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles)
@@ -544,7 +545,6 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);
-    const bool grouped = S <= 4 && N % 4 != 0;
 
     if constexpr (G == 1) {
         if (nvec > 0) {
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
                     for (int u = 0; u < UU; ++u) b[u].load(brow.row(ee[u].x), cols, sd.cb);
 #pragma unroll
                     for (int u = 0; u < UU; ++u) {
-                        if (S > 4 || UU == 1 || !grouped) {
+                        if (!GROUPED || UU == 1) {
                             acc.fma(__int_as_float(ee[u].y), b[u]);
                         } else if (u % 2 == 0) {           // UU is a power of two
                             b[u].scale(__int_as_float(ee[u].y));
