@@ -72,6 +72,7 @@ struct Geometry {
     int V, G, NV, chunk;
     bool pin;   // pin column tiles to XCDs when the tile count is 2, 4 or 8
     int stripe; // blocks per stripe when a prepared matrix's chunk order is dealt to the XCDs (0: off)
+    bool order; // take a prepared matrix's chunk order
 };
 
 constexpr int kSweepStripe = 256;
@@ -262,11 +263,23 @@ int chunk_size(bool cm, bool pr, int64_t N, bool whole, const Geometry& g, const
 // issue fewer loads but put 8 or 4 workers on a wave instead of 2 or 1, see wide_lanes_pay.
 // Setting DA_SPMM_TUNE=1 lets DA_SPMM_V / _G / _NV / _CHUNK override the choice (for tuning runs only;
 // invalid combinations are rejected).
-int pick_geometry(bool cm, bool pr, bool eb, int64_t N, const Strides& sd, bool aligned,
-                  const MatrixHint& hint, const PlanInfo& plan, Geometry* out) {
-    const int64_t known_nnz = hint.nnz;
+//
+// Small matrices of mostly empty rows do without their plan up to 32 columns: the stored rows are short and far
+// apart, few rows of B are read twice, and chunks in the order of their columns scatter the additions to neighbouring rows of
+// C over the XCDs.  SR from 5 columns: fewer than 3 entries a row (0.64 M entries, 1.6 a row, N = 8: 33 us with the plan, 27 without;
+// 0.4 M, 0.4 a row, N = 24: 86 and 60; N = 64: 48 and 52; 0.2 M, 6.7 a row, N = 8: 18 and 20).  PR: fewer than 8 where
+// the size without a plan is none of the plan's (0.64 M, 1.6 a row, N = 16, EB+CM+PR: 39 and 34; 2 M, 6.7 a row,
+// N = 4: 30 and 25; 0.2 M, 6.7 a row, N = 8, with chunks of 64 either way: 14 and 16).
+int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides& sd, bool aligned,
+                  const MatrixHint& hint, PlanInfo plan, Geometry* out) {
     const bool vec4_ok = N >= 4 && sd.cb == 1 && sd.cc == 1;      // 16-byte accesses, at any alignment
-    Geometry g{1, 1, 1, 0, false, kSweepStripe};
+    Geometry g{1, 1, 1, 0, false, kSweepStripe, true};
+    if (plan.found && N <= 32 && hint.nnz >= 0) {
+        const int64_t waves = (int64_t)cu_count() * 16;
+        const bool bare = pr ? hint.nnz < 8 * m && hint.nnz > 64 * waves && hint.nnz < kEntriesPerWavePR * waves
+                             : !cm && N > 4 && hint.nnz < 3 * m && hint.nnz <= kSmallPlanMaxNnz;
+        if (bare) { plan.found = false; g.order = false; }
+    }
     if (cm) {
         g.V = vec4_ok ? 4 : 1;
         const long vecs = (N + g.V - 1) / g.V;
@@ -365,7 +378,7 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         std::shared_ptr<DeviceBlock> keep;                 // dropped after the launch
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(p.stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
-        Schedule sch = env_int("DA_SPMM_NO_SCHEDULE", 0)
+        Schedule sch = !geo.order || env_int("DA_SPMM_NO_SCHEDULE", 0)
                            ? Schedule{nullptr, 0, 0, 0, 0, 0, 0, 0, 3, nullptr, nullptr}
                            : lookup_schedule(p.rowptr, p.colind, p.m, chunk, cap == hipStreamCaptureStatusActive, &keep);
         // EB+SR on a prepared matrix never splits rows of at most a chunk (the plan's row hints make
@@ -739,7 +752,7 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     Geometry g;
     const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
     const bool ask = eb || (!cm && !pr && N > 16);
-    const int st = pick_geometry(cm, pr, eb, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
+    const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
     const Family fam = eb ? (pr ? EB_PR : EB_SR) : (pr ? RB_PR : RB_SR);
