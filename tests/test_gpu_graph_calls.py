@@ -278,9 +278,11 @@ def test_graphs_with_methods_of_their_own(kind):
 
 
 # ---- sizes beyond the own dense kernels ------------------------------------------------------------------------------
-@pytest.mark.parametrize("fin,fout", [(4, 2 ** 22 + 3), (65600, 4160)], ids=["columns", "tiles"])
+@pytest.mark.parametrize("fin,fout", [(4, 2 ** 22 + 3), (65600, 4160), (448, 512), (449, 512)],
+                         ids=["columns", "tiles", "56_tiles", "64_tiles"])
 def test_layers_beyond_the_own_dense_kernels(fin, fout):
-    """More columns than the kernels take, more tiles of a weight gradient than a grid holds: the library's."""
+    """More columns than the kernels take, more tiles of a weight gradient than a grid holds, and both sides of the
+    number of tiles from which the library is faster."""
     a = matrix(5, 6)
     A, graph, layer = dense(a).float().cuda(), graph_of(a), layer_of(fin, fout, relu=False)
     X = torch.randn((a.k, fin), device="cuda", requires_grad=True)
