@@ -751,7 +751,7 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     const bool pr = (algo & 1) != 0;
     Geometry g;
     const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
-    const bool ask = eb || (!cm && !pr && N > 16);
+    const bool ask = eb || (!cm && !pr && N > 16 && (N < 32 || N % 4 != 0 || ends % 16 != 0));   // RB: only where the lanes depend on it
     const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
