@@ -124,7 +124,7 @@ def test_degenerate_shapes(gpu):
     da.da_spmm(4, 4, 0, z, z, C, C, C, 4)
     torch.cuda.synchronize()
     assert torch.all(C == 7.0)
-    # unaligned B / C base (offset by one float) forces the scalar-width path
+    # unaligned B / C base (offset by one float): 16-byte accesses that begin anywhere, one column per lane in SR
     a = gen.uniform_csr(m=500, k=400, mean_len=7, seed=8)
     N = 8
     Bh = gen.dense(a.k, N, "uniform", seed=9)

@@ -234,14 +234,15 @@ def test_eb_schedule_has_the_promised_properties(a, units):
     assert da.da_eb_schedule_status(a.m, a.k, nnz, None, ci, 64, order, None, ws, nbytes) == da.DA_ERR_INVALID_ARG
 
 
-def rows_around_the_chunk_size(seed=71):
-    """Row lengths at and around the EB+SR chunk sizes (128, 256), rows that begin or end exactly
-    on chunk boundaries, runs of rows without entries and single-entry rows in between: the shapes
-    the rule "rows of at most a chunk are never split" has to get right."""
+def rows_around_the_chunk_size(seed=71, menu=(0, 0, 1, 2, 3, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300, 511, 512, 513, 1024),
+                               rows=1500):
+    """Row lengths at and around the EB+SR chunk sizes (32 ... 256; this matrix takes 32, with the shorter menu and
+    30 000 rows 64), rows that begin or end exactly on chunk boundaries, runs of rows without entries and
+    single-entry rows in between: the shapes the rule "rows of at most a chunk are never split" has to get right."""
     rng = np.random.default_rng(seed)
-    menu = np.array([0, 0, 1, 2, 127, 128, 129, 255, 256, 257, 300, 511, 512, 513, 1024, 33, 64])
-    lens = rng.choice(menu, size=1500)
+    lens = rng.choice(np.array(menu), size=rows)
     lens[:8] = [256, 256, 128, 128, 0, 256, 255, 1]                 # boundaries that fall on row starts
+    lens[8:20] = [32, 32, 64, 31, 1, 32, 0, 33, 31, 64, 63, 1]
     lens[100:140] = 0                                               # a run of rows without entries
     k = 6000
     rowptr, colind = gen.csr_from_lens(rng, lens, k)
@@ -261,6 +262,7 @@ PREPARED = [("skewed", lambda: gen.skewed_csr(m=16384, heavy_lo=3000, heavy_hi=9
             ("few_entries", lambda: gen.uniform_csr(m=9, k=11, mean_len=3, seed=5), [4]),
             # lane groups of 32 / 16 (rows of at most a chunk stay whole) and of 8 (they are split)
             ("rows_around_chunk", rows_around_the_chunk_size, [128, 64, 32]),
+            ("rows_around_64", lambda: rows_around_the_chunk_size(72, (1, 2, 31, 32, 33, 62, 63, 64, 65, 66, 127, 128, 129), 30000), [64]),
             ("hypersparse", lambda: gen.hypersparse_csr(200000, 25000, 0.01, 100.0, seed=73), [128])]
 
 
