@@ -110,8 +110,8 @@ enum { DA_ROW_MAJOR = 0, DA_COL_MAJOR = 1 };
  * ldc >= m.  Everything else is as for da_spmm, which equals
  * da_spmm_ex(..., B, N, DA_ROW_MAJOR, C, N, DA_ROW_MAJOR, ...).  Only the elements (r, n) with
  * r < m (k for B), n < N are read or written; padding between rows / columns is left untouched.
- * 16-byte accesses are used only for row-major operands whose leading dimensions are multiples
- * of 4 and whose bases are 16-byte aligned; any other combination runs with 4-byte accesses.
+ * 16-byte accesses are used for row-major operands of 4 columns and more at any alignment, where they
+ * pay; column-major operands run with 4-byte accesses.
  * Returns DA_ERR_INVALID_ARG for an unknown layout or a leading dimension that is too small.
  */
 int da_spmm_ex(int64_t m, int64_t k, int64_t N,
@@ -135,10 +135,10 @@ int da_spmm_select(const da_features *f);
  * (DA_ERR_HIP) while `stream` is being captured.  m == 0 gives all-zero features.  A call takes a
  * slot of device scratch and pinned memory from a pool that it creates as needed and that keeps at
  * most 8 idle slots per device.
- * Side effect: the library remembers nnz for this (rowptr, m) pair in a small host table and
- * later da_spmm calls on the same matrix use it to size the grids of the EB algorithms (a
- * missing or stale entry only costs speed: EB kernels read nnz on the device and cover every
- * stored entry whatever the grid size).
+ * Side effect: the library remembers nnz and the length of the row that an average entry lies in
+ * for this (rowptr, m) pair in a small host table and later da_spmm calls on the same matrix use
+ * them for the lane mapping, chunk sizes and grids (a missing or stale entry only costs speed: EB
+ * kernels read nnz on the device and cover every stored entry whatever the grid size).
  */
 int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, da_features *out);
 
@@ -157,8 +157,8 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, 
  * nnz/11 ints, nnz/5.5 up to 4 M entries) until da_spmm_release
  * (rowptr == NULL releases every matrix) or until 16 other matrices have been prepared.  Later
  * da_spmm / da_spmm_ex calls with the same rowptr, colind and m and an EB algorithm id pick the
- * order up by themselves; results are the same up to fp32 rounding order.  It also records nnz
- * like da_spmm_features does.  A kernel that finds another nnz on the device than the plan was
+ * order up by themselves; results are the same up to fp32 rounding order.  It also records what
+ * da_spmm_features records.  A kernel that finds another nnz on the device than the plan was
  * built for ignores the plan, so a stale plan costs speed, never correctness; the contents of
  * colind may change freely.  Allocates and frees temporary device memory, synchronises `stream`.
  * Prepare, release and the product calls may be issued from several host threads; product calls do
@@ -170,7 +170,7 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, 
  * later prepares; a re-prepare of the same matrix keeps it): only da_spmm_release frees it, which
  * the caller must not do while the graph is still replayed.  da_spmm_release(NULL) also frees plans
  * that a re-prepare with another nnz has set aside.
- * These two host tables (nnz hints, plans) and the slots of da_spmm_features are the library's only
+ * These two host tables (matrix hints, plans) and the slots of da_spmm_features are the library's only
  * mutable global state; the tables only steer launch geometry and chunk order, never the result.
  *
  * da_eb_schedule is the building block: order[u], u = 0 .. ceil(nnz/unit)-1, lists the chunk
@@ -281,8 +281,8 @@ int da_spmm_bias_relu(int64_t rows, int64_t n, float *Z, const float *bias, int 
 /*
  * C = A . W on the fp32 matrix cores: A fp32[rows x k] row-major (lda >= k), element (p, q) of W at
  * W[p*wk + q*wn] (wk = n, wn = 1 for a row-major k x n matrix; wk = 1, wn = k for the transpose of a row-major
- * n x k matrix), C fp32[rows x n] row-major (ldc >= n), overwritten.  1 <= k <= 256 and at most 144 KiB of W
- * per 128 columns (a block keeps them in LDS), n <= 2^20, rows <= 2^30; DA_ERR_UNSUPPORTED beyond.
+ * n x k matrix), C fp32[rows x n] row-major (ldc >= n), overwritten.  1 <= k <= 256 (a block keeps 128 columns of W
+ * in LDS), n <= 2^20, rows <= 2^30; DA_ERR_UNSUPPORTED beyond.
  */
 int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float *A, int64_t lda, const float *W, int64_t wk, int64_t wn,
                   float *C, int64_t ldc, void *stream);

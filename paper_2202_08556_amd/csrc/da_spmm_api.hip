@@ -1188,7 +1188,6 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
 }
 
 namespace {
-constexpr int kDenseMaxLds = 144 << 10;
 constexpr int64_t kDenseMaxRows = 1 << 30;         // the kernels count rows, and a block's rows past the end, in 32 bits
 constexpr int64_t kDenseMaxCols = 1 << 20, kSumsMaxCols = 1 << 22;
 
@@ -1307,9 +1306,7 @@ int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float* A, int64_t ld
     if (lda < k || ldc < n || wk < 1 || wn < 1) return fail(DA_ERR_INVALID_ARG, "leading dimension smaller than the extent it strides over%s");
     if (!A || !W || !C) return fail(DA_ERR_INVALID_ARG, "null A, W or C%s");
     hipStream_t s = (hipStream_t)stream;
-    const int64_t widest = n <= 128 ? (n + 15) / 16 * 16 : 128;
-    if (k > 256 || (size_t)widest * dense_pitch((int)k) * sizeof(float) > (size_t)kDenseMaxLds)
-        return fail(DA_ERR_UNSUPPORTED, "weight matrix beyond what a block keeps in LDS%s");
+    if (k > 256) return fail(DA_ERR_UNSUPPORTED, "weight matrix beyond what a block keeps in LDS%s");   // 130 KiB at 128 columns
     auto go = [&](auto nt, auto kmax) {
         constexpr int NT = decltype(nt)::value, KS = decltype(kmax)::value;
         const size_t lds = dense_lds<NT>((int)k);
