@@ -258,7 +258,9 @@ int chunk_size(bool cm, bool pr, int64_t N, bool whole, const Geometry& g, const
 // full rate, 8-byte gathers at about half.  SR narrows to one column per lane for N <= 16: lane groups of
 // 4 lanes or fewer walk 16 or more rows or chunks per wave and wait for the longest (power-law N = 8,
 // EB+RM+SR: 110 us with 8 lanes of one column, 176 with 2 lanes of 4).  PR has no such spread, its slots
-// share a row: there 16-byte gathers win at any width (power-law N = 16, RB+RM+PR: 159 us against 265).
+// share a row: there 16-byte gathers win or tie at any width (power-law N = 16, RB+RM+PR: 159 us against 265; at N = 4,
+// where a lane then takes an entry of its own like in CM: RB+RM+PR on rows of 175 entries 51 and 51, EB+RM+PR on 12
+// entries a row 25 and 29, on lognormal rows 26 and 27).
 // Between (17 ... 31 columns, and up to 63 where rows of B are not whole 16-byte pieces) 16-byte gathers
 // issue fewer loads but put 8 or 4 workers on a wave instead of 2 or 1, see wide_lanes_pay.
 // Setting DA_SPMM_TUNE=1 lets DA_SPMM_V / _G / _NV / _CHUNK override the choice (for tuning runs only;

@@ -406,3 +406,26 @@ def test_sizes_given_as_floats():
     assert (graph.m, graph.k) == (a.m, a.k) and isinstance(graph.m, int)
     with pytest.raises(ValueError):
         gcn.SparseGraph(a.m + 0.5, a.k, arrays.rowptr, arrays.colind, arrays.vals)
+
+
+# ---- gradients of gradients ------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("relu", [False, True])
+def test_gradients_of_gradients_are_those_of_separate_operations(relu):
+    """The dense parts stay differentiable under create_graph; the aggregation's gradient is a constant either way."""
+    from paper_2202_08556_amd import gcn
+    a = gen.powerlaw_csr(m=500, seed=17)
+    graph, layer = graph_of(a), layer_of(6, 5, relu=relu)
+    X = torch.randn((a.m, 6), device="cuda", requires_grad=True)
+    dY = torch.randn((a.m, 5), device="cuda")
+
+    def separate():
+        Z = gcn.aggregate(graph, X @ layer.weight) + layer.bias
+        return torch.relu(Z) if relu else Z
+
+    results = []
+    for Y in (layer(graph, X), separate()):
+        gx, gw = torch.autograd.grad(Y, (X, layer.weight), dY, create_graph=True)
+        assert gx.requires_grad and gw.requires_grad
+        results.append((gx, gw, *torch.autograd.grad((gw ** 2).sum() + (gx ** 2).sum(), (X, layer.weight))))
+    for got, want in zip(*results):
+        assert torch.allclose(got, want, rtol=1e-3, atol=1e-4 * float(want.abs().max()))
