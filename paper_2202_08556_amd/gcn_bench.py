@@ -98,10 +98,12 @@ def main():
         def infer(_i):
             return l2(graph, l1(graph, X))
         t, reps = time_algo(infer, budget_ms=50.0)
-        e0.record()
-        for _ in range(5):
-            H = X @ l1.weight
-            H2 = torch.relu(H) @ l2.weight
+        for timed in (False, True):                           # the library chooses and loads its kernels once
+            if timed:
+                e0.record()
+            for _ in range(5):
+                H = X @ l1.weight
+                H2 = torch.relu(H) @ l2.weight
         e1.record()
         torch.cuda.synchronize()
         dense_us = e0.elapsed_time(e1) / 5 * 1e3
