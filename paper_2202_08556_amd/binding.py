@@ -29,7 +29,8 @@ DA_ROW_MAJOR, DA_COL_MAJOR = 0, 1
 EXPORTS = ("da_spmm", "da_spmm_ex", "da_spmm_select", "da_spmm_features", "da_csr_transpose_workspace",
            "da_csr_transpose", "da_csr_transpose_noalloc", "da_csr_validate", "da_spmm_prepare", "da_spmm_release",
            "da_eb_schedule_workspace", "da_eb_schedule", "da_spmm_weight_grad_workspace", "da_spmm_weight_grad", "da_spmm_column_sums_workspace",
-           "da_spmm_column_sums", "da_spmm_bias_relu", "da_spmm_dense",
+           "da_spmm_column_sums", "da_spmm_bias_relu", "da_spmm_dense", "da_spmm_dense_split_workspace",
+           "da_spmm_dense_split",
            "da_spmm_algo_name", "da_spmm_last_error")
 
 
@@ -77,6 +78,10 @@ _lib.da_spmm_bias_relu.restype = ctypes.c_int
 _lib.da_spmm_weight_grad.restype = ctypes.c_int
 _lib.da_spmm_dense.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _i64, _vp, _i64, _vp]
 _lib.da_spmm_dense.restype = ctypes.c_int
+_lib.da_spmm_dense_split_workspace.argtypes = [_i64, _i64, ctypes.POINTER(ctypes.c_size_t)]
+_lib.da_spmm_dense_split_workspace.restype = ctypes.c_int
+_lib.da_spmm_dense_split.argtypes = [*_lib.da_spmm_dense.argtypes[:-1], _vp, ctypes.c_size_t, _vp]
+_lib.da_spmm_dense_split.restype = ctypes.c_int
 _lib.da_spmm_algo_name.argtypes = [ctypes.c_int]
 _lib.da_spmm_algo_name.restype = ctypes.c_char_p
 _lib.da_spmm_last_error.argtypes = []
@@ -284,6 +289,18 @@ def da_spmm_dense(rows, k, n, A, lda, W, wk, wn, C, ldc, stream=None) -> None:
     """C = A . W for a tall A and a small W with element strides (wk, wn); see include/da_spmm.h."""
     _check(int(_lib.da_spmm_dense(int(rows), int(k), int(n), _ptr(A), int(lda), _ptr(W), int(wk), int(wn), _ptr(C), int(ldc),
                                   _stream(stream))))
+
+
+def da_spmm_dense_split_workspace(k, n) -> int:
+    out = ctypes.c_size_t()
+    _check(int(_lib.da_spmm_dense_split_workspace(int(k), int(n), ctypes.byref(out))))
+    return out.value
+
+
+def da_spmm_dense_split(rows, k, n, A, lda, W, wk, wn, C, ldc, workspace, workspace_bytes, stream=None) -> None:
+    """The same on the bf16 matrix cores, fp32 numbers as sums of three bf16 numbers; see include/da_spmm.h."""
+    _check(int(_lib.da_spmm_dense_split(int(rows), int(k), int(n), _ptr(A), int(lda), _ptr(W), int(wk), int(wn), _ptr(C),
+                                        int(ldc), _ptr(workspace), int(workspace_bytes), _stream(stream))))
 
 
 def da_spmm_algo_name(algo: int):

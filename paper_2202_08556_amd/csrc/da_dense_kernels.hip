@@ -359,4 +359,222 @@ __global__ __launch_bounds__(kDpBlock) void dense_product_kernel(
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// The same product with every fp32 number taken as the exact sum of three bf16 numbers (rounded to nearest one
+// after another: 8 + 8 + 8 significant bits) and six of the nine products of the pieces on the bf16 matrix cores
+// (v_mfma_f32_16x16x32_bf16, fp32 accumulation); the three left out are below 2^-24 of the product.  The leading
+// product has accumulators of its own, to which the sum of the other five is added once at the end.
+//
+// dense_split_weights_kernel lays the pieces of W out in the order in which lanes read them, 32 inner positions a
+// step.  A block of dense_split_kernel is 4 waves of 32 rows of A each and up to 128 columns.  A wave reads its
+// rows itself, whole 64-byte pieces, and converts each number once; the step's piece of W goes through LDS (two
+// buffers, one barrier a step), and what the next step needs is in flight while this one is multiplied.  The last
+// step begins 32 positions before the end; the weights of positions that an earlier step had are zero there.
+//
+// Lane l holds A row (or column of W) l % 16 and inner positions 4 (l / 16) + {0 ... 3, 16 ... 19} of a step.
+//
+// 262 144 x 602 times 602 x 128: the GEMM library's fp32 product 358 us (113 TFLOP/s; the fp32 matrix cores give at most
+// 157), this one 255: 950 TFLOP/s of bf16 products, where a large bf16 product of the library reaches 1200, with the
+// conversions and 765 MB of A and C (150 us at copy rate) beside it.  One instead of two steps in flight, one accumulator
+// instead of two, blocks of 8 waves and blocks that stay over several sets of rows all came out within 5 % of it;
+// splitting W in every block instead of once per call took 300 us.  Error against float64 (2-norm, relative): 1.4e-7,
+// the library's 4.4e-7.
+//
+// Results that the pieces do not carry are computed again on the fp32 matrix cores, wave by wave: where one is
+// not finite (infinities split into infinity and NaN, numbers next to the largest round to infinity) or so small
+// that pieces may have been lost below the smallest normal number, or where an operand is that small.
+// ------------------------------------------------------------------------------------------
+constexpr int kSplitBlock = 256, kSplitRows = 128, kSplitStep = 32;   // 4 waves of 32 rows
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// The pieces of 8 numbers.
+struct SplitFrag { bf16x8 p[3]; };
+
+__device__ __forceinline__ SplitFrag split8(const float* x) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    SplitFrag f;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        f2 r = {x[e], x[e + 1]};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const bf16x2 b = __builtin_convertvector(r, bf16x2);
+            f.p[q][e] = b[0];
+            f.p[q][e + 1] = b[1];
+            if (q < 2) { r[0] -= (float)b[0]; r[1] -= (float)b[1]; }
+        }
+    }
+    return f;
+}
+
+// Order of |x| in which zero is the largest; keys below kSplitTiny are numbers other than zero below 2^-100.
+constexpr unsigned kSplitTiny = (27u << 24) - 1u;
+__device__ __forceinline__ unsigned tiny_key(float x) { return (__float_as_uint(x) << 1) - 1u; }
+
+// A barrier that orders LDS only: loads from memory stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+__host__ __device__ constexpr int split_steps(int k) { return (k + kSplitStep - 1) / kSplitStep; }
+
+// Pieces of W: frag[((step * tiles + tile) * 3 + piece) * 64 + lane], tile = 16 columns; columns past the last repeat it.
+// tiny[step * tiles + tile]: whether a weight is that small.  One wave per step and tile.
+__global__ __launch_bounds__(64) void dense_split_weights_kernel(int k, int n, const float* __restrict__ W, long wk, long wn,
+                                                                 bf16x8* __restrict__ frag, int* __restrict__ tiny)
+{
+    const int step = blockIdx.x, tile = blockIdx.y, tiles = gridDim.y, lane = threadIdx.x;
+    const int p0 = min(step * kSplitStep, k - kSplitStep) + 4 * (lane >> 4);
+    const float* __restrict__ w = W + (long)min(tile * 16 + (lane & 15), n - 1) * wn;
+    float x[8];
+    unsigned least = ~0u;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int p = p0 + (e & 3) + 16 * (e >> 2);
+        x[e] = w[(long)p * wk];
+        x[e] = p >= step * kSplitStep ? x[e] : 0.f;
+        least = min(least, tiny_key(x[e]));
+    }
+    const SplitFrag f = split8(x);
+    const long at = (long)step * tiles + tile;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) frag[(at * 3 + q) * 64 + lane] = f.p[q];
+    const bool any = __any(least < kSplitTiny);
+    if (lane == 0) tiny[at] = any;
+}
+
+// NT tiles of 16 columns.  k >= 32; `tiles` tiles to a step of `frag`.
+template <int NT>
+__global__ __launch_bounds__(kSplitBlock, 2) void dense_split_kernel(
+    int rows, int n, int k, const float* __restrict__ A, long lda, const float* __restrict__ W, long wk, long wn,
+    const bf16x8* __restrict__ frag, const int* __restrict__ tiny, int tiles, float* __restrict__ C, long ldc)
+{
+    constexpr int kFrags = 3 * NT * 64;                    // 16-byte pieces of a step
+    constexpr int WL = (kFrags + kSplitBlock - 1) / kSplitBlock;
+    __shared__ bf16x8 buf[2][kFrags];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = lane & 15, h = lane >> 4;
+    const int tile0 = blockIdx.y * NT, n0 = tile0 * 16;
+    const int steps = split_steps(k);
+    // the tiles of the last column block that do not exist read the last one that does
+    const bf16x8* __restrict__ wsrc[WL];
+    bool wuse[WL];
+#pragma unroll
+    for (int j = 0; j < WL; ++j) {
+        const int at = threadIdx.x + j * kSplitBlock;
+        wuse[j] = at < kFrags;
+        const int tile = min(tile0 + at / 192, tiles - 1);
+        wsrc[j] = frag + (long)tile * 192 + at % 192;
+    }
+    bool w_tiny = false;
+    for (int s = lane; s < steps * tiles; s += 64) w_tiny |= tiny[s] != 0;
+
+    float x[16];
+    bf16x8 w[WL];
+    auto fetch_w = [&](int s) {
+#pragma unroll
+        for (int j = 0; j < WL; ++j) w[j] = wsrc[j][(long)s * tiles * 192];
+    };
+    const long first = (long)blockIdx.x * kSplitRows + wave * 32 + i;
+    const float* __restrict__ arow[2] = {A + min(first, (long)rows - 1) * lda + 4 * h, A + min(first + 16, (long)rows - 1) * lda + 4 * h};
+    auto fetch_a = [&](int s) {
+        const int p = min(s * kSplitStep, k - kSplitStep);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const float4 v = load4(arow[r] + p + 16 * q);
+                x[8 * r + 4 * q] = v.x; x[8 * r + 4 * q + 1] = v.y; x[8 * r + 4 * q + 2] = v.z; x[8 * r + 4 * q + 3] = v.w;
+            }
+    };
+    mfma_acc big[2][NT], small[2][NT];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) big[r][t] = small[r][t] = mfma_acc{0.f, 0.f, 0.f, 0.f};
+    unsigned least = ~0u;
+    fetch_w(0);
+    fetch_a(0);
+    for (int s = 0; s < steps; ++s) {
+        bf16x8* __restrict__ b = buf[s & 1];
+#pragma unroll
+        for (int j = 0; j < WL; ++j) if (WL * kSplitBlock == kFrags || wuse[j]) b[threadIdx.x + j * kSplitBlock] = w[j];
+        SplitFrag a[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            a[r] = split8(x + 8 * r);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) least = min(least, tiny_key(x[8 * r + q]));
+        }
+        fetch_w(min(s + 1, steps - 1));                // in flight across the barrier and the matrix instructions
+        fetch_a(min(s + 1, steps - 1));
+        lds_barrier();                                 // the other buffer's readers are past the barrier before this one
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const bf16x8 w0 = b[(t * 3) * 64 + lane], w1 = b[(t * 3 + 1) * 64 + lane], w2 = b[(t * 3 + 2) * 64 + lane];
+            auto dot = [&](bf16x8 u, int piece, mfma_acc (&c)[2][NT]) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) c[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u, a[r].p[piece], c[r][t], 0, 0, 0);
+            };
+            dot(w0, 0, big);
+            dot(w0, 2, small);
+            dot(w1, 1, small);
+            dot(w2, 0, small);
+            dot(w0, 1, small);
+            dot(w1, 0, small);
+        }
+    }
+
+    bool again = least < kSplitTiny || w_tiny;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            big[r][t] += small[r][t];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float size = fabsf(big[r][t][q]);
+                again |= !(size <= 3.402823466e38f) || (size != 0.f && size < 8.077936e-28f);      // 2^-90
+            }
+        }
+    if (__any(again)) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) big[r][t] = mfma_acc{0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < k; p0 += 4) {
+            const int p = p0 + h;
+            float u[2], v[NT];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) u[r] = p < k ? A[min(first + 16 * r, (long)rows - 1) * lda + p] : 0.f;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) v[t] = p < k ? W[(long)p * wk + (long)min(n0 + 16 * t + i, n - 1) * wn] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) big[r][t] = mfma16(v[t], u[r], big[r][t]);
+        }
+    }
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        if (first + 16 * r >= rows) continue;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int col = n0 + 16 * t + 4 * h;
+            float* __restrict__ c = C + (first + 16 * r) * ldc + col;
+            if (col + 4 <= n) {
+                *reinterpret_cast<f4*>(c) = f4{big[r][t][0], big[r][t][1], big[r][t][2], big[r][t][3]};
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) if (col + q < n) c[q] = big[r][t][q];
+            }
+        }
+    }
+}
+
 }  // namespace daspmm

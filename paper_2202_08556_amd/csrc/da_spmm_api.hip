@@ -1192,6 +1192,7 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
 namespace {
 constexpr int64_t kDenseMaxRows = 1 << 30;         // the kernels count rows, and a block's rows past the end, in 32 bits
 constexpr int64_t kDenseMaxCols = 1 << 20, kSumsMaxCols = 1 << 22;
+constexpr int64_t kSplitMaxInner = 1 << 20, kSplitMaxCols = 1 << 14;
 
 // Row blocks of the weight gradient: two blocks to a CU over all tiles, and no fewer than 64 rows each.
 int weight_grad_blocks(int64_t rows, int64_t tiles) {
@@ -1334,6 +1335,51 @@ int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float* A, int64_t ld
     else by_k(Count<8>{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "da_spmm_dense launch");
+    return DA_OK;
+}
+
+int da_spmm_dense_split_workspace(int64_t k, int64_t n, size_t* bytes)
+{
+    if (!bytes) return fail(DA_ERR_INVALID_ARG, "null bytes%s");
+    if (k < 0 || n < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
+    if (k > kSplitMaxInner || n > kSplitMaxCols) return fail(DA_ERR_UNSUPPORTED, "size too large%s");
+    const size_t pieces = (size_t)split_steps((int)k) * (size_t)((n + 15) / 16);
+    *bytes = pieces * (192 * sizeof(bf16x8) + sizeof(int));
+    return DA_OK;
+}
+
+int da_spmm_dense_split(int64_t rows, int64_t k, int64_t n, const float* A, int64_t lda, const float* W, int64_t wk, int64_t wn,
+                        float* C, int64_t ldc, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (rows < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
+    size_t need = 0;
+    const int st = da_spmm_dense_split_workspace(k, n, &need);
+    if (st != DA_OK) return st;
+    if (rows > kDenseMaxRows) return fail(DA_ERR_UNSUPPORTED, "size too large%s");
+    if (rows == 0 || n == 0) return DA_OK;
+    if (k < kSplitStep) return fail(DA_ERR_UNSUPPORTED, "fewer than 32 columns in A%s");
+    if (lda < k || ldc < n || wk < 1 || wn < 1) return fail(DA_ERR_INVALID_ARG, "leading dimension smaller than the extent it strides over%s");
+    if (!A || !W || !C) return fail(DA_ERR_INVALID_ARG, "null A, W or C%s");
+    if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
+        return fail(DA_ERR_INVALID_ARG, "workspace missing, misaligned or smaller than da_spmm_dense_split_workspace reports%s");
+    hipStream_t s = (hipStream_t)stream;
+    const int steps = split_steps((int)k), tiles = (int)((n + 15) / 16);
+    bf16x8* frag = static_cast<bf16x8*>(workspace);
+    int* tiny = reinterpret_cast<int*>(frag + (size_t)steps * tiles * 192);
+    hipLaunchKernelGGL(dense_split_weights_kernel, dim3((unsigned)steps, (unsigned)tiles), dim3(64), 0, s, (int)k, (int)n, W, (long)wk,
+                       (long)wn, frag, tiny);
+    auto go = [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        hipLaunchKernelGGL((dense_split_kernel<NT>), dim3((unsigned)((rows + kSplitRows - 1) / kSplitRows), (unsigned)((tiles + NT - 1) / NT)),
+                           dim3(kSplitBlock), 0, s, (int)rows, (int)n, (int)k, A, (long)lda, W, (long)wk, (long)wn, frag, tiny, tiles, C,
+                           (long)ldc);
+    };
+    if (tiles <= 2) go(Count<2>{});
+    else if (tiles <= 4) go(Count<4>{});
+    else if (tiles <= 6) go(Count<6>{});
+    else go(Count<8>{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_dense_split launch");
     return DA_OK;
 }
 

@@ -473,14 +473,30 @@ Tensor aggregate(const GraphPtr& g, const Arrays& a, const Tensor& X, const Tens
     return Y;
 }
 
-// A . W, into `out` (unit column stride).  The own kernel keeps W in LDS: it wins while the inner dimension is
-// at most 128 and, whatever the size, where the GEMM library's 18 us of host time are the larger part.
+// A . W, into `out` (unit column stride): three ways.  Products of bf16 pieces from some 5000 weights on where the
+// fp32 matrix cores are the bound (100 000 rows: 128 x 128 55 us on them, 36 in pieces; 262 144 rows: 128 x 41 49 and
+// 42, 64 x 32 22 and 24), if that pays for the launch that lays the weights out (100 003 rows: 96 x 64 25 and 23, but a
+// training step of such a layer 294 and 299), and for long sums (262 144 rows: 256 x 16 62 and 51).  A block of theirs has
+// 128 rows and walks the whole sum, so few rows of long sums are the GEMM library's, which splits them (k = 602,
+// n = 128: 20 000 rows 44 us there, 40 here; 8000 rows 21 and 37; 262 144 rows 358 and 259).  Small weights: the fp32
+// kernel, which keeps them in LDS, while the inner dimension is at most 128 and, whatever the size, where the
+// library's 18 us of host time are the larger part.
 void dense_product(const Tensor& A, const Tensor& W, bool transpose_w, Tensor& out) {
     const int64_t rows = A.size(0), k = A.size(1), n = out.size(1);
-    if (k >= 1 && (k <= 128 || (k <= 256 && rows * k * n <= 300000000)) && A.stride(1) == 1 && W.is_contiguous()) {
-        const int st = da_spmm_dense(rows, k, n, data<float>(A), leading(A), data<float>(W), transpose_w ? 1 : n,
-                                     transpose_w ? k : 1, data<float>(out), leading(out), stream_of(A));
-        if (st != DA_ERR_UNSUPPORTED) return check(st);
+    if (A.stride(1) == 1 && W.is_contiguous()) {
+        const int64_t wk = transpose_w ? 1 : n, wn = transpose_w ? k : 1;
+        size_t bytes = 0;
+        if (k >= 32 && ((k * n >= 5000 && rows * k * n >= 1000000000) || k > 192) && (k <= 256 || rows >= 30 * k) && n <= 512 &&
+            da_spmm_dense_split_workspace(k, n, &bytes) == DA_OK) {
+            Tensor ws = at::empty({(int64_t)bytes}, A.options().dtype(at::kByte));
+            const int st = da_spmm_dense_split(rows, k, n, data<float>(A), leading(A), data<float>(W), wk, wn, data<float>(out),
+                                               leading(out), data<void>(ws), bytes, stream_of(A));
+            if (st != DA_ERR_UNSUPPORTED) return check(st);
+        } else if (k >= 1 && (k <= 128 || (k <= 256 && rows * k * n <= 300000000))) {
+            const int st = da_spmm_dense(rows, k, n, data<float>(A), leading(A), data<float>(W), wk, wn, data<float>(out),
+                                         leading(out), stream_of(A));
+            if (st != DA_ERR_UNSUPPORTED) return check(st);
+        }
     }
     at::mm_out(out, A, transpose_w ? W.t() : W);
 }
