@@ -5,6 +5,7 @@
 #include "da_spmm_kernels.hip"
 #include "da_transpose_kernels.hip"
 #include "da_dense_kernels.hip"
+#include "da_heavy_kernels.hip"
 
 #include <algorithm>
 #include <atomic>
@@ -62,6 +63,7 @@ struct Problem {
     float* C;
     hipStream_t stream;
     int64_t k;
+    LeftOut left_out;    // RB_SR: rows that heavy_rows_kernel sums
 };
 
 enum Family { RB_SR, RB_PR, EB_SR, EB_PR };
@@ -135,6 +137,10 @@ struct Plan {
     int units[kPlans] = {};
     int first_units[kPlans] = {};   // chunks of the first schedule segment (multi-row chunks)
     std::shared_ptr<DeviceBlock> block;
+    HeavyPlan heavy{};                   // count > 0: rows that heavy_rows_kernel takes from EB+RM+SR
+    const unsigned* heavy_bits = nullptr;
+    double rest_len = 0.0;               // length of the row that an average entry of the other rows lies in
+    std::shared_ptr<DeviceBlock> heavy_block;
     bool captured = false;               // a stream capture recorded a kernel that reads the orders
 };
 std::mutex g_plan_mu;
@@ -170,6 +176,29 @@ Schedule lookup_schedule(const void* rowptr, const void* colind, int64_t m, int 
                     return Schedule{pl.order[i], pl.units[i], (int)pl.nnz, 0, pl.first_units[i], 0, 0, 0, 3, pl.first_row[i], pl.row_by_chunk[i]};
                 }
     return Schedule{nullptr, 0, 0, 0, 0, 0, 0, 0, 3, nullptr, nullptr};
+}
+
+bool is_capturing(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
+    return cap == hipStreamCaptureStatusActive;
+}
+
+// The heavy rows of a prepared matrix; references and captures as for lookup_schedule.
+struct HeavyLookup { HeavyPlan plan{}; const unsigned* bits = nullptr; double rest_len = 0.0; std::shared_ptr<DeviceBlock> keep; };
+HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, hipStream_t stream) {
+    HeavyLookup out;
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    for (auto& pl : g_plans)
+        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m && pl.heavy.count > 0) {
+            out.plan = pl.heavy;
+            out.bits = pl.heavy_bits;
+            out.rest_len = pl.rest_len;
+            out.keep = pl.heavy_block;
+            if (is_capturing(stream)) pl.captured = true;
+            break;
+        }
+    return out;
 }
 
 // SR from 17 columns, where rows of B and C are not whole 16-byte pieces: whether a wave is better off with 8, 4 or 2
@@ -340,7 +369,7 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     case RB_SR: {
         const long rows_per_block = (long)kWavesPerBlock * (kWave / G);
         hipLaunchKernelGGL((rb_sr_kernel<V, G, NV, WIDE>), grid_for((p.m + rows_per_block - 1) / rows_per_block),
-                           block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin);
+                           block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin, p.left_out);
         break;
     }
     case RB_PR: {
@@ -378,11 +407,9 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         if (blocks < 1) blocks = 1;
         // chunk order of a prepared matrix (column sweep), if one exists for this chunk size
         std::shared_ptr<DeviceBlock> keep;                 // dropped after the launch
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(p.stream, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
         Schedule sch = !geo.order || env_int("DA_SPMM_NO_SCHEDULE", 0)
                            ? Schedule{nullptr, 0, 0, 0, 0, 0, 0, 0, 3, nullptr, nullptr}
-                           : lookup_schedule(p.rowptr, p.colind, p.m, chunk, cap == hipStreamCaptureStatusActive, &keep);
+                           : lookup_schedule(p.rowptr, p.colind, p.m, chunk, is_capturing(p.stream), &keep);
         // EB+SR on a prepared matrix never splits rows of at most a chunk (the plan's row hints make
         // the second boundary look-up cheap); the zero pass and the product kernel are told alike
         const int own_short = (fam == EB_SR && kOwnShortRows<G> && sch.order != nullptr &&
@@ -447,6 +474,40 @@ int launch(Family fam, const Problem& p, const Geometry& geo) {
     const bool narrow = p.k <= (1 << 24) && p.sd.rb * 4 < (1 << 24) && (last + 4) * 4 < (1ull << 32) &&
                         env_int("DA_SPMM_WIDE", 0) == 0;
     return narrow ? launch_w<V, G, NV, false>(fam, p, geo) : launch_w<V, G, NV, true>(fam, p, geo);
+}
+
+// Beyond 32 columns LDS is the bound, and the kernel the better one only where its 16 waves have about equal numbers of
+// rows (N = 64, 72 heavy rows: 92 us, EB 76; 322: 198 and 217; 524: 330 and 469).
+constexpr int kHeavyWideRows = 256;
+// Entries of a row that one block adds up, at least: every block's part is one more rounding of the row's sum, and chunks
+// of EB+SR have 64 to 128 (rows of 8000, all of one sign, N = 3: error 1.5e-7 there, 2.8e-7 with parts of 32).
+constexpr int kHeavyPart = 128;
+
+// The heavy rows' part of a product whose other rows are on the stream already.  A block has 131 KB of LDS and 16
+// waves, one to a CU: as many ranges of columns as make one block per CU over all sets of rows and column tiles.
+// Lanes: 4 of two columns up to 8 columns (N = 8: 90 us, 16 lanes of one column 114), 16 beyond (N = 16, 1.6 M entries: 16 us,
+// 4 lanes of four columns, whose random 64-byte reads meet in the banks of LDS, 33).
+
+int launch_heavy(const Problem& p, const HeavyPlan& pl) {
+    auto go = [&](auto kernel, int tile) {
+        const int tiles = (p.N + tile - 1) / tile;
+        const int sets = (pl.count + 3) / 4;
+        const int groups = (sets + kHeavyWaves * kHeavyQuads - 1) / (kHeavyWaves * kHeavyQuads);
+        const int quads = (sets + kHeavyWaves * groups - 1) / (kHeavyWaves * groups);
+        long wanted = cu_count() / ((long)groups * tiles);
+        wanted = std::max<long>(1, std::min<long>(wanted, pl.mean_len / kHeavyPart));
+        const int per = (int)((pl.cells + wanted - 1) / wanted);
+        const int slabs = (pl.cells + per - 1) / per;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(groups * slabs), (unsigned)tiles), dim3(kHeavyBlock), kHeavyLds, p.stream, p.m, (int)p.k,
+                           p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pl, groups, quads, per);
+    };
+    if (p.N <= 8) go(heavy_rows_kernel<4, 2>, 8);
+    else if (p.N <= 16) go(heavy_rows_kernel<16, 1>, 16);
+    else if (p.N <= 32) go(heavy_rows_kernel<16, 2>, 32);
+    else go(heavy_rows_kernel<16, 4>, 64);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "kernel launch");
+    return DA_OK;
 }
 
 template <int V>
@@ -747,12 +808,24 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     sd.cb = layout_b == DA_ROW_MAJOR ? 1 : ldb;
     sd.rc = layout_c == DA_ROW_MAJOR ? ldc : 1;
     sd.cc = layout_c == DA_ROW_MAJOR ? 1 : ldc;
-    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k};
+    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{nullptr, 0, 0}};
     const bool eb = algo >= DA_EB_RM_SR;
     const bool cm = (algo & 2) != 0;
     const bool pr = (algo & 1) != 0;
     Geometry g;
     const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
+    if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
+        // heavy rows in a kernel of their own, the others, which are short and even, row by row
+        const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, p.stream);
+        if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows)) {
+            const int st = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
+                                         PlanInfo{false, 0.0}, &g);
+            if (st != DA_OK) return st;
+            p.left_out = LeftOut{heavy.bits, heavy.plan.min_len, heavy.plan.nnz};
+            const int rest = dispatch(RB_SR, g, p);
+            return rest != DA_OK ? rest : launch_heavy(p, heavy.plan);
+        }
+    }
     const bool ask = eb || (!cm && !pr && N > 16 && (N < 32 || N % 4 != 0 || ends % 16 != 0));   // RB: only where the lanes depend on it
     const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
@@ -1091,18 +1164,109 @@ int da_spmm_release(const int32_t* rowptr)
 {
     // the references are dropped outside the mutex: the last one frees device memory, which waits
     // for the device
-    std::shared_ptr<DeviceBlock> dropped[16];
+    std::shared_ptr<DeviceBlock> dropped[32];
     {
         std::lock_guard<std::mutex> lk(g_plan_mu);
         int n = 0;
         for (auto& pl : g_plans)
             if (pl.block && (!rowptr || pl.rowptr == rowptr)) {
                 dropped[n++] = std::move(pl.block);
+                dropped[n++] = std::move(pl.heavy_block);
                 pl = Plan{};
             }
     }
     return DA_OK;
 }
+
+}  // extern "C"
+
+namespace {
+
+// Heavy rows: a 32nd of all columns and more (at fewer, a row has so few entries in a band of B that the walk over the
+// rows costs more than the entries).  Worth a kernel of their own where they hold most entries, every row of B serves
+// at least 8 of them, and the other rows are even enough to be taken one by one.
+constexpr int64_t kHeavyShare = 32, kHeavyMinCols = 16384, kHeavyMinEntries = 400000, kHeavyUses = 8;
+constexpr int kHeavyMost = 8192, kHeavyCells = 1024, kRestLongest = 1024;
+constexpr double kRestLen = 64.0;
+
+int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, const int32_t* colind, hipStream_t s, Plan* pl)
+{
+    if (k < kHeavyMinCols || nnz < kHeavyMinEntries || nnz >= (1LL << 30)) return DA_OK;
+    const int min_len = (int)(k / kHeavyShare);
+    DeviceBlock tmp;                                       // count and flag, sums, list
+    const size_t tmp_bytes = 64 + kHeavyMost * sizeof(int);
+    hipError_t e = hipMalloc(&tmp.p, tmp_bytes);
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+    int* count = static_cast<int*>(tmp.p);
+    unsigned long long* sums = reinterpret_cast<unsigned long long*>(count + 4);
+    int* list = count + 16;
+    struct { int count, unsorted, pad[2]; unsigned long long sq, mx; } host{};
+    std::vector<int> rows;
+    e = hipMemsetAsync(tmp.p, 0, 64, s);
+    if (e == hipSuccess) {
+        const long blocks = std::min<long>((m + 255) / 256, (long)cu_count() * 8);
+        hipLaunchKernelGGL(heavy_rows_list_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (int)m, rowptr, min_len, kHeavyMost, list, sums, count);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(&host, tmp.p, sizeof host, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_prepare");
+    if (host.count < 1 || host.count > kHeavyMost || host.mx > (unsigned long long)kRestLongest) return DA_OK;
+    // the lengths come with the rows' pointers, two at a time
+    rows.resize(host.count);
+    e = hipMemcpyAsync(rows.data(), list, rows.size() * sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    std::vector<int> ptr(2 * rows.size());
+    DeviceBlock pairs;
+    if (e == hipSuccess) e = hipMalloc(&pairs.p, 2 * rows.size() * sizeof(int));
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(heavy_row_ends_kernel, dim3((unsigned)((rows.size() + 255) / 256)), dim3(256), 0, s, (int)rows.size(), list, rowptr,
+                           static_cast<int*>(pairs.p));
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(ptr.data(), pairs.p, ptr.size() * sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_prepare");
+    int64_t entries = 0;
+    std::vector<std::pair<int, int>> by_length(rows.size());
+    for (size_t i = 0; i < rows.size(); ++i) {
+        by_length[i] = {ptr[2 * i + 1] - ptr[2 * i], rows[i]};
+        entries += by_length[i].first;
+    }
+    const double rest_len = nnz > entries ? (double)host.sq / (double)(nnz - entries) : 0.0;
+    if (entries < kHeavyMinEntries || 2 * entries < nnz || entries < kHeavyUses * k || rest_len > kRestLen) return DA_OK;
+    std::sort(by_length.begin(), by_length.end());         // neighbours walk side by side: rows of one length
+    for (size_t i = 0; i < rows.size(); ++i) rows[i] = by_length[i].second;
+
+    const int cell = (int)((k + kHeavyCells - 1) / kHeavyCells), cells = (int)((k + cell - 1) / cell);
+    const size_t words = (size_t)(m + 31) / 32, n = rows.size();
+    auto block = std::make_shared<DeviceBlock>();
+    const size_t ints = ((n + 63) & ~size_t(63)) + ((words + 63) & ~size_t(63)) + n * (size_t)(cells + 1);
+    e = hipMalloc(&block->p, ints * sizeof(int));
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+    int* drows = static_cast<int*>(block->p);
+    unsigned* bits = reinterpret_cast<unsigned*>(drows + ((n + 63) & ~size_t(63)));
+    int* at = reinterpret_cast<int*>(bits + ((words + 63) & ~size_t(63)));
+    e = hipMemsetAsync(bits, 0, words * sizeof(unsigned), s);
+    if (e == hipSuccess) e = hipMemcpyAsync(drows, rows.data(), n * sizeof(int), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(heavy_cells_kernel, dim3((unsigned)n, 8), dim3(256), 0, s, rowptr, colind, drows, cells, cell, at, bits, count + 1);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(&host, tmp.p, sizeof host, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "da_spmm_prepare");
+    if (host.unsorted) return DA_OK;
+    pl->heavy = HeavyPlan{drows, at, (int)n, cells, cell, min_len, (int)nnz, (int)(entries / (int64_t)n)};
+    pl->heavy_bits = bits;
+    pl->rest_len = rest_len;
+    pl->heavy_block = block;
+    return DA_OK;
+}
+
+}  // namespace
+
+extern "C" {
 
 int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, const int32_t* colind, void* stream)
 {
@@ -1161,7 +1325,11 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     if (status == DA_OK && summed) give_slot(dev, sums); else free_slot(sums);
     if (status != DA_OK) return status;
     remember_matrix(rowptr, m, nnz, seen_len);
-    std::shared_ptr<DeviceBlock> old;                      // freed after the mutex is released
+    if (seen_len >= (double)(k / kHeavyShare)) {
+        const int hs = plan_heavy_rows(m, k, nnz, rowptr, colind, (hipStream_t)stream, &pl);
+        if (hs != DA_OK) return hs;
+    }
+    std::shared_ptr<DeviceBlock> old, old_heavy;           // freed after the mutex is released
     {
         std::lock_guard<std::mutex> lk(g_plan_mu);
         Plan* slot = nullptr;
@@ -1184,6 +1352,7 @@ int da_spmm_prepare(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
             if (!slot) return DA_OK;                       // every slot is pinned by a graph: no plan for this matrix
         }
         old = std::move(slot->block);
+        old_heavy = std::move(slot->heavy_block);
         *slot = pl;
     }
     return DA_OK;

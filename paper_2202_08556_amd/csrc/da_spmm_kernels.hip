@@ -443,6 +443,13 @@ __device__ __forceinline__ void for_blocks(int begin, int cnt, F&& f) {
 template <int UMAX, class F>
 __device__ __forceinline__ void for_blocks(int cnt, F&& f) { for_blocks<UMAX>(0, cnt, f); }
 
+// Rows whose sums another kernel adds to C (heavy_rows_kernel): one bit a row, for rows of at least min_len entries in
+// a matrix of nnz; they are written as zeros.  rows == nullptr: none.
+struct LeftOut {
+    const unsigned* rows;
+    int min_len, nnz;
+};
+
 // ------------------------------------------------------------------------------------------
 // RB + SR : a lane group owns a row and adds its products one after another
 // (Sec. 3.2 design M1, Sec. 3.4 design K1).  For G > 1 the group's lanes load a batch of stored
@@ -452,7 +459,7 @@ __device__ __forceinline__ void for_blocks(int cnt, F&& f) { for_blocks<UMAX>(0,
 template <int V, int G, int NV, bool WIDE>
 __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
-    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles)
+    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles, LeftOut out)
 {
     constexpr int RPW = kWave / G;                       // rows per wave
     constexpr int SB = StageBatch<G>::value;
@@ -466,6 +473,7 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
     const int n0 = cols.n0, nvec = cols.nvec;
     int start = 0, end = 0;
     if (row < m) { start = rowptr[row]; end = rowptr[row + 1]; }
+    if (out.rows != nullptr && end - start >= out.min_len && (out.rows[row >> 5] >> (row & 31) & 1u) && rowptr[m] == out.nnz) end = start;
     Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);

@@ -1,0 +1,154 @@
+"""Rows that hold a good part of all columns (heavy_rows_kernel, EB+RM+SR on prepared matrices): every lane mapping at its
+edges, and plans that no longer describe the matrix.  Integer values: any order of summation gives the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import reference as orc
+
+pytestmark = pytest.mark.gpu
+
+K, M, HEAVY = 20011, 2500, 300                    # heavy: from a 32nd of the columns, 625, on; 256 of them for N > 32
+
+
+def matrix(seed, heavy=HEAVY, lo=640, hi=4000):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    lens = rng.poisson(3.0, M)
+    lens[rng.choice(M, heavy, replace=False)] = rng.integers(lo, hi, heavy)
+    lens[:2], lens[-1] = 0, K                     # empty rows, and one with every column
+    return _csr(lens, rng)
+
+
+def _csr(lens, rng):
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colind = np.concatenate([np.sort(rng.choice(K, n, replace=False)) for n in lens]).astype(np.int32)
+    vals = rng.choice(np.array([-3, -2, -1, 1, 2, 3], np.float32), colind.size)
+    return rowptr, colind, vals
+
+
+@pytest.fixture(scope="module")
+def prepared():
+    from paper_2202_08556_amd import binding as da
+    host = matrix(5)
+    dev = [torch.from_numpy(x).cuda() for x in host]
+    da.da_spmm_prepare(M, K, host[1].size, dev[0], dev[1])
+    yield host, dev
+    da.da_spmm_release(dev[0])
+
+
+def product(dev, B, N):
+    from paper_2202_08556_amd import binding as da
+    C = torch.full((M, N), float("nan"), device="cuda")
+    da.da_spmm(M, K, N, *dev, B, C, da.DA_EB_RM_SR)
+    return C.cpu().numpy()
+
+
+def dense(N, seed=1):
+    return np.random.Generator(np.random.PCG64(seed)).integers(-4, 5, (K, N)).astype(np.float32)
+
+
+@pytest.mark.parametrize("N", [1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 130])
+def test_every_width(prepared, N):
+    host, dev = prepared
+    print("heavy rows N", N, flush=True)
+    B = dense(N)
+    want, _ = orc.spmm(*host, B)
+    assert np.array_equal(product(dev, torch.from_numpy(B).cuda(), N), want.astype(np.float32) + 0.0)
+
+
+@pytest.mark.parametrize("N", [8, 40])
+@pytest.mark.parametrize("order", ["row", "col"])
+def test_stored_orders(prepared, N, order):
+    from paper_2202_08556_amd import binding as da
+    host, dev = prepared
+    B = dense(N)
+    want, _ = orc.spmm(*host, B)
+    if order == "row":
+        Bd = torch.full((K, N + 3), float("nan"), device="cuda")
+        Bd[:, :N] = torch.from_numpy(B)
+        C = torch.full((M, N + 5), -7.0, device="cuda")
+        da.da_spmm_ex(M, K, N, *dev, Bd, N + 3, da.DA_ROW_MAJOR, C, N + 5, da.DA_ROW_MAJOR, da.DA_EB_RM_SR)
+        assert (C[:, N:] == -7.0).all()
+        got = C[:, :N]
+    else:
+        C = torch.full((N, M), float("nan"), device="cuda")
+        da.da_spmm_ex(M, K, N, *dev, torch.from_numpy(np.ascontiguousarray(B.T)).cuda(), K, da.DA_COL_MAJOR, C, M, da.DA_COL_MAJOR,
+                      da.DA_EB_RM_SR)
+        got = C.t()
+    assert np.array_equal(got.cpu().numpy(), want.astype(np.float32) + 0.0)
+
+
+def test_infinities_stay_in_their_rows(prepared):
+    host, dev = prepared
+    B = dense(24)
+    col = int(host[1][host[0][HEAVY]])
+    B[col] = np.inf
+    want, _ = orc.spmm(*host, B)
+    got = product(dev, torch.from_numpy(B).cuda(), 24)
+    assert np.isfinite(want).any() and np.array_equal(got, want.astype(np.float32) + 0.0, equal_nan=True)
+
+
+# the same arrays with other contents after prepare: another matrix with as many entries, columns out of order,
+# and columns that descend
+@pytest.mark.parametrize("change", ["other", "shuffled", "descending", "fewer"])
+@pytest.mark.parametrize("N", [8, 20, 64])
+def test_plans_of_another_matrix(change, N):
+    from paper_2202_08556_amd import binding as da
+    rowptr, colind, vals = matrix(7)
+    dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals)]
+    da.da_spmm_prepare(M, K, colind.size, dev[0], dev[1])
+    rng = np.random.Generator(np.random.PCG64(9))
+    if change == "other":                          # rows in another order
+        lens = np.diff(rowptr)[rng.permutation(M)]
+        rowptr, colind, vals = _csr(lens, rng)
+    elif change == "fewer":
+        rowptr = np.minimum(rowptr, rowptr[-1] - 1)
+    else:
+        for r in range(M):
+            part = colind[rowptr[r]:rowptr[r + 1]]
+            part[:] = rng.permutation(part) if change == "shuffled" else part[::-1].copy()
+    for d, h in zip(dev, (rowptr, colind, vals)):
+        d.copy_(torch.from_numpy(h))
+    B = dense(N)
+    want, _ = orc.spmm(rowptr, colind[:rowptr[-1]], vals[:rowptr[-1]], B)
+    got = product(dev, torch.from_numpy(B).cuda(), N)
+    da.da_spmm_release(dev[0])
+    assert np.array_equal(got, want.astype(np.float32) + 0.0)
+
+
+def test_unsorted_columns_have_no_plan_and_stay_right():
+    from paper_2202_08556_amd import binding as da
+    rowptr, colind, vals = matrix(11)
+    rng = np.random.Generator(np.random.PCG64(2))
+    for r in range(M):
+        part = colind[rowptr[r]:rowptr[r + 1]]
+        part[:] = rng.permutation(part)
+    dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals)]
+    da.da_spmm_prepare(M, K, colind.size, dev[0], dev[1])
+    B = dense(16)
+    want, _ = orc.spmm(rowptr, colind, vals, B)
+    got = product(dev, torch.from_numpy(B).cuda(), 16)
+    da.da_spmm_release(dev[0])
+    assert np.array_equal(got, want.astype(np.float32) + 0.0)
+
+
+def test_recorded_calls_keep_their_plan():
+    from paper_2202_08556_amd import binding as da
+    host = matrix(13)
+    dev = [torch.from_numpy(x).cuda() for x in host]
+    da.da_spmm_prepare(M, K, host[1].size, dev[0], dev[1])
+    B = dense(12)
+    want = orc.spmm(*host, B)[0].astype(np.float32) + 0.0
+    Bd, C = torch.from_numpy(B).cuda(), torch.zeros((M, 12), device="cuda")
+    da.da_spmm(M, K, 12, *dev, Bd, C, da.DA_EB_RM_SR)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        da.da_spmm(M, K, 12, *dev, Bd, C, da.DA_EB_RM_SR)
+    da.da_spmm_prepare(M, K, host[1].size, dev[0], dev[1])         # the recorded plan stays
+    for _ in range(3):
+        C.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(C.cpu().numpy(), want)
+    da.da_spmm_release(dev[0])
