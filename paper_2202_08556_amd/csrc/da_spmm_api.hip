@@ -483,6 +483,34 @@ constexpr int kHeavyWideRows = 256;
 // of EB+SR have 64 to 128 (rows of 8000, all of one sign, N = 3: error 1.5e-7 there, 2.8e-7 with parts of 32).
 constexpr int kHeavyPart = 128;
 
+// Column-major B under the RB ids whose sums rb_columns_kernel makes at least as exact (SR; RM+PR from 5 columns on, which
+// has 8 slots).  Lanes per row by the length of the row that an average entry lies in: 4 below 6 (3 a row, N = 1: 6.7 us,
+// with 8 lanes 7.9, with lanes along N 6.8), 16 from 40 on (rows of 170, N = 8: 93 us with 8, 87 with 16, lanes along N: SR 105,
+// PR 99; 27-point stencil: 25 with 8, 35 with 16), 64 from 200 on, where a few rows are much longer than the others
+// (power-law, N = 8: 71 with 16, 59 with 64, PR along N 63).  Unknown: 8.
+int launch_columns(const Problem& p, const MatrixHint& hint) {
+    auto go = [&](auto l, auto nc) {
+        constexpr int L = decltype(l)::value, NC = decltype(nc)::value;
+        const long rows = (long)kWavesPerBlock * (kWave / L);
+        hipLaunchKernelGGL((rb_columns_kernel<L, NC>), dim3((unsigned)((p.m + rows - 1) / rows), (unsigned)((p.N + NC - 1) / NC)),
+                           dim3(kBlock), 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C);
+    };
+    auto by_columns = [&](auto l) {
+        if (p.N >= 5) go(l, Count<8>{});
+        else if (p.N >= 3) go(l, Count<4>{});
+        else if (p.N == 2) go(l, Count<2>{});
+        else go(l, Count<1>{});
+    };
+    const double len = hint.seen_len > 0.0 ? hint.seen_len : 8.0;
+    if (len < 6.0 && p.N < 5) by_columns(Count<4>{});
+    else if (len < 40.0) by_columns(Count<8>{});
+    else if (len < 200.0) by_columns(Count<16>{});
+    else by_columns(Count<64>{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "kernel launch");
+    return DA_OK;
+}
+
 // The heavy rows' part of a product whose other rows are on the stream already.  A block has 131 KB of LDS and 16
 // waves, one to a CU: as many ranges of columns as make one block per CU over all sets of rows and column tiles.
 // Lanes: 4 of two columns up to 8 columns (N = 8: 90 us, 16 lanes of one column 114), 16 beyond (N = 16, 1.6 M entries: 16 us,
@@ -826,6 +854,9 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
             return rest != DA_OK ? rest : launch_heavy(p, heavy.plan);
         }
     }
+    if (sd.rb == 1 && N <= 8L * kMaxGridY && (algo == DA_RB_RM_SR || algo == DA_RB_CM_SR || (algo == DA_RB_RM_PR && N >= 5)) &&
+        std::getenv("DA_SPMM_TUNE") == nullptr)
+        return launch_columns(p, lookup_matrix(rowptr, m));
     const bool ask = eb || (!cm && !pr && N > 16 && (N < 32 || N % 4 != 0 || ends % 16 != 0));   // RB: only where the lanes depend on it
     const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);

@@ -628,6 +628,68 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
+// RB on a column-major B (columns contiguous, rb = 1): L lanes share a row and take its entries in turn, each for the NC
+// columns of the tile; neighbouring lanes hold neighbouring rows.  A load then fetches one column of B for the entries of
+// 64 / L rows, which lie side by side in a banded or stencil matrix.  Lanes along N instead, as the row-major
+// kernels have them, fetch every element from a line of its own, and write C in 4-byte pieces where its columns
+// are contiguous, too.  What bounds it: the lines a load touches.  27-point stencil of 64^3, N = 8: 58 us with lanes along N,
+// 25 here (52 with the L lanes of a row side by side, 27 with every lane reading its own entries: a third of the
+// time), N = 16: 197 and 45; 12 random columns a row, N = 8: 43 and 43, N = 20: 206 and 102.
+// Sums: a lane adds n / L entries one after another, then the lanes' sums are added in a tree.
+// ------------------------------------------------------------------------------------------
+template <int L, int NC>
+__global__ __launch_bounds__(kBlock) void rb_columns_kernel(
+    int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
+    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C)
+{
+    constexpr int U = 4, R = kWave / L;                    // entries of a lane in flight, rows of a wave
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int j = lane / R;
+    const long row0 = ((long)blockIdx.x * kWavesPerBlock + wave) * R, row = row0 + lane % R;
+    const int n0 = blockIdx.y * NC, left = min(N - n0, NC);
+    // Entries are read by L neighbouring lanes to a row, in the order of memory, and change lanes once: the lane of
+    // row r and turn j receives the one that lane r * L + j read.
+    const int source = (lane % R) * L + j;
+    int start = 0, end = 0, from = 0, to = 0;
+    if (row < m) { start = rowptr[row]; end = rowptr[row + 1]; }
+    if (row0 + lane / L < m) { from = rowptr[row0 + lane / L] + lane % L; to = rowptr[row0 + lane / L + 1]; }
+    const float* __restrict__ Bn = B + (long)n0 * sd.cb;
+    float acc[NC];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) acc[n] = 0.f;
+    for (int p = start + j; __any(p < end); p += U * L, from += U * L) {
+        int c[U];
+        float a[U], b[U][NC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            c[u] = 0;
+            a[u] = 0.f;
+            if (from + u * L < to) { c[u] = colind[from + u * L]; a[u] = vals[from + u * L]; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) { c[u] = __shfl(c[u], source); a[u] = __shfl(a[u], source); }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n) b[u][n] = 0.f;
+            if (p + u * L < end) {                         // zeros otherwise: no product with what column 0 holds
+#pragma unroll
+                for (int n = 0; n < NC; ++n) if (n < left) b[u][n] = Bn[n * sd.cb + (unsigned)c[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int n = 0; n < NC; ++n) acc[n] = fmaf(a[u], b[u][n], acc[n]);
+    }
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        const float x = slot_allreduce<R>(acc[n]);
+        if (j == n % L && row < m && n < left) __builtin_nontemporal_store(x, C + row * sd.rc + (long)(n0 + n) * sd.cc);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // EB pre-pass.  EB workers own fixed-size chunks of consecutive stored entries (Sec. 3.2 design
 // M2).  A row whose entries all fall into one chunk is written by exactly one worker with a plain
 // store; a row that straddles a chunk boundary receives atomic additions from several workers and

@@ -1,0 +1,51 @@
+"""Column-major B under the RB ids (rb_columns_kernel): lanes per row by what is known of the matrix, column tiles, last
+rows, and values that must not leak from lanes without an entry.  Integer values: any order gives the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import reference as orc
+from paper_2202_08556_amd import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+MATRICES = {"short": lambda: gen.uniform_csr(m=1003, k=777, mean_len=3.0, seed=1),               # 4 lanes
+            "stencil": lambda: gen.stencil27_csr(nx=9, ny=7, nz=5, seed=2),                      # 8
+            "longer": lambda: gen.lognormal_csr(m=211, mean_len=90.0, cv=0.4, seed=3, k=900),    # 16
+            "uneven": lambda: gen.skewed_csr(m=700, heavy_frac=0.01, heavy_lo=300, heavy_hi=650, seed=4)}   # 64
+
+
+@pytest.mark.parametrize("name", MATRICES)
+@pytest.mark.parametrize("known", [False, True])
+@pytest.mark.parametrize("c_col", [False, True])
+def test_column_major_products(name, known, c_col):
+    from paper_2202_08556_amd import binding as da
+    a = gen.integer_twin(MATRICES[name](), seed=8)
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (a.rowptr, a.colind, a.vals)]
+    if known:
+        da.da_spmm_features(a.m, 8, dev[0])
+    for N in (1, 2, 3, 4, 5, 7, 8, 9, 16, 21):
+        ldb, ldc = a.k + 3, (a.m + 2 if c_col else N + 2)
+        B = np.full((N, ldb), np.nan, np.float32)
+        B[:, :a.k] = gen.dense_int(a.k, N, seed=N).T
+        want = orc.spmm(a.rowptr, a.colind, a.vals, np.ascontiguousarray(B[:, :a.k].T))[0].astype(np.float32) + 0.0
+        Bd = torch.from_numpy(B).cuda()
+        for algo in (da.DA_RB_RM_SR, da.DA_RB_CM_SR, da.DA_RB_RM_PR):
+            C = torch.full((N, ldc) if c_col else (a.m, ldc), -7.0, device="cuda")
+            da.da_spmm_ex(a.m, a.k, N, *dev, Bd, ldb, da.DA_COL_MAJOR, C, ldc, da.DA_COL_MAJOR if c_col else da.DA_ROW_MAJOR, algo)
+            got = C.cpu().numpy()
+            assert (got[:, a.m:] == -7.0).all() if c_col else (got[:, N:] == -7.0).all()
+            got = got[:, :a.m].T if c_col else got[:, :N]
+            assert np.array_equal(got, want), (N, algo)
+
+
+def test_infinities_stay_in_their_rows():
+    from paper_2202_08556_amd import binding as da
+    a = gen.integer_twin(gen.uniform_csr(m=500, k=400, mean_len=6.0, seed=9), seed=9)
+    B = gen.dense_int(a.k, 6, seed=1)
+    B[0], B[17] = np.inf, np.nan                      # column 0 is what lanes without an entry would read
+    want = orc.spmm(a.rowptr, a.colind, a.vals, B)[0].astype(np.float32) + 0.0
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (a.rowptr, a.colind, a.vals, B.T)]
+    C = torch.empty((6, a.m), device="cuda")
+    da.da_spmm_ex(a.m, a.k, 6, *dev, a.k, da.DA_COL_MAJOR, C, a.m, da.DA_COL_MAJOR, da.DA_RB_RM_SR)
+    assert np.isfinite(want).any() and np.array_equal(C.t().cpu().numpy(), want, equal_nan=True)
