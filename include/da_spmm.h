@@ -281,6 +281,12 @@ int da_spmm_column_sums(int64_t rows, int64_t n, const float *G, int64_t ldg, fl
 /* Z = Z + bias (fp32[n], may be NULL), then max(Z, 0) when relu != 0, in place; Z dense rows x n. */
 int da_spmm_bias_relu(int64_t rows, int64_t n, float *Z, const float *bias, int relu, void *stream);
 
+/* C = A . B + bias (fp32[N], may be NULL), then max(C, 0) when relu != 0: da_spmm_ex with row-major operands (ldb >= N,
+ * C dense m x N) and da_spmm_bias_relu in one call, with the same results and without a pass over C of its own where the
+ * product kernel can do it.  C may not overlap bias. */
+int da_spmm_layer(int64_t m, int64_t k, int64_t N, const int32_t *rowptr, const int32_t *colind, const float *vals,
+                  const float *B, int64_t ldb, float *C, const float *bias, int relu, int algo, void *stream);
+
 /*
  * C = A . W on the fp32 matrix cores: A fp32[rows x k] row-major (lda >= k), element (p, q) of W at
  * W[p*wk + q*wn] (wk = n, wn = 1 for a row-major k x n matrix; wk = 1, wn = k for the transpose of a row-major

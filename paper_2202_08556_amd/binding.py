@@ -29,7 +29,7 @@ DA_ROW_MAJOR, DA_COL_MAJOR = 0, 1
 EXPORTS = ("da_spmm", "da_spmm_ex", "da_spmm_select", "da_spmm_features", "da_csr_transpose_workspace",
            "da_csr_transpose", "da_csr_transpose_noalloc", "da_csr_validate", "da_spmm_prepare", "da_spmm_release",
            "da_eb_schedule_workspace", "da_eb_schedule", "da_spmm_weight_grad_workspace", "da_spmm_weight_grad", "da_spmm_column_sums_workspace",
-           "da_spmm_column_sums", "da_spmm_bias_relu", "da_spmm_dense", "da_spmm_dense_split_workspace",
+           "da_spmm_column_sums", "da_spmm_bias_relu", "da_spmm_layer", "da_spmm_dense", "da_spmm_dense_split_workspace",
            "da_spmm_dense_split",
            "da_spmm_algo_name", "da_spmm_last_error")
 
@@ -75,6 +75,8 @@ _lib.da_spmm_column_sums.argtypes = [_i64, _i64, _vp, _i64, _vp, _vp, ctypes.c_s
 _lib.da_spmm_column_sums.restype = ctypes.c_int
 _lib.da_spmm_bias_relu.argtypes = [_i64, _i64, _vp, _vp, ctypes.c_int, _vp]
 _lib.da_spmm_bias_relu.restype = ctypes.c_int
+_lib.da_spmm_layer.argtypes = [_i64, _i64, _i64, _vp, _vp, _vp, _vp, _i64, _vp, _vp, ctypes.c_int, ctypes.c_int, _vp]
+_lib.da_spmm_layer.restype = ctypes.c_int
 _lib.da_spmm_weight_grad.restype = ctypes.c_int
 _lib.da_spmm_dense.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _i64, _vp, _i64, _vp]
 _lib.da_spmm_dense.restype = ctypes.c_int
@@ -283,6 +285,12 @@ def da_spmm_column_sums(rows, n, G, ldg, sums, workspace, workspace_bytes, strea
 
 def da_spmm_bias_relu(rows, n, Z, bias, relu, stream=None) -> None:
     _check(int(_lib.da_spmm_bias_relu(int(rows), int(n), _ptr(Z), _ptr(bias), int(bool(relu)), _stream(stream))))
+
+
+def da_spmm_layer(m, k, N, rowptr, colind, vals, B, ldb, C, bias, relu, algo, stream=None) -> None:
+    """C = A.B + bias, then max(C, 0) if relu (B row-major with leading dimension ldb, C dense m x N)."""
+    _check(int(_lib.da_spmm_layer(int(m), int(k), int(N), _ptr(rowptr), _ptr(colind), _ptr(vals), _ptr(B), int(ldb), _ptr(C),
+                                  _ptr(bias), int(bool(relu)), int(algo), _stream(stream))))
 
 
 def da_spmm_dense(rows, k, n, A, lda, W, wk, wn, C, ldc, stream=None) -> None:

@@ -64,6 +64,8 @@ struct Problem {
     hipStream_t stream;
     int64_t k;
     LeftOut left_out;    // RB_SR: rows that heavy_rows_kernel sums
+    LayerSums* layer;    // what C takes besides the sums; null: nothing
+    bool* finished;      // set when the product's kernels have done that
 };
 
 enum Family { RB_SR, RB_PR, EB_SR, EB_PR };
@@ -365,21 +367,34 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         return dim3((unsigned)bx, tiles);
     };
     const dim3 block(kBlock);
+    // Bias and rectification in the product kernel: the lane groups of row-major products from 8 columns on.
+    constexpr bool kLayers = !WIDE && NV == 1 && G >= (V == 4 ? 4 : 8);
+    const bool layer = kLayers && p.layer != nullptr;
+    if (layer) *p.finished = true;
+    auto ended = [&](auto launch_with) {
+        if constexpr (kLayers)
+            if (layer) return launch_with(*p.layer);
+        launch_with(PlainSums{});
+    };
     switch (fam) {
     case RB_SR: {
         const long rows_per_block = (long)kWavesPerBlock * (kWave / G);
-        hipLaunchKernelGGL((rb_sr_kernel<V, G, NV, WIDE>), grid_for((p.m + rows_per_block - 1) / rows_per_block),
-                           block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin, p.left_out);
+        ended([&](auto after) {
+            hipLaunchKernelGGL((rb_sr_kernel<V, G, NV, WIDE, decltype(after)>), grid_for((p.m + rows_per_block - 1) / rows_per_block),
+                               block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin, p.left_out, after);
+        });
         break;
     }
     case RB_PR: {
         if constexpr (G <= kMaxGroupPR) {
-            auto go = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, grid_for((p.m + kWavesPerBlock - 1) / kWavesPerBlock),
-                                   block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin);
-            };
-            if (V == 4 && G >= 16 && p.N % 4 != 0) go(rb_pr_kernel<V, G, NV, WIDE, V == 4 && G >= 16>);
-            else go(rb_pr_kernel<V, G, NV, WIDE, false>);
+            ended([&](auto after) {
+                auto go = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, grid_for((p.m + kWavesPerBlock - 1) / kWavesPerBlock),
+                                       block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin, after);
+                };
+                if (V == 4 && G >= 16 && p.N % 4 != 0) go(rb_pr_kernel<V, G, NV, WIDE, V == 4 && G >= 16, decltype(after)>);
+                else go(rb_pr_kernel<V, G, NV, WIDE, false, decltype(after)>);
+            });
         }
         break;
     }
@@ -449,14 +464,19 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
             }
             if (!pin) blocks = (blocks + 7) / 8 * 8;       // block b stays on XCD b % 8 on every pass
         }
-        if (fam == EB_SR) {
-            hipLaunchKernelGGL((eb_sr_kernel<V, G, NV, WIDE>), grid_for(blocks), block, 0, p.stream,
-                               p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, chunk, pin, sch, own_short);
-        } else {
-            if constexpr (G <= kMaxGroupPR)
-                hipLaunchKernelGGL((eb_pr_kernel<V, G, NV, WIDE>), grid_for(blocks), block, 0, p.stream,
-                                   p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, chunk, pin, sch);
-        }
+        ended([&](auto after) {
+            if (fam == EB_SR) {
+                hipLaunchKernelGGL((eb_sr_kernel<V, G, NV, WIDE, decltype(after)>), grid_for(blocks), block, 0, p.stream,
+                                   p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, chunk, pin, sch, own_short, after);
+            } else {
+                if constexpr (G <= kMaxGroupPR)
+                    hipLaunchKernelGGL((eb_pr_kernel<V, G, NV, WIDE, decltype(after)>), grid_for(blocks), block, 0, p.stream,
+                                       p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, chunk, pin, sch, after);
+            }
+        });
+        if (layer)
+            hipLaunchKernelGGL((eb_finish_kernel<V>), zgrid, block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.C, chunk, own_short,
+                               *p.layer);
         break;
     }
     }
@@ -810,9 +830,14 @@ int da_csr_validate(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     return status;
 }
 
-int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_t* colind,
-               const float* vals, const float* B, int64_t ldb, int layout_b, float* C, int64_t ldc,
-               int layout_c, int algo, void* stream)
+}  // extern "C"
+
+namespace {
+
+// da_spmm_ex; with a layer also what C takes besides the sums, if *finished comes back true.
+int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_t* colind,
+            const float* vals, const float* B, int64_t ldb, int layout_b, float* C, int64_t ldc,
+            int layout_c, int algo, void* stream, LayerSums* layer, bool* finished)
 {
     if (m < 0 || k < 0 || N < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
     if (m > 0x7ffffffeLL || k > 0x7fffffffLL || N > 0x7fffffffLL)
@@ -836,7 +861,7 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     sd.cb = layout_b == DA_ROW_MAJOR ? 1 : ldb;
     sd.rc = layout_c == DA_ROW_MAJOR ? ldc : 1;
     sd.cc = layout_c == DA_ROW_MAJOR ? 1 : ldc;
-    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{nullptr, 0, 0}};
+    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{nullptr, 0, 0}, nullptr, nullptr};
     const bool eb = algo >= DA_EB_RM_SR;
     const bool cm = (algo & 2) != 0;
     const bool pr = (algo & 1) != 0;
@@ -854,6 +879,8 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
             return rest != DA_OK ? rest : launch_heavy(p, heavy.plan);
         }
     }
+    p.layer = layer;
+    p.finished = finished;
     if (sd.rb == 1 && N <= 8L * kMaxGridY && (algo == DA_RB_RM_SR || algo == DA_RB_CM_SR || (algo == DA_RB_RM_PR && N >= 5)) &&
         std::getenv("DA_SPMM_TUNE") == nullptr)
         return launch_columns(p, lookup_matrix(rowptr, m));
@@ -863,6 +890,28 @@ int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int
     if (st != DA_OK) return st;
     const Family fam = eb ? (pr ? EB_PR : EB_SR) : (pr ? RB_PR : RB_SR);
     return dispatch(fam, g, p);
+}
+
+}  // namespace
+
+extern "C" {
+
+int da_spmm_ex(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_t* colind,
+               const float* vals, const float* B, int64_t ldb, int layout_b, float* C, int64_t ldc,
+               int layout_c, int algo, void* stream)
+{
+    return product(m, k, N, rowptr, colind, vals, B, ldb, layout_b, C, ldc, layout_c, algo, stream, nullptr, nullptr);
+}
+
+int da_spmm_layer(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_t* colind, const float* vals,
+                  const float* B, int64_t ldb, float* C, const float* bias, int relu, int algo, void* stream)
+{
+    LayerSums after{bias, relu};
+    const bool sums_only = bias == nullptr && relu == 0;
+    bool finished = sums_only;
+    const int st = product(m, k, N, rowptr, colind, vals, B, ldb, DA_ROW_MAJOR, C, N, DA_ROW_MAJOR, algo, stream,
+                           sums_only ? nullptr : &after, &finished);
+    return st != DA_OK || finished ? st : da_spmm_bias_relu(m, N, C, bias, relu, stream);
 }
 
 int da_spmm(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_t* colind,

@@ -184,10 +184,48 @@ struct Acc {
 #pragma unroll
             for (int v = 0; v < V; ++v) a[i][v] += b.a[i][v];
     }
+    // b = bias of the column that vector 0 would begin at (in memory or LDS), or null
+    template <class END> __device__ __forceinline__ void finish(const END& after, const float* b, const C& c) {
+        static_assert(NV == 1, "one vector per lane");
+#pragma unroll
+        for (int v = 0; v < V; ++v) a[0][v] = after(a[0][v], b != nullptr ? b[v] : 0.f);
+    }
     __device__ __forceinline__ void emit(float* __restrict__ p, const C& c, bool atomic, long cs) const {
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             if (i < c.nvec) emit_vec<V>(p + (V == 1 ? c.offset(i) * cs : c.offset(i)), a[i], atomic, c.skip(i));
+    }
+};
+
+// What happens to a sum on its way to C: nothing, or a layer's bias (may be null) and rectification.  In the
+// product kernel this costs the rows that one worker owns no memory traffic; a pass over C of its own reads and writes
+// all of it once more (two layers on 262 144 nodes, 602 -> 128 -> 41: 982 us with such passes, 924 without; gradients of
+// a layer 96 -> 64 on 100 003 nodes: 294 and 286).  Rows that several workers add to get theirs from
+// eb_finish_kernel after the product.
+struct PlainSums { static constexpr bool layer = false; };
+struct LayerSums {
+    static constexpr bool layer = true;
+    const float* bias;
+    int relu;
+    __device__ __forceinline__ float operator()(float x, float b) const {
+        x += b;
+        return relu ? (x > 0.f || x != x ? x : 0.f) : x;   // NaN stays NaN
+    }
+};
+
+// EB: the bias of the tile's columns waits in LDS, four columns to the left of the tile included (Cols::shift).  A load
+// from memory at a row's end would wait for the stores before it.
+template <class END, int TILE>
+struct TileBias {
+    static constexpr int kSize = END::layer ? TILE + 4 : 1;
+    __device__ static __forceinline__ void fill(float* lds, const END& after, int tile0, int N) {
+        if constexpr (END::layer) {
+            for (int i = threadIdx.x; i < kSize; i += kBlock) {
+                const int n = tile0 - 4 + i;
+                lds[i] = after.bias != nullptr && n >= 0 && n < N ? after.bias[n] : 0.f;
+            }
+            __syncthreads();
+        }
     }
 };
 
@@ -456,10 +494,11 @@ struct LeftOut {
 // entries with coalesced requests and pass them round through LDS, so that every entry is fetched
 // once and reused for all columns of the tile (the sparse-element cache of Sec. 4).
 // ------------------------------------------------------------------------------------------
-template <int V, int G, int NV, bool WIDE>
+template <int V, int G, int NV, bool WIDE, class END>
 __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
-    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles, LeftOut out)
+    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles, LeftOut out,
+    END after)
 {
     constexpr int RPW = kWave / G;                       // rows per wave
     constexpr int SB = StageBatch<G>::value;
@@ -518,6 +557,8 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
             wave_lds_sync();
         }
     }
+    if constexpr (END::layer)
+        if (row < m && nvec > 0) acc.finish(after, after.bias ? after.bias + n0 : nullptr, cols);
     if (row < m && nvec > 0) acc.emit(C + row * sd.rc + (long)n0 * sd.cc, cols, false, sd.cc);
 }
 
@@ -534,10 +575,10 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
 // 45 -> 54 us; multiples of four keep one addition an entry (GROUPED = false; rows of 1000, N = 36: 46 us, 49 with
 // groups, and as many with the choice made at run time).
 // ------------------------------------------------------------------------------------------
-template <int V, int G, int NV, bool WIDE, bool GROUPED>
+template <int V, int G, int NV, bool WIDE, bool GROUPED, class END>
 __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
-    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles)
+    const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int pin_tiles, END after)
 {
     constexpr int S = kWave / G;
     constexpr int UL = G == 1 ? (NV > 2 ? 2 : 4) : (G < kU ? G : kU);
@@ -624,6 +665,8 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
     for (int i = 0; i < NV; ++i)
 #pragma unroll
         for (int v = 0; v < V; ++v) acc.a[i][v] = slot_allreduce<G>(acc.a[i][v]);
+    if constexpr (END::layer)
+        if (s == 0 && nvec > 0) acc.finish(after, after.bias ? after.bias + n0 : nullptr, cols);
     if (s == 0 && nvec > 0) acc.emit(C + row * sd.rc + (long)n0 * sd.cc, cols, false, sd.cc);
 }
 
@@ -698,11 +741,12 @@ __global__ __launch_bounds__(kBlock) void rb_columns_kernel(
 // worker of the product kernel that follows.  own_short: that kernel gives every row of at most
 // `chunk` entries to a single worker (see eb_sr_kernel), so only longer rows are shared.  A wave inspects 64 rows (one per lane) and then
 // clears the flagged ones together: one row at a time with full-width stores when a row takes
-// more than 32 stores, several rows per store instruction otherwise.
+// more than 32 stores, several rows per store instruction otherwise.  eb_finish_kernel takes the same
+// rows after the product, which has given all others their bias and rectification (LayerSums).
 // ------------------------------------------------------------------------------------------
-template <int V>
-__global__ __launch_bounds__(kBlock) void eb_zero_kernel(
-    int m, int N, Strides sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short)
+template <int V, class END>
+__device__ __forceinline__ void for_split_rows(
+    int m, int N, const Strides& sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short, const END& after)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long base = ((long)blockIdx.x * kWavesPerBlock + wave) * kWave;
@@ -714,16 +758,32 @@ __global__ __launch_bounds__(kBlock) void eb_zero_kernel(
         need = (end == start) || (start / chunk != (end - 1) / chunk && (!own_short || end - start > chunk));
     }
     unsigned long long mask = __ballot(need);
-    float z[V];
+    auto put = [&](float* __restrict__ crow, int n0) {
+        if constexpr (!END::layer) {
+            float z[V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) z[v] = 0.f;
+            for (int v = 0; v < V; ++v) z[v] = 0.f;
+            store_vec<V>(crow + (long)min(n0, N - V) * sd.cc, z);
+        } else if (n0 + V <= N) {
+            float x[V];
+            load_vec<V>(crow + (long)n0 * sd.cc, x);
+#pragma unroll
+            for (int v = 0; v < V; ++v) x[v] = after(x[v], after.bias ? after.bias[n0 + v] : 0.f);
+            store_vec<V>(crow + (long)n0 * sd.cc, x);
+        } else {                                          // every element once
+            for (int n = n0; n < N; ++n) {
+                float* c = crow + (long)n * sd.cc;
+                *c = after(*c, after.bias ? after.bias[n] : 0.f);
+            }
+        }
+    };
     const int vecs = (N + V - 1) / V;                     // stores per row
     if (vecs > kWave / 2) {
         while (mask) {
             const int r = __ffsll((long long)mask) - 1;
             mask &= mask - 1;
             float* __restrict__ crow = C + (base + r) * sd.rc;
-            for (int n0 = lane * V; n0 < N; n0 += kWave * V) store_vec<V>(crow + (long)min(n0, N - V) * sd.cc, z);
+            for (int n0 = lane * V; n0 < N; n0 += kWave * V) put(crow, n0);
         }
     } else {
         // short rows of C: T lanes per row, 64/T flagged rows per store instruction.  The flagged
@@ -737,9 +797,23 @@ __global__ __launch_bounds__(kBlock) void eb_zero_kernel(
         const int n0 = (lane & (T - 1)) * V;
         for (int s = lane / T; s < count; s += kWave / T) {
             const int r = listed[wave][s];
-            if (n0 < N) store_vec<V>(C + (base + r) * sd.rc + (long)min(n0, N - V) * sd.cc, z);
+            if (n0 < N) put(C + (base + r) * sd.rc, n0);
         }
     }
+}
+
+template <int V>
+__global__ __launch_bounds__(kBlock) void eb_zero_kernel(
+    int m, int N, Strides sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short)
+{
+    for_split_rows<V>(m, N, sd, rowptr, C, chunk, own_short, PlainSums{});
+}
+
+template <int V>
+__global__ __launch_bounds__(kBlock) void eb_finish_kernel(
+    int m, int N, Strides sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short, LayerSums after)
+{
+    for_split_rows<V>(m, N, sd, rowptr, C, chunk, own_short, after);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -761,17 +835,19 @@ template <int G> constexpr bool kOwnShortRows = G >= 16;
 // Bound for 6 waves per SIMD: groups of 8 lanes with 16-byte vectors would take registers for 5 and spill 2 instead
 // (4 with wide addresses); with 5 waves the power-law graph takes 113 us at N = 32 instead of 111, but rows of 1000
 // entries 36.5 instead of 38.4.  No other instantiation spills.
-template <int V, int G, int NV, bool WIDE>
+template <int V, int G, int NV, bool WIDE, class END>
 __global__ __launch_bounds__(kBlock, 6) void eb_sr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
     const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int chunk,
-    int pin_tiles, Schedule sch, int own_short)
+    int pin_tiles, Schedule sch, int own_short, END after)
 {
     constexpr int GPW = kWave / G;                        // workers per wave
     constexpr int SB = StageBatch<G>::value;
     constexpr int UL = G == 1 ? kU / NV : kU;             // entries whose gathers are issued together
     __shared__ int2 stage[G > 1 ? kWavesPerBlock * GPW * SB : 1];
     __shared__ float turns[V == 4 && G >= 4 ? kBlock * V : 1];
+    typedef TileBias<END, G * V * NV> Bias;
+    __shared__ float bias[Bias::kSize];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane / G, j = lane % G;
     const BlockMap bm = block_map(pin_tiles);
@@ -780,6 +856,12 @@ __global__ __launch_bounds__(kBlock, 6) void eb_sr_kernel(
     const BRows<WIDE> brow(B, n0, sd);
     const int tile0 = bm.tile * G * V * NV;                // first column of the tile
     float* __restrict__ Ct = C + (long)tile0 * sd.cc;
+    Bias::fill(bias, after, tile0, N);
+    // a row that this worker alone owns
+    auto put_row = [&](long row, Acc<V, G, NV> x) {
+        if constexpr (END::layer) x.finish(after, bias + 4 + (n0 - tile0), cols);
+        x.emit(Ct + row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+    };
     float* turn = turns + (V == 4 && G >= 4 ? (wave * GPW + g) * G * V : 0);
     const int nnz = rowptr[m];
     int2* st = stage + (G > 1 ? (wave * GPW + g) * SB : 0);
@@ -891,7 +973,7 @@ __global__ __launch_bounds__(kBlock, 6) void eb_sr_kernel(
                         const int next = q0 + t + u + 1;
                         if (next == row_end) {                 // the row is complete
                             if (shared_with_prev) add_row(Ct + (long)row * sd.rc, acc, cols, j, N - tile0, sd.cc, turn);
-                            else if (nvec > 0) acc.emit(Ct + (long)row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                            else if (nvec > 0) put_row(row, acc);
                             acc.clear();
                             shared_with_prev = false;
                             if (next < hi) {
@@ -959,17 +1041,19 @@ __device__ __forceinline__ int wave_inclusive_scan_dpp(int v) {
 
 constexpr int kStagedChunk = 512;   // EB+PR: largest chunk whose row starts are staged in LDS
 
-template <int V, int G, int NV, bool WIDE>
+template <int V, int G, int NV, bool WIDE, class END>
 __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
     const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int chunk,
-    int pin_tiles, Schedule sch)
+    int pin_tiles, Schedule sch, END after)
 {
     constexpr int S = kWave / G;
     constexpr int UU = G < 4 ? G : 4;                     // steps whose gathers are issued together (8 measured slower)
     __shared__ int4 stage[G > 1 ? kBlock : 1];
     __shared__ int starts[kWavesPerBlock][kStagedChunk + 2];
     __shared__ float turns[V == 4 && G >= 4 ? kBlock * V : 1];
+    typedef TileBias<END, G * V * NV> Bias;
+    __shared__ float bias[Bias::kSize];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int s = lane / G, j = lane % G;
     const BlockMap bm = block_map(pin_tiles);
@@ -978,6 +1062,12 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
     const BRows<WIDE> brow(B, n0, sd);
     const int tile0 = bm.tile * G * V * NV;                // first column of the tile
     float* __restrict__ Ct = C + (long)tile0 * sd.cc;
+    Bias::fill(bias, after, tile0, N);
+    // a row that this worker alone owns
+    auto put_row = [&](long row, Acc<V, G, NV> x) {
+        if constexpr (END::layer) x.finish(after, bias + 4 + (n0 - tile0), cols);
+        x.emit(Ct + row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+    };
     float* turn = turns + (V == 4 && G >= 4 ? (wave * kWave + s * G) * V : 0);
     const int nnz = rowptr[m];
     int4* st = stage + (G > 1 ? wave * kWave : 0);
@@ -1118,7 +1208,7 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                             const Acc<V, G, NV> total = slots_allreduce<V, G, NV>(acc);
                             if (s == 0) {
                                 if (!cur_started) add_row(Ct + (long)cur * sd.rc, total, cols, j, N - tile0, sd.cc, turn);
-                                else if (nvec > 0) total.emit(Ct + (long)cur * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                                else if (nvec > 0) put_row(cur, total);
                             }
                             acc.clear();
                             cur = -1;
@@ -1154,7 +1244,7 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                         const bool in_last_run = evalid && er == last_row;
                         if (head && evalid && (!in_last_run || last_ended)) {
                             if (!started) add_row(Ct + (long)er * sd.rc, x, cols, j, N - tile0, sd.cc, turn);
-                            else if (nvec > 0) x.emit(Ct + (long)er * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                            else if (nvec > 0) put_row(er, x);
                         }
                         if (last_ended) {
                             acc.clear();

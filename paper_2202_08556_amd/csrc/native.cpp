@@ -387,8 +387,9 @@ struct Graph : std::enable_shared_from_this<Graph> {
     // a . X for X with unit column stride, a = this graph's arrays.  The matrix is prepared (chunk order of the EB
     // algorithms) before the second product with an EB algorithm that the selector chose, and before the first one
     // the caller chose, unless the stream is being captured: preparing allocates and waits, and its orders only
-    // cost speed where they are missing.
-    Tensor product(const Arrays& a, const Tensor& X, int64_t N, std::optional<int> given = std::nullopt) {
+    // cost speed where they are missing.  bias, relu: what a layer does to the sums.
+    Tensor product(const Arrays& a, const Tensor& X, int64_t N, std::optional<int> given = std::nullopt,
+                   const Tensor& bias = Tensor(), bool relu = false) {
         c10::DeviceGuard guard(a.rowptr.device());
         const int id = given ? *given : algo_for(N);
         if (id >= DA_EB_RM_SR && !prepared && !capturing(a.rowptr)) {
@@ -397,8 +398,8 @@ struct Graph : std::enable_shared_from_this<Graph> {
             ++eb_products;
         }
         Tensor C = at::empty({a.m, N}, a.vals.options());
-        check(da_spmm_ex(a.m, a.k, N, data<int32_t>(a.rowptr), data<int32_t>(a.colind), data<float>(a.vals), data<float>(X),
-                         leading(X), DA_ROW_MAJOR, data<float>(C), N, DA_ROW_MAJOR, id, stream_of(a.rowptr)));
+        check(da_spmm_layer(a.m, a.k, N, data<int32_t>(a.rowptr), data<int32_t>(a.colind), data<float>(a.vals), data<float>(X),
+                            leading(X), data<float>(C), data<float>(bias), relu ? 1 : 0, id, stream_of(a.rowptr)));
         return C;
     }
 };
@@ -608,8 +609,7 @@ Tensor graph_conv(const GraphPtr& g, const Tensor& X, const Tensor& W, const std
         c10::DeviceGuard guard(a->rowptr.device());
         Tensor H = at::empty({X.size(0), row_pitch(n)}, X.options()).narrow(1, 0, n);
         dense_product(X, W, false, H);
-        Z = g->product(*a, H, n);
-        check(da_spmm_bias_relu(a->m, n, data<float>(Z), data<float>(b), relu ? 1 : 0, stream_of(Z)));
+        Z = g->product(*a, H, n, std::nullopt, b, relu);
     }
     if (at::GradMode::is_enabled() && (wants_grad(X) || wants_grad(W) || wants_grad(b))) {
         auto node = std::shared_ptr<GraphConvBackward>(new GraphConvBackward(), torch::autograd::deleteNode);
