@@ -360,7 +360,14 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     const long tiles_l = (p.N + tile_cols - 1) / tile_cols;
     if (tiles_l > kMaxGridY) return fail(DA_ERR_UNSUPPORTED, "N needs more than 65535 column tiles%s");
     const unsigned tiles = (unsigned)tiles_l;
-    const int pin = (geo.pin && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
+    // RB with 2, 4 or 8 about equal tiles: each tile on XCDs of its own, whose L2s then hold its slice of B alone.  It pays
+    // while a good part of the slice fits the 4 MB of an L2 and all of B does not (RB+RM+PR, random columns, 23 entries a
+    // row, k = 12 000: N = 128 13.3 -> 10.9 us, N = 256 23.3 -> 19.2; 24 000: 26.3 -> 23.2 and 47.9 -> 42.4; 40 000, slices of 10 MB:
+    // 49.6 -> 48.0 and 94.8 -> 92.9; 61 417, 15.7 MB: 105 and 101, with 100 entries a row 328 and 334.  RB+RM+SR, N = 256:
+    // 5000 11.3 -> 9.3, 24 000 62.2 -> 60.9, 27-point stencil of 28^3 28.6 -> 24.2.  4096 columns, N = 256, 4.2 MB: 6.1 and 6.2).
+    const bool slices_fit = V == 4 && G >= 16 && (fam == RB_SR || fam == RB_PR) && p.sd.cb == 1 &&
+                            tiles_l * tile_cols - p.N <= tile_cols / 8 && p.k * tile_cols * 4 <= 12 << 20 && (long)p.k * p.N * 4 > 9 << 19;
+    const int pin = ((geo.pin || slices_fit) && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
     // grid for `bx` blocks per column tile
     auto grid_for = [&](long bx) {
         if (pin) { const long per = 8 / pin; return dim3((unsigned)(8 * ((bx + per - 1) / per)), 1); }
