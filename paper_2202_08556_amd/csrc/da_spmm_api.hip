@@ -140,6 +140,7 @@ struct Plan {
     int first_units[kPlans] = {};   // chunks of the first schedule segment (multi-row chunks)
     std::shared_ptr<DeviceBlock> block;
     HeavyPlan heavy{};                   // count > 0: rows that heavy_rows_kernel takes from EB+RM+SR
+    int64_t heavy_k = 0;                 // columns that the cells of `heavy` cover
     const unsigned* heavy_bits = nullptr;
     double rest_len = 0.0;               // length of the row that an average entry of the other rows lies in
     std::shared_ptr<DeviceBlock> heavy_block;
@@ -186,13 +187,14 @@ bool is_capturing(hipStream_t s) {
     return cap == hipStreamCaptureStatusActive;
 }
 
-// The heavy rows of a prepared matrix; references and captures as for lookup_schedule.
+// The heavy rows of a prepared matrix; references and captures as for lookup_schedule.  The kernel reads every row of B
+// that the cells cover, used or not: products that declare other columns than da_spmm_prepare did go without.
 struct HeavyLookup { HeavyPlan plan{}; const unsigned* bits = nullptr; double rest_len = 0.0; std::shared_ptr<DeviceBlock> keep; };
-HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, hipStream_t stream) {
+HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, int64_t k, hipStream_t stream) {
     HeavyLookup out;
     std::lock_guard<std::mutex> lk(g_plan_mu);
     for (auto& pl : g_plans)
-        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m && pl.heavy.count > 0) {
+        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m && pl.heavy.count > 0 && pl.heavy_k == k) {
             out.plan = pl.heavy;
             out.bits = pl.heavy_bits;
             out.rest_len = pl.rest_len;
@@ -876,7 +878,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
     if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
         // heavy rows in a kernel of their own, the others, which are short and even, row by row
-        const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, p.stream);
+        const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
         if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows)) {
             const int st = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
                                          PlanInfo{false, 0.0}, &g);
@@ -1345,6 +1347,7 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     if (e != hipSuccess) return hip_fail(e, "da_spmm_prepare");
     if (host.unsorted) return DA_OK;
     pl->heavy = HeavyPlan{drows, at, (int)n, cells, cell, min_len, (int)nnz, (int)(entries / (int64_t)n)};
+    pl->heavy_k = k;
     pl->heavy_bits = bits;
     pl->rest_len = rest_len;
     pl->heavy_block = block;

@@ -116,6 +116,23 @@ def test_plans_of_another_matrix(change, N):
     assert np.array_equal(got, want.astype(np.float32) + 0.0)
 
 
+# the kernel would read every row of B that its plan covers: B ends at the columns that the product declares
+@pytest.mark.parametrize("declared", [K + 9000, K + 1, K - 1])
+@pytest.mark.parametrize("N", [8, 64])
+def test_products_that_declare_other_columns_than_prepare(declared, N):
+    from paper_2202_08556_amd import binding as da
+    rowptr, colind, vals = matrix(15)
+    dev = [torch.from_numpy(x).cuda() for x in (rowptr, np.minimum(colind, declared - 1), vals)]
+    print("prepared for", declared, "columns, N", N, flush=True)
+    da.da_spmm_prepare(M, declared, colind.size, dev[0], dev[1])
+    dev[1].copy_(torch.from_numpy(colind))
+    B = dense(N)
+    want, _ = orc.spmm(rowptr, colind, vals, B)
+    got = product(dev, torch.from_numpy(B).cuda(), N)
+    da.da_spmm_release(dev[0])
+    assert np.array_equal(got, want.astype(np.float32) + 0.0)
+
+
 def test_unsorted_columns_have_no_plan_and_stay_right():
     from paper_2202_08556_amd import binding as da
     rowptr, colind, vals = matrix(11)
