@@ -693,14 +693,14 @@ __global__ __launch_bounds__(kBlock) void rb_columns_kernel(
     // Entries are read by L neighbouring lanes to a row, in the order of memory, and change lanes once: the lane of
     // row r and turn j receives the one that lane r * L + j read.
     const int source = (lane % R) * L + j;
-    int start = 0, end = 0, from = 0, to = 0;
+    unsigned start = 0, end = 0, from = 0, to = 0;        // the last steps pass 2^31 where nnz is next to it
     if (row < m) { start = rowptr[row]; end = rowptr[row + 1]; }
     if (row0 + lane / L < m) { from = rowptr[row0 + lane / L] + lane % L; to = rowptr[row0 + lane / L + 1]; }
     const float* __restrict__ Bn = B + (long)n0 * sd.cb;
     float acc[NC];
 #pragma unroll
     for (int n = 0; n < NC; ++n) acc[n] = 0.f;
-    for (int p = start + j; __any(p < end); p += U * L, from += U * L) {
+    for (unsigned p = start + j; __any(p < end); p += U * L, from += U * L) {
         int c[U];
         float a[U], b[U][NC];
 #pragma unroll
