@@ -438,9 +438,12 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         // the second boundary look-up cheap); the zero pass and the product kernel are told alike
         const int own_short = (fam == EB_SR && kOwnShortRows<G> && sch.order != nullptr &&
                                env_int("DA_SPMM_SPLIT_SHORT_ROWS", 0) == 0) ? 1 : 0;
-        // pre-pass: zero the rows that receive atomic additions, and the rows without entries
+        // pre-pass: the rows that receive atomic additions, and the rows without entries
         const dim3 zgrid((unsigned)((p.m + kBlock - 1) / kBlock));
-        hipLaunchKernelGGL((eb_zero_kernel<V>), zgrid, block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.C, chunk, own_short);
+        ended([&](auto after) {
+            hipLaunchKernelGGL((eb_zero_kernel<V, decltype(after)>), zgrid, block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.C, chunk,
+                               own_short, after);
+        });
         const int first_chunks = sch.split;
         sch.split = 0;
         if (sch.order && geo.stripe > 0) {

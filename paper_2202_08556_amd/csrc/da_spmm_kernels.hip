@@ -741,49 +741,34 @@ __global__ __launch_bounds__(kBlock) void rb_columns_kernel(
 // worker of the product kernel that follows.  own_short: that kernel gives every row of at most
 // `chunk` entries to a single worker (see eb_sr_kernel), so only longer rows are shared.  A wave inspects 64 rows (one per lane) and then
 // clears the flagged ones together: one row at a time with full-width stores when a row takes
-// more than 32 stores, several rows per store instruction otherwise.  eb_finish_kernel takes the same
-// rows after the product, which has given all others their bias and rectification (LayerSums).
+// more than 32 stores, several rows per store instruction otherwise.
+// A layer (LayerSums): rows without entries get what bias and rectification make of zero at once, the product kernel finishes
+// the rows of one worker, and eb_finish_kernel after it those that several workers add to.  Reading rows without entries
+// again after the product costs more than it looks, since loads wait where stores do not (150 000 rows, 3000 of them
+// stored, 40 -> 32 -> 37: 102 us, 76 as here; 86 with a pass over all of C).
 // ------------------------------------------------------------------------------------------
-template <int V, class END>
-__device__ __forceinline__ void for_split_rows(
-    int m, int N, const Strides& sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short, const END& after)
-{
+struct EbRow { bool empty, split; };
+__device__ __forceinline__ EbRow eb_row(int m, long row, const int* __restrict__ rowptr, int chunk, int own_short) {
+    if (row >= m) return EbRow{false, false};
+    const int start = rowptr[row], end = rowptr[row + 1];
+    return EbRow{end == start, end != start && start / chunk != (end - 1) / chunk && (!own_short || end - start > chunk)};
+}
+
+// The flagged ones of the wave's 64 rows: what `rows` reads of up to U pieces of V columns, then what it writes.
+template <int V, int U, class ROWS>
+__device__ __forceinline__ void for_flagged_rows(long base, int N, bool flagged, ROWS rows) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long base = ((long)blockIdx.x * kWavesPerBlock + wave) * kWave;
-    if (base >= m) return;
-    const long row = base + lane;
-    bool need = false;
-    if (row < m) {
-        const int start = rowptr[row], end = rowptr[row + 1];
-        need = (end == start) || (start / chunk != (end - 1) / chunk && (!own_short || end - start > chunk));
-    }
-    unsigned long long mask = __ballot(need);
-    auto put = [&](float* __restrict__ crow, int n0) {
-        if constexpr (!END::layer) {
-            float z[V];
-#pragma unroll
-            for (int v = 0; v < V; ++v) z[v] = 0.f;
-            store_vec<V>(crow + (long)min(n0, N - V) * sd.cc, z);
-        } else if (n0 + V <= N) {
-            float x[V];
-            load_vec<V>(crow + (long)n0 * sd.cc, x);
-#pragma unroll
-            for (int v = 0; v < V; ++v) x[v] = after(x[v], after.bias ? after.bias[n0 + v] : 0.f);
-            store_vec<V>(crow + (long)n0 * sd.cc, x);
-        } else {                                          // every element once
-            for (int n = n0; n < N; ++n) {
-                float* c = crow + (long)n * sd.cc;
-                *c = after(*c, after.bias ? after.bias[n] : 0.f);
-            }
-        }
-    };
+    unsigned long long mask = __ballot(flagged);
+    if (mask == 0) return;
     const int vecs = (N + V - 1) / V;                     // stores per row
     if (vecs > kWave / 2) {
-        while (mask) {
-            const int r = __ffsll((long long)mask) - 1;
-            mask &= mask - 1;
-            float* __restrict__ crow = C + (base + r) * sd.rc;
-            for (int n0 = lane * V; n0 < N; n0 += kWave * V) put(crow, n0);
+        for (int n0 = lane * V; n0 < N; n0 += kWave * V) {
+            rows.columns(n0);
+            for (unsigned long long left = mask; left; left &= left - 1) {
+                const long row = base + __ffsll((long long)left) - 1;
+                rows.read(row, 0);
+                rows.write(row, 0);
+            }
         }
     } else {
         // short rows of C: T lanes per row, 64/T flagged rows per store instruction.  The flagged
@@ -791,29 +776,92 @@ __device__ __forceinline__ void for_split_rows(
         // s, s + 64/T, ...
         __shared__ unsigned char listed[kWavesPerBlock][kWave];
         const int count = __popcll(mask);
-        if (need) listed[wave][__popcll(mask & ((1ull << lane) - 1ull))] = (unsigned char)lane;
+        if (flagged) listed[wave][__popcll(mask & ((1ull << lane) - 1ull))] = (unsigned char)lane;
         wave_lds_sync();
         const int T = vecs <= 1 ? 1 : 1 << (32 - __clz(vecs - 1));   // power of two >= vecs, <= 32
         const int n0 = (lane & (T - 1)) * V;
-        for (int s = lane / T; s < count; s += kWave / T) {
-            const int r = listed[wave][s];
-            if (n0 < N) put(C + (base + r) * sd.rc, n0);
+        if (n0 >= N) return;
+        rows.columns(n0);
+        for (int s = lane / T; s < count; s += kWave / T * U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (s + kWave / T * u < count) rows.read(base + listed[wave][s + kWave / T * u], u);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (s + kWave / T * u < count) rows.write(base + listed[wave][s + kWave / T * u], u);
         }
     }
 }
 
-template <int V>
+// Rows of C that become zero, or what a layer makes of zero.
+template <int V, class END>
+struct FillRows {
+    int N;
+    const Strides& sd;
+    float* C;
+    END after;
+    float* at;
+    float z[V];
+    __device__ __forceinline__ void columns(int n0) {
+        const int n = min(n0, N - V);
+        at = C + (long)n * sd.cc;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            z[v] = 0.f;
+            if constexpr (END::layer) z[v] = after(0.f, after.bias ? after.bias[n + v] : 0.f);
+        }
+    }
+    __device__ __forceinline__ void read(long, int) {}
+    __device__ __forceinline__ void write(long row, int) { store_vec<V>(at + row * sd.rc, z); }
+};
+
+template <int V, class END>
 __global__ __launch_bounds__(kBlock) void eb_zero_kernel(
-    int m, int N, Strides sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short)
+    int m, int N, Strides sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short, END after)
 {
-    for_split_rows<V>(m, N, sd, rowptr, C, chunk, own_short, PlainSums{});
+    const long base = ((long)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * kWave;
+    if (base >= m) return;
+    const EbRow r = eb_row(m, base + (threadIdx.x & 63), rowptr, chunk, own_short);
+    if constexpr (END::layer) for_flagged_rows<V, 1>(base, N, r.empty, FillRows<V, END>{N, sd, C, after});
+    for_flagged_rows<V, 1>(base, N, r.split || (!END::layer && r.empty), FillRows<V, PlainSums>{N, sd, C, PlainSums{}});
 }
+
+// Bias and rectification of rows that are complete.  Where N is no multiple of V the last lane of a row begins
+// left of its columns and writes its own ones only, so that every element is finished once.
+template <int V, int U>
+struct FinishRows {
+    int N;
+    const Strides& sd;
+    float* C;
+    LayerSums after;
+    float* at;
+    int skip;
+    float b[V], x[U][V];
+    __device__ __forceinline__ void columns(int n0) {
+        const int n = min(n0, N - V);
+        at = C + (long)n * sd.cc;
+        skip = n0 - n;
+#pragma unroll
+        for (int v = 0; v < V; ++v) b[v] = after.bias ? after.bias[n + v] : 0.f;
+    }
+    __device__ __forceinline__ void read(long row, int u) { load_vec<V>(at + row * sd.rc, x[u]); }
+    __device__ __forceinline__ void write(long row, int u) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) x[u][v] = after(x[u][v], b[v]);
+        if (skip == 0) return store_vec<V>(at + row * sd.rc, x[u]);
+#pragma unroll
+        for (int v = 0; v < V; ++v) if (v >= skip) at[row * sd.rc + v * sd.cc] = x[u][v];
+    }
+};
 
 template <int V>
 __global__ __launch_bounds__(kBlock) void eb_finish_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, float* __restrict__ C, int chunk, int own_short, LayerSums after)
 {
-    for_split_rows<V>(m, N, sd, rowptr, C, chunk, own_short, after);
+    const long base = ((long)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * kWave;
+    if (base >= m) return;
+    const bool split = eb_row(m, base + (threadIdx.x & 63), rowptr, chunk, own_short).split;
+    for_flagged_rows<V, 4>(base, N, split, FinishRows<V, 4>{N, sd, C, after});
 }
 
 // ------------------------------------------------------------------------------------------
@@ -857,7 +905,7 @@ __global__ __launch_bounds__(kBlock, 6) void eb_sr_kernel(
     const int tile0 = bm.tile * G * V * NV;                // first column of the tile
     float* __restrict__ Ct = C + (long)tile0 * sd.cc;
     Bias::fill(bias, after, tile0, N);
-    // a row that this worker alone owns
+    // a layer's row that this worker alone owns (sums without one keep to emit: through here, power-law graph, N = 32, 134 us for 131)
     auto put_row = [&](long row, Acc<V, G, NV> x) {
         if constexpr (END::layer) x.finish(after, bias + 4 + (n0 - tile0), cols);
         x.emit(Ct + row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
@@ -973,7 +1021,10 @@ __global__ __launch_bounds__(kBlock, 6) void eb_sr_kernel(
                         const int next = q0 + t + u + 1;
                         if (next == row_end) {                 // the row is complete
                             if (shared_with_prev) add_row(Ct + (long)row * sd.rc, acc, cols, j, N - tile0, sd.cc, turn);
-                            else if (nvec > 0) put_row(row, acc);
+                            else if (nvec > 0) {
+                                if constexpr (END::layer) put_row(row, acc);
+                                else acc.emit(Ct + (long)row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                            }
                             acc.clear();
                             shared_with_prev = false;
                             if (next < hi) {
@@ -1063,7 +1114,7 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
     const int tile0 = bm.tile * G * V * NV;                // first column of the tile
     float* __restrict__ Ct = C + (long)tile0 * sd.cc;
     Bias::fill(bias, after, tile0, N);
-    // a row that this worker alone owns
+    // a layer's row that this worker alone owns (sums without one keep to emit: through here, power-law graph, N = 32, 134 us for 131)
     auto put_row = [&](long row, Acc<V, G, NV> x) {
         if constexpr (END::layer) x.finish(after, bias + 4 + (n0 - tile0), cols);
         x.emit(Ct + row * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
@@ -1208,7 +1259,10 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                             const Acc<V, G, NV> total = slots_allreduce<V, G, NV>(acc);
                             if (s == 0) {
                                 if (!cur_started) add_row(Ct + (long)cur * sd.rc, total, cols, j, N - tile0, sd.cc, turn);
-                                else if (nvec > 0) put_row(cur, total);
+                                else if (nvec > 0) {
+                                    if constexpr (END::layer) put_row(cur, total);
+                                    else total.emit(Ct + (long)cur * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                                }
                             }
                             acc.clear();
                             cur = -1;
@@ -1244,7 +1298,10 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
                         const bool in_last_run = evalid && er == last_row;
                         if (head && evalid && (!in_last_run || last_ended)) {
                             if (!started) add_row(Ct + (long)er * sd.rc, x, cols, j, N - tile0, sd.cc, turn);
-                            else if (nvec > 0) put_row(er, x);
+                            else if (nvec > 0) {
+                                if constexpr (END::layer) put_row(er, x);
+                                else x.emit(Ct + (long)er * sd.rc + (long)(n0 - tile0) * sd.cc, cols, false, sd.cc);
+                            }
                         }
                         if (last_ended) {
                             acc.clear();
