@@ -355,6 +355,8 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides
     return DA_OK;
 }
 
+constexpr long kLayerElements = 2L << 20;   // of C, for layers that EB kernels finish
+
 template <int V, int G, int NV, bool WIDE>
 int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     const int chunk = geo.chunk;
@@ -376,9 +378,11 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         return dim3((unsigned)bx, tiles);
     };
     const dim3 block(kBlock);
-    // Bias and rectification in the product kernel: the lane groups of row-major products from 8 columns on.
+    // Bias and rectification in the product kernel: the lane groups of row-major products from 8 columns on.  EB needs
+    // eb_finish_kernel after it, which takes as long as the pass over a small C (30 000 rows, 64 -> 64 -> 32: 87.3 us, 85.3 with
+    // the pass; 60 000 rows, 64 -> 64 -> 24: 114.7 and 119.4): from 2 M elements on.
     constexpr bool kLayers = !WIDE && NV == 1 && G >= (V == 4 ? 4 : 8);
-    const bool layer = kLayers && p.layer != nullptr;
+    const bool layer = kLayers && p.layer != nullptr && (fam == RB_SR || fam == RB_PR || (long)p.m * p.N >= kLayerElements);
     if (layer) *p.finished = true;
     auto ended = [&](auto launch_with) {
         if constexpr (kLayers)

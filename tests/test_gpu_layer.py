@@ -55,6 +55,43 @@ def test_layer_is_product_and_pass(N, kind, prepared):
         da.da_spmm_release(rowptr)
 
 
+# EB finishes layers itself from 2 M elements of C on: either side of the line, empty rows, short ones, rows of several chunks
+@pytest.mark.parametrize("N", [8, 16, 30, 37, 64, 67, 128, 130, 257])
+@pytest.mark.parametrize("rows", [-1, 0, 301])
+@pytest.mark.parametrize("prepared", [False, True])
+def test_layers_of_many_rows(N, rows, prepared):
+    from paper_2202_08556_amd import binding as da
+    m, k = (2 * 2 ** 20 + N - 1) // N + rows, 3001
+    g = torch.Generator().manual_seed(N)
+    lens = torch.randint(0, 6, (m,), generator=g)
+    lens[::3] = 0
+    lens[5::900] = 130
+    lens[[0, m // 2, m - 1]] = 2900
+    rowptr = torch.zeros(m + 1, dtype=torch.int32)
+    rowptr[1:] = lens.cumsum(0)
+    nnz = int(rowptr[-1])
+    colind = torch.randint(0, k, (nnz,), generator=g).to(torch.int32).cuda()
+    vals = torch.randint(-3, 4, (nnz,), generator=g).float().cuda()
+    rowptr = rowptr.cuda()
+    B = torch.randint(-4, 5, (k, N), generator=g).float().cuda()
+    bias = torch.randint(-9, 10, (N + 1,), generator=g).float().cuda()[1:]
+    try:
+        if prepared:
+            da.da_spmm_prepare(m, k, nnz, rowptr, colind)
+        for algo in (da.DA_EB_RM_SR, da.DA_EB_RM_PR):
+            want = torch.empty((m, N), device="cuda")
+            da.da_spmm(m, k, N, rowptr, colind, vals, B, want, algo)
+            for b, relu in ((bias, True), (bias, False), (None, True)):
+                print(f"layer m={m} N={N} prepared={prepared} algo={algo} bias={b is not None} relu={relu}", flush=True)
+                full = want.clone()
+                da.da_spmm_bias_relu(m, N, full, b, relu)
+                C = torch.full((m * N + 1,), float("nan"), device="cuda")[1:]
+                da.da_spmm_layer(m, k, N, rowptr, colind, vals, B, N, C, b, relu, algo)
+                assert torch.equal(C.view(m, N), full)
+    finally:
+        da.da_spmm_release(rowptr)
+
+
 @pytest.mark.parametrize("algo", range(8))
 def test_layer_keeps_what_is_not_finite(algo):
     from paper_2202_08556_amd import binding as da
