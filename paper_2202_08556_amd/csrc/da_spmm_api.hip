@@ -82,6 +82,7 @@ struct Geometry {
 constexpr int kSweepStripe = 256;
 
 constexpr int kMaxGridY = 65535;
+constexpr int64_t kMaxGridX = (1LL << 32) / kBlock - 1;   // blocks; of 2^32 threads and more the high bits are lost
 constexpr int kMaxGroupPR = 32;        // PR needs at least two slots along the entries
 constexpr int kDefaultGroupPR = 8;     // 4-byte accesses: at least 8 slots along the entries
 constexpr int kEntriesPerWavePR = 512; // EB+PR: stored entries per wave and pass
@@ -357,6 +358,21 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides
 
 constexpr long kLayerElements = 2L << 20;   // of C, for layers that EB kernels finish
 
+// Calls launch with the whole product or, where its rows make more than max_blocks blocks, with one part of them after
+// another (67 M rows of a wave each).
+template <class F>
+void for_row_parts(const Problem& p, int64_t rows_per_block, int64_t max_blocks, F launch) {
+    const int64_t most = max_blocks * rows_per_block / 64 * 64;        // whole words of LeftOut's bits
+    for (int64_t first = 0; first < p.m; first += most) {
+        Problem part = p;
+        part.m = (int)std::min<int64_t>(most, p.m - first);
+        part.rowptr += first;
+        part.C += first * p.sd.rc;
+        if (part.left_out.rows) part.left_out.rows += first / 32;
+        launch(part);
+    }
+}
+
 template <int V, int G, int NV, bool WIDE>
 int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     const int chunk = geo.chunk;
@@ -377,6 +393,7 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         if (pin) { const long per = 8 / pin; return dim3((unsigned)(8 * ((bx + per - 1) / per)), 1); }
         return dim3((unsigned)bx, tiles);
     };
+    const int64_t max_blocks = pin ? kMaxGridX / 8 * (8 / pin) : kMaxGridX;
     const dim3 block(kBlock);
     // Bias and rectification in the product kernel: the lane groups of row-major products from 8 columns on.  EB needs
     // eb_finish_kernel after it, which takes as long as the pass over a small C (30 000 rows, 64 -> 64 -> 32: 87.3 us, 85.3 with
@@ -393,8 +410,10 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     case RB_SR: {
         const long rows_per_block = (long)kWavesPerBlock * (kWave / G);
         ended([&](auto after) {
-            hipLaunchKernelGGL((rb_sr_kernel<V, G, NV, WIDE, decltype(after)>), grid_for((p.m + rows_per_block - 1) / rows_per_block),
-                               block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin, p.left_out, after);
+            for_row_parts(p, rows_per_block, max_blocks, [&](const Problem& q) {
+                hipLaunchKernelGGL((rb_sr_kernel<V, G, NV, WIDE, decltype(after)>), grid_for((q.m + rows_per_block - 1) / rows_per_block),
+                                   block, 0, q.stream, q.m, q.N, q.sd, q.rowptr, q.colind, q.vals, q.B, q.C, pin, q.left_out, after);
+            });
         });
         break;
     }
@@ -402,8 +421,10 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
         if constexpr (G <= kMaxGroupPR) {
             ended([&](auto after) {
                 auto go = [&](auto kernel) {
-                    hipLaunchKernelGGL(kernel, grid_for((p.m + kWavesPerBlock - 1) / kWavesPerBlock),
-                                       block, 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pin, after);
+                    for_row_parts(p, kWavesPerBlock, max_blocks, [&](const Problem& q) {
+                        hipLaunchKernelGGL(kernel, grid_for(((int64_t)q.m + kWavesPerBlock - 1) / kWavesPerBlock),
+                                           block, 0, q.stream, q.m, q.N, q.sd, q.rowptr, q.colind, q.vals, q.B, q.C, pin, after);
+                    });
                 };
                 if (V == 4 && G >= 16 && p.N % 4 != 0) go(rb_pr_kernel<V, G, NV, WIDE, V == 4 && G >= 16, decltype(after)>);
                 else go(rb_pr_kernel<V, G, NV, WIDE, false, decltype(after)>);
@@ -528,8 +549,10 @@ int launch_columns(const Problem& p, const MatrixHint& hint) {
     auto go = [&](auto l, auto nc) {
         constexpr int L = decltype(l)::value, NC = decltype(nc)::value;
         const long rows = (long)kWavesPerBlock * (kWave / L);
-        hipLaunchKernelGGL((rb_columns_kernel<L, NC>), dim3((unsigned)((p.m + rows - 1) / rows), (unsigned)((p.N + NC - 1) / NC)),
-                           dim3(kBlock), 0, p.stream, p.m, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C);
+        for_row_parts(p, rows, kMaxGridX, [&](const Problem& q) {
+            hipLaunchKernelGGL((rb_columns_kernel<L, NC>), dim3((unsigned)((q.m + rows - 1) / rows), (unsigned)((q.N + NC - 1) / NC)),
+                               dim3(kBlock), 0, q.stream, q.m, q.N, q.sd, q.rowptr, q.colind, q.vals, q.B, q.C);
+        });
     };
     auto by_columns = [&](auto l) {
         if (p.N >= 5) go(l, Count<8>{});
@@ -877,7 +900,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     sd.cb = layout_b == DA_ROW_MAJOR ? 1 : ldb;
     sd.rc = layout_c == DA_ROW_MAJOR ? ldc : 1;
     sd.cc = layout_c == DA_ROW_MAJOR ? 1 : ldc;
-    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{nullptr, 0, 0}, nullptr, nullptr};
+    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{nullptr, nullptr, 0, 0}, nullptr, nullptr};
     const bool eb = algo >= DA_EB_RM_SR;
     const bool cm = (algo & 2) != 0;
     const bool pr = (algo & 1) != 0;
@@ -890,7 +913,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
             const int st = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
                                          PlanInfo{false, 0.0}, &g);
             if (st != DA_OK) return st;
-            p.left_out = LeftOut{heavy.bits, heavy.plan.min_len, heavy.plan.nnz};
+            p.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz};
             const int rest = dispatch(RB_SR, g, p);
             return rest != DA_OK ? rest : launch_heavy(p, heavy.plan);
         }

@@ -482,9 +482,10 @@ template <int UMAX, class F>
 __device__ __forceinline__ void for_blocks(int cnt, F&& f) { for_blocks<UMAX>(0, cnt, f); }
 
 // Rows whose sums another kernel adds to C (heavy_rows_kernel): one bit a row, for rows of at least min_len entries in
-// a matrix of nnz; they are written as zeros.  rows == nullptr: none.
+// a matrix of nnz (the number at `end`); they are written as zeros.  rows == nullptr: none.
 struct LeftOut {
     const unsigned* rows;
+    const int* end;
     int min_len, nnz;
 };
 
@@ -512,7 +513,7 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
     const int n0 = cols.n0, nvec = cols.nvec;
     int start = 0, end = 0;
     if (row < m) { start = rowptr[row]; end = rowptr[row + 1]; }
-    if (out.rows != nullptr && end - start >= out.min_len && (out.rows[row >> 5] >> (row & 31) & 1u) && rowptr[m] == out.nnz) end = start;
+    if (out.rows != nullptr && end - start >= out.min_len && (out.rows[row >> 5] >> (row & 31) & 1u) && *out.end == out.nnz) end = start;
     Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);
