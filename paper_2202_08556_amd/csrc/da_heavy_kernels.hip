@@ -41,7 +41,14 @@ constexpr size_t kHeavyLds = 2 * 65536 + 256;              // two buffers and a 
 struct HeavyPlan {
     const int* rows;     // count row numbers, by length
     const int* at;       // at[h * (cells + 1) + c]: position of the first entry of row h with column >= c * cell
-    int count, cells, cell, min_len, nnz, mean_len;
+    int count, cells, cell, min_len, nnz;
+};
+
+// Blocks of a launch: group i has the rows row[i] ... row[i + 1] - 1 of the plan and the blocks block[i] ... block[i + 1] - 1,
+// each with the rows' entries in per[i] cells.
+constexpr int kHeavyGroups = 16;
+struct HeavyGroups {
+    int count, block[kHeavyGroups + 1], row[kHeavyGroups + 1], per[kHeavyGroups];
 };
 
 // Rows of at least min_len entries, in no order (count[0], list[] up to `most`), and of the others the sum of squared
@@ -139,7 +146,7 @@ struct HeavySteps {
 template <int GL, int V>
 __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     int m, int k, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind, const float* __restrict__ vals,
-    const float* __restrict__ B, float* __restrict__ C, HeavyPlan plan, int groups, int quads, int cells_per_block)
+    const float* __restrict__ B, float* __restrict__ C, HeavyPlan plan, HeavyGroups groups)
 {
     if (rowptr[m] != plan.nnz) return;                     // a plan of another matrix: the EB kernel takes everything
     extern __shared__ __align__(16) char heavy_lds[];
@@ -148,12 +155,14 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     constexpr int kZero = 2 * 65536;                       // offset of the row of zeros
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, j = lane & 15, jc = lane & (GL - 1);
-    const int group = blockIdx.x % groups, slab = blockIdx.x / groups;
+    int group = 0;
+    while (group + 1 < groups.count && (int)blockIdx.x >= groups.block[group + 1]) ++group;
+    const int slab = blockIdx.x - groups.block[group], row0 = groups.row[group], row1 = groups.row[group + 1];
+    const int quads = (row1 - row0 + kHeavyWaves * 4 - 1) / (kHeavyWaves * 4);
     const int tile0 = blockIdx.y * GL * V;
-    const int cell0 = slab * cells_per_block, cell1 = min(cell0 + cells_per_block, plan.cells);
+    const int cell0 = slab * groups.per[group], cell1 = min(cell0 + groups.per[group], plan.cells);
     const int col0 = cell0 * plan.cell;
     const int col1 = cell1 == plan.cells ? k : cell1 * plan.cell;
-    const int per_group = quads * kHeavyWaves * 4;
 
     // rows of B, in four parts: thread t brings rows t / GL + kBlock / GL * p of the band, columns jc + GL v
     constexpr int kParts = 4, kPasses = 16 / V / kParts, kStep = kHeavyBlock / GL;
@@ -189,7 +198,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     auto index = [&](int i) {
         int q = wave + kHeavyWaves * i + (int)(slab * 5u % (unsigned)(kHeavyWaves * quads));
         if (q >= kHeavyWaves * quads) q -= kHeavyWaves * quads;
-        return group * per_group + 4 * q + g;
+        return row0 + 4 * q + g;
     };
 #pragma unroll
     for (int i = 0; i < kHeavyQuads; ++i) {
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
         for (int v = 0; v < V; ++v) acc[i][v] = 0.f;
         if (i < quads) {
             const int h = index(i);
-            if (h < plan.count) {
+            if (h < row1) {
                 const int r = plan.rows[h];
                 const int s = rowptr[r], e = rowptr[r + 1];
                 const int* at = plan.at + (long)h * (plan.cells + 1);
@@ -312,7 +321,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     for (int i = 0; i < kHeavyQuads; ++i) {
         if (i < quads) {
             const int h = index(i);
-            if (h < plan.count) {
+            if (h < row1) {
                 const int r = plan.rows[h];
                 if (rowptr[r + 1] - rowptr[r] >= plan.min_len) {
 #pragma unroll

@@ -144,6 +144,7 @@ struct Plan {
     int64_t heavy_k = 0;                 // columns that the cells of `heavy` cover
     const unsigned* heavy_bits = nullptr;
     double rest_len = 0.0;               // length of the row that an average entry of the other rows lies in
+    std::shared_ptr<const std::vector<int64_t>> heavy_sums;   // entries of the first 0, 1, ... heavy rows by length
     std::shared_ptr<DeviceBlock> heavy_block;
     bool captured = false;               // a stream capture recorded a kernel that reads the orders
 };
@@ -190,7 +191,13 @@ bool is_capturing(hipStream_t s) {
 
 // The heavy rows of a prepared matrix; references and captures as for lookup_schedule.  The kernel reads every row of B
 // that the cells cover, used or not: products that declare other columns than da_spmm_prepare did go without.
-struct HeavyLookup { HeavyPlan plan{}; const unsigned* bits = nullptr; double rest_len = 0.0; std::shared_ptr<DeviceBlock> keep; };
+struct HeavyLookup {
+    HeavyPlan plan{};
+    const unsigned* bits = nullptr;
+    double rest_len = 0.0;
+    std::shared_ptr<const std::vector<int64_t>> sums;
+    std::shared_ptr<DeviceBlock> keep;
+};
 HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, int64_t k, hipStream_t stream) {
     HeavyLookup out;
     std::lock_guard<std::mutex> lk(g_plan_mu);
@@ -199,6 +206,7 @@ HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, int6
             out.plan = pl.heavy;
             out.bits = pl.heavy_bits;
             out.rest_len = pl.rest_len;
+            out.sums = pl.heavy_sums;
             out.keep = pl.heavy_block;
             if (is_capturing(stream)) pl.captured = true;
             break;
@@ -533,13 +541,6 @@ int launch(Family fam, const Problem& p, const Geometry& geo) {
     return narrow ? launch_w<V, G, NV, false>(fam, p, geo) : launch_w<V, G, NV, true>(fam, p, geo);
 }
 
-// Beyond 32 columns LDS is the bound, and the kernel the better one only where its 16 waves have about equal numbers of
-// rows (N = 64, 72 heavy rows: 92 us, EB 76; 322: 198 and 217; 524: 330 and 469).
-constexpr int kHeavyWideRows = 256;
-// Entries of a row that one block adds up, at least: every block's part is one more rounding of the row's sum, and chunks
-// of EB+SR have 64 to 128 (rows of 8000, all of one sign, N = 3: error 1.5e-7 there, 2.8e-7 with parts of 32).
-constexpr int kHeavyPart = 128;
-
 // Column-major B under the RB ids whose sums rb_columns_kernel makes at least as exact (SR; RM+PR from 5 columns on, which
 // has 8 slots).  Lanes per row by the length of the row that an average entry lies in: 4 below 6 (3 a row, N = 1: 6.7 us,
 // with 8 lanes 7.9, with lanes along N 6.8), 16 from 40 on (rows of 170, N = 8: 93 us with 8, 87 with 16, lanes along N: SR 105,
@@ -570,28 +571,95 @@ int launch_columns(const Problem& p, const MatrixHint& hint) {
     return DA_OK;
 }
 
-// The heavy rows' part of a product whose other rows are on the stream already.  A block has 131 KB of LDS and 16
-// waves, one to a CU: as many ranges of columns as make one block per CU over all sets of rows and column tiles.
+// Beyond 32 columns LDS is the bound, and the kernel the better one only where its 16 waves have about equal numbers of
+// rows (N = 64, 72 heavy rows: 92 us, EB 76; 322: 198 and 217; 524: 330 and 469).
+constexpr int kHeavyWideRows = 256;
+
+// How the heavy rows' part of a product is dealt to the blocks.  A block has 131 KB of LDS and 16 waves, one to a CU: as many
+// ranges of columns as make one block per CU over all groups of rows and column tiles.  Every block's part of a row is one
+// more rounding of the row's sum, as every chunk of EB+SR is: a group has no more ranges than its shortest row's sum
+// takes.  Rows of similar length make a group, so that the ranges of long rows need not be as few as those of short ones,
+// and the ranges are as many as the group's entries want.  524 rows of 20 000 to 100 000, N = 64: 64, 94 and 94 ranges for
+// 192, 192 and 140 rows, 326 us; one group of 256 ranges 323, the shortest rows in parts of 78 entries; N = 8: 121 and 130;
+// N = 16: 183 and 166; 1500 rows of 3200 to 30 000, N = 64: 170 and 205.
+struct HeavyLaunch {
+    HeavyGroups groups;
+    double load;         // entries, and work of as much time, of the block that has most
+};
+
+constexpr double kHeavyLeast = 5000.0;   // work of a block that is worth a range of its own (40 rows of 16 000, N = 8: 16 us, 18 in twice as many)
+
+constexpr int heavy_tile(int64_t N) { return N <= 8 ? 8 : (N <= 16 ? 16 : (N <= 32 ? 32 : 64)); }
+
+// Entries of a heavy row of n entries that a block has to add up, at least, for a sum as exact as EB's in chunks of c: as
+// one_sign_error, with sums of 16 entries that are added one after another inside a part.
+double heavy_part(double n, double c) {
+    const double bound = one_sign_error(c, 1.0, n) - 256.0;
+    double part = n * n / bound;
+    for (int i = 0; i < 3; ++i) part = n * n / (bound - part * part / 16.0);
+    return part;
+}
+
+HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sums, int64_t k, int64_t N, int chunk) {
+    const int tile = heavy_tile(N), band = 16384 / tile;
+    const int64_t tiles = (N + tile - 1) / tile;
+    const int quads = (pl.count + 3) / 4, most = kHeavyWaves * kHeavyQuads, least = (quads + most - 1) / most;
+    HeavyLaunch best{};
+    auto deal = [&](int n, int unit) {                      // n groups of whole units of 4 * unit rows
+        HeavyLaunch x{};
+        x.groups.count = n;
+        const int64_t blocks = std::max<int64_t>(cu_count() / tiles, n);
+        const int units = (quads + unit - 1) / unit;
+        double cost[kHeavyGroups], all = 0.0;
+        int fewest[kHeavyGroups];                           // cells of a range, at least
+        for (int i = 0; i <= n; ++i) x.groups.row[i] = std::min(pl.count, 4 * unit * (int)((int64_t)units * i / n));
+        for (int i = 0; i < n; ++i) {
+            const int r0 = x.groups.row[i], r1 = x.groups.row[i + 1], here = (r1 - r0 + 3) / 4;
+            const double entries = (double)(sums[r1] - sums[r0]) + 8.0 * (r1 - r0) * ((double)k / band);
+            // a CU needs some 12 of its waves to be busy
+            const double longest = entries * ((here + kHeavyWaves - 1) / kHeavyWaves) / here;
+            cost[i] = std::max(entries, 12.0 * longest) + 2.0 * (double)k;
+            all += cost[i];
+            const double shortest = (double)(sums[r0 + 1] - sums[r0]);
+            const int ranges = std::max(1, (int)(shortest / heavy_part(shortest, chunk)));
+            fewest[i] = (pl.cells + ranges - 1) / ranges;
+        }
+        for (double target = std::max(kHeavyLeast, all / (double)blocks);; target *= 1.02) {
+            x.load = 0.0;
+            for (int i = 0; i < n; ++i) {
+                const int per = std::max(fewest[i], std::max(1, (int)(std::min(target / cost[i], 1.0) * pl.cells)));
+                x.groups.per[i] = per;
+                x.groups.block[i + 1] = x.groups.block[i] + (pl.cells + per - 1) / per;
+                x.load = std::max(x.load, cost[i] * per / pl.cells);
+            }
+            if (x.groups.block[n] <= blocks) break;
+        }
+        if (best.groups.count == 0 || x.load < 0.97 * best.load) best = x;
+    };
+    // every wave of a block with as many rows as the others, as far as that goes
+    deal(least, 1);
+    for (int n = least; n <= std::min(kHeavyGroups, least + 3); ++n) {
+        if (n * kHeavyWaves <= quads) deal(n, kHeavyWaves);
+        else if (n == 2 && quads >= 2) deal(n, 1);
+    }
+    return best;
+}
+
+// The heavy rows' part of a product whose other rows are on the stream already.
 // Lanes: 4 of two columns up to 8 columns (N = 8: 90 us, 16 lanes of one column 114), 16 beyond (N = 16, 1.6 M entries: 16 us,
 // 4 lanes of four columns, whose random 64-byte reads meet in the banks of LDS, 33).
-
-int launch_heavy(const Problem& p, const HeavyPlan& pl) {
-    auto go = [&](auto kernel, int tile) {
-        const int tiles = (p.N + tile - 1) / tile;
-        const int sets = (pl.count + 3) / 4;
-        const int groups = (sets + kHeavyWaves * kHeavyQuads - 1) / (kHeavyWaves * kHeavyQuads);
-        const int quads = (sets + kHeavyWaves * groups - 1) / (kHeavyWaves * groups);
-        long wanted = cu_count() / ((long)groups * tiles);
-        wanted = std::max<long>(1, std::min<long>(wanted, pl.mean_len / kHeavyPart));
-        const int per = (int)((pl.cells + wanted - 1) / wanted);
-        const int slabs = (pl.cells + per - 1) / per;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(groups * slabs), (unsigned)tiles), dim3(kHeavyBlock), kHeavyLds, p.stream, p.m, (int)p.k,
-                           p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pl, groups, quads, per);
+int launch_heavy(const Problem& p, const HeavyPlan& pl, const HeavyGroups& groups) {
+    auto go = [&](auto kernel) {
+        const int tile = heavy_tile(p.N);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups.block[groups.count], (unsigned)((p.N + tile - 1) / tile)), dim3(kHeavyBlock), kHeavyLds,
+                           p.stream, p.m, (int)p.k, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pl, groups);
     };
-    if (p.N <= 8) go(heavy_rows_kernel<4, 2>, 8);
-    else if (p.N <= 16) go(heavy_rows_kernel<16, 1>, 16);
-    else if (p.N <= 32) go(heavy_rows_kernel<16, 2>, 32);
-    else go(heavy_rows_kernel<16, 4>, 64);
+    switch (heavy_tile(p.N)) {
+    case 8: go(heavy_rows_kernel<4, 2>); break;
+    case 16: go(heavy_rows_kernel<16, 1>); break;
+    case 32: go(heavy_rows_kernel<16, 2>); break;
+    default: go(heavy_rows_kernel<16, 4>);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return DA_OK;
@@ -906,18 +974,6 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     const bool pr = (algo & 1) != 0;
     Geometry g;
     const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
-    if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
-        // heavy rows in a kernel of their own, the others, which are short and even, row by row
-        const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
-        if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows)) {
-            const int st = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
-                                         PlanInfo{false, 0.0}, &g);
-            if (st != DA_OK) return st;
-            p.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz};
-            const int rest = dispatch(RB_SR, g, p);
-            return rest != DA_OK ? rest : launch_heavy(p, heavy.plan);
-        }
-    }
     p.layer = layer;
     p.finished = finished;
     if (sd.rb == 1 && N <= 8L * kMaxGridY && (algo == DA_RB_RM_SR || algo == DA_RB_CM_SR || (algo == DA_RB_RM_PR && N >= 5)) &&
@@ -927,6 +983,22 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
+    if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
+        // heavy rows in a kernel of their own, the others, which are short and even, row by row
+        const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
+        if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows)) {
+            const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk);
+            Problem q = p;
+            q.layer = nullptr;
+            Geometry rest;
+            const int rs = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
+                                         PlanInfo{false, 0.0}, &rest);
+            if (rs != DA_OK) return rs;
+            q.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz};
+            const int done = dispatch(RB_SR, rest, q);
+            return done != DA_OK ? done : launch_heavy(q, heavy.plan, dealt.groups);
+        }
+    }
     const Family fam = eb ? (pr ? EB_PR : EB_SR) : (pr ? RB_PR : RB_SR);
     return dispatch(fam, g, p);
 }
@@ -1355,7 +1427,11 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     const double rest_len = nnz > entries ? (double)host.sq / (double)(nnz - entries) : 0.0;
     if (entries < kHeavyMinEntries || 2 * entries < nnz || entries < kHeavyUses * k || rest_len > kRestLen) return DA_OK;
     std::sort(by_length.begin(), by_length.end());         // neighbours walk side by side: rows of one length
-    for (size_t i = 0; i < rows.size(); ++i) rows[i] = by_length[i].second;
+    auto row_sums = std::make_shared<std::vector<int64_t>>(rows.size() + 1, 0);
+    for (size_t i = 0; i < rows.size(); ++i) {
+        rows[i] = by_length[i].second;
+        (*row_sums)[i + 1] = (*row_sums)[i] + by_length[i].first;
+    }
 
     const int cell = (int)((k + kHeavyCells - 1) / kHeavyCells), cells = (int)((k + cell - 1) / cell);
     const size_t words = (size_t)(m + 31) / 32, n = rows.size();
@@ -1376,10 +1452,11 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "da_spmm_prepare");
     if (host.unsorted) return DA_OK;
-    pl->heavy = HeavyPlan{drows, at, (int)n, cells, cell, min_len, (int)nnz, (int)(entries / (int64_t)n)};
+    pl->heavy = HeavyPlan{drows, at, (int)n, cells, cell, min_len, (int)nnz};
     pl->heavy_k = k;
     pl->heavy_bits = bits;
     pl->rest_len = rest_len;
+    pl->heavy_sums = row_sums;
     pl->heavy_block = block;
     return DA_OK;
 }

@@ -20,3 +20,14 @@ class DeviceProblem:
         da.da_spmm(self.a.m, self.a.k, self.N, self.rowptr, self.colind, self.vals, self.B, C, algo)
         torch.cuda.synchronize()
         return C.cpu().numpy()
+
+
+def kernels_of(call):
+    """Names of the kernels that a call launches."""
+    from torch.autograd import DeviceType
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return {e.name for e in prof.events() if e.device_type == DeviceType.CUDA}
