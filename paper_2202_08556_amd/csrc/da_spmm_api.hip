@@ -144,6 +144,7 @@ struct Plan {
     int64_t heavy_k = 0;                 // columns that the cells of `heavy` cover
     const unsigned* heavy_bits = nullptr;
     double rest_len = 0.0;               // length of the row that an average entry of the other rows lies in
+    int rest_longest = 0;                // the longest of them
     std::shared_ptr<const std::vector<int64_t>> heavy_sums;   // entries of the first 0, 1, ... heavy rows by length
     std::shared_ptr<DeviceBlock> heavy_block;
     bool captured = false;               // a stream capture recorded a kernel that reads the orders
@@ -195,6 +196,7 @@ struct HeavyLookup {
     HeavyPlan plan{};
     const unsigned* bits = nullptr;
     double rest_len = 0.0;
+    int rest_longest = 0;
     std::shared_ptr<const std::vector<int64_t>> sums;
     std::shared_ptr<DeviceBlock> keep;
 };
@@ -206,6 +208,7 @@ HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, int6
             out.plan = pl.heavy;
             out.bits = pl.heavy_bits;
             out.rest_len = pl.rest_len;
+            out.rest_longest = pl.rest_longest;
             out.sums = pl.heavy_sums;
             out.keep = pl.heavy_block;
             if (is_capturing(stream)) pl.captured = true;
@@ -984,9 +987,10 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
     if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
-        // heavy rows in a kernel of their own, the others, which are short and even, row by row
+        // Heavy rows in a kernel of their own, the others, which are short and even, row by row.  A row is then added up
+        // entry by entry; EB does that with up to a chunk of them.
         const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
-        if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows)) {
+        if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows) && heavy.rest_longest <= g.chunk) {
             const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk);
             Problem q = p;
             q.layer = nullptr;
@@ -1456,6 +1460,7 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     pl->heavy_k = k;
     pl->heavy_bits = bits;
     pl->rest_len = rest_len;
+    pl->rest_longest = (int)host.mx;
     pl->heavy_sums = row_sums;
     pl->heavy_block = block;
     return DA_OK;

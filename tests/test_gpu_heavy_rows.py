@@ -173,9 +173,9 @@ def test_recorded_calls_keep_their_plan():
 
 
 # Products of one sign, whose error grows with the number of parts of a row and with the terms that are added one after
-# another: short and long heavy rows side by side.
+# another: short and long heavy rows side by side, other rows up to the length of a chunk and far beyond it.
 @pytest.mark.parametrize("N", [1, 4, 8, 16, 24, 32, 64])
-@pytest.mark.parametrize("longest_other", [30])
+@pytest.mark.parametrize("longest_other", [30, 900])
 def test_sums_are_as_exact_as_in_chunks(N, longest_other, monkeypatch):
     from paper_2202_08556_amd import binding as da
     m, k = 8000, 60000
