@@ -574,10 +574,6 @@ int launch_columns(const Problem& p, const MatrixHint& hint) {
     return DA_OK;
 }
 
-// Beyond 32 columns LDS is the bound, and the kernel the better one only where its 16 waves have about equal numbers of
-// rows (N = 64, 72 heavy rows: 92 us, EB 76; 322: 198 and 217; 524: 330 and 469).
-constexpr int kHeavyWideRows = 256;
-
 // How the heavy rows' part of a product is dealt to the blocks.  A block has 131 KB of LDS and 16 waves, one to a CU: as many
 // ranges of columns as make one block per CU over all groups of rows and column tiles.  Every block's part of a row is one
 // more rounding of the row's sum, as every chunk of EB+SR is: a group has no more ranges than its shortest row's sum
@@ -646,6 +642,27 @@ HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sum
         else if (n == 2 && quads >= 2) deal(n, 1);
     }
     return best;
+}
+
+// Whether the heavy rows' kernel beats EB, which has all rows in one kernel and as many blocks as it likes.  share: the load of
+// the block that has most, in shares of a CU of all entries.  EB's additions to the same few lines of C are what costs it
+// most, so that few rows of many entries always gain up to 32 columns (72 rows of 24 000, N = 32: 72 us in EB, 27 here; 300
+// of 2300, N = 8: 19.4 and 14.7, N = 24: 21.5 and 17.8; 800 of 6000, N = 24: 50.5 and 50.1).  Many short rows are EB's unless they
+// fill the CUs evenly (2000 of 3300, 6.8 M entries, N = 16: 43.5 and 46.1; 5000 of 3000, 15 M, N = 16, share 1.3: 79 and 89; 1500 of
+// 17 000, 25 M, share 1.13: 117 and 110).  Up to four columns EB has 16 and more workers to a wave and waits for them (4000 rows
+// of 1000, N = 4: 44 and 35).  Beyond 32 columns LDS is the bound, and the rows that are not heavy cost a kernel of their
+// own (12 M entries, 300 000 rows, N = 64: 142 and 149; 33 M, 524 000: 445 and 326; 800 rows of 6000, share 2.2: 69 and 71; 8000 of
+// 3000, share 1.4: 231 and 171); beyond 64 the entries are read for every tile (N = 96: 5 M 88 and 88, 12 M 240 and 242, 25 M
+// 385 and 284), beyond 128 in EB, too (N = 130: 12 M 520 and 390, 33 M 1543 and 880).  Column-major B gathers every element from a
+// line of its own in EB (300 heavy rows, N = 32: 65 and 52; 5000: 1224 and 392).
+bool heavy_rows_pay(int64_t m, int64_t N, bool row_major, int count, int64_t nnz, double share) {
+    const bool many = nnz >= 10000000;
+    if (!row_major) return (N > 8 || count <= 2048 || many) && (N <= 32 || count >= 256);
+    if (N <= 4) return true;
+    if (N <= 32) return count <= 1024 || (many && share <= 1.25);
+    if (count < 256) return false;
+    if (N > 128) return true;
+    return nnz / 48 >= m && (N <= 64 ? count <= 640 || share <= 1.6 : many);
 }
 
 // The heavy rows' part of a product whose other rows are on the stream already.
@@ -990,17 +1007,19 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
         // Heavy rows in a kernel of their own, the others, which are short and even, row by row.  A row is then added up
         // entry by entry; EB does that with up to a chunk of them.
         const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
-        if (heavy.plan.count >= (N <= 32 ? 1 : kHeavyWideRows) && heavy.rest_longest <= g.chunk) {
+        if (heavy.plan.count > 0 && heavy.rest_longest <= g.chunk) {
             const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk);
-            Problem q = p;
-            q.layer = nullptr;
-            Geometry rest;
-            const int rs = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
-                                         PlanInfo{false, 0.0}, &rest);
-            if (rs != DA_OK) return rs;
-            q.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz};
-            const int done = dispatch(RB_SR, rest, q);
-            return done != DA_OK ? done : launch_heavy(q, heavy.plan, dealt.groups);
+            if (heavy_rows_pay(m, N, sd.cb == 1, heavy.plan.count, heavy.plan.nnz, dealt.load * cu_count() / heavy.plan.nnz)) {
+                Problem q = p;
+                q.layer = nullptr;
+                Geometry rest;
+                const int rs = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
+                                             PlanInfo{false, 0.0}, &rest);
+                if (rs != DA_OK) return rs;
+                q.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz};
+                const int done = dispatch(RB_SR, rest, q);
+                return done != DA_OK ? done : launch_heavy(q, heavy.plan, dealt.groups);
+            }
         }
     }
     const Family fam = eb ? (pr ? EB_PR : EB_SR) : (pr ? RB_PR : RB_SR);

@@ -48,13 +48,35 @@ def dense(N, seed=1):
     return np.random.Generator(np.random.PCG64(seed)).integers(-4, 5, (K, N)).astype(np.float32)
 
 
+# between 65 and 128 columns a matrix of less than 10 M entries is the EB kernels'
 @pytest.mark.parametrize("N", [1, 2, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 130])
 def test_every_width(prepared, N):
+    from tests.gpu_util import kernels_of
     host, dev = prepared
     print("heavy rows N", N, flush=True)
     B = dense(N)
     want, _ = orc.spmm(*host, B)
-    assert np.array_equal(product(dev, torch.from_numpy(B).cuda(), N), want.astype(np.float32) + 0.0)
+    got = []
+    names = kernels_of(lambda: got.append(product(dev, torch.from_numpy(B).cuda(), N)))
+    assert np.array_equal(got[0], want.astype(np.float32) + 0.0)
+    assert any("heavy_rows_kernel" in n for n in names) == (not 65 <= N <= 128), names
+    assert any("eb_sr_kernel" in n for n in names) == (65 <= N <= 128), names
+
+
+# rows around a wave's 4 and a block's 64 and 576, groups of rows of other lengths, with ranges of their own
+@pytest.mark.parametrize("heavy", [21, 64, 65, 127, 129, 576, 577, 1030])
+@pytest.mark.parametrize("N", [4, 8, 20, 64, 130])
+def test_groups_of_rows(heavy, N):
+    from paper_2202_08556_amd import binding as da
+    host = matrix(heavy, heavy, *((18000, 20012) if heavy < 64 else (640, 12000) if heavy < 500 else (640, 2000)))
+    dev = [torch.from_numpy(x).cuda() for x in host]
+    da.da_spmm_prepare(M, K, host[1].size, dev[0], dev[1])
+    print(f"heavy rows {heavy} N {N}", flush=True)
+    B = dense(N)
+    want, _ = orc.spmm(*host, B)
+    got = product(dev, torch.from_numpy(B).cuda(), N)
+    da.da_spmm_release(dev[0])
+    assert np.array_equal(got, want.astype(np.float32) + 0.0)
 
 
 @pytest.mark.parametrize("N", [8, 40])
@@ -178,10 +200,10 @@ def test_recorded_calls_keep_their_plan():
 @pytest.mark.parametrize("longest_other", [30, 900])
 def test_sums_are_as_exact_as_in_chunks(N, longest_other, monkeypatch):
     from paper_2202_08556_amd import binding as da
-    m, k = 8000, 60000
+    m, k = 30000, 60000
     rng = np.random.Generator(np.random.PCG64(21))
     lens = np.full(m, 30)
-    lens[10:20] = longest_other
+    lens[10:50] = longest_other
     lens[100:250], lens[300:450] = rng.integers(1900, 2600, 150), rng.integers(15000, 30000, 150)
     lens = lens[rng.permutation(m)]
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -206,4 +228,6 @@ def test_sums_are_as_exact_as_in_chunks(N, longest_other, monkeypatch):
                        ("long", lens >= 15000)):
         a, b = (np.sqrt(x[rows].mean() / 3) for x in (here, chunks))
         print(f"N={N} {name}: {a:.2e}, in chunks {b:.2e}", flush=True)
-        assert a <= 1.15 * b                      # the order of additions changes the figures by a tenth from run to run
+        # The order of additions changes the figures by a tenth from run to run; the mean over n sums is off by
+        # 1 / sqrt(2 n), 4 % of it for 300.
+        assert rows.sum() * N < 300 or a <= 1.15 * b
