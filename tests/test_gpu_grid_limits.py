@@ -52,3 +52,28 @@ def test_rows_of_two_tiles(algo):
     for n in (0, 63, 64, 127):
         assert torch.equal(C[:, n], product(rowptr, colind, vals, B[:, n].contiguous()) + bias[n])
     assert not torch.isnan(C.sum(1)).any()
+
+
+# heavy rows on both sides of the first part's end: the other rows' kernel leaves them to the kernel of their own
+def test_heavy_rows_of_both_parts():
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    m, k, N, each = (1 << 27) + 4097, 20011, 17, 18000
+    heavy = torch.cat([torch.arange(20) * 1000 + 3, m - 4 - torch.arange(20) * 100]).sort()[0].cuda()
+    lens = torch.zeros(m, dtype=torch.int32, device="cuda")
+    lens[heavy] = each
+    rowptr = torch.zeros(m + 1, dtype=torch.int32, device="cuda")
+    torch.cumsum(lens, 0, out=rowptr[1:])
+    colind = (torch.arange(each, device="cuda")[None, :] + 50 * torch.arange(40, device="cuda")[:, None]).reshape(-1).to(torch.int32)
+    vals = (torch.arange(40 * each, device="cuda") % 5 - 2).float()
+    B = (torch.arange(k * N, device="cuda") % 9 - 4).float().view(k, N)
+    da.da_spmm_prepare(m, k, colind.numel(), rowptr, colind)
+    C = torch.full((m, N), float("nan"), device="cuda")
+    print("rows", m, flush=True)
+    names = kernels_of(lambda: da.da_spmm(m, k, N, rowptr, colind, vals, B, C, da.DA_EB_RM_SR))
+    da.da_spmm_release(rowptr)
+    assert any("heavy_rows_kernel" in n for n in names)
+    want = torch.stack([(vals[i * each:(i + 1) * each, None] * B[colind[i * each:(i + 1) * each].long()]).sum(0) for i in range(40)])
+    assert torch.equal(C[heavy], want)
+    C[heavy] = 0.0
+    assert not torch.isnan(C.sum(1)).any() and not C.any()
