@@ -545,10 +545,41 @@ int launch(Family fam, const Problem& p, const Geometry& geo) {
 }
 
 // Column-major B under the RB ids whose sums rb_columns_kernel makes at least as exact (SR; RM+PR from 5 columns on, which
-// has 8 slots).  Lanes per row by the length of the row that an average entry lies in: 4 below 6 (3 a row, N = 1: 6.7 us,
+// has 8 slots).  Lanes per row by the length of the row that an average entry lies in: 4 below 7 (3 a row, N = 1: 6.7 us,
 // with 8 lanes 7.9, with lanes along N 6.8), 16 from 40 on (rows of 170, N = 8: 93 us with 8, 87 with 16, lanes along N: SR 105,
 // PR 99; 27-point stencil: 25 with 8, 35 with 16), 64 from 200 on, where a few rows are much longer than the others
 // (power-law, N = 8: 71 with 16, 59 with 64, PR along N 63).  Unknown: 8.
+// Whether rb_columns_kernel beats the lanes along N: algo is one of those three ids, mean and len are the lengths of an average row
+// and of the row that an average entry lies in.  Its lanes wait for memory a row at a time, so rows want some entries (1 M
+// rows of 1: SR, N = 1 7.3 us along N, 10.6 here), and lanes of neighbouring rows write a row-major C in pieces of 4 bytes (SR, rows of
+// 3, N = 8: 12.2 and 14.1; of 10: 34.7 and 35.8; from 16 and 24 columns on the loads decide: N = 24, rows of 2 333 and 240, N = 32, of 10 365 and 142).  Nine or ten
+// columns are a tile of 8 and one of next to nothing (SR, rows of 3, N = 9: 15.3 and 16.7).  CM has a lane for a row, which is good
+// where rows are even and short and 8 columns of B do not fit an L2 (300 000 random rows of 5, N = 8: 91 and 123; 200 000 of 13, N = 16:
+// 255 and 279, N = 5 100 and 60; 100 000 of 10, N = 8: 46 and 35) and waits for the longest of 64 where they are not (lognormal rows
+// of 8, N = 8: 147 and 55).  PR has a wave for a row and 8 slots along it already: short rows leave them empty (rows of 1, N = 8: 185
+// and 49; of 10: 41 and 35; lognormal rows of 60: 40 and 50; 500 rows of 40, N = 64: 8.2 and 4.9; few very long ones, N = 16: 155 and
+// 115), above 64 columns it is as good with uneven ones (few very long ones, N = 128: 363 and 396).  Of a
+// matrix that nothing is known of every law is possible: the ids keep their lanes along N (PR on 64 rows of 8000, N = 12: 61 and
+// 345; SR on 1 M rows of 1, N = 1: 7.4 and 22) but for SR with a column-major C from 24 columns on (1 M rows of 1, N = 24: 400 and 149;
+// 64 rows of 8000: 670 and 350; lognormal rows of 25: 123 and 132).
+bool columns_pay(int algo, int64_t m, int64_t k, int64_t N, bool c_by_rows, const MatrixHint& hint) {
+    const bool sr = algo == DA_RB_RM_SR;
+    if (hint.nnz < 0 || hint.seen_len <= 0.0) return sr && !c_by_rows && N >= 24;
+    const double mean = (double)hint.nnz / (double)m, len = hint.seen_len;
+    if (algo == DA_RB_RM_PR) {
+        const bool even = len < 1.15 * mean;
+        if (len >= 200.0) return c_by_rows ? N <= 64 && (len >= 2000.0 || (mean < 2.0 && N <= 8)) : N <= 64 || even;
+        if (c_by_rows) return (len < 28.0 && (N <= 12 || mean >= 20.0)) || (mean < 2.0 && N <= 8);
+        return len < 28.0 || mean < 2.0 || (N > 8 && ((len < 40.0 && len < 2.0 * mean) || even));
+    }
+    if (!sr) return len >= 35.0 || mean >= 15.0 || (mean >= 3.0 && k <= 1 << 17) || (mean >= 5.0 && N <= 5) ||
+                    (c_by_rows && mean < 3.5 && N >= 16);
+    if (N >= 24) return mean >= 2.0 || !c_by_rows;
+    if (N == 9 || N == 10) return mean >= (c_by_rows ? 20.0 : 8.0) || (len >= 200.0 && mean >= 8.0);
+    if (c_by_rows) return mean >= 12.0 || (N >= 16 && mean >= 4.0 && len < 6.0 * mean);
+    return mean >= (N > 10 ? 2.0 : 2.5) || (N >= 16 && len < 35.0);
+}
+
 int launch_columns(const Problem& p, const MatrixHint& hint) {
     auto go = [&](auto l, auto nc) {
         constexpr int L = decltype(l)::value, NC = decltype(nc)::value;
@@ -565,7 +596,7 @@ int launch_columns(const Problem& p, const MatrixHint& hint) {
         else go(l, Count<1>{});
     };
     const double len = hint.seen_len > 0.0 ? hint.seen_len : 8.0;
-    if (len < 6.0 && p.N < 5) by_columns(Count<4>{});
+    if (len < 7.0 && p.N < 5) by_columns(Count<4>{});
     else if (len < 40.0) by_columns(Count<8>{});
     else if (len < 200.0) by_columns(Count<16>{});
     else by_columns(Count<64>{});
@@ -997,8 +1028,11 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     p.layer = layer;
     p.finished = finished;
     if (sd.rb == 1 && N <= 8L * kMaxGridY && (algo == DA_RB_RM_SR || algo == DA_RB_CM_SR || (algo == DA_RB_RM_PR && N >= 5)) &&
-        std::getenv("DA_SPMM_TUNE") == nullptr)
-        return launch_columns(p, lookup_matrix(rowptr, m));
+        std::getenv("DA_SPMM_TUNE") == nullptr) {
+        // a single column of C lies the same way in either order
+        const MatrixHint hint = lookup_matrix(rowptr, m);
+        if (columns_pay(algo, m, k, N, sd.rc != 1, hint)) return launch_columns(p, hint);
+    }
     const bool ask = eb || (!cm && !pr && N > 16 && (N < 32 || N % 4 != 0 || ends % 16 != 0));   // RB: only where the lanes depend on it
     const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);

@@ -24,7 +24,7 @@ def test_column_major_products(name, known, c_col):
     dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (a.rowptr, a.colind, a.vals)]
     if known:
         da.da_spmm_features(a.m, 8, dev[0])
-    for N in (1, 2, 3, 4, 5, 7, 8, 9, 16, 21):
+    for N in (1, 2, 3, 4, 5, 7, 8, 9, 16, 21, 24, 33):
         ldb, ldc = a.k + 3, (a.m + 2 if c_col else N + 2)
         B = np.full((N, ldb), np.nan, np.float32)
         B[:, :a.k] = gen.dense_int(a.k, N, seed=N).T
@@ -49,3 +49,23 @@ def test_infinities_stay_in_their_rows():
     C = torch.empty((6, a.m), device="cuda")
     da.da_spmm_ex(a.m, a.k, 6, *dev, a.k, da.DA_COL_MAJOR, C, a.m, da.DA_COL_MAJOR, da.DA_RB_RM_SR)
     assert np.isfinite(want).any() and np.array_equal(C.t().cpu().numpy(), want, equal_nan=True)
+
+
+# known: the lanes follow the rows; unknown: only where no sparsity law was slower for it
+@pytest.mark.parametrize("name,known,N,algo,here", [
+    ("stencil", True, 8, 0, True), ("stencil", True, 8, 1, True), ("stencil", True, 8, 2, True), ("uneven", True, 8, 1, True),
+    ("short", True, 1, 0, True), ("longer", True, 8, 1, False), ("longer", True, 16, 0, True),
+    ("stencil", False, 8, 0, False), ("stencil", False, 8, 1, False), ("short", False, 1, 2, False), ("uneven", False, 23, 0, False), ("uneven", False, 24, 0, True)])
+def test_which_calls_take_the_kernel(name, known, N, algo, here):
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    a = MATRICES[name]()
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (a.rowptr, a.colind, a.vals)]
+    others = [torch.zeros(10, dtype=torch.int32, device="cuda") for _ in range(16)]
+    for rowptr in others:                             # push out what is known of a matrix that lay here before
+        da.da_spmm_features(9, 1, rowptr)
+    if known:
+        da.da_spmm_features(a.m, N, dev[0])
+    B, C = torch.ones((N, a.k), device="cuda"), torch.empty((N, a.m), device="cuda")
+    names = kernels_of(lambda: da.da_spmm_ex(a.m, a.k, N, *dev, B, a.k, da.DA_COL_MAJOR, C, a.m, da.DA_COL_MAJOR, algo))
+    assert any("rb_columns_kernel" in n for n in names) == here, names
