@@ -474,26 +474,36 @@ Tensor aggregate(const GraphPtr& g, const Arrays& a, const Tensor& X, const Tens
     return Y;
 }
 
-// A . W, into `out` (unit column stride): three ways.  Products of bf16 pieces from some 5000 weights on where the
-// fp32 matrix cores are the bound (100 000 rows: 128 x 128 55 us on them, 36 in pieces; 262 144 rows: 128 x 41 49 and
-// 42, 64 x 32 22 and 24), if that pays for the launch that lays the weights out (100 003 rows: 96 x 64 25 and 23, but a
-// training step of such a layer 294 and 299), and for long sums (262 144 rows: 256 x 16 62 and 51).  A block of theirs has
-// 128 rows and walks the whole sum, so few rows of long sums are the GEMM library's, which splits them (k = 602,
-// n = 128: 20 000 rows 44 us there, 40 here; 8000 rows 21 and 37; 262 144 rows 358 and 259).  Small weights: the fp32
-// kernel, which keeps them in LDS, while the inner dimension is at most 128 and, whatever the size, where the
-// library's 18 us of host time are the larger part.
+// Whether bf16 pieces are the best way for rows x k times k x n.
+// Up to 192 inner positions: from some 5000 weights on where the fp32 matrix cores are the bound (100 000 rows: 128 x 128 55 us on
+// them, 36 in pieces; 262 144 rows: 128 x 41 49 and 42, 64 x 32 22 and 24), if that pays for the launch that lays the weights
+// out (100 003 rows: 96 x 64 25 and 23, but a training step of such a layer 294 and 299); below 64 positions C is most of the
+// traffic, which the fp32 kernel writes faster (200 000 rows, 32 x 256: 56 and 64; 300 000, 32 x 512: 255 and 170).
+// Up to 256 the fp32 kernel has its weights in LDS for few columns and saves a launch (256 x 16: 1000 rows 7.1 and 11.0,
+// 100 000 22.7 and 27.5, 300 000 67.7 and 60.7; 256 x 41: 10 000 rows 11.6 and 13.0, 30 000 17.2 and 14.2; 256 x 64: 12.8 and 12.2).
+// Beyond, the library: a block of pieces has 128 rows and walks the whole sum, so few rows of long sums are the library's,
+// which splits them (layers, with the library's host time: 602 x 128: 5000 rows 25 and 28; 400 x 128: 15 000 27 and 30; 1000 x 8:
+// 40 000 35 and 41; kernels alone: 602 x 128: 20 000 rows 44 and 40, 262 144 358 and 259; 602 x 24: 100 000 116 and 54).
+bool pieces_pay(int64_t rows, int64_t k, int64_t n) {
+    if (k < 32 || n > 512) return false;
+    if (k <= 192) return k * n >= 5000 && rows * k * n >= (k < 64 ? 1800000000 : 1000000000);
+    if (k <= 256) return n > (rows < 20000 ? 48 : rows < 200000 ? 16 : rows < 250000 || k < 224 ? 8 : 0);
+    return rows >= (n <= 16 && k >= 900 ? 50 : n == 96 || n == 128 ? 40 : 30) * k;
+}
+
+// A . W, into `out` (unit column stride): bf16 pieces, the fp32 kernel, which keeps the weights in LDS (up to 128 inner positions,
+// and up to 256 for few columns and where the library's 18 us of host time are the larger part), or the GEMM library.
 void dense_product(const Tensor& A, const Tensor& W, bool transpose_w, Tensor& out) {
     const int64_t rows = A.size(0), k = A.size(1), n = out.size(1);
     if (A.stride(1) == 1 && W.is_contiguous()) {
         const int64_t wk = transpose_w ? 1 : n, wn = transpose_w ? k : 1;
         size_t bytes = 0;
-        if (k >= 32 && ((k * n >= 5000 && rows * k * n >= 1000000000) || k > 192) && (k <= 256 || rows >= 30 * k) && n <= 512 &&
-            da_spmm_dense_split_workspace(k, n, &bytes) == DA_OK) {
+        if (pieces_pay(rows, k, n) && da_spmm_dense_split_workspace(k, n, &bytes) == DA_OK) {
             Tensor ws = at::empty({(int64_t)bytes}, A.options().dtype(at::kByte));
             const int st = da_spmm_dense_split(rows, k, n, data<float>(A), leading(A), data<float>(W), wk, wn, data<float>(out),
                                                leading(out), data<void>(ws), bytes, stream_of(A));
             if (st != DA_ERR_UNSUPPORTED) return check(st);
-        } else if (k >= 1 && (k <= 128 || (k <= 256 && rows * k * n <= 300000000))) {
+        } else if (k >= 1 && (k <= 128 || (k <= 256 && (n <= 16 || rows * k * n <= 300000000)))) {
             const int st = da_spmm_dense(rows, k, n, data<float>(A), leading(A), data<float>(W), wk, wn, data<float>(out),
                                          leading(out), stream_of(A));
             if (st != DA_ERR_UNSUPPORTED) return check(st);

@@ -129,3 +129,27 @@ def test_graph_outside_plain_backward_differentiation():
         assert torch.allclose(gcn.aggregate(twin, X), Y, rtol=1e-4, atol=1e-6)
     graph.vals = graph.vals * 2
     assert torch.allclose(gcn.aggregate(graph, X), 2 * Y, rtol=1e-4, atol=1e-6)
+
+
+# either side of the lines between the fp32 kernel, the one of bf16 pieces and the GEMM library
+@pytest.mark.parametrize("rows,fin,fout,way", [
+    (1000, 128, 128, "dense_product"), (70000, 128, 128, "dense_split"), (1000, 256, 16, "dense_product"), (100000, 256, 16, "dense_product"),
+    (10000, 200, 41, "dense_product"), (20000, 200, 41, "dense_split"), (100, 256, 64, "dense_split"), (20000, 256, 256, "dense_split"),
+    (11000, 300, 128, "library"), (12000, 300, 128, "dense_split"), (9000, 300, 64, "dense_split"), (8000, 300, 64, "library"), (40000, 300, 513, "library"),
+    (60000, 200, 193, "dense_split"), (4000, 31, 300, "dense_product")])
+def test_ways_of_the_dense_product(rows, fin, fout, way):
+    from paper_2202_08556_amd import gcn
+    from tests.gpu_util import kernels_of
+    print(f"dense {rows} x {fin} x {fout}", flush=True)
+    picked = torch.tensor([0, 1, rows // 2, rows - 1], dtype=torch.int32, device="cuda")
+    graph = gcn.SparseGraph(4, rows, torch.arange(5, dtype=torch.int32, device="cuda"), picked, torch.ones(4, device="cuda"))
+    layer = gcn.GraphConv(fin, fout, bias=False, relu=False).cuda()
+    X = torch.randn((rows, fin), device="cuda")
+    with torch.no_grad():
+        got = layer(graph, X)
+        names = kernels_of(lambda: layer(graph, X))
+    x = X[picked.long()].double()
+    want, size = x @ layer.weight.double(), x.abs() @ layer.weight.double().abs()
+    assert ((got - want).abs() <= (3 + fin ** 0.5) * 2.0 ** -24 * size).all()
+    ours = [w for w in ("dense_product", "dense_split") if any(w + "_kernel" in n for n in names)]
+    assert ours == ([] if way == "library" else [way]), names
