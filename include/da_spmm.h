@@ -300,7 +300,7 @@ int da_spmm_dense(int64_t rows, int64_t k, int64_t n, const float *A, int64_t ld
  * The same product, arguments and results (as exact) on the bf16 matrix cores: every fp32 number is the exact sum of
  * three bf16 numbers, six products of pieces stand for one; results that the pieces do not carry (not finite, or near
  * the smallest numbers) are computed in fp32.  32 <= k <= 2^20, n <= 2^14, rows <= 2^30; DA_ERR_UNSUPPORTED beyond.
- *   workspace  device scratch of the size da_spmm_dense_split_workspace reports (6.2 bytes per weight, columns rounded
+ *   workspace  device scratch of the size da_spmm_dense_split_workspace reports (6.14 bytes per weight, columns rounded
  *              up to 16, inner positions to 32), 16-byte aligned, free for reuse once the stream has passed the call
  */
 int da_spmm_dense_split_workspace(int64_t k, int64_t n, size_t *bytes /* host, out */);

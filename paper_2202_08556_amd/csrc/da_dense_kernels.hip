@@ -380,10 +380,16 @@ __global__ __launch_bounds__(kDpBlock) void dense_product_kernel(
 // splitting W in every block instead of once per call took 300 us.  Error against float64 (2-norm, relative): 1.4e-7,
 // the library's 4.4e-7.
 //
-// Results that the pieces do not carry are computed again on the fp32 matrix cores, wave by wave: where one is
-// not finite (infinities split into infinity and NaN, numbers next to the largest round to infinity) or so small
-// that pieces may have been lost below the smallest normal number, or where an operand is that small.
+// Results that the pieces do not carry are computed again on the fp32 matrix cores, 32 rows of 16 columns at a time: where one
+// is not finite (infinities split into infinity and NaN, numbers next to the largest round to infinity) or so small that
+// products of pieces may have been lost below the smallest normal number.  Pieces of numbers below 2^-100 may be lost
+// there, too, up to 2^-125 of a number and with it that much of the largest number it is multiplied by, k times over at
+// most: results are computed again that are not 2^26 times as large.  Only waves that hold such a number, or whose weights
+// do, look for the largest ones, so that one among ordinary numbers costs next to nothing (262 144 x 602 x 128: 270 us with such
+// a weight, 274 with such a number in one row of 64, 263 without; 576 where these rows hold nothing larger, 705 where
+// all results are that small).
 // ------------------------------------------------------------------------------------------
+template <bool B> struct Truth { static constexpr bool value = B; };
 constexpr int kSplitBlock = 256, kSplitRows = 128, kSplitStep = 32;   // 4 waves of 32 rows
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -423,26 +429,36 @@ __device__ __forceinline__ void lds_barrier() {
 __host__ __device__ constexpr int split_steps(int k) { return (k + kSplitStep - 1) / kSplitStep; }
 
 // Pieces of W: frag[((step * tiles + tile) * 3 + piece) * 64 + lane], tile = 16 columns; columns past the last repeat it.
-// tiny[step * tiles + tile]: whether a weight is that small.  One wave per step and tile.
+// tiny[step * tiles + tile]: whether a weight is that small.  sizes[(step * tiles + tile) * 16 + column]: the largest weight of
+// the column, the sign bit set where one is that small.  One wave per step and tile.
+constexpr size_t kSplitBytes = 192 * sizeof(bf16x8) + 17 * sizeof(int);   // of the workspace, for a step and tile
+
 __global__ __launch_bounds__(64) void dense_split_weights_kernel(int k, int n, const float* __restrict__ W, long wk, long wn,
-                                                                 bf16x8* __restrict__ frag, int* __restrict__ tiny)
+                                                                 bf16x8* __restrict__ frag, unsigned* __restrict__ sizes, int* __restrict__ tiny)
 {
     const int step = blockIdx.x, tile = blockIdx.y, tiles = gridDim.y, lane = threadIdx.x;
     const int p0 = min(step * kSplitStep, k - kSplitStep) + 4 * (lane >> 4);
     const float* __restrict__ w = W + (long)min(tile * 16 + (lane & 15), n - 1) * wn;
     float x[8];
-    unsigned least = ~0u;
+    unsigned least = ~0u, most = 0u;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int p = p0 + (e & 3) + 16 * (e >> 2);
         x[e] = w[(long)p * wk];
         x[e] = p >= step * kSplitStep ? x[e] : 0.f;
         least = min(least, tiny_key(x[e]));
+        most = max(most, __float_as_uint(x[e]) & 0x7fffffffu);
     }
     const SplitFrag f = split8(x);
     const long at = (long)step * tiles + tile;
 #pragma unroll
     for (int q = 0; q < 3; ++q) frag[(at * 3 + q) * 64 + lane] = f.p[q];
+#pragma unroll
+    for (int d = 16; d <= 32; d *= 2) {
+        least = min(least, (unsigned)__shfl_xor((int)least, d));
+        most = max(most, (unsigned)__shfl_xor((int)most, d));
+    }
+    if (lane < 16) sizes[at * 16 + lane] = most | (least < kSplitTiny ? 0x80000000u : 0u);
     const bool any = __any(least < kSplitTiny);
     if (lane == 0) tiny[at] = any;
 }
@@ -451,7 +467,8 @@ __global__ __launch_bounds__(64) void dense_split_weights_kernel(int k, int n, c
 template <int NT>
 __global__ __launch_bounds__(kSplitBlock, 2) void dense_split_kernel(
     int rows, int n, int k, const float* __restrict__ A, long lda, const float* __restrict__ W, long wk, long wn,
-    const bf16x8* __restrict__ frag, const int* __restrict__ tiny, int tiles, float* __restrict__ C, long ldc)
+    const bf16x8* __restrict__ frag, const unsigned* __restrict__ sizes, const int* __restrict__ tiny, int tiles, float* __restrict__ C,
+    long ldc)
 {
     constexpr int kFrags = 3 * NT * 64;                    // 16-byte pieces of a step
     constexpr int WL = (kFrags + kSplitBlock - 1) / kSplitBlock;
@@ -472,6 +489,7 @@ __global__ __launch_bounds__(kSplitBlock, 2) void dense_split_kernel(
     }
     bool w_tiny = false;
     for (int s = lane; s < steps * tiles; s += 64) w_tiny |= tiny[s] != 0;
+    w_tiny = __any(w_tiny);
 
     float x[16];
     bf16x8 w[WL];
@@ -496,7 +514,7 @@ __global__ __launch_bounds__(kSplitBlock, 2) void dense_split_kernel(
     for (int r = 0; r < 2; ++r)
 #pragma unroll
         for (int t = 0; t < NT; ++t) big[r][t] = small[r][t] = mfma_acc{0.f, 0.f, 0.f, 0.f};
-    unsigned least = ~0u;
+    unsigned least[2] = {~0u, ~0u}, most[2] = {0u, 0u};   // of the rows' numbers; most only if w_tiny
     fetch_w(0);
     fetch_a(0);
     for (int s = 0; s < steps; ++s) {
@@ -508,7 +526,13 @@ __global__ __launch_bounds__(kSplitBlock, 2) void dense_split_kernel(
         for (int r = 0; r < 2; ++r) {
             a[r] = split8(x + 8 * r);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) least = min(least, tiny_key(x[8 * r + q]));
+            for (int q = 0; q < 8; ++q) least[r] = min(least[r], tiny_key(x[8 * r + q]));
+        }
+        if (w_tiny) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) most[r] = max(most[r], __float_as_uint(x[8 * r + q]) & 0x7fffffffu);
         }
         fetch_w(min(s + 1, steps - 1));                // in flight across the barrier and the matrix instructions
         fetch_a(min(s + 1, steps - 1));
@@ -529,35 +553,122 @@ __global__ __launch_bounds__(kSplitBlock, 2) void dense_split_kernel(
         }
     }
 
-    bool again = least < kSplitTiny || w_tiny;
+    // sizes of results, sign dropped: other than zero below 2^-90, not finite
+    constexpr unsigned kResultTiny = (37u << 24) - 1u, kResultMost = 0xfefffffeu;
+    unsigned low = ~0u, high = 0u;
+    auto look = [&](const mfma_acc& x) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            low = min(low, tiny_key(x[q]));
+            high = max(high, __float_as_uint(x[q]) << 1);
+        }
+    };
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             big[r][t] += small[r][t];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float size = fabsf(big[r][t][q]);
-                again |= !(size <= 3.402823466e38f) || (size != 0.f && size < 8.077936e-28f);      // 2^-90
-            }
+            look(big[r][t]);
         }
-    if (__any(again)) {
+    unsigned again = 0u;                                   // bit t: tile t
+    if (__any((low < kResultTiny) | (high > kResultMost))) {
 #pragma unroll
-        for (int r = 0; r < 2; ++r)
+        for (int t = 0; t < NT; ++t) {
+            low = ~0u;
+            high = 0u;
+            look(big[0][t]);
+            look(big[1][t]);
+            again |= (unsigned)((low < kResultTiny) | (high > kResultMost)) << t;
+        }
+    }
+    if (w_tiny || __any(min(least[0], least[1]) < kSplitTiny)) {
+        float row_most[2];                                 // what tiny weights may have lost is that much times 2^-125
+        bool row_tiny[2];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) big[r][t] = mfma_acc{0.f, 0.f, 0.f, 0.f};
-        for (int p0 = 0; p0 < k; p0 += 4) {
-            const int p = p0 + h;
-            float u[2], v[NT];
+        for (int r = 0; r < 2; ++r) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) u[r] = p < k ? A[min(first + 16 * r, (long)rows - 1) * lda + p] : 0.f;
+            for (int d = 16; d <= 32; d *= 2) {
+                least[r] = min(least[r], (unsigned)__shfl_xor((int)least[r], d));
+                most[r] = max(most[r], (unsigned)__shfl_xor((int)most[r], d));
+            }
+            row_most[r] = __uint_as_float(most[r]);
+            row_tiny[r] = least[r] < kSplitTiny;
+        }
+        const float per = (float)k * 1.5777218e-30f;       // 2^-99
 #pragma unroll
-            for (int t = 0; t < NT; ++t) v[t] = p < k ? W[(long)p * wk + (long)min(n0 + 16 * t + i, n - 1) * wn] : 0.f;
+        for (int t = 0; t < NT; ++t) {
+            const unsigned* __restrict__ of_tile = sizes + (long)min(tile0 + t, tiles - 1) * 16 + 4 * h;
+            unsigned col_most[4] = {0u, 0u, 0u, 0u}, col_tiny = 0u;
+            for (int s = i; s < steps; s += 16)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const unsigned x = of_tile[(long)s * tiles * 16 + q];
+                    col_most[q] = max(col_most[q], x & 0x7fffffffu);
+                    col_tiny |= (x >> 31) << q;
+                }
+#pragma unroll
+            for (int d = 1; d <= 8; d *= 2) {
+                col_tiny |= (unsigned)__shfl_xor((int)col_tiny, d);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) col_most[q] = max(col_most[q], (unsigned)__shfl_xor((int)col_most[q], d));
+            }
+            float spare = 0.f;                             // below zero where a result is too small
 #pragma unroll
             for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int t = 0; t < NT; ++t) big[r][t] = mfma16(v[t], u[r], big[r][t]);
+                for (int q = 0; q < 4; ++q) {
+                    const float a = row_tiny[r] ? __uint_as_float(col_most[q]) : 0.f, b = (col_tiny >> q & 1u) ? row_most[r] : 0.f;
+                    spare = fminf(spare, fabsf(big[r][t][q]) - per * fmaxf(a, b));
+                }
+            again |= (unsigned)(spare < 0.f) << t;
         }
+    }
+    if (__any(again != 0u)) {
+        unsigned redo = 0u;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) redo |= __any(again >> t & 1u) ? 1u << t : 0u;
+        // 16 positions at a time, 4 of them a lane's own; the last ones begin 16 before the end and leave out what was there.
+        // From three tiles on all of them: loads of all tiles are then in flight together.
+        auto fp32 = [&](auto all) {
+            constexpr bool ALL = decltype(all)::value;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                if (ALL || (redo >> t & 1u)) big[0][t] = big[1][t] = mfma_acc{0.f, 0.f, 0.f, 0.f};
+            for (int p0 = 0; p0 < k; p0 += 16) {
+                const int p = min(p0, k - 16) + 4 * h;
+                float u[2][4], v[NT][4];
+                auto fetch = [&](int t) {
+                    const float* __restrict__ wcol = W + (long)min(n0 + 16 * t + i, n - 1) * wn;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[t][e] = wcol[(long)(p + e) * wk];
+                };
+                auto multiply = [&](int t) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = p + e >= p0 ? v[t][e] : 0.f;
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) big[r][t] = mfma16(x, u[r][e], big[r][t]);
+                    }
+                };
+                if constexpr (ALL)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) fetch(t);
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const float4 x4 = load4(arow[r] - 4 * h + p);
+                    u[r][0] = x4.x; u[r][1] = x4.y; u[r][2] = x4.z; u[r][3] = x4.w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) u[r][e] = p + e >= p0 ? u[r][e] : 0.f;
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    if constexpr (ALL) multiply(t);
+                    else if (redo >> t & 1u) { fetch(t); multiply(t); }
+                }
+            }
+        };
+        if (__popc(redo) > 2) fp32(Truth<true>{});
+        else fp32(Truth<false>{});
     }
     typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll

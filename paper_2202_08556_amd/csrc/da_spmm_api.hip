@@ -1768,7 +1768,7 @@ int da_spmm_dense_split_workspace(int64_t k, int64_t n, size_t* bytes)
     if (k < 0 || n < 0) return fail(DA_ERR_INVALID_ARG, "negative size%s");
     if (k > kSplitMaxInner || n > kSplitMaxCols) return fail(DA_ERR_UNSUPPORTED, "size too large%s");
     const size_t pieces = (size_t)split_steps((int)k) * (size_t)((n + 15) / 16);
-    *bytes = pieces * (192 * sizeof(bf16x8) + sizeof(int));
+    *bytes = pieces * kSplitBytes;
     return DA_OK;
 }
 
@@ -1789,13 +1789,14 @@ int da_spmm_dense_split(int64_t rows, int64_t k, int64_t n, const float* A, int6
     hipStream_t s = (hipStream_t)stream;
     const int steps = split_steps((int)k), tiles = (int)((n + 15) / 16);
     bf16x8* frag = static_cast<bf16x8*>(workspace);
-    int* tiny = reinterpret_cast<int*>(frag + (size_t)steps * tiles * 192);
+    unsigned* sizes = reinterpret_cast<unsigned*>(frag + (size_t)steps * tiles * 192);
+    int* tiny = reinterpret_cast<int*>(sizes + (size_t)steps * tiles * 16);
     hipLaunchKernelGGL(dense_split_weights_kernel, dim3((unsigned)steps, (unsigned)tiles), dim3(64), 0, s, (int)k, (int)n, W, (long)wk,
-                       (long)wn, frag, tiny);
+                       (long)wn, frag, sizes, tiny);
     auto go = [&](auto nt) {
         constexpr int NT = decltype(nt)::value;
         hipLaunchKernelGGL((dense_split_kernel<NT>), dim3((unsigned)((rows + kSplitRows - 1) / kSplitRows), (unsigned)((tiles + NT - 1) / NT)),
-                           dim3(kSplitBlock), 0, s, (int)rows, (int)n, (int)k, A, (long)lda, W, (long)wk, (long)wn, frag, tiny, tiles, C,
+                           dim3(kSplitBlock), 0, s, (int)rows, (int)n, (int)k, A, (long)lda, W, (long)wk, (long)wn, frag, sizes, tiny, tiles, C,
                            (long)ldc);
     };
     if (tiles <= 2) go(Count<2>{});

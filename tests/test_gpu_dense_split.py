@@ -1,5 +1,5 @@
 """da_spmm_dense_split (fp32 products as products of bf16 pieces) at the edges of its tiles and steps against float64,
-its error against the fp32 kernel's, and numbers that the pieces do not carry."""
+its error against the fp32 kernel's, and numbers that the pieces do not carry or carry in part."""
 import pytest
 import torch
 
@@ -67,6 +67,47 @@ def test_numbers_that_pieces_do_not_carry(value, where):
     assert torch.equal(got[~finite & ~torch.isnan(want)].double().sign(), want[~finite & ~torch.isnan(want)].sign())
     bound = (3 + k ** 0.5) * 2.0 ** -24 * (X.double().abs() @ W.double().abs()) + k * 2.0 ** -149
     assert ((got.double() - want).abs() <= bound)[finite].all()
+
+
+# small numbers among ordinary ones: what their pieces lose matters where they meet large ones, and in columns of nothing else
+@pytest.mark.parametrize("where", ["X", "W"])
+@pytest.mark.parametrize("value,other", [(1e-40, 1.0), (1e-36, 1e30), (3e-34, 1e24), (1e-31, 1e12), (1e-38, 0.0)])
+@pytest.mark.parametrize("rows,k,n", [(300, 70, 50), (129, 33, 130), (64, 47, 16)])
+def test_small_numbers_among_others(where, value, other, rows, k, n):
+    g = torch.Generator().manual_seed(5)
+    X, W = torch.randn((rows, k), generator=g), torch.randn((k, n), generator=g)
+    X[5], W[:, 3] = 0.0, 0.0                                      # rows and columns of zeros stay zeros
+    if where == "X":
+        X[20, 10] = X[40, 10] = X[63, k - 1] = value
+        W[10, ::2], W[k - 1, 1] = other, other
+        X[40] *= 1e-30                                            # a row of nothing but small numbers
+    else:
+        W[10, 7], W[k - 1, 15] = value, -value
+        W[:, n - 1] *= 1e-33
+        X[::3, 10], X[7, k - 1] = other, other
+    want = X.double() @ W.double()
+    got = split(X.cuda(), k, W.cuda(), n, 1, rows, k, n, n).cpu()
+    bound = (3 + k ** 0.5) * 2.0 ** -24 * (X.double().abs() @ W.double().abs()) + k * 2.0 ** -149
+    assert ((got.double() - want).abs() <= bound).all()
+    assert not got[5].any() and not got[:, 3].any()
+
+
+# infinities and NaN beside small numbers, in the last positions, which the last step reads once more
+@pytest.mark.parametrize("k", [32, 33, 47, 48, 49, 70])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_what_is_not_finite_stays_where_it_is(k, value):
+    g = torch.Generator().manual_seed(7)
+    X, W = torch.randn((200, k), generator=g), torch.randn((k, 40), generator=g).abs() + 1.0
+    for j, p in enumerate(range(max(0, k - 34), k)):
+        X[3 * j, p] = value
+    X[150, 2], W[1, 30] = 1e-42, 1e-42
+    want = X.double() @ W.double()
+    got = split(X.cuda(), k, W.cuda(), 40, 1, 200, k, 40, 40).cpu()
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.equal(got[torch.isinf(got)].double(), want[torch.isinf(want)])
+    fine = torch.isfinite(want)
+    bound = (3 + k ** 0.5) * 2.0 ** -24 * (X.double().abs() @ W.double().abs())
+    assert ((got.double() - want).abs() <= bound)[fine].all()
 
 
 def test_split_errors():
