@@ -15,6 +15,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <vector>
 
 namespace {
@@ -1437,14 +1438,17 @@ constexpr int64_t kHeavyShare = 32, kHeavyMinCols = 16384, kHeavyMinEntries = 40
 constexpr int kHeavyMost = 8192, kHeavyCells = 1024, kRestLongest = 1024;
 constexpr double kRestLen = 64.0;
 
+// Without the memory for it there is no list: it steers the launches of products, the orders do without it.
+int no_heavy_rows() { (void)hipGetLastError(); return DA_OK; }
+
 int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, const int32_t* colind, hipStream_t s, Plan* pl)
-{
+try {
     if (k < kHeavyMinCols || nnz < kHeavyMinEntries || nnz >= (1LL << 30)) return DA_OK;
     const int min_len = (int)(k / kHeavyShare);
     DeviceBlock tmp;                                       // count and flag, sums, list
     const size_t tmp_bytes = 64 + kHeavyMost * sizeof(int);
     hipError_t e = hipMalloc(&tmp.p, tmp_bytes);
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+    if (e != hipSuccess) return no_heavy_rows();
     int* count = static_cast<int*>(tmp.p);
     unsigned long long* sums = reinterpret_cast<unsigned long long*>(count + 4);
     int* list = count + 16;
@@ -1466,7 +1470,7 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     std::vector<int> ptr(2 * rows.size());
     DeviceBlock pairs;
-    if (e == hipSuccess) e = hipMalloc(&pairs.p, 2 * rows.size() * sizeof(int));
+    if (e == hipSuccess && hipMalloc(&pairs.p, 2 * rows.size() * sizeof(int)) != hipSuccess) return no_heavy_rows();
     if (e == hipSuccess) {
         hipLaunchKernelGGL(heavy_row_ends_kernel, dim3((unsigned)((rows.size() + 255) / 256)), dim3(256), 0, s, (int)rows.size(), list, rowptr,
                            static_cast<int*>(pairs.p));
@@ -1494,8 +1498,7 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     const size_t words = (size_t)(m + 31) / 32, n = rows.size();
     auto block = std::make_shared<DeviceBlock>();
     const size_t ints = ((n + 63) & ~size_t(63)) + ((words + 63) & ~size_t(63)) + n * (size_t)(cells + 1);
-    e = hipMalloc(&block->p, ints * sizeof(int));
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+    if (hipMalloc(&block->p, ints * sizeof(int)) != hipSuccess) return no_heavy_rows();
     int* drows = static_cast<int*>(block->p);
     unsigned* bits = reinterpret_cast<unsigned*>(drows + ((n + 63) & ~size_t(63)));
     int* at = reinterpret_cast<int*>(bits + ((words + 63) & ~size_t(63)));
@@ -1516,6 +1519,8 @@ int plan_heavy_rows(int64_t m, int64_t k, int64_t nnz, const int32_t* rowptr, co
     pl->rest_longest = (int)host.mx;
     pl->heavy_sums = row_sums;
     pl->heavy_block = block;
+    return DA_OK;
+} catch (const std::bad_alloc&) {
     return DA_OK;
 }
 

@@ -156,6 +156,41 @@ def test_products_that_declare_other_columns_than_prepare(declared, N):
     assert np.array_equal(got, want.astype(np.float32) + 0.0)
 
 
+# 8000 rows' list takes 32 MB, the orders some 8: with 20 MB left prepare goes without the list
+def test_prepare_without_the_memory_for_the_list():
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    m, each = 8200, 640
+    rng = np.random.Generator(np.random.PCG64(3))
+    lens = np.where(np.arange(m) % 41 < 40, each, 2)
+    first = rng.integers(0, K - 20 * each, m)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    colind = np.concatenate([first[r] + 20 * np.arange(n) for r, n in enumerate(lens)]).astype(np.int32)
+    vals = rng.choice(np.array([-2, -1, 1, 2], np.float32), colind.size)
+    B = dense(4)
+    want, _ = orc.spmm(rowptr, colind, vals, B)
+    dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals, B)]
+    C = torch.empty((m, 4), device="cuda")
+    call = lambda: da.da_spmm(m, K, 4, *dev, C, da.DA_EB_RM_SR)  # noqa: E731
+    da.da_spmm_prepare(m, K, colind.size, dev[0], dev[1])          # with memory: all code is loaded, pools are filled
+    assert any("heavy_rows_kernel" in n for n in kernels_of(call))
+    da.da_spmm_release(dev[0])
+    torch.cuda.empty_cache()
+    fill = []
+    while (free := torch.cuda.mem_get_info()[0]) > 22 << 20:
+        fill.append(torch.empty(max(free - (20 << 20), 1 << 20), dtype=torch.uint8, device="cuda"))
+    print("left free", free >> 20, "MB", flush=True)
+    try:
+        da.da_spmm_prepare(m, K, colind.size, dev[0], dev[1])
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    names = kernels_of(call)
+    da.da_spmm_release(dev[0])
+    assert any("eb_sr_kernel" in n for n in names) and not any("heavy_rows_kernel" in n for n in names)
+    assert np.array_equal(C.cpu().numpy(), want.astype(np.float32) + 0.0)
+
+
 def test_unsorted_columns_have_no_plan_and_stay_right():
     from paper_2202_08556_amd import binding as da
     rowptr, colind, vals = matrix(11)
