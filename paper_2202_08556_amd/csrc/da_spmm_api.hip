@@ -75,7 +75,7 @@ enum Family { RB_SR, RB_PR, EB_SR, EB_PR };
 // the number of stored entries per worker.
 struct Geometry {
     int V, G, NV, chunk;
-    bool pin;   // pin column tiles to XCDs when the tile count is 2, 4 or 8
+    int pin;    // pin column tiles to XCDs when the tile count is 2, 4 or 8: 1 yes, 0 no, -1 as launch_w finds it best
     int stripe; // blocks per stripe when a prepared matrix's chunk order is dealt to the XCDs (0: off)
     bool order; // take a prepared matrix's chunk order
 };
@@ -321,7 +321,7 @@ int chunk_size(bool cm, bool pr, int64_t N, bool whole, const Geometry& g, const
 int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides& sd, bool aligned,
                   const MatrixHint& hint, PlanInfo plan, Geometry* out) {
     const bool vec4_ok = N >= 4 && sd.cb == 1 && sd.cc == 1;      // 16-byte accesses, at any alignment
-    Geometry g{1, 1, 1, 0, false, kSweepStripe, true};
+    Geometry g{1, 1, 1, 0, -1, kSweepStripe, true};
     if (plan.found && N <= 32 && hint.nnz >= 0) {
         const int64_t waves = (int64_t)cu_count() * 16;
         const bool bare = pr ? hint.nnz < 8 * m && hint.nnz > 64 * waves && hint.nnz < kEntriesPerWavePR * waves
@@ -351,7 +351,7 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides
         g.V = env_int("DA_SPMM_V", g.V);
         g.G = env_int("DA_SPMM_G", g.G);
         g.NV = env_int("DA_SPMM_NV", g.NV);
-        g.pin = env_int("DA_SPMM_PIN", g.pin ? 1 : 0) != 0;
+        g.pin = env_int("DA_SPMM_PIN", -1);
         g.stripe = env_int("DA_SPMM_STRIPE", g.stripe);
         if (g.stripe < 0 || g.stripe > 4096) return fail(DA_ERR_UNSUPPORTED, "DA_SPMM_STRIPE outside 0..4096%s");
         if ((g.V != 1 && g.V != 4) || (g.V == 4 && !vec4_ok) || !is_pow2(g.G) || g.G > kWave ||
@@ -399,7 +399,7 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     // 5000 11.3 -> 9.3, 24 000 62.2 -> 60.9, 27-point stencil of 28^3 28.6 -> 24.2.  4096 columns, N = 256, 4.2 MB: 6.1 and 6.2).
     const bool slices_fit = V == 4 && G >= 16 && (fam == RB_SR || fam == RB_PR) && p.sd.cb == 1 &&
                             tiles_l * tile_cols - p.N <= tile_cols / 8 && p.k * tile_cols * 4 <= 12 << 20 && (long)p.k * p.N * 4 > 9 << 19;
-    const int pin = ((geo.pin || slices_fit) && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
+    const int pin = ((geo.pin < 0 ? slices_fit : geo.pin != 0) && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
     // grid for `bx` blocks per column tile
     auto grid_for = [&](long bx) {
         if (pin) { const long per = 8 / pin; return dim3((unsigned)(8 * ((bx + per - 1) / per)), 1); }
@@ -1028,8 +1028,8 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     const uintptr_t ends = reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C) | (uintptr_t)(sd.rb * 4) | (uintptr_t)(sd.rc * 4);
     p.layer = layer;
     p.finished = finished;
-    if (sd.rb == 1 && N <= 8L * kMaxGridY && (algo == DA_RB_RM_SR || algo == DA_RB_CM_SR || (algo == DA_RB_RM_PR && N >= 5)) &&
-        std::getenv("DA_SPMM_TUNE") == nullptr) {
+    const bool tuned = std::getenv("DA_SPMM_TUNE") != nullptr;        // the launch geometry is that of the ids' own kernels
+    if (sd.rb == 1 && N <= 8L * kMaxGridY && (algo == DA_RB_RM_SR || algo == DA_RB_CM_SR || (algo == DA_RB_RM_PR && N >= 5)) && !tuned) {
         // a single column of C lies the same way in either order
         const MatrixHint hint = lookup_matrix(rowptr, m);
         if (columns_pay(algo, m, k, N, sd.rc != 1, hint)) return launch_columns(p, hint);
@@ -1038,7 +1038,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
-    if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
+    if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && !tuned && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
         // Heavy rows in a kernel of their own, the others, which are short and even, row by row.  A row is then added up
         // entry by entry; EB does that with up to a chunk of them.
         const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
