@@ -163,7 +163,10 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, 
  * order up by themselves; results are the same up to fp32 rounding order.  It also records what
  * da_spmm_features records.  A kernel that finds another nnz on the device than the plan was
  * built for ignores the plan, so a stale plan costs speed, never correctness; the contents of
- * colind may change freely.  Allocates and frees temporary device memory, synchronises `stream`.
+ * colind may change freely.  A list of such rows that turns out to be another matrix's (other rows are long
+ * now, or entries lie in other columns) makes one EB+RM+SR product many times slower than the EB kernels;
+ * the products after it go without the list, until the matrix is prepared again or da_spmm_features
+ * records another nnz for it.  Allocates and frees temporary device memory, synchronises `stream`.
  * Prepare, release and the product calls may be issued from several host threads; product calls do
  * not serialise each other (the plan table is locked only for the lookup; the plan's memory is
  * reference-counted and freed only after every call that looked it up has launched, and the free

@@ -21,8 +21,10 @@
 // The plan (da_spmm_prepare) lists the heavy rows and, per row and cell of columns, the position at which the cell's
 // entries begin.  As everywhere, a plan only steers: positions are clamped to the row, so that whatever they hold the
 // entries of a row are dealt to the blocks exactly once; an entry whose column is not in the band takes its operand
-// from memory; a listed row that is not heavy any more is left to the EB kernel, which leaves out a row only if it is
-// heavy by its present length and listed.
+// from memory; a listed row that is not heavy any more is left to the other rows' kernel, which leaves out a row only if it
+// is heavy by its present length and listed.  All that is slow: long rows that are not listed are added up row by row
+// (33 M entries, N = 64: 22 ms, 1.3 in the EB kernels), entries outside the band one after another.  So both kernels
+// mark a plan that does not describe the matrix, and later products do without it.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -42,6 +44,7 @@ struct HeavyPlan {
     const int* rows;     // count row numbers, by length
     const int* at;       // at[h * (cells + 1) + c]: position of the first entry of row h with column >= c * cell
     int count, cells, cell, min_len, nnz;
+    int* stale;          // in host memory
 };
 
 // Blocks of a launch: group i has the rows row[i] ... row[i + 1] - 1 of the plan and the blocks block[i] ... block[i + 1] - 1,
@@ -148,7 +151,11 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     int m, int k, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind, const float* __restrict__ vals,
     const float* __restrict__ B, float* __restrict__ C, HeavyPlan plan, HeavyGroups groups)
 {
-    if (rowptr[m] != plan.nnz) return;                     // a plan of another matrix: the EB kernel takes everything
+    if (rowptr[m] != plan.nnz) {                           // a plan of another matrix: the other rows' kernel takes everything
+        if (threadIdx.x == 0) *plan.stale = 1;
+        return;
+    }
+    bool strayed = false;                                  // whether the wave met an entry outside its band
     extern __shared__ __align__(16) char heavy_lds[];
     char* const lds = heavy_lds;
     constexpr int kBand = kHeavyBand<GL, V>, kRow = 4 * GL * V;              // rows of a band; bytes of a row in LDS
@@ -285,6 +292,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
 #pragma unroll
                     for (int w = 0; w < V; ++w) acc[i][w] += sum[w];           // one rounding of the long sum for 16 entries
                     if (__any(take && !inside)) {          // columns out of order, or a plan of another matrix
+                        strayed = true;
                         for (int n = 0; n < 16; ++n) {
                             const int cn = __shfl(now.c, 16 * g + n);
                             const float vn = __shfl(now.v, 16 * g + n);
@@ -317,6 +325,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
             buffer ^= 1;
         }
     }
+    if (strayed && lane == 0) *plan.stale = 1;
 #pragma unroll
     for (int i = 0; i < kHeavyQuads; ++i) {
         if (i < quads) {

@@ -129,7 +129,8 @@ constexpr int kPlanUnits[kPlans] = {32, 64, 128, 256, 512};     // plan_info rea
 constexpr int64_t kSmallPlanMaxNnz = 4 << 20;   // beyond, launches never take the smallest chunks: no order for them
 struct DeviceBlock {
     void* p = nullptr;
-    ~DeviceBlock() { if (p) (void)hipFree(p); }
+    ~DeviceBlock() { if (p) (void)hipFree(p); if (pinned) (void)hipHostFree(pinned); }
+    int* pinned = nullptr;
 };
 struct Plan {
     const void* rowptr = nullptr;
@@ -192,7 +193,8 @@ bool is_capturing(hipStream_t s) {
 }
 
 // The heavy rows of a prepared matrix; references and captures as for lookup_schedule.  The kernel reads every row of B
-// that the cells cover, used or not: products that declare other columns than da_spmm_prepare did go without.
+// that the cells cover, used or not: products that declare other columns than da_spmm_prepare did go without, and so do
+// those after one that found the list to be of another matrix.
 struct HeavyLookup {
     HeavyPlan plan{};
     const unsigned* bits = nullptr;
@@ -205,7 +207,8 @@ HeavyLookup lookup_heavy(const void* rowptr, const void* colind, int64_t m, int6
     HeavyLookup out;
     std::lock_guard<std::mutex> lk(g_plan_mu);
     for (auto& pl : g_plans)
-        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m && pl.heavy.count > 0 && pl.heavy_k == k) {
+        if (pl.block && pl.rowptr == rowptr && pl.colind == colind && pl.m == m && pl.heavy.count > 0 && pl.heavy_k == k &&
+            __atomic_load_n(pl.heavy.stale, __ATOMIC_RELAXED) == 0) {
             out.plan = pl.heavy;
             out.bits = pl.heavy_bits;
             out.rest_len = pl.rest_len;
@@ -1020,7 +1023,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
     sd.cb = layout_b == DA_ROW_MAJOR ? 1 : ldb;
     sd.rc = layout_c == DA_ROW_MAJOR ? ldc : 1;
     sd.cc = layout_c == DA_ROW_MAJOR ? 1 : ldc;
-    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{nullptr, nullptr, 0, 0}, nullptr, nullptr};
+    Problem p{(int)m, (int)N, sd, rowptr, colind, vals, B, C, (hipStream_t)stream, k, LeftOut{}, nullptr, nullptr};
     const bool eb = algo >= DA_EB_RM_SR;
     const bool cm = (algo & 2) != 0;
     const bool pr = (algo & 1) != 0;
@@ -1042,7 +1045,8 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
         // Heavy rows in a kernel of their own, the others, which are short and even, row by row.  A row is then added up
         // entry by entry; EB does that with up to a chunk of them.
         const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
-        if (heavy.plan.count > 0 && heavy.rest_longest <= g.chunk) {
+        const int64_t known = lookup_matrix(rowptr, m).nnz;              // the features may have been taken of another matrix since
+        if (heavy.plan.count > 0 && heavy.rest_longest <= g.chunk && (known < 0 || known == heavy.plan.nnz)) {
             const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk);
             if (heavy_rows_pay(m, N, sd.cb == 1, heavy.plan.count, heavy.plan.nnz, dealt.load * cu_count() / heavy.plan.nnz)) {
                 Problem q = p;
@@ -1051,7 +1055,8 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
                 const int rs = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
                                              PlanInfo{false, 0.0}, &rest);
                 if (rs != DA_OK) return rs;
-                q.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz};
+                q.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz, std::min(g.chunk, heavy.plan.min_len - 1),
+                                     heavy.plan.stale};
                 const int done = dispatch(RB_SR, rest, q);
                 return done != DA_OK ? done : launch_heavy(q, heavy.plan, dealt.groups);
             }
@@ -1498,7 +1503,9 @@ try {
     const size_t words = (size_t)(m + 31) / 32, n = rows.size();
     auto block = std::make_shared<DeviceBlock>();
     const size_t ints = ((n + 63) & ~size_t(63)) + ((words + 63) & ~size_t(63)) + n * (size_t)(cells + 1);
-    if (hipMalloc(&block->p, ints * sizeof(int)) != hipSuccess) return no_heavy_rows();
+    if (hipMalloc(&block->p, ints * sizeof(int)) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&block->pinned), sizeof(int), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) return no_heavy_rows();
+    *block->pinned = 0;
     int* drows = static_cast<int*>(block->p);
     unsigned* bits = reinterpret_cast<unsigned*>(drows + ((n + 63) & ~size_t(63)));
     int* at = reinterpret_cast<int*>(bits + ((words + 63) & ~size_t(63)));
@@ -1512,7 +1519,7 @@ try {
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "da_spmm_prepare");
     if (host.unsorted) return DA_OK;
-    pl->heavy = HeavyPlan{drows, at, (int)n, cells, cell, min_len, (int)nnz};
+    pl->heavy = HeavyPlan{drows, at, (int)n, cells, cell, min_len, (int)nnz, block->pinned};
     pl->heavy_k = k;
     pl->heavy_bits = bits;
     pl->rest_len = rest_len;

@@ -482,11 +482,13 @@ template <int UMAX, class F>
 __device__ __forceinline__ void for_blocks(int cnt, F&& f) { for_blocks<UMAX>(0, cnt, f); }
 
 // Rows whose sums another kernel adds to C (heavy_rows_kernel): one bit a row, for rows of at least min_len entries in
-// a matrix of nnz (the number at `end`); they are written as zeros.  rows == nullptr: none.
+// a matrix of nnz (the number at `end`); they are written as zeros.  rows == nullptr: none.  *stale (in host memory)
+// becomes 1 where another row has more than `longest` entries: the list is of another matrix.
 struct LeftOut {
     const unsigned* rows;
     const int* end;
-    int min_len, nnz;
+    int min_len, nnz, longest;
+    int* stale;
 };
 
 // ------------------------------------------------------------------------------------------
@@ -513,7 +515,10 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
     const int n0 = cols.n0, nvec = cols.nvec;
     int start = 0, end = 0;
     if (row < m) { start = rowptr[row]; end = rowptr[row + 1]; }
-    if (out.rows != nullptr && end - start >= out.min_len && (out.rows[row >> 5] >> (row & 31) & 1u) && *out.end == out.nnz) end = start;
+    if (out.rows != nullptr && end - start > out.longest) {
+        if (end - start >= out.min_len && (out.rows[row >> 5] >> (row & 31) & 1u) && *out.end == out.nnz) end = start;
+        else *out.stale = 1;
+    }
     Acc<V, G, NV> acc;
     acc.clear();
     const BRows<WIDE> brow(B, n0, sd);

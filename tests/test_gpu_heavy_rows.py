@@ -117,6 +117,7 @@ def test_infinities_stay_in_their_rows(prepared):
 @pytest.mark.parametrize("N", [8, 20, 64])
 def test_plans_of_another_matrix(change, N):
     from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
     rowptr, colind, vals = matrix(7)
     dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals)]
     da.da_spmm_prepare(M, K, colind.size, dev[0], dev[1])
@@ -134,9 +135,36 @@ def test_plans_of_another_matrix(change, N):
         d.copy_(torch.from_numpy(h))
     B = dense(N)
     want, _ = orc.spmm(rowptr, colind[:rowptr[-1]], vals[:rowptr[-1]], B)
-    got = product(dev, torch.from_numpy(B).cuda(), N)
+    Bd = torch.from_numpy(B).cuda()
+    assert np.array_equal(product(dev, Bd, N), want.astype(np.float32) + 0.0)
+    # the list is another matrix's, and found to be: the EB kernels from now on, until the matrix is prepared again
+    got = []
+    names = kernels_of(lambda: got.append(product(dev, Bd, N)))
+    assert np.array_equal(got[0], want.astype(np.float32) + 0.0)
+    assert any("eb_sr_kernel" in n for n in names) and not any("heavy_rows_kernel" in n for n in names)
+    da.da_spmm_prepare(M, K, int(rowptr[-1]), dev[0], dev[1])
+    names = kernels_of(lambda: product(dev, Bd, N))
+    assert any("heavy_rows_kernel" in n for n in names) == (change in ("other", "fewer"))          # not of columns out of order
     da.da_spmm_release(dev[0])
-    assert np.array_equal(got, want.astype(np.float32) + 0.0)
+
+
+# what da_spmm_features has seen since
+def test_features_of_another_matrix_put_the_list_aside():
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    rowptr, colind, vals = matrix(17)
+    dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals)]
+    da.da_spmm_prepare(M, K, colind.size, dev[0], dev[1])
+    rowptr = np.minimum(rowptr, rowptr[-1] - 1)
+    dev[0].copy_(torch.from_numpy(rowptr))
+    da.da_spmm_features(M, 8, dev[0])
+    B = dense(8)
+    want, _ = orc.spmm(rowptr, colind[:-1], vals[:-1], B)
+    got = []
+    names = kernels_of(lambda: got.append(product(dev, torch.from_numpy(B).cuda(), 8)))
+    da.da_spmm_release(dev[0])
+    assert np.array_equal(got[0], want.astype(np.float32) + 0.0)
+    assert any("eb_sr_kernel" in n for n in names) and not any("heavy_rows_kernel" in n for n in names)
 
 
 # the kernel would read every row of B that its plan covers: B ends at the columns that the product declares
