@@ -400,8 +400,14 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     // row, k = 12 000: N = 128 13.3 -> 10.9 us, N = 256 23.3 -> 19.2; 24 000: 26.3 -> 23.2 and 47.9 -> 42.4; 40 000, slices of 10 MB:
     // 49.6 -> 48.0 and 94.8 -> 92.9; 61 417, 15.7 MB: 105 and 101, with 100 entries a row 328 and 334.  RB+RM+SR, N = 256:
     // 5000 11.3 -> 9.3, 24 000 62.2 -> 60.9, 27-point stencil of 28^3 28.6 -> 24.2.  4096 columns, N = 256, 4.2 MB: 6.1 and 6.2).
+    // Not where many entries lie in rows of uneven length, whose XCDs then wait for each other (50 000 lognormal rows of 60,
+    // PR, N = 256: k = 6000 133 and 140, 49 152 331 and 345; 5000 such rows, 12 000: 37 and 20).
+    auto uneven = [&] {
+        const MatrixHint hint = lookup_matrix(p.rowptr, p.m);
+        return hint.nnz >= 2000000 && hint.seen_len * (double)p.m > 1.5 * (double)hint.nnz;
+    };
     const bool slices_fit = V == 4 && G >= 16 && (fam == RB_SR || fam == RB_PR) && p.sd.cb == 1 &&
-                            tiles_l * tile_cols - p.N <= tile_cols / 8 && p.k * tile_cols * 4 <= 12 << 20 && (long)p.k * p.N * 4 > 9 << 19;
+                            tiles_l * tile_cols - p.N <= tile_cols / 8 && p.k * tile_cols * 4 <= 12 << 20 && (long)p.k * p.N * 4 > 9 << 19 && !uneven();
     const int pin = ((geo.pin < 0 ? slices_fit : geo.pin != 0) && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
     // grid for `bx` blocks per column tile
     auto grid_for = [&](long bx) {
@@ -410,7 +416,7 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     };
     const int64_t max_blocks = pin ? kMaxGridX / 8 * (8 / pin) : kMaxGridX;
     const dim3 block(kBlock);
-    // Bias and rectification in the product kernel: the lane groups of row-major products from 8 columns on.  EB needs
+    // Bias and rectification in the product kernel: groups of 8 and more lanes of one column, of 4 and more of four.  EB needs
     // eb_finish_kernel after it, which takes as long as the pass over a small C (30 000 rows, 64 -> 64 -> 32: 87.3 us, 85.3 with
     // the pass; 60 000 rows, 64 -> 64 -> 24: 114.7 and 119.4): from 2 M elements on.
     constexpr bool kLayers = !WIDE && NV == 1 && G >= (V == 4 ? 4 : 8);
