@@ -96,9 +96,17 @@ def bench_line(path: str) -> dict:
 
 def product_kernels(names, algo: str):
     """The kernels one da_spmm call of the algorithm family launches: the main kernel that ran most
-    often in the timed region, plus the EB zero pre-pass."""
+    often in the timed region, plus the EB zero pre-pass; or the kernel of the heavy rows, plus the other rows'
+    (run with --no-variants: RB+RM+SR shares that one)."""
+    if algo == "EB+RM+SR" and any("heavy_rows_kernel" in n for n in names):
+        return [n for n in names if "heavy_rows_kernel" in n or "rb_sr_kernel" in n]
     fam = {"RB": "rb", "EB": "eb"}[algo[:2]] + "_" + {"SR": "sr", "PR": "pr"}[algo[-2:]] + "_kernel"
     return [n for n in names if fam in n or (algo.startswith("EB") and "eb_zero_kernel" in n)]
+
+
+def first_pass(name: str, algo: str) -> bool:
+    """Whether the kernel of product_kernels() runs before the main one."""
+    return algo.startswith("EB") and ("eb_zero_kernel" in name or "rb_sr_kernel" in name)
 
 
 def write_kernel_trace(trace_dir: str, bench_json: str, out: str, command: str) -> dict:
@@ -108,8 +116,8 @@ def write_kernel_trace(trace_dir: str, bench_json: str, out: str, command: str) 
     algo = bench["config"]["algo"]
     mains = [r for r in rows if r[0] in product_kernels([r[0] for r in rows], algo)]
     # the timed region dominates the call counts: the instantiation of the chosen family with the most calls
-    main = max((r for r in mains if "eb_zero" not in r[0]), key=lambda r: r[1])
-    zero = max((r for r in mains if "eb_zero" in r[0]), key=lambda r: r[1], default=None)
+    main = max((r for r in mains if not first_pass(r[0], algo)), key=lambda r: r[1])
+    zero = max((r for r in mains if first_pass(r[0], algo)), key=lambda r: r[1], default=None)
     per_call = main[2] + (zero[2] if zero else 0.0)
     lines = [f"rocprofv3 kernel-trace summary: {bench['config']['workload']}",
              "command (from the repository root, after __graft_entry__.build()):", f"  {command}",
@@ -150,8 +158,8 @@ def write_hbm_traffic(fetch: str, write: str, tcc: str | None, calib_fetch: str,
     def per_call(directory, counter):
         rows = [r for r in counter_rows(find_db(directory)) if r[1] == counter]
         names = product_kernels([r[0] for r in rows], algo)
-        mains = [r for r in rows if r[0] in names and "eb_zero" not in r[0]]
-        zeros = [r for r in rows if r[0] in names and "eb_zero" in r[0]]
+        mains = [r for r in rows if r[0] in names and not first_pass(r[0], algo)]
+        zeros = [r for r in rows if r[0] in names and first_pass(r[0], algo)]
         main = max(mains, key=lambda r: r[2])
         zero = max(zeros, key=lambda r: r[2], default=None)
         return main, zero, rows

@@ -69,3 +69,29 @@ def test_which_calls_take_the_kernel(name, known, N, algo, here):
     B, C = torch.ones((N, a.k), device="cuda"), torch.empty((N, a.m), device="cuda")
     names = kernels_of(lambda: da.da_spmm_ex(a.m, a.k, N, *dev, B, a.k, da.DA_COL_MAJOR, C, a.m, da.DA_COL_MAJOR, algo))
     assert any("rb_columns_kernel" in n for n in names) == here, names
+
+
+def test_positions_next_to_2_to_the_31():
+    """2^31 - 1 entries in rows of 512: the last steps of the last rows pass 2^31."""
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    m, k, each = 1 << 22, 1 << 20, 512
+    rowptr = (torch.arange(m + 1, device="cuda") * each).clamp_(max=(1 << 31) - 1).to(torch.int32)
+    colind = torch.empty(m * each, dtype=torch.int32, device="cuda")
+    vals = torch.empty(m * each, device="cuda")
+    b = (torch.arange(k, device="cuda") % 9 - 4).float()
+    want = torch.empty(m, device="cuda")
+    for r in range(0, m, 1 << 17):                    # in parts of 64 M entries
+        at = torch.arange(r * each, (r + (1 << 17)) * each, device="cuda")
+        c, v = (at * 7919) % k, (at % 5 - 2).float()
+        if r + (1 << 17) == m:
+            v[-1] = 0.0                               # the entry that the last row does not have
+        colind[at[0]:at[-1] + 1], vals[at[0]:at[-1] + 1] = c.to(torch.int32), v
+        want[r:r + (1 << 17)] = (v * b[c]).view(-1, each).sum(1)
+        del at, c, v
+    vals[-1] = float("nan")
+    assert int(da.da_spmm_features(m, 1, rowptr)["nnz"]) == (1 << 31) - 1
+    C = torch.full((m,), float("nan"), device="cuda")
+    print("2^31 - 1 entries", flush=True)
+    names = kernels_of(lambda: da.da_spmm(m, k, 1, rowptr, colind, vals, b, C, da.DA_RB_RM_SR))
+    assert any("rb_columns_kernel" in n for n in names) and torch.equal(C, want)

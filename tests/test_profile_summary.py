@@ -38,6 +38,9 @@ def test_short_name_and_product_kernels():
     names = [ps.short_name(x) for x in (EB, ZERO, OTHER)]
     assert ps.product_kernels(names, "EB+RM+SR") == names[:2]
     assert ps.product_kernels(names, "RB+RM+SR") == names[2:]
+    heavy = "daspmm::heavy_rows_kernel<16, 4>"
+    assert ps.product_kernels([*names, heavy], "EB+RM+SR") == [names[2], heavy]
+    assert ps.first_pass(names[2], "EB+RM+SR") and not ps.first_pass(names[2], "RB+RM+SR") and not ps.first_pass(heavy, "EB+RM+SR")
 
 
 def test_kernel_trace_summary(tmp_path):
