@@ -27,7 +27,8 @@
  *   DA_SPMM_SPLIT_SHORT_ROWS=1 EB+SR on prepared matrices: split short rows at chunk boundaries again
  *   DA_SPMM_WIDE=1             force the kernels with 64-bit gather addresses
  *   DA_SPMM_TUNE=1             honour DA_SPMM_V / _G / _NV / _CHUNK / _PIN / _STRIPE, which override the
- *                              launch geometry; unsupported combinations return DA_ERR_UNSUPPORTED
+ *                              launch geometry; unsupported combinations return DA_ERR_UNSUPPORTED.  Products
+ *                              then keep to the kernels that the geometry is of (none for heavy rows or by columns)
  */
 #ifndef DA_SPMM_H
 #define DA_SPMM_H
@@ -177,7 +178,8 @@ int da_spmm_features(int64_t m, int64_t N, const int32_t *rowptr, void *stream, 
  * the caller must not do while the graph is still replayed.  da_spmm_release(NULL) also frees plans
  * that a re-prepare with another nnz has set aside.
  * These two host tables (matrix hints, plans) and the slots of da_spmm_features are the library's only
- * mutable global state; the tables only steer launch geometry and chunk order, never the result.
+ * mutable global state (a plan's mark that its list of rows is another matrix's among it); the tables only
+ * steer launch geometry, chunk order and which kernels run, never the result.
  *
  * da_eb_schedule is the building block: order[u], u = 0 .. ceil(nnz/unit)-1, lists the chunk
  * numbers (chunk c = stored entries [c*unit, (c+1)*unit)) sorted by a key in [0, 2k), ties in

@@ -3,13 +3,13 @@
 // them, but the EB kernels fetch it anew for every stored entry, and that rate, 64 bytes a clock and CU from the
 // vector L1, is what bounds them (33 M entries, N = 64: 460 us).
 //
-// heavy_rows_kernel turns the loops round: a block owns a range of columns and all heavy rows (or 576 of them).  It
+// heavy_rows_kernel turns the loops round: a block owns a range of columns and heavy rows of similar length (up to 576).  It
 // brings its rows of B into LDS once, a band at a time in two buffers, and walks the stored entries of all its heavy
 // rows that lie in the band, with the rows' sums in registers from the first band to the last; they are added to C
-// atomically once per block.  The same matrix takes 330 us at N = 64 (270 of them here, the rest for the other rows),
-// 132 instead of 176 at N = 8, 208 instead of 270 at N = 32.  What bounds it: LDS, 128 bytes a clock and CU (126 us at
-// N = 64), and the vector units (6 operations for 4 entries and 64 columns, some 25 for a batch of 64 entries: 123 us),
-// which overlap little; at N = 8 the stream of entries (50 us).
+// atomically once per block.  The same matrix takes 326 us at N = 64, EB 445 (under
+// the profiler 265 here and 98 for the other rows), 121 and 172 at N = 8 (85 and 41), 217 and 268 at N = 32.  What bounds it: the vector
+// units, busy in 76 % of the cycles at N = 64 (6 operations for 4 entries and 64 columns, some 25 for a batch of 64
+// entries), LDS in 35 %, without bank conflicts; at N = 8 63 and 26 %, besides the stream of entries (50 us).
 //
 // Lane groups of 16 walk one row each, 16 entries at a time, one per lane; an entry's column and value reach the
 // lanes by DPP broadcasts, the column as an operand of the address addition.  An entry takes the 16 lanes, or a
