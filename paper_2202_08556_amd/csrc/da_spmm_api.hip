@@ -1206,6 +1206,7 @@ template <int ROUNDS>
 void launch_transpose_passes(const TransposeFast& t, TransposePass P, int64_t k, int32_t* t_rowptr, float* t_vals,
                              char* ws, hipStream_t s) {
     const dim3 grid((unsigned)(8 * ((t.ntiles + 7) / 8))), block(kSortBlock);
+    const bool wide = P.n >= (1 << 30);
     unsigned* mid = reinterpret_cast<unsigned*>(ws + t.off_mid);
     float* mid_vals = reinterpret_cast<float*>(ws + t.off_vals);
     int* totals = reinterpret_cast<int*>(ws + t.off_total);
@@ -1224,13 +1225,23 @@ void launch_transpose_passes(const TransposeFast& t, TransposePass P, int64_t k,
         P.mid_out = mid;
         P.vals_in = p == 0 ? vals : mid_vals;
         P.vals_out = last ? t_vals : mid_vals;
-        if (p == 0) hipLaunchKernelGGL((transpose_count_kernel<ROUNDS, true>), dim3((unsigned)t.ngroups), dim3(1024), 0, s, P);
-        else hipLaunchKernelGGL((transpose_count_kernel<ROUNDS, false>), dim3((unsigned)t.ngroups), dim3(1024), 0, s, P);
+        if (p == 0) hipLaunchKernelGGL((transpose_count_kernel<ROUNDS, true>), dim3((unsigned)t.ngroups), dim3(kCountBlock), 0, s, P);
+        else hipLaunchKernelGGL((transpose_count_kernel<ROUNDS, false>), dim3((unsigned)t.ngroups), dim3(kCountBlock), 0, s, P);
         hipLaunchKernelGGL(transpose_scan_kernel, dim3((unsigned)(bins / kScanDigits)), dim3(1024), 0, s, P.group_hist, t.ngroups, bins,
                            P.total);
-        if (p == 0 && last) hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, true, true>), grid, block, lds, s, P);
-        else if (p == 0) hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, true, false>), grid, block, lds, s, P);
-        else hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, false, true>), grid, block, lds, s, P);
+        auto scatter = [&](auto width, auto far) {
+            constexpr int BITS = decltype(width)::value;
+            constexpr bool WIDE = decltype(far)::value;
+            if (p == 0 && last) hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, true, true, BITS, WIDE>), grid, block, lds, s, P);
+            else if (p == 0) hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, true, false, BITS, WIDE>), grid, block, lds, s, P);
+            else hipLaunchKernelGGL((transpose_scatter_kernel<ROUNDS, false, true, BITS, WIDE>), grid, block, lds, s, P);
+        };
+        if (wide) scatter(Count<kDigitBitsMax>{}, Truth<true>{});
+        else if (P.bits <= 6) scatter(Count<6>{}, Truth<false>{});
+        else if (P.bits == 7) scatter(Count<7>{}, Truth<false>{});
+        else if (P.bits == 8) scatter(Count<8>{}, Truth<false>{});
+        else if (P.bits == 9) scatter(Count<9>{}, Truth<false>{});
+        else scatter(Count<kDigitBitsMax>{}, Truth<false>{});
     }
     if (t.passes == 1)
         hipLaunchKernelGGL(transpose_rowptr_one_kernel, dim3(1), dim3(256), 0, s, totals, 1 << t.bits[0], P.n, (int)k, t_rowptr);

@@ -33,6 +33,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
+#include "da_dense_kernels.hip"
+#include "da_spmm_kernels.hip"
+
 namespace daspmm {
 
 constexpr int kRadixBits = 8;                            // widest digit
@@ -437,6 +442,7 @@ __global__ __launch_bounds__(kSortBlock) void rowptr_from_sorted_kernel(const in
 constexpr int kDigitBitsMax = 10;
 constexpr int kDigitBinsMax = 1 << kDigitBitsMax;
 constexpr int kGroupMax = 8;                             // tiles counted by one block
+constexpr int kCountBlock = 512;
 constexpr int kScanDigits = 16;                          // digits per block of transpose_scan_kernel
 
 // One pass.  Entries come from the matrix (colind, vals, row numbers from rowptr) in the first pass and
@@ -496,27 +502,34 @@ __device__ __forceinline__ void count_digit(int* cnt, unsigned d, bool valid) {
     else if (below == 0) atomicAdd(&cnt[d], __popcll(same));
 }
 
-// A block counts the tiles of one group one after another, so that what remains to be scanned is one row
-// of counts per group (one row per tile took as long to scan as the tiles take to count).  All keys of
-// the group are requested before the first one is counted.
+// A block counts the tiles of one group, so that what remains to be scanned is one row of counts per group (one row
+// per tile took as long to scan as the tiles take to count).  Every tile has counters of its own, so that nothing waits
+// between the group's request for all of its keys and the sums over its tiles (22 us at 13 M entries, 23 with one set of
+// counters and two barriers a tile).
 template <int ROUNDS, bool FIRST>
-__global__ __launch_bounds__(1024) void transpose_count_kernel(TransposePass P)
+__global__ __launch_bounds__(kCountBlock) void transpose_count_kernel(TransposePass P)
 {
-    constexpr int THREADS = 1024, T = kSortBlock * ROUNDS, PER = T / THREADS;
-    static_assert(PER * THREADS == T && kGroupMax <= THREADS / 64, "whole rounds per tile, one wave per tile's row search");
-    __shared__ int cnt[kDigitBinsMax];
+    constexpr int THREADS = kCountBlock, T = kSortBlock * ROUNDS, PER = T / THREADS;
+    static_assert(PER * THREADS == T && kGroupMax <= THREADS / 64, "whole loads per tile, one wave per tile's row search");
+    typedef unsigned keys_of_tile __attribute__((ext_vector_type(PER), aligned(4)));
+    __shared__ int cnt[kGroupMax * kDigitBinsMax];
     const int bins = 1 << P.bits;
     const int tile0 = blockIdx.x * P.group, tiles = min(P.group, P.ntiles - tile0);
     const long base = (long)tile0 * T;
     const int count = (int)min((long)tiles * T, (long)P.n - base);
     const unsigned* __restrict__ keys = (FIRST ? reinterpret_cast<const unsigned*>(P.colind) : P.mid_in) + base;
-    unsigned key[kGroupMax * PER];
+    const int own = (int)threadIdx.x * PER;
+    keys_of_tile key[kGroupMax];
 #pragma unroll
-    for (int r = 0; r < kGroupMax * PER; ++r) {
-        const int e = r * THREADS + (int)threadIdx.x;
-        key[r] = e < count ? keys[e] : 0u;
+    for (int g = 0; g < kGroupMax; ++g) {
+        if ((g + 1) * T <= count) {
+            key[g] = *reinterpret_cast<const keys_of_tile*>(keys + g * T + own);
+        } else {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) key[g][i] = g * T + own + i < count ? keys[g * T + own + i] : 0u;
+        }
     }
-    if ((int)threadIdx.x < bins) cnt[threadIdx.x] = 0;
+    for (int d = threadIdx.x; d < tiles * bins; d += THREADS) cnt[d] = 0;
     if constexpr (FIRST) {                                // the scatter kernel starts its row walk from here
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
         if (w < tiles) {
@@ -529,19 +542,23 @@ __global__ __launch_bounds__(1024) void transpose_count_kernel(TransposePass P)
             }
         }
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int g = 0; g < kGroupMax; ++g) {
         if (g < tiles) {
-            if ((int)threadIdx.x < bins) P.hist[(long)(tile0 + g) * bins + threadIdx.x] = cnt[threadIdx.x];
-            __syncthreads();
 #pragma unroll
-            for (int r = g * PER; r < (g + 1) * PER; ++r)
-                count_digit(cnt, pass_digit<FIRST>(key[r], P), r * THREADS + (int)threadIdx.x < count);
-            __syncthreads();
+            for (int i = 0; i < PER; ++i) count_digit(cnt + g * bins, pass_digit<FIRST>(key[g][i], P), g * T + own + i < count);
         }
     }
-    if ((int)threadIdx.x < bins) P.group_hist[(long)blockIdx.x * bins + threadIdx.x] = cnt[threadIdx.x];
+    lds_barrier();
+    for (int d = threadIdx.x; d < bins; d += THREADS) {
+        int before = 0;
+        for (int g = 0; g < tiles; ++g) {
+            P.hist[(long)(tile0 + g) * bins + d] = before;
+            before += cnt[g * bins + d];
+        }
+        P.group_hist[(long)blockIdx.x * bins + d] = before;
+    }
 }
 
 // Exclusive prefix over the groups for every digit, in place, and the digit totals.  A block owns 16
@@ -590,35 +607,34 @@ __device__ __forceinline__ void block_scan_bins(int (&v)[4], int* sh) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) { const int x = v[i]; v[i] = sum; sum += x; }
     const int inc = wave_inclusive_scan_dpp(sum);
-    __syncthreads();
+    lds_barrier();
     if (lane == 63) sh[wave] = inc;
-    __syncthreads();
+    lds_barrier();
     const int s0 = sh[0], s1 = sh[1], s2 = sh[2];
     const int off = inc - sum + (wave > 0 ? s0 : 0) + (wave > 1 ? s1 : 0) + (wave > 2 ? s2 : 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] += off;
 }
 
-// Values 4 t ... 4 t + 3 of p for thread t, zeros at and behind `bins` (p is read inside its bins only).
+// Values 4 t ... 4 t + 3 of p for thread t, zeros at and behind `bins`, a multiple of 4; p on a 16-byte boundary.
 __device__ __forceinline__ void load_bins(const int* __restrict__ p, int bins, int (&v)[4]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int d = (int)threadIdx.x * 4 + i, x = p[min(d, bins - 1)];
-        v[i] = d < bins ? x : 0;
-    }
+    const bool own = (int)threadIdx.x * 4 < bins;
+    const int4 x = *reinterpret_cast<const int4*>(p + (own ? threadIdx.x * 4 : 0));
+    v[0] = own ? x.x : 0; v[1] = own ? x.y : 0; v[2] = own ? x.z : 0; v[3] = own ? x.w : 0;
 }
 
-// Lanes of the wave that hold the same digit of `bits` bits, among the lanes of `valid`.
-__device__ __forceinline__ unsigned long long digit_peers_of(unsigned d, int bits, unsigned long long valid) {
+// Lanes of the wave that hold the same digit, among the lanes of `valid`.  The width is known to the compiler, so that the
+// votes are straight code and no branch stands around every bit.
+template <int BITS>
+__device__ __forceinline__ unsigned long long digit_peers_of(unsigned d, unsigned long long valid) {
     unsigned lo = (unsigned)valid, hi = (unsigned)(valid >> 32);
 #pragma unroll
-    for (int b = 0; b < kDigitBitsMax; ++b)
-        if (b < bits) {
-            const int m = (int)(d << (31 - b)) >> 31;                 // all ones when the bit is set
-            const unsigned long long vote = __ballot(m < 0);
-            lo &= ~((unsigned)vote ^ (unsigned)m);
-            hi &= ~((unsigned)(vote >> 32) ^ (unsigned)m);
-        }
+    for (int b = 0; b < BITS; ++b) {
+        const int m = __builtin_amdgcn_sbfe((int)d, b, 1);            // all ones when the bit is set
+        const unsigned long long vote = __builtin_amdgcn_ballot_w64(m < 0);
+        lo &= ~((unsigned)vote ^ (unsigned)m);
+        hi &= ~((unsigned)(vote >> 32) ^ (unsigned)m);
+    }
     return (unsigned long long)hi << 32 | lo;
 }
 
@@ -628,17 +644,30 @@ constexpr size_t transpose_scatter_lds(int bins) {
     return (size_t)kSortBlock * ROUNDS * 10 + (size_t)bins * 4 + (size_t)bins * 2 * kSortWaves + kSortWaves * 4;
 }
 
-// Stable placement of one tile.  FIRST: input is the matrix; LAST: output is the arrays of A^T.
+// Inclusive maximum over the lanes of a wave.
+__device__ __forceinline__ unsigned wave_inclusive_max(unsigned v) {
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));   // row_shr:2
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));   // row_shr:4
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));   // row_shr:8
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+}
+
+// Stable placement of one tile.  FIRST: input is the matrix; LAST: output is the arrays of A^T.  WIDE: byte offsets of
+// entries do not fit 32 bits.  BITS: at least P.bits; the votes of bits that no digit has change nothing.
 //
 // Row numbers (FIRST): the rows that begin inside the tile leave a mark at their first entry, in a
 // coalesced walk over their row pointers, and an entry's row is the last mark at or before it.  (A binary
 // search per entry took as long as the rest of the pass: 175 against 82 us at 13 M entries.)  A tile that
 // spans very many rows without entries searches after all.
 //
-// What bounds a pass: memory (8 bytes in and out per entry, and partly filled lines: a tile holds only a
-// few entries per digit) and, close behind, the vector instructions of the ranking; small tiles keep
-// enough waves resident to overlap the two.
-template <int ROUNDS, bool FIRST, bool LAST>
+// What bounds a pass: memory (8 bytes in and out per entry) and, close behind, the vector instructions of the ranking;
+// small tiles keep enough waves resident to overlap the two (13 M entries, k = 262 144: 76 and 46 us; with a branch around every
+// vote 79 and 51).  The tiles that an XCD has in hand at a time are
+// neighbours: blocks that stay and take several neighbouring tiles one after another, the next one's entries on their
+// way, took 125 and 80 us instead of 74 and 49, since their runs meet in L2 only when many lines have left it half full.
+template <int ROUNDS, bool FIRST, bool LAST, int BITS, bool WIDE>
 __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(TransposePass P)
 {
     constexpr int THREADS = kSortBlock, T = THREADS * ROUNDS, WAVES = kSortWaves, RUN = ROUNDS * 64;
@@ -656,25 +685,29 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long base = (long)tile * T;
     const int count = (int)min((long)T, (long)P.n - base);
-    const int own = wave * RUN + lane;                    // the lane's first entry
-    const unsigned* __restrict__ keys = (FIRST ? reinterpret_cast<const unsigned*>(P.colind) : P.mid_in) + base;
-    const float* __restrict__ vals = P.vals_in + base;
+    const unsigned own = wave * RUN + lane;               // the thread's first entry
+    auto request = [&](const auto* from, auto& x) {
+        typedef std::remove_reference_t<decltype(*from)> number;
+        const char* p = reinterpret_cast<const char*>(from + base);
+        if (count == T) {
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) x[q] = *reinterpret_cast<number*>(p + own * 4u + q * 256);
+        } else {
+            const unsigned last = (unsigned)count - 1;
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) x[q] = *reinterpret_cast<number*>(p + min(own + q * 64, last) * 4u);
+        }
+    };
     unsigned key[ROUNDS];
     float val[ROUNDS];
-#pragma unroll
-    for (int q = 0; q < ROUNDS; ++q) {
-        const unsigned e = (unsigned)min(own + q * 64, count - 1);
-        key[q] = keys[e];
-        val[q] = vals[e];
-    }
+    request(FIRST ? reinterpret_cast<const unsigned*>(P.colind) : P.mid_in, key);
+    request(P.vals_in, val);
     // thread t owns digits 4 t ... 4 t + 3: the global position of the tile's first entry of the digit
     const bool owner = (int)threadIdx.x * 4 < bins;
     int gpos[4], before[4], in_group[4];
     load_bins(P.total, bins, gpos);
     load_bins(P.group_hist + (long)(tile / P.group) * bins, bins, before);
     load_bins(P.hist + (long)tile * bins, bins, in_group);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) before[i] += in_group[i];
     if (owner) {
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) *reinterpret_cast<uint2*>(&wcnt[w * (bins / 2) + 2 * threadIdx.x]) = make_uint2(0u, 0u);
@@ -686,58 +719,55 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
         if (row_hi - row_lo <= 8 * T) {
 #pragma unroll
             for (int q = 0; q < ROUNDS; ++q) skey[q * THREADS + threadIdx.x] = 0;
-            __syncthreads();
+            lds_barrier();
             for (int r = row_lo + 1 + (int)threadIdx.x; r <= row_hi; r += THREADS) {
-                const int p = rowptr[r] - (int)base;      // row_hi may begin with the next tile
+                const int p = rowptr[r] - (int)base;  // row_hi may begin with the next tile
                 if (p < count) atomicMax(&skey[p], r - row_lo);
             }
-            __syncthreads();
-            int last = 0;                                 // the last mark of the wave's run
+            lds_barrier();
+            // marks ascend: the last one at or before an entry is the largest
+            unsigned upto = 0;
 #pragma unroll
             for (int q = 0; q < ROUNDS; ++q) {
-                row[q] = skey[own + q * 64];
-                const unsigned long long some = __ballot(row[q] != 0);
-                if (some) last = __builtin_amdgcn_readlane(row[q], 63 - __clzll((long long)some));
+                const unsigned v = max(wave_inclusive_max((unsigned)skey[own + q * 64]), upto);
+                row[q] = (int)v;
+                upto = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
             }
-            if (lane == 0) sh[wave] = last;
-            __syncthreads();
+            if (lane == 0) sh[wave] = (int)upto;
+            lds_barrier();
             int carry = 0;
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) { const int x = sh[w]; if (w < wave && x != 0) carry = x; }
-            const unsigned long long upto = ~0ull >> (63 - lane);
+            for (int w = 0; w < WAVES - 1; ++w) { const int x = sh[w]; if (w < wave) carry = max(carry, x); }
 #pragma unroll
-            for (int q = 0; q < ROUNDS; ++q) {
-                const unsigned long long some = __ballot(row[q] != 0), mine = some & upto;
-                const int v = __shfl(row[q], mine ? 63 - __clzll((long long)mine) : 0);
-                const int next = some ? __builtin_amdgcn_readlane(row[q], 63 - __clzll((long long)some)) : carry;
-                row[q] = row_lo + (mine ? v : carry);
-                carry = next;
-            }
+            for (int q = 0; q < ROUNDS; ++q) row[q] = row_lo + max(row[q], carry);
         } else {
 #pragma unroll
-            for (int q = 0; q < ROUNDS; ++q) row[q] = owner_row(rowptr, row_lo, row_hi, (int)base + min(own + q * 64, count - 1));
-            __syncthreads();
+            for (int q = 0; q < ROUNDS; ++q) row[q] = owner_row(rowptr, row_lo, row_hi, (int)base + min((int)own + q * 64, count - 1));
+            lds_barrier();
         }
     } else {
-        __syncthreads();
+        lds_barrier();
     }
     // rank of every entry among the wave's entries of the same digit
     unsigned* counter = wcnt + wave * (bins / 2);
+    const unsigned short* counted = reinterpret_cast<const unsigned short*>(counter);
     unsigned rank[ROUNDS];
 #pragma unroll
     for (int q = 0; q < ROUNDS; ++q) {
-        const bool valid = own + q * 64 < count;
+        const bool valid = (int)own + q * 64 < count;
         const unsigned d = pass_digit<FIRST>(key[q], P);
-        const unsigned long long peers = digit_peers_of(d, P.bits, __ballot(valid));
+        const unsigned long long peers = digit_peers_of<BITS>(d, __builtin_amdgcn_ballot_w64(valid));
         const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(peers >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)peers, 0u));
-        const int leader = (__ffsll((long long)peers) - 1) & 63;
-        const int sft = (int)(d & 1u) * 16;
-        unsigned old = 0;
-        if (valid && below == 0) old = atomicAdd(&counter[d >> 1], (unsigned)__popcll(peers) << sft);
-        rank[q] = ((__shfl(old, leader) >> sft) & 0xffffu) + below;
-        __builtin_amdgcn_sched_barrier(0);                // keep the ballots of one round together
+        // every lane reads, then one lane per digit adds: the LDS unit serves a wave's requests in issue order, so that
+        // no round waits for the one before
+        rank[q] = counted[d] + below;
+        wave_lds_sync();
+        if (valid && below == 0) atomicAdd(&counter[d >> 1], (unsigned)__popcll(peers) << ((d & 1u) * 16));
+        wave_lds_sync();
+        __builtin_amdgcn_sched_barrier(0);            // keep the votes of one round together
     }
-    block_scan_bins(gpos, sh);                            // digit totals -> first positions (synchronises)
+    lds_barrier();
+    block_scan_bins(gpos, sh);                        // digit totals -> first positions
     {
         // two digits to a word: no sum of a tile's counts leaves 16 bits
         uint2 c[WAVES], sum = make_uint2(0u, 0u);
@@ -751,8 +781,8 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
         block_scan_bins(slot, sh);
         if (owner) {
             *reinterpret_cast<int4*>(&gofs[4 * threadIdx.x]) =
-                make_int4(gpos[0] + before[0] - slot[0], gpos[1] + before[1] - slot[1], gpos[2] + before[2] - slot[2],
-                          gpos[3] + before[3] - slot[3]);
+                make_int4(gpos[0] + before[0] + in_group[0] - slot[0], gpos[1] + before[1] + in_group[1] - slot[1],
+                          gpos[2] + before[2] + in_group[2] - slot[2], gpos[3] + before[3] + in_group[3] - slot[3]);
             uint2 run = make_uint2((unsigned)slot[0] | (unsigned)slot[1] << 16, (unsigned)slot[2] | (unsigned)slot[3] << 16);
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) {
@@ -762,13 +792,12 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
             }
         }
     }
-    __syncthreads();
-    const unsigned short* first_slot = reinterpret_cast<const unsigned short*>(counter);
+    lds_barrier();
 #pragma unroll
     for (int q = 0; q < ROUNDS; ++q) {
-        if (own + q * 64 < count) {
+        if ((int)own + q * 64 < count) {
             const unsigned d = pass_digit<FIRST>(key[q], P);
-            const unsigned slot = first_slot[d] + rank[q];
+            const unsigned slot = counted[d] + rank[q];
             unsigned out = key[q];
             if constexpr (FIRST) out = LAST ? (unsigned)row[q] : (unsigned)row[q] | (key[q] >> P.bits) << P.row_bits;
             skey[slot] = (int)out;
@@ -776,17 +805,22 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
             if constexpr (FIRST) sdig[slot] = (unsigned short)d;
         }
     }
-    __syncthreads();
+    lds_barrier();
     // copy out: neighbouring tile slots of one digit are neighbouring global positions
     const unsigned row_mask = (1u << P.row_bits) - 1u;
-#pragma unroll 4
-    for (int i = threadIdx.x; i < count; i += THREADS) {
-        const unsigned x = (unsigned)skey[i];
-        const int d = FIRST ? (int)sdig[i] : (int)(x >> P.row_bits);
-        const int pos = gofs[d] + i;
-        if constexpr (LAST) P.t_colind[pos] = (int)(FIRST ? x : x & row_mask);
-        else P.mid_out[pos] = x;
-        P.vals_out[pos] = sval[i];
+    char* out_keys = reinterpret_cast<char*>(LAST ? reinterpret_cast<unsigned*>(P.t_colind) : P.mid_out);
+    char* out_vals = reinterpret_cast<char*>(P.vals_out);
+#pragma unroll
+    for (int q = 0; q < ROUNDS; ++q) {
+        const int i = q * THREADS + (int)threadIdx.x;
+        if (i < count) {
+            const unsigned x = (unsigned)skey[i];
+            const int d = FIRST ? (int)sdig[i] : (int)(x >> P.row_bits);
+            const unsigned pos = (unsigned)(gofs[d] + i);
+            const size_t at = WIDE ? (size_t)pos * 4 : (size_t)(pos * 4u);
+            *reinterpret_cast<unsigned*>(out_keys + at) = LAST && !FIRST ? x & row_mask : x;
+            *reinterpret_cast<float*>(out_vals + at) = sval[i];
+        }
     }
 }
 
