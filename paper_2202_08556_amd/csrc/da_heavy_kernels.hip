@@ -3,20 +3,25 @@
 // them, but the EB kernels fetch it anew for every stored entry, and that rate, 64 bytes a clock and CU from the
 // vector L1, is what bounds them (33 M entries, N = 64: 460 us).
 //
-// heavy_rows_kernel turns the loops round: a block owns a range of columns and heavy rows of similar length (up to 576).  It
+// heavy_rows_kernel turns the loops round: a block owns a range of columns and heavy rows of similar length (up to 540).  It
 // brings its rows of B into LDS once, a band at a time in two buffers, and walks the stored entries of all its heavy
 // rows that lie in the band, with the rows' sums in registers from the first band to the last; they are added to C
-// atomically once per block.  The same matrix takes 326 us at N = 64, EB 445 (under
-// the profiler 265 here and 98 for the other rows), 121 and 172 at N = 8 (85 and 41), 217 and 268 at N = 32.  What bounds it: the vector
-// units, busy in 76 % of the cycles at N = 64 (6 operations for 4 entries and 64 columns, some 25 for a batch of 64
-// entries), LDS in 35 %, without bank conflicts; at N = 8 63 and 26 %, besides the stream of entries (50 us).
+// atomically once per block.  The same matrix takes 294 us at N = 64, EB 445 (under
+// the profiler 205 here and 98 for the other rows), 130 and 172 at N = 8 (85 and 41).  What bounds it: latency.  The waves wait
+// in half of their cycles; LDS is busy in 38 % of them at N = 64, the vector units in about half (4 entries and 64 columns take two
+// operations with DPP, 4 cycles each, and four multiply-adds, 2 each; a batch of 64 entries some 20 operations).
+//
+// One wave, up to 8 columns two, does nothing but bring B, from memory to LDS directly.  While every wave brought a share through its
+// registers, in parts between its rows, each part's entries waited for B's latency, since loads come back in order (N = 64: 335 us; 303
+// with two waves that bring B, 294 with one and the ranges below).  Lanes in order of memory: with the columns of a lane
+// side by side in LDS, 64 bytes apart in memory, four such waves took 243 us where now one takes 205.
 //
 // Lane groups of 16 walk one row each, 16 entries at a time, one per lane; an entry's column and value reach the
-// lanes by DPP broadcasts, the column as an operand of the address addition.  An entry takes the 16 lanes, or a
-// quarter of them (GL = 4, up to 8 columns).  Lane j of them owns columns j, j + GL, ... of the tile, side by side in
-// LDS, so that one read of 4 V bytes serves V columns and additions to C cover neighbouring elements.  Rows of similar
-// length share a wave (in storage order: 318 us instead of 270 at N = 64).  Two buffers of 64 KiB; 8 instead of 4 entries
-// read ahead at V = 4 take more steps for the last entries of a band: 288 us.
+// lanes by DPP broadcasts, the column as an operand of the address addition (the value as an operand of the multiply-adds: DPP
+// halves their rate, no gain).  An entry takes the 16 lanes, or a quarter of them (GL = 4, up to 8 columns).  Lane j of them owns
+// V neighbouring columns, one read of 4 V bytes; before the additions to C the lanes exchange their sums through LDS, so that an
+// addition covers neighbouring elements.  Rows of similar length share a wave (in storage order: 318 us instead of 270 at N = 64).
+// Two buffers of 64 KiB.  More requests for entries ahead (4 batches at V = 4, 8 at GL = 4) or two entries a lane: no gain.
 //
 // The plan (da_spmm_prepare) lists the heavy rows and, per row and cell of columns, the position at which the cell's
 // entries begin.  As everywhere, a plan only steers: positions are clamped to the row, so that whatever they hold the
@@ -34,11 +39,11 @@
 
 namespace daspmm {
 
-constexpr int kHeavyBlock = 1024, kHeavyWaves = kHeavyBlock / 64;
+constexpr int kHeavyBlock = 1024;
+constexpr int heavy_waves(int tile) { return kHeavyBlock / 64 - (tile <= 8 ? 2 : 1); }   // waves that walk rows; the others bring B
 constexpr int kHeavyQuads = 9;                             // sets of 4 rows a wave holds
-constexpr int kHeavyRows = kHeavyWaves * 4 * kHeavyQuads;  // heavy rows of a block
 template <int GL, int V> constexpr int kHeavyBand = 16384 / (GL * V);   // rows of B in a buffer of 64 KiB
-constexpr size_t kHeavyLds = 2 * 65536 + 256;              // two buffers and a row of zeros
+constexpr size_t kHeavyLds = 2 * 65536 + 256 + heavy_waves(64) * 1024;   // two buffers, a row of zeros, and a row's sums per lane group
 
 struct HeavyPlan {
     const int* rows;     // count row numbers, by length
@@ -49,7 +54,7 @@ struct HeavyPlan {
 
 // Blocks of a launch: group i has the rows row[i] ... row[i + 1] - 1 of the plan and the blocks block[i] ... block[i + 1] - 1,
 // each with the rows' entries in per[i] cells.
-constexpr int kHeavyGroups = 16;
+constexpr int kHeavyGroups = 17;
 struct HeavyGroups {
     int count, block[kHeavyGroups + 1], row[kHeavyGroups + 1], per[kHeavyGroups];
 };
@@ -118,33 +123,54 @@ __device__ __forceinline__ int group_lane(int x) {
     return __builtin_amdgcn_update_dpp(0, x, GL == 16 ? 0x150 + n : n * 0x55, 0xf, 0xf, true);   // row_newbcast:n, quad_perm
 }
 
-// Entries n0 ... n0 + L - 1 of the groups' batches: reads of their rows of B in LDS first, then the multiply-adds.
-template <int GL, int V, int n0, int L>
+// Entries n0 ... n0 + L - 1 of the groups' batches: their rows of B from LDS, and the multiply-adds with them.
+template <int GL, int V, int L>
 struct HeavySteps {
     typedef float vec __attribute__((ext_vector_type(V)));
     vec b[L];
-    template <int n>
+    template <int n0, int n = 0>
     __device__ __forceinline__ void read(const char* lds, int off, int lane_off) {
         if constexpr (n < L) {
             b[n] = *reinterpret_cast<const vec*>(lds + (group_lane<GL, n0 + n>(off) + lane_off));
-            read<n + 1>(lds, off, lane_off);
+            read<n0, n + 1>(lds, off, lane_off);
         }
     }
-    template <int n>
+    template <int n0, int n = 0>
     __device__ __forceinline__ void fma(float val, float (&acc)[V]) const {
         if constexpr (n < L) {
             const float s = __int_as_float(group_lane<GL, n0 + n>(__float_as_int(val)));
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[v] = fmaf(s, b[n][v], acc[v]);
-            fma<n + 1>(val, acc);
+            fma<n0, n + 1>(val, acc);
         }
     }
-    static __device__ __forceinline__ void run(const char* lds, int off, float val, int lane_off, float (&acc)[V]) {
-        HeavySteps x;
-        x.template read<0>(lds, off, lane_off);
-        x.template fma<0>(val, acc);
-    }
 };
+
+// A batch of 16 entries, as far as the leading ones that `any` tells of, from n0 on.  Up to two columns a lane the next L
+// entries' reads are on their way during the multiply-adds of L; with four there are no registers for them.
+template <int GL, int V, int L, int n0>
+__device__ __forceinline__ void heavy_batch(HeavySteps<GL, V, L>& now, unsigned any, const char* lds, int off, float val, int lane_off,
+                                            float (&sum)[V]) {
+    if constexpr (V == 4) now.template fma<n0>(val, sum);
+    if constexpr (n0 + L < GL) {
+        if (any >> (n0 + L)) {
+            HeavySteps<GL, V, L> next;
+            next.template read<n0 + L>(lds, off, lane_off);
+            if constexpr (V < 4) now.template fma<n0>(val, sum);
+            heavy_batch<GL, V, L, n0 + L>(next, any, lds, off, val, lane_off, sum);
+            return;
+        }
+    }
+    if constexpr (V < 4) now.template fma<n0>(val, sum);
+}
+
+// Calls batch with 0, 1, ... D - 1 until it returns false.
+template <int D, int d = 0, class BATCH>
+__device__ __forceinline__ bool each_batch(BATCH& batch) {
+    if (!batch(Count<d>{})) return false;
+    if constexpr (d + 1 < D) return each_batch<D, d + 1>(batch);
+    return true;
+}
 
 template <int GL, int V>
 __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
@@ -160,56 +186,59 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     char* const lds = heavy_lds;
     constexpr int kBand = kHeavyBand<GL, V>, kRow = 4 * GL * V;              // rows of a band; bytes of a row in LDS
     constexpr int kZero = 2 * 65536;                       // offset of the row of zeros
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int kWaves = heavy_waves(GL * V), kLoaders = kHeavyBlock / 64 - kWaves;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15, jc = lane & (GL - 1);
     int group = 0;
     while (group + 1 < groups.count && (int)blockIdx.x >= groups.block[group + 1]) ++group;
     const int slab = blockIdx.x - groups.block[group], row0 = groups.row[group], row1 = groups.row[group + 1];
-    const int quads = (row1 - row0 + kHeavyWaves * 4 - 1) / (kHeavyWaves * 4);
+    const int quads = (row1 - row0 + kWaves * 4 - 1) / (kWaves * 4);
     const int tile0 = blockIdx.y * GL * V;
     const int cell0 = slab * groups.per[group], cell1 = min(cell0 + groups.per[group], plan.cells);
     const int col0 = cell0 * plan.cell;
     const int col1 = cell1 == plan.cells ? k : cell1 * plan.cell;
 
-    // rows of B, in four parts: thread t brings rows t / GL + kBlock / GL * p of the band, columns jc + GL v
-    constexpr int kParts = 4, kPasses = 16 / V / kParts, kStep = kHeavyBlock / GL;
-    static_assert(kPasses >= 1, "at most 4 columns a lane");
-    float stage[kPasses * V];
-    int bcol[V];
+    if (wave >= kWaves) {
+        // From memory to LDS, a wave's lanes one after another: 4 bytes a lane, 16 where rows of B and tiles are whole
+        // 16-byte pieces.
+        auto bring = [&](auto width) {
+            constexpr int W = decltype(width)::value, kLanes = GL * V / W, kPer = 64 / kLanes, kLoads = kBand / kPer;
+            const int col = min(tile0 + lane % kLanes * W, N - W), r = lane / kLanes;
+            const float* const mine = B + (long)col * sd.cb;
+            int buffer = 0;
+            for (int first = col0; first < col1; first += kBand, buffer ^= 1) {
+                for (int i = wave - kWaves; i < kLoads; i += kLoaders) {
+                    const int row = min(first + i * kPer + r, col1 - 1);
+                    const auto from = (const __attribute__((address_space(1))) void*)(mine + (long)row * sd.rb);
+                    const auto to = (__attribute__((address_space(3))) void*)(lds + buffer * 65536 + i * 256 * W);
+                    if constexpr (W == 4) __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+                    else __builtin_amdgcn_global_load_lds(from, to, 4, 0, 0);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+            }
+        };
+        if (wave == kWaves) reinterpret_cast<float*>(lds + kZero)[lane] = 0.f;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (sd.cb == 1 && ((unsigned long long)B % 16 | N % 4 | sd.rb % 4) == 0) bring(Count<4>{});
+        else bring(Count<1>{});
+        return;
+    }
+    int bcol[V];                                           // the lane's columns
 #pragma unroll
-    for (int v = 0; v < V; ++v) bcol[v] = min(tile0 + jc + GL * v, N - 1);
-    auto fetch = [&](int first, int part) {
-#pragma unroll
-        for (int p = 0; p < kPasses; ++p) {
-            const long row = min(first + (int)threadIdx.x / GL + kStep * (part * kPasses + p), col1 - 1);
-#pragma unroll
-            for (int v = 0; v < V; ++v) stage[p * V + v] = B[row * sd.rb + (long)bcol[v] * sd.cb];
-        }
-    };
-    auto put = [&](int buffer, int part) {
-        typedef float vec __attribute__((ext_vector_type(V)));
-#pragma unroll
-        for (int p = 0; p < kPasses; ++p) {
-            vec x;
-#pragma unroll
-            for (int v = 0; v < V; ++v) x[v] = stage[p * V + v];
-            *reinterpret_cast<vec*>(lds + buffer * 65536 + ((int)threadIdx.x / GL + kStep * (part * kPasses + p)) * kRow + jc * 4 * V) = x;
-        }
-    };
-    if (threadIdx.x < 64) reinterpret_cast<float*>(lds + kZero)[threadIdx.x] = 0.f;
-    fetch(col0, 0);
+    for (int v = 0; v < V; ++v) bcol[v] = min(tile0 + jc * V + v, N - 1);
 
     // rows of the lane groups; blocks begin at different rows so that their additions to C do not meet
-    int pos[kHeavyQuads], stop[kHeavyQuads];
+    unsigned pos[kHeavyQuads], stop[kHeavyQuads];          // byte offsets: of the lane's next entry, and of the row's end
     float acc[kHeavyQuads][V];
     auto index = [&](int i) {
-        int q = wave + kHeavyWaves * i + (int)(slab * 5u % (unsigned)(kHeavyWaves * quads));
-        if (q >= kHeavyWaves * quads) q -= kHeavyWaves * quads;
+        int q = wave + kWaves * i + (int)(slab * 5u % (unsigned)(kWaves * quads));
+        if (q >= kWaves * quads) q -= kWaves * quads;
         return row0 + 4 * q + g;
     };
 #pragma unroll
     for (int i = 0; i < kHeavyQuads; ++i) {
-        pos[i] = stop[i] = 0;
+        int from = 0, to = 0;
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[i][v] = 0.f;
         if (i < quads) {
@@ -219,34 +248,35 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
                 const int s = rowptr[r], e = rowptr[r + 1];
                 const int* at = plan.at + (long)h * (plan.cells + 1);
                 if (e - s >= plan.min_len) {
-                    pos[i] = cell0 == 0 ? s : min(max(at[cell0], s), e);
-                    stop[i] = cell1 == plan.cells ? e : min(max(at[cell1], pos[i]), e);
+                    from = cell0 == 0 ? s : min(max(at[cell0], s), e);
+                    to = cell1 == plan.cells ? e : min(max(at[cell1], from), e);
                 }
             }
         }
+        pos[i] = (unsigned)(from + j) * 4u;
+        stop[i] = (unsigned)to * 4u;
     }
-#pragma unroll
-    for (int q = 0; q < kParts; ++q) { put(0, q); if (q + 1 < kParts) fetch(col0, q + 1); }
-    __syncthreads();
     struct Entry { int c; float v; };
-    auto request = [&](int p, int end) {                   // the lane's entry of a batch; past the end any entry
-        const unsigned at = p + j < end ? (unsigned)(p + j) * 4u : 0u;
+    // entries at byte offset p; past the last one of the matrix zeros
+    const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(colind), 0, plan.nnz * 4, 0x00027000);
+    const __amdgpu_buffer_rsrc_t numbers = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vals), 0, plan.nnz * 4, 0x00027000);
+    auto request = [&](unsigned p) {
         Entry e;
-        e.c = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(colind) + at);
-        e.v = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(vals) + at);
+        e.c = (int)__builtin_amdgcn_raw_buffer_load_b32(cols, (int)p, 0, 0);
+        e.v = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(numbers, (int)p, 0, 0));
         return e;
     };
-    constexpr int D = GL * V == 64 ? 2 : 4, L = GL * V == 32 ? 8 : 4;      // batches in flight; entries read together
+    constexpr int D = V == 4 ? 2 : 4, L = 4;               // batches in flight; entries read together
     Entry next[D];
-    auto request_first = [&](int p, int end) {
+    auto request_first = [&](unsigned p) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) next[d] = request(p + 16 * d, end);
+        for (int d = 0; d < D; ++d) next[d] = request(p + 64 * d);
     };
-    request_first(pos[0], stop[0]);
+    request_first(pos[0]);
     int buffer = 0;
     for (int first = col0; first < col1; first += kBand) {
         const bool last = first + kBand >= col1;           // the last band takes what is left
-        if (!last) fetch(first + kBand, 0);
+        lds_barrier();                                     // the band is here
         const unsigned here = (unsigned)min(kBand, col1 - first);              // rows of the band
         const int base = buffer * 65536, lane_off = jc * 4 * V;
 #pragma unroll
@@ -255,80 +285,81 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
                 Entry e[D];
 #pragma unroll
                 for (int d = 0; d < D; ++d) e[d] = next[d];
-                int p = pos[i];
-                const int end = stop[i];
+                unsigned p = pos[i];
+                const unsigned end = stop[i];
+                unsigned long long alive = ~0ull;          // lanes of groups that are not done with the band
                 // the next set's first batches are on their way while this one is worked on
-                if (i + 1 < kHeavyQuads && i + 1 < quads) request_first(pos[(i + 1) % kHeavyQuads], stop[(i + 1) % kHeavyQuads]);
-                int limit = last ? 0x7fffffff : first + kBand;
-                auto batch = [&](Entry& ahead) {           // whether some group took all of its batch
-                    const Entry now = ahead;
-                    ahead = request(p + 16 * D, end);
+                if (i + 1 < kHeavyQuads && i + 1 < quads) request_first(pos[(i + 1) % kHeavyQuads]);
+                const int limit = last ? 0x7fffffff : first + kBand;
+                auto batch = [&](auto which) {
+                    constexpr int d = decltype(which)::value;
+                    const Entry now = e[d];
+                    e[d] = request(p + 64 * D);
+                    asm volatile("; batch %0" ::"n"(d));   // one loop over batches of changing registers would wait for each request
                     // leading entries of the batch that lie in the band or before it
-                    bool take = p + j < end && now.c < limit;
-                    unsigned long long bits = __ballot(take);
+                    unsigned long long bits = alive & __builtin_amdgcn_ballot_w64(p < end) & __builtin_amdgcn_ballot_w64(now.c < limit);
                     if (bits & ~(bits << 1 | 0x0001000100010001ull)) {         // columns out of order
                         const unsigned m16 = (unsigned)(bits >> (16 * g)) & 0xffffu;
-                        take = j < __builtin_ctz(~m16);
-                        bits = __ballot(take);
+                        bits = __builtin_amdgcn_ballot_w64(j < __builtin_ctz(~m16));
                     }
-                    const unsigned half = lane & 32 ? (unsigned)(bits >> 32) : (unsigned)bits;
-                    const int cnt = __popc((half >> (lane & 16)) & 0xffffu);
                     const int local = now.c - first;
-                    const bool inside = take && (unsigned)local < here;
+                    const unsigned long long within = bits & __builtin_amdgcn_ballot_w64((unsigned)local < here);
+                    const bool inside = __builtin_amdgcn_inverse_ballot_w64(within);
                     const int off = inside ? base + local * kRow : kZero;
                     const float val = inside ? now.v : 0.f;
                     const unsigned any = ((unsigned)bits | (unsigned)(bits >> 16) | (unsigned)(bits >> 32) | (unsigned)(bits >> 48)) & 0xffffu;
                     float sum[V];
 #pragma unroll
                     for (int w = 0; w < V; ++w) sum[w] = 0.f;
-                    if constexpr (GL == 16) {
-                        if (any) HeavySteps<GL, V, 0, L>::run(lds, off, val, lane_off, sum);
-                        if constexpr (L == 4) { if (any & 0xfff0u) HeavySteps<GL, V, 4, L>::run(lds, off, val, lane_off, sum); }
-                        if (any & 0xff00u) HeavySteps<GL, V, 8, L>::run(lds, off, val, lane_off, sum);
-                        if constexpr (L == 4) { if (any & 0xf000u) HeavySteps<GL, V, 12, L>::run(lds, off, val, lane_off, sum); }
-                    } else {
-                        HeavySteps<GL, V, 0, L>::run(lds, off, val, lane_off, sum);
+                    if (GL == 4 || any) {
+                        HeavySteps<GL, V, L> steps;
+                        steps.template read<0>(lds, off, lane_off);
+                        heavy_batch<GL, V, L, 0>(steps, any, lds, off, val, lane_off, sum);
                     }
 #pragma unroll
                     for (int w = 0; w < V; ++w) acc[i][w] += sum[w];           // one rounding of the long sum for 16 entries
-                    if (__any(take && !inside)) {          // columns out of order, or a plan of another matrix
+                    if (within != bits) {                  // columns out of order, or a plan of another matrix
                         strayed = true;
+                        const int far = (int)__builtin_amdgcn_inverse_ballot_w64(bits & ~within);
                         for (int n = 0; n < 16; ++n) {
                             const int cn = __shfl(now.c, 16 * g + n);
                             const float vn = __shfl(now.v, 16 * g + n);
-                            if (__shfl((int)(take && !inside), 16 * g + n) && (GL == 16 || j / GL == n / GL)) {
+                            if (__shfl(far, 16 * g + n) && (GL == 16 || j / GL == n / GL)) {
 #pragma unroll
                                 for (int w = 0; w < V; ++w) acc[i][w] = fmaf(vn, B[(long)cn * sd.rb + (long)bcol[w] * sd.cb], acc[i][w]);
                             }
                         }
                     }
-                    p += cnt;
-                    if (cnt < 16) limit = (int)0x80000000; // this group is done with the band
+                    if (bits == ~0ull) {
+                        p += 64;
+                    } else {
+                        const unsigned half = lane & 32 ? (unsigned)(bits >> 32) : (unsigned)bits;
+                        const unsigned cnt = __popc((half >> (lane & 16)) & 0xffffu);
+                        p += 4 * cnt;
+                        alive &= __builtin_amdgcn_ballot_w64(cnt == 16);
+                    }
                     return (any & 0x8000u) != 0;
                 };
-                if constexpr (D == 2) while (batch(e[0]) && batch(e[1])) {}
-                else while (batch(e[0]) && batch(e[1]) && batch(e[2]) && batch(e[3])) {}
+                while (each_batch<D>(batch)) {}
                 pos[i] = p;
-                // the next band's parts follow one another, two sets of rows apart
-                if (!last && i % 2 == 1 && i / 2 + 1 < kParts) { put(buffer ^ 1, i / 2); fetch(first + kBand, i / 2 + 1); }
             }
         }
-        if (!last) {
-            request_first(pos[0], stop[0]);
-#pragma unroll
-            for (int q = 0; q < kParts; ++q) {
-                if (q < quads / 2 && q + 1 < kParts) continue;                 // done above
-                put(buffer ^ 1, q);
-                if (q + 1 < kParts) fetch(first + kBand, q + 1);
-            }
-            lds_barrier();
-            buffer ^= 1;
-        }
+        if (!last) request_first(pos[0]);
+        buffer ^= 1;
     }
     if (strayed && lane == 0) *plan.stale = 1;
 #pragma unroll
     for (int i = 0; i < kHeavyQuads; ++i) {
         if (i < quads) {
+            if constexpr (GL == 16 && V > 1) {             // the sums of 16 lanes change hands, so that an addition covers neighbouring columns
+                float* turn = reinterpret_cast<float*>(lds + kZero + 256) + (wave * 4 + g) * GL * V;
+#pragma unroll
+                for (int v = 0; v < V; ++v) turn[j * V + v] = acc[i][v];
+                wave_lds_sync();
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc[i][v] = turn[j + GL * v];
+                wave_lds_sync();
+            }
             const int h = index(i);
             if (h < row1) {
                 const int r = plan.rows[h];
@@ -339,7 +370,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
                             acc[i][v] = dpp_add<0x128>(acc[i][v]);
                             acc[i][v] = dpp_add<0x124>(acc[i][v]);
                         }
-                        const int n = tile0 + jc + GL * v;
+                        const int n = tile0 + (GL == 16 ? j + GL * v : jc * V + v);
                         if (n < N && j < GL) unsafeAtomicAdd(C + (long)r * sd.rc + (long)n * sd.cc, acc[i][v]);
                     }
                 }

@@ -615,19 +615,22 @@ int launch_columns(const Problem& p, const MatrixHint& hint) {
     return DA_OK;
 }
 
-// How the heavy rows' part of a product is dealt to the blocks.  A block has 131 KB of LDS and 16 waves, one to a CU: as many
+// How the heavy rows' part of a product is dealt to the blocks.  A block has 147 KB of LDS and 16 waves, one to a CU: as many
 // ranges of columns as make one block per CU over all groups of rows and column tiles.  Every block's part of a row is one
 // more rounding of the row's sum, as every chunk of EB+SR is: a group has no more ranges than its shortest row's sum
 // takes.  Rows of similar length make a group, so that the ranges of long rows need not be as few as those of short ones,
-// and the ranges are as many as the group's entries want.  524 rows of 20 000 to 100 000, N = 64: 64, 94 and 94 ranges for
-// 192, 192 and 140 rows, 326 us; one group of 256 ranges 323, the shortest rows in parts of 78 entries; N = 8: 121 and 130;
-// N = 16: 183 and 166; 1500 rows of 3200 to 30 000, N = 64: 170 and 205.
+// and the ranges are as many as the group's entries want.  524 rows of 20 000 to 100 000, N = 64: 61, 90 and 103 ranges for
+// 180, 180 and 164 rows, whose blocks take 186, 181 and 188 us (before, with the ranges in cells twice as large and less for a
+// row's turn, two groups' 198 and 170).
 struct HeavyLaunch {
     HeavyGroups groups;
     double load;         // entries, and work of as much time, of the block that has most
 };
 
 constexpr double kHeavyLeast = 5000.0;   // work of a block that is worth a range of its own (40 rows of 16 000, N = 8: 16 us, 18 in twice as many)
+
+// Entries that take as long as a row's turn in a band of B, by the times of blocks with short and with long rows.
+constexpr double kHeavyVisit = 12.0;
 
 constexpr int heavy_tile(int64_t N) { return N <= 8 ? 8 : (N <= 16 ? 16 : (N <= 32 ? 32 : 64)); }
 
@@ -643,7 +646,7 @@ double heavy_part(double n, double c) {
 HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sums, int64_t k, int64_t N, int chunk) {
     const int tile = heavy_tile(N), band = 16384 / tile;
     const int64_t tiles = (N + tile - 1) / tile;
-    const int quads = (pl.count + 3) / 4, most = kHeavyWaves * kHeavyQuads, least = (quads + most - 1) / most;
+    const int waves = heavy_waves(tile), quads = (pl.count + 3) / 4, most = waves * kHeavyQuads, least = (quads + most - 1) / most;
     HeavyLaunch best{};
     auto deal = [&](int n, int unit) {                      // n groups of whole units of 4 * unit rows
         HeavyLaunch x{};
@@ -655,9 +658,9 @@ HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sum
         for (int i = 0; i <= n; ++i) x.groups.row[i] = std::min(pl.count, 4 * unit * (int)((int64_t)units * i / n));
         for (int i = 0; i < n; ++i) {
             const int r0 = x.groups.row[i], r1 = x.groups.row[i + 1], here = (r1 - r0 + 3) / 4;
-            const double entries = (double)(sums[r1] - sums[r0]) + 8.0 * (r1 - r0) * ((double)k / band);
+            const double entries = (double)(sums[r1] - sums[r0]) + kHeavyVisit * (r1 - r0) * ((double)k / band);
             // a CU needs some 12 of its waves to be busy
-            const double longest = entries * ((here + kHeavyWaves - 1) / kHeavyWaves) / here;
+            const double longest = entries * ((here + waves - 1) / waves) / here;
             cost[i] = std::max(entries, 12.0 * longest) + 2.0 * (double)k;
             all += cost[i];
             const double shortest = (double)(sums[r0 + 1] - sums[r0]);
@@ -679,7 +682,7 @@ HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sum
     // every wave of a block with as many rows as the others, as far as that goes
     deal(least, 1);
     for (int n = least; n <= std::min(kHeavyGroups, least + 3); ++n) {
-        if (n * kHeavyWaves <= quads) deal(n, kHeavyWaves);
+        if (n * waves <= quads) deal(n, waves);
         else if (n == 2 && quads >= 2) deal(n, 1);
     }
     return best;
@@ -1457,7 +1460,7 @@ namespace {
 // rows costs more than the entries).  Worth a kernel of their own where they hold most entries, every row of B serves
 // at least 8 of them, and the other rows are even enough to be taken one by one.
 constexpr int64_t kHeavyShare = 32, kHeavyMinCols = 16384, kHeavyMinEntries = 400000, kHeavyUses = 8;
-constexpr int kHeavyMost = 8192, kHeavyCells = 1024, kRestLongest = 1024;
+constexpr int kHeavyMost = 8192, kHeavyCells = 2048, kRestLongest = 1024;   // at more than half as many rows half as many cells: 32 MB
 constexpr double kRestLen = 64.0;
 
 // Without the memory for it there is no list: it steers the launches of products, the orders do without it.
@@ -1516,7 +1519,8 @@ try {
         (*row_sums)[i + 1] = (*row_sums)[i] + by_length[i].first;
     }
 
-    const int cell = (int)((k + kHeavyCells - 1) / kHeavyCells), cells = (int)((k + cell - 1) / cell);
+    const int64_t finest = rows.size() <= kHeavyMost / 2 ? kHeavyCells : kHeavyCells / 2;
+    const int cell = (int)((k + finest - 1) / finest), cells = (int)((k + cell - 1) / cell);
     const size_t words = (size_t)(m + 31) / 32, n = rows.size();
     auto block = std::make_shared<DeviceBlock>();
     const size_t ints = ((n + 63) & ~size_t(63)) + ((words + 63) & ~size_t(63)) + n * (size_t)(cells + 1);

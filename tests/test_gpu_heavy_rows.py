@@ -294,3 +294,26 @@ def test_sums_are_as_exact_as_in_chunks(N, longest_other, monkeypatch):
         # The order of additions changes the figures by a tenth from run to run; the mean over n sums is off by
         # 1 / sqrt(2 n), 4 % of it for 300.
         assert rows.sum() * N < 300 or a <= 1.15 * b
+
+
+# B comes in pieces of 16 bytes where its rows are such pieces, and in single numbers where they are not
+@pytest.mark.parametrize("N", [4, 8, 20, 64])
+@pytest.mark.parametrize("offset, more", [(0, 4), (0, 3), (1, 4), (4, 0), (2, 1)])
+def test_rows_of_b_at_any_alignment(prepared, N, offset, more):
+    from paper_2202_08556_amd import binding as da
+    host, dev = prepared
+    print("heavy rows N", N, "offset", offset, "pitch", N + more, flush=True)
+    B = dense(N)
+    want, _ = orc.spmm(*host, B)
+    room = torch.full((K * (N + more) + offset,), float("nan"), device="cuda")
+    inner = room[offset:].view(K, N + more)
+    inner[:, :N] = torch.from_numpy(B).cuda()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    da.da_spmm_ex(M, K, N, *dev, inner, N + more, da.DA_ROW_MAJOR, C, N, da.DA_ROW_MAJOR, da.DA_EB_RM_SR)
+    assert np.array_equal(C.cpu().numpy(), want.astype(np.float32) + 0.0)
+
+
+# as many rows as the waves of a block hold, and one more: 504 up to 8 columns, 540 beyond
+@pytest.mark.parametrize("heavy, N", [(504, 8), (505, 8), (540, 16), (541, 64)])
+def test_rows_that_fill_a_block(heavy, N):
+    test_groups_of_rows(heavy, N)
