@@ -246,6 +246,27 @@ bool wide_lanes_pay(bool eb, int64_t N, const MatrixHint& hint, const PlanInfo& 
     return waves >= (int64_t)cu_count() * 4 * 12 || (hint.nnz >= 600000 && hint.seen_len >= 16.0 && hint.seen_len <= 1500.0);
 }
 
+// Entries of a matrix that are many and lie in rows of uneven length: tiles on XCDs of their own wait for each other.
+bool uneven_rows(int64_t m, const MatrixHint& hint) { return hint.nnz >= 2000000 && hint.seen_len * (double)m > 1.5 * (double)hint.nnz; }
+
+// RB tiles of tile_cols columns on XCDs of their own, see launch_w.
+bool slices_fit_l2(int64_t k, int64_t N, int64_t tile_cols) { return k * tile_cols * 4 <= 12 << 20 && k * N * 4 > 9 << 19; }
+
+// RB+PR with whole 128-byte pieces of B: whether tiles of 32 columns beat tiles of 64.  They give a row 8 slots instead of
+// 4, which long rows fill, but read the entries twice as often.  Rows of more than a hundred entries gain where they are uneven
+// (lognormal, coefficient 0.9, mean 60: k = 3000, N = 64 11.5 -> 8.4 us, N = 128 13.6 -> 10.0; 60 000: 115 -> 86 and 212 -> 161) or B is
+// larger than an L2 (rows of 120 +- 11: k = 60 000, N = 64 191 -> 144, N = 128 380 -> 286, 20 000: 33.2 -> 31.4 and, N = 192,
+// 114 -> 91; 8000: N = 64 13.5 and 14.8, N = 128 23.6 and 26.5), shorter ones do not (lognormal rows of 23, seen as 62: 49.9 and
+// 51.2, k = 40 000, N = 128 58 and 66; rows of 25: 46 and 49).  Not where tiles of 64 have XCDs of their own (mean 60, k = 8000,
+// N = 256: 30 and 36), and not where rows are very uneven: most are then short or empty (20 000 rows of 180 among a million: N = 64
+// 168 and 316), and in graphs popular columns go with that (power-law, N = 64: 104 and 115, N = 128 175 and 205).
+bool narrow_tiles_pay(int64_t m, int64_t k, int64_t N, const MatrixHint& hint) {
+    if (N % 32 != 0 || hint.nnz <= 0 || hint.seen_len < 100.0) return false;
+    const double unevenness = hint.seen_len * (double)m / (double)hint.nnz;
+    if (unevenness > 3.0 || ((N == 128 || N == 256 || N == 512) && slices_fit_l2(k, N, 64) && !uneven_rows(m, hint))) return false;
+    return k > 16384 || unevenness >= 1.4;
+}
+
 // Rounding error of a row of n entries that is summed in chunks of c entries, relative to n: every chunk is summed
 // one entry after another by each of `chains` partial sums, and the chunks are added one after another.  For
 // products of random sign the errors of a sum of c terms grow with c, for products of one sign with c^2.
@@ -321,7 +342,7 @@ int chunk_size(bool cm, bool pr, int64_t N, bool whole, const Geometry& g, const
 // 0.4 M, 0.4 a row, N = 24: 86 and 60; N = 64: 48 and 52; 0.2 M, 6.7 a row, N = 8: 18 and 20).  PR: fewer than 8 where
 // the size without a plan is none of the plan's (0.64 M, 1.6 a row, N = 16, EB+CM+PR: 39 and 34; 2 M, 6.7 a row,
 // N = 4: 30 and 25; 0.2 M, 6.7 a row, N = 8, with chunks of 64 either way: 14 and 16).
-int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides& sd, bool aligned,
+int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t k, int64_t N, const Strides& sd, bool aligned,
                   const MatrixHint& hint, PlanInfo plan, Geometry* out) {
     const bool vec4_ok = N >= 4 && sd.cb == 1 && sd.cc == 1;      // 16-byte accesses, at any alignment
     Geometry g{1, 1, 1, 0, -1, kSweepStripe, true};
@@ -347,6 +368,7 @@ int pick_geometry(bool cm, bool pr, bool eb, int64_t m, int64_t N, const Strides
         // 574 us for groups of 8 / 16 / 32) and 4 under RB (wave per row: 629 / 559 / 636 us)
         const int cap = g.V == 4 ? ((pr && !eb) ? 16 : 32) : (pr ? kDefaultGroupPR : kWave);
         if (g.G > cap) g.G = cap;
+        if (pr && !eb && whole && N >= 64 && narrow_tiles_pay(m, k, N, hint)) g.G = 8;
         g.NV = 1;
     }
     static const bool tune = std::getenv("DA_SPMM_TUNE") != nullptr;
@@ -402,12 +424,13 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     // 5000 11.3 -> 9.3, 24 000 62.2 -> 60.9, 27-point stencil of 28^3 28.6 -> 24.2.  4096 columns, N = 256, 4.2 MB: 6.1 and 6.2).
     // Not where many entries lie in rows of uneven length, whose XCDs then wait for each other (50 000 lognormal rows of 60,
     // PR, N = 256: k = 6000 133 and 140, 49 152 331 and 345; 5000 such rows, 12 000: 37 and 20).
-    auto uneven = [&] {
-        const MatrixHint hint = lookup_matrix(p.rowptr, p.m);
-        return hint.nnz >= 2000000 && hint.seen_len * (double)p.m > 1.5 * (double)hint.nnz;
-    };
-    const bool slices_fit = V == 4 && G >= 16 && (fam == RB_SR || fam == RB_PR) && p.sd.cb == 1 &&
-                            tiles_l * tile_cols - p.N <= tile_cols / 8 && p.k * tile_cols * 4 <= 12 << 20 && (long)p.k * p.N * 4 > 9 << 19 && !uneven();
+    // Tiles of 32 columns (narrow_tiles_pay): up to 6 MB, and then uneven rows gain, too (lognormal rows of 100, coefficient 0.7: N = 64,
+    // k = 15 000 27.4 -> 24.9, 40 000 70.9 -> 66.6, 61 417 132 and 131, 150 000 449 and 459).
+    const bool narrow = G == 8 && fam == RB_PR;
+    const bool slices_fit = V == 4 && (G >= 16 || narrow) && (fam == RB_SR || fam == RB_PR) && p.sd.cb == 1 &&
+                            tiles_l * tile_cols - p.N <= tile_cols / 8 &&
+                            (narrow ? tiles_l > 1 && p.k * tile_cols * 4 <= 6 << 20
+                                    : slices_fit_l2(p.k, p.N, tile_cols) && !uneven_rows(p.m, lookup_matrix(p.rowptr, p.m)));
     const int pin = ((geo.pin < 0 ? slices_fit : geo.pin != 0) && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
     // grid for `bx` blocks per column tile
     auto grid_for = [&](long bx) {
@@ -1046,8 +1069,8 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
         const MatrixHint hint = lookup_matrix(rowptr, m);
         if (columns_pay(algo, m, k, N, sd.rc != 1, hint)) return launch_columns(p, hint);
     }
-    const bool ask = eb || (!cm && !pr && N > 16 && (N < 32 || N % 4 != 0 || ends % 16 != 0));   // RB: only where the lanes depend on it
-    const int st = pick_geometry(cm, pr, eb, m, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
+    const bool ask = eb || (pr && !cm && N >= 64 && N % 32 == 0) || (!cm && !pr && N > 16 && (N < 32 || N % 4 != 0 || ends % 16 != 0));   // RB: only where the lanes depend on it
+    const int st = pick_geometry(cm, pr, eb, m, k, N, sd, ends % 16 == 0, ask ? lookup_matrix(rowptr, m) : MatrixHint{nullptr, 0, -1, 0.0},
                                  eb ? plan_info(rowptr, colind, m) : PlanInfo{false, 0.0}, &g);
     if (st != DA_OK) return st;
     if (algo == DA_EB_RM_SR && N <= 64L * kMaxGridY && !tuned && env_int("DA_SPMM_NO_HEAVY", 0) == 0) {
@@ -1061,7 +1084,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
                 Problem q = p;
                 q.layer = nullptr;
                 Geometry rest;
-                const int rs = pick_geometry(false, false, false, m, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
+                const int rs = pick_geometry(false, false, false, m, k, N, sd, ends % 16 == 0, MatrixHint{rowptr, m, heavy.plan.nnz, heavy.rest_len},
                                              PlanInfo{false, 0.0}, &rest);
                 if (rs != DA_OK) return rs;
                 q.left_out = LeftOut{heavy.bits, rowptr + m, heavy.plan.min_len, heavy.plan.nnz, std::min(g.chunk, heavy.plan.min_len - 1),
