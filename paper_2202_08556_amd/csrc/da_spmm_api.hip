@@ -256,15 +256,21 @@ bool slices_fit_l2(int64_t k, int64_t N, int64_t tile_cols) { return k * tile_co
 // 4, which long rows fill, but read the entries twice as often.  Rows of more than a hundred entries gain where they are uneven
 // (lognormal, coefficient 0.9, mean 60: k = 3000, N = 64 11.5 -> 8.4 us, N = 128 13.6 -> 10.0; 60 000: 115 -> 86 and 212 -> 161) or B is
 // larger than an L2 (rows of 120 +- 11: k = 60 000, N = 64 191 -> 144, N = 128 380 -> 286, 20 000: 33.2 -> 31.4 and, N = 192,
-// 114 -> 91; 8000: N = 64 13.5 and 14.8, N = 128 23.6 and 26.5), shorter ones do not (lognormal rows of 23, seen as 62: 49.9 and
-// 51.2, k = 40 000, N = 128 58 and 66; rows of 25: 46 and 49).  Not where tiles of 64 have XCDs of their own (mean 60, k = 8000,
-// N = 256: 30 and 36), and not where rows are very uneven: most are then short or empty (20 000 rows of 180 among a million: N = 64
-// 168 and 316), and in graphs popular columns go with that (power-law, N = 64: 104 and 115, N = 128 175 and 205).
+// 114 -> 91; 8000: N = 64 13.5 and 14.8, N = 128 23.6 and 26.5).  From 55 on it takes more of that: uneven rows (mean 23, seen as 62:
+// k = 4000, N = 64 9.2 -> 6.9, N = 128 12.9 -> 8.9; 20 000, N = 64 23.6 -> 19.9; 61 417, N = 64 59.0 -> 56.1, N = 96 82 -> 77;
+// 150 000, N = 128 240 and 251; mean 30, seen as 60: 61 417, N = 128 116 -> 105, 20 000, N = 96 26.9 and 27.9), even ones of a very wide B
+// (rows of 60: 61 417, N = 64 103 -> 81, N = 128 201 -> 159; 20 000, N = 64 19.9 and 21.8).  Shorter ones lose (mean 12, seen as 36: 61 417, N = 64
+// 36 and 45).  Not where tiles of 64 have XCDs of their own (mean 60, k = 8000, N = 256: 30 and 36), and not where rows are very
+// uneven: most are then short or empty (20 000 rows of 180 among a million: N = 64 168 and 316), and in graphs popular columns
+// go with that (power-law, N = 64: 104 and 115, N = 128 175 and 205).
 bool narrow_tiles_pay(int64_t m, int64_t k, int64_t N, const MatrixHint& hint) {
-    if (N % 32 != 0 || hint.nnz <= 0 || hint.seen_len < 100.0) return false;
+    if (N % 32 != 0 || hint.nnz <= 0 || hint.seen_len < 55.0) return false;
     const double unevenness = hint.seen_len * (double)m / (double)hint.nnz;
     if (unevenness > 3.0 || ((N == 128 || N == 256 || N == 512) && slices_fit_l2(k, N, 64) && !uneven_rows(m, hint))) return false;
-    return k > 16384 || unevenness >= 1.4;
+    const bool uneven = unevenness >= 1.4;
+    if (hint.seen_len >= 100.0) return k > 16384 || uneven;
+    if (N > 128) return false;
+    return uneven ? k <= 16384 || N == 64 || (k > 40000 && (N < 128 || hint.nnz >= 28 * m)) : k > 40000;
 }
 
 // Rounding error of a row of n entries that is summed in chunks of c entries, relative to n: every chunk is summed

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 def matrix(m, k, even, seed):
     rng = np.random.default_rng(seed)
-    lens = np.full(m, 130) if even else np.where(np.arange(m) % 3 == 0, 300, 60)
+    lens = np.full(m, even) if even else np.where(np.arange(m) % 3 == 0, 300, 60)
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     colind = rng.integers(0, k, size=int(rowptr[-1])).astype(np.int32)
     return rowptr, colind, rng.choice(np.array([-2, -1, 1, 2], np.float32), colind.size)
@@ -21,7 +21,8 @@ def matrix(m, k, even, seed):
 # where tiles of 64 are pinned
 @pytest.mark.parametrize("m,k,even,N,narrow", [
     (301, 900, False, 64, True), (301, 900, False, 96, True), (301, 900, False, 256, True), (1000, 60_000, False, 128, True),
-    (1000, 60_000, True, 64, True), (1000, 20_000, True, 192, True), (301, 900, True, 64, False), (301, 900, False, 72, False), (301, 12_000, False, 128, False),
+    (1000, 60_000, 130, 64, True), (1000, 20_000, 130, 192, True), (1000, 60_000, 60, 128, True), (301, 900, 130, 64, False),
+    (1000, 20_000, 60, 64, False), (301, 900, False, 72, False), (301, 12_000, False, 128, False),
 ])
 def test_tiles_of_32_columns(m, k, even, N, narrow):
     from paper_2202_08556_amd import binding as da
@@ -29,7 +30,7 @@ def test_tiles_of_32_columns(m, k, even, N, narrow):
     B = np.random.default_rng(1).integers(-4, 5, (k, N)).astype(np.float32)
     want, _ = orc.spmm(rowptr, colind, vals, B)
     dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals, B)]
-    print(f"tiles of 32 columns m={m} k={k} N={N} even={even}", flush=True)
+    print(f"tiles of 32 columns m={m} k={k} N={N} rows={even}", flush=True)
     da.da_spmm_features(m, N, dev[0])
     C = torch.full((m, N), float("nan"), device="cuda")
     names = kernels_of(lambda: da.da_spmm(m, k, N, *dev, C, da.DA_RB_RM_PR))
