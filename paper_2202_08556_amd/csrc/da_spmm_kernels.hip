@@ -635,7 +635,10 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
             if (p0 + kWave < end) next.fetch(colind, vals, p0 + kWave, end, lane);
             const int cnt = min(kWave, end - p0);
             if (nvec > 0) {
-                for_blocks<UL>(cnt / S, [&](auto uc, int t) {
+                // The last step may be ragged: slots behind the last entry gather row 0 and take zeros in its place.  A step of
+                // its own was one more round trip to memory (lognormal rows of 23, k = 61 417, N = 64: 54.6 -> 47 us, N = 32
+                // 33.1 -> 29.7; 25 entries a row, N = 32 18.2 -> 16.1; 27-point stencil of 30^3, N = 32 11.5 -> 10.0).
+                for_blocks<UL>((cnt + S - 1) / S, [&](auto uc, int t) {
                     constexpr int UU = decltype(uc)::value;
                     int2 ee[UU];
                     Acc<V, G, NV> b[UU];
@@ -643,6 +646,11 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
                     for (int u = 0; u < UU; ++u) ee[u] = st[(t + u) * S + s];
 #pragma unroll
                     for (int u = 0; u < UU; ++u) b[u].load(brow.row(ee[u].x), cols, sd.cb);
+                    const bool held = (t + UU - 1) * S + s < cnt;
+#pragma unroll
+                    for (int i = 0; i < NV; ++i)
+#pragma unroll
+                        for (int v = 0; v < V; ++v) b[UU - 1].a[i][v] = held ? b[UU - 1].a[i][v] : 0.f;
 #pragma unroll
                     for (int u = 0; u < UU; ++u) {
                         if (!GROUPED || UU == 1) {
@@ -655,13 +663,6 @@ __global__ __launch_bounds__(kBlock) void rb_pr_kernel(
                         }
                     }
                 });
-                const int t = (cnt / S) * S + s;              // ragged last step
-                if (t < cnt) {
-                    const int2 ee = st[t];
-                    Acc<V, G, NV> b;
-                    b.load(brow.row(ee.x), cols, sd.cb);
-                    acc.fma(__int_as_float(ee.y), b);
-                }
             }
             wave_lds_sync();
         }
