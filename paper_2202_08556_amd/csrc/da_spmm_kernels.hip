@@ -1099,8 +1099,11 @@ __device__ __forceinline__ int wave_inclusive_scan_dpp(int v) {
 
 constexpr int kStagedChunk = 512;   // EB+PR: largest chunk whose row starts are staged in LDS
 
+// Six waves per SIMD up to 80 registers: with 81 the kernel takes five, and rows shorter than a chunk a tenth longer.  Steps inside
+// one row, without selects and with half of the additions in multiply-adds: A^T of a power-law graph, 4.5 M entries, N = 64 101 -> 96 us;
+// rows of 200, N = 64 17.2 -> 15.7, N = 128 23.1 -> 21.0.
 template <int V, int G, int NV, bool WIDE, class END>
-__global__ __launch_bounds__(kBlock) void eb_pr_kernel(
+__global__ __launch_bounds__(kBlock, V == 4 && G >= 4 ? 6 : 1) void eb_pr_kernel(
     int m, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind,
     const float* __restrict__ vals, const float* __restrict__ B, float* __restrict__ C, int chunk,
     int pin_tiles, Schedule sch, END after)
@@ -1213,38 +1216,41 @@ __global__ __launch_bounds__(kBlock) void eb_pr_kernel(
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {
                     if constexpr (G > 1) e[u] = st[((tb + u) * S + s) & (kWave - 1)]; else e[u] = mine;
-                    if ((tb + u) * S + s >= cnt) e[u].z = -1;
                 }
                 // branch-free gathers: slots past the end of the chunk hold column 0
                 if (nvec > 0) {
 #pragma unroll
                     for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), cols, sd.cb);
                 }
+                // all steps in one row that does not end here: their products are added to each other first, so that
+                // a slot's sum takes one addition for four entries and no step looks for row boundaries (N = 65, rows of
+                // 400: error 2.3e-7 with an addition each, 1.3e-7 now, as with 8 slots; 296 -> 182 us).  Every slot holds an
+                // entry then, and two of the products are multiply-adds.
+                if constexpr (UU == 4) {
+                    const int row0 = __builtin_amdgcn_readfirstlane(e[0].z);
+                    if ((tb + UU) * S <= cnt && row0 == __builtin_amdgcn_readlane(e[UU - 1].z, (S - 1) * G) &&
+                        (__builtin_amdgcn_readlane(e[UU - 1].w, (S - 1) * G) & 2) == 0) {
+                        if (cur < 0) { cur = row0; cur_started = (__builtin_amdgcn_readfirstlane(e[0].w) & 1) != 0; }
+                        b[0].scale(__int_as_float(e[0].y));
+                        b[0].fma(__int_as_float(e[1].y), b[1]);
+                        b[2].scale(__int_as_float(e[2].y));
+                        b[2].fma(__int_as_float(e[3].y), b[3]);
+                        b[0].add(b[2]);
+                        acc.add(b[0]);
+                        continue;
+                    }
+                }
                 // all products first: no store or atomic is issued while a gather is outstanding
                 // (stores share the in-order memory counter with loads)
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {
+                    if ((tb + u) * S + s >= cnt) e[u].z = -1;
                     const bool ok = e[u].z >= 0 && nvec > 0;
                     const float a = __int_as_float(e[u].y);
 #pragma unroll
                     for (int i = 0; i < NV; ++i)
 #pragma unroll
                         for (int v = 0; v < V; ++v) b[u].a[i][v] = ok ? a * b[u].a[i][v] : 0.f;
-                }
-                // all steps in one row that does not end here: their products are added to each other first, so that
-                // a slot's sum takes one addition for four entries and no step looks for row boundaries (N = 65, rows of
-                // 400: error 2.3e-7 with an addition each, 1.3e-7 now, as with 8 slots; 296 -> 182 us)
-                if constexpr (UU == 4) {
-                    const int row0 = __builtin_amdgcn_readfirstlane(e[0].z);
-                    if ((tb + UU) * S <= cnt && row0 == __builtin_amdgcn_readlane(e[UU - 1].z, (S - 1) * G) &&
-                        (__builtin_amdgcn_readlane(e[UU - 1].w, (S - 1) * G) & 2) == 0) {
-                        if (cur < 0) { cur = row0; cur_started = (__builtin_amdgcn_readfirstlane(e[0].w) & 1) != 0; }
-                        b[0].add(b[1]);
-                        b[2].add(b[3]);
-                        b[0].add(b[2]);
-                        acc.add(b[0]);
-                        continue;
-                    }
                 }
 #pragma unroll
                 for (int u = 0; u < UU; ++u) {
