@@ -641,7 +641,7 @@ __device__ __forceinline__ unsigned long long digit_peers_of(unsigned d, unsigne
 // LDS of a scatter block in bytes: tile (key, value, digit), digit offsets, 16-bit counters per wave.
 template <int ROUNDS>
 constexpr size_t transpose_scatter_lds(int bins) {
-    return (size_t)kSortBlock * ROUNDS * 10 + (size_t)bins * 4 + (size_t)bins * 2 * kSortWaves + kSortWaves * 4;
+    return (size_t)kSortBlock * ROUNDS * 10 + (size_t)bins * 4 + (size_t)bins * 2 * kSortWaves + kSortWaves * 8;
 }
 
 // Inclusive maximum over the lanes of a wave.
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
     int* gofs = lds + 2 * T;                              // [bins]: global position minus tile slot, per digit
     unsigned* wcnt = reinterpret_cast<unsigned*>(gofs + bins);                       // [WAVES][bins / 2]: count, then first slot
     unsigned short* sdig = reinterpret_cast<unsigned short*>(wcnt + WAVES * (bins / 2));   // [T]
-    int* sh = reinterpret_cast<int*>(sdig + T);           // [WAVES]
+    int* sh = reinterpret_cast<int*>(sdig + T);           // [WAVES], and the waves' last marks
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long base = (long)tile * T;
     const int count = (int)min((long)T, (long)P.n - base);
@@ -712,42 +712,17 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) *reinterpret_cast<uint2*>(&wcnt[w * (bins / 2) + 2 * threadIdx.x]) = make_uint2(0u, 0u);
     }
-    int row[ROUNDS];
-    if constexpr (FIRST) {
-        const int* __restrict__ rowptr = P.rowptr;
-        const int row_lo = P.tile_row[tile], row_hi = P.tile_row[tile + 1];
-        if (row_hi - row_lo <= 8 * T) {
+    // FIRST: the pointers of the rows that begin in the tile, one a thread, are on their way during the ranking
+    const int* __restrict__ rowptr = P.rowptr;
+    const int row_lo = FIRST ? P.tile_row[tile] : 0, row_hi = FIRST ? P.tile_row[tile + 1] : 0;
+    const bool marked = FIRST && row_hi - row_lo <= 8 * T;
+    int begins = 0;
+    if (marked) {
+        begins = rowptr[min(row_lo + 1 + (int)threadIdx.x, row_hi)];
 #pragma unroll
-            for (int q = 0; q < ROUNDS; ++q) skey[q * THREADS + threadIdx.x] = 0;
-            lds_barrier();
-            for (int r = row_lo + 1 + (int)threadIdx.x; r <= row_hi; r += THREADS) {
-                const int p = rowptr[r] - (int)base;  // row_hi may begin with the next tile
-                if (p < count) atomicMax(&skey[p], r - row_lo);
-            }
-            lds_barrier();
-            // marks ascend: the last one at or before an entry is the largest
-            unsigned upto = 0;
-#pragma unroll
-            for (int q = 0; q < ROUNDS; ++q) {
-                const unsigned v = max(wave_inclusive_max((unsigned)skey[own + q * 64]), upto);
-                row[q] = (int)v;
-                upto = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-            }
-            if (lane == 0) sh[wave] = (int)upto;
-            lds_barrier();
-            int carry = 0;
-#pragma unroll
-            for (int w = 0; w < WAVES - 1; ++w) { const int x = sh[w]; if (w < wave) carry = max(carry, x); }
-#pragma unroll
-            for (int q = 0; q < ROUNDS; ++q) row[q] = row_lo + max(row[q], carry);
-        } else {
-#pragma unroll
-            for (int q = 0; q < ROUNDS; ++q) row[q] = owner_row(rowptr, row_lo, row_hi, (int)base + min((int)own + q * 64, count - 1));
-            lds_barrier();
-        }
-    } else {
-        lds_barrier();
+        for (int q = 0; q < ROUNDS; ++q) skey[q * THREADS + threadIdx.x] = 0;
     }
+    lds_barrier();
     // rank of every entry among the wave's entries of the same digit
     unsigned* counter = wcnt + wave * (bins / 2);
     const unsigned short* counted = reinterpret_cast<const unsigned short*>(counter);
@@ -766,7 +741,31 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
         wave_lds_sync();
         __builtin_amdgcn_sched_barrier(0);            // keep the votes of one round together
     }
+    if (marked) {
+        for (int r = row_lo + 1 + (int)threadIdx.x; r <= row_hi; r += THREADS) {
+            const int p = begins - (int)base;             // row_hi may begin with the next tile
+            if (p < count) atomicMax(&skey[p], r - row_lo);
+            if (r + THREADS <= row_hi) begins = rowptr[r + THREADS];
+        }
+    }
     lds_barrier();
+    int row[ROUNDS];
+    if constexpr (FIRST) {
+        if (marked) {
+            // marks ascend: the last one at or before an entry is the largest
+            unsigned upto = 0;
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) {
+                const unsigned v = max(wave_inclusive_max((unsigned)skey[own + q * 64]), upto);
+                row[q] = (int)v;
+                upto = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+            }
+            if (lane == 0) sh[WAVES + wave] = (int)upto;
+        } else {
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) row[q] = owner_row(rowptr, row_lo, row_hi, (int)base + min((int)own + q * 64, count - 1));
+        }
+    }
     block_scan_bins(gpos, sh);                        // digit totals -> first positions
     {
         // two digits to a word: no sum of a tile's counts leaves 16 bits
@@ -790,6 +789,15 @@ __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(Transpose
                 run.x += c[w].x;
                 run.y += c[w].y;
             }
+        }
+    }
+    if constexpr (FIRST) {
+        if (marked) {                                     // the scans' barriers lie between
+            int carry = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES - 1; ++w) { const int x = sh[WAVES + w]; if (w < wave) carry = max(carry, x); }
+#pragma unroll
+            for (int q = 0; q < ROUNDS; ++q) row[q] = row_lo + max(row[q], carry);
         }
     }
     lds_barrier();
