@@ -51,3 +51,30 @@ def test_transpose_edges(m, k, nnz, kind):
         torch.cuda.synchronize()
         for g, w in zip(out, want):
             assert np.array_equal(g.cpu().numpy().view(np.uint32), np.ascontiguousarray(w).view(np.uint32))
+
+
+def test_entries_beyond_32_bit_offsets():
+    """2^30 entries and a few: byte offsets of entries no longer fit 32 bits."""
+    from paper_2202_08556_amd import binding as da
+    m, each, dev = (1 << 20) + 5, 1024, torch.device("cuda:0")
+    k, nnz = each * 1024, m * each
+    print(f"transpose m={m} k={k} nnz={nnz}", flush=True)
+    r, i = torch.arange(m, dtype=torch.int32, device=dev)[:, None], torch.arange(each, dtype=torch.int32, device=dev)[None, :]
+    rp = torch.arange(m + 1, dtype=torch.int32, device=dev) * each
+    ci = (i * 1024 + r * 7 % 1024).view(-1)                  # entry i of row r: column 1024 i + 7 r mod 1024
+    va = ((r * 31 + i) % 1000).to(torch.float32).view(-1)
+    size = da.da_csr_transpose_workspace(m, k, nnz)
+    ws = torch.empty(size, dtype=torch.uint8, device=dev)
+    out = (torch.empty(k + 1, dtype=torch.int32, device=dev), torch.empty_like(ci), torch.empty_like(va))
+    da.da_csr_transpose(m, k, nnz, rp, ci, va, *out, ws, size)
+    del ws
+    # every 1024 neighbouring columns hold all rows once, ordered by 7 r mod 1024 and then by r
+    rows = torch.arange(m, dtype=torch.int64, device=dev)
+    order = torch.sort(rows * 7 % 1024 * m + rows)[1]
+    first = torch.cumsum(torch.bincount(rows * 7 % 1024, minlength=1024), 0)
+    assert int(out[0][0]) == 0
+    for i in range(each):
+        part = slice(i * m, (i + 1) * m)
+        assert torch.equal(out[0][i * 1024 + 1:(i + 1) * 1024 + 1].long(), first + i * m)
+        assert torch.equal(out[1][part].long(), order)
+        assert torch.equal(out[2][part], ((order * 31 + i) % 1000).float())
