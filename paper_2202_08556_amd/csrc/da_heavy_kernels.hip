@@ -7,14 +7,14 @@
 // brings its rows of B into LDS once, a band at a time in two buffers, and walks the stored entries of all its heavy
 // rows that lie in the band, with the rows' sums in registers from the first band to the last; they are added to C
 // atomically once per block.  The same matrix takes 294 us at N = 64, EB 445 (under
-// the profiler 205 here and 98 for the other rows), 130 and 172 at N = 8 (85 and 41).  What bounds it: latency.  The waves wait
+// the profiler 232 here and 98 for the other rows), 129 and 172 at N = 8 (85 and 38).  What bounds it: latency.  The waves wait
 // in half of their cycles; LDS is busy in 38 % of them at N = 64, the vector units in about half (4 entries and 64 columns take two
 // operations with DPP, 4 cycles each, and four multiply-adds, 2 each; a batch of 64 entries some 20 operations).
 //
 // One wave, up to 8 columns two, does nothing but bring B, from memory to LDS directly.  While every wave brought a share through its
 // registers, in parts between its rows, each part's entries waited for B's latency, since loads come back in order (N = 64: 335 us; 303
 // with two waves that bring B, 294 with one and the ranges below).  Lanes in order of memory: with the columns of a lane
-// side by side in LDS, 64 bytes apart in memory, four such waves took 243 us where now one takes 205.
+// side by side in LDS, 64 bytes apart in memory, the kernel took 324 us with two such waves where it now takes 235.
 //
 // Lane groups of 16 walk one row each, 16 entries at a time, one per lane; an entry's column and value reach the
 // lanes by DPP broadcasts, the column as an operand of the address addition (the value as an operand of the multiply-adds: DPP

@@ -543,12 +543,19 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
         int2* st = stage + (wave * RPW + g) * SB;
         BatchRegs<G, SB> next;
         next.fetch(colind, vals, start, end, j);
+        // The last entries of a row in one block, whose gathers behind the end fetch row 0 and give way to zeros, or exactly, in
+        // blocks of 4, 2 and 1, each a round trip that the wave's other rows wait for.  Lanes of one column gain from one block
+        // (27-point stencil of 64 x 128 x 128, N = 8 91 -> 87 us, N = 16 145 -> 138; 2 entries a row, 300 000 rows, N = 16 24.1 -> 21.4;
+        // lognormal rows of 10, N = 16 17.2 -> 16.4), but for groups of four (the stencil, N = 4: 86 and 88); four columns a lane lose by
+        // the gathers (the stencil, N = 32: 168 and 172), also where only waves of short rows take it.
+        constexpr bool kInOne = V == 1 && G >= 8;
         for (int p0 = start; p0 < end; p0 += SB) {
             next.put(st, j);
             wave_lds_sync();
             if (p0 + SB < end) next.fetch(colind, vals, p0 + SB, end, j);
             if (nvec > 0) {
-                for_blocks<UL>(min(SB, end - p0), [&](auto uc, int t) {
+                const int cnt = min(SB, end - p0);
+                auto block = [&](auto uc, auto whole, int t) {
                     constexpr int UU = decltype(uc)::value;
                     int2 e[UU];
                     Acc<V, G, NV> b[UU];
@@ -557,8 +564,22 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
 #pragma unroll
                     for (int u = 0; u < UU; ++u) b[u].load(brow.row(e[u].x), cols, sd.cb);
 #pragma unroll
-                    for (int u = 0; u < UU; ++u) acc.fma(__int_as_float(e[u].y), b[u]);
-                });
+                    for (int u = 0; u < UU; ++u) {
+                        if (!decltype(whole)::value && u >= UU / 2 - (UU == 4)) {
+#pragma unroll
+                            for (int v = 0; v < V; ++v) b[u].a[0][v] = t + u < cnt ? b[u].a[0][v] : 0.f;
+                        }
+                        acc.fma(__int_as_float(e[u].y), b[u]);
+                    }
+                };
+                if constexpr (kInOne) {
+                    int t = 0;
+                    for (; t + UL <= cnt; t += UL) block(Count<UL>{}, Count<1>{}, t);
+                    if (cnt - t > UL / 2) block(Count<UL>{}, Count<0>{}, t);
+                    else if (cnt > t) block(Count<UL / 2>{}, Count<0>{}, t);
+                } else {
+                    for_blocks<UL>(cnt, [&](auto uc, int t) { block(uc, Count<1>{}, t); });
+                }
             }
             wave_lds_sync();
         }
