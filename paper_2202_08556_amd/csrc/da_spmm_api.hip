@@ -264,7 +264,7 @@ bool slices_fit_l2(int64_t k, int64_t N, int64_t tile_cols) { return k * tile_co
 // uneven: most are then short or empty (20 000 rows of 180 among a million: N = 64 168 and 316), and in graphs popular columns
 // go with that (power-law, N = 64: 104 and 115, N = 128 175 and 205).
 bool narrow_tiles_pay(int64_t m, int64_t k, int64_t N, const MatrixHint& hint) {
-    if (N % 32 != 0 || hint.nnz <= 0 || hint.seen_len < 55.0) return false;
+    if (N % 32 != 0 || N > 32L * kMaxGridY || hint.nnz <= 0 || hint.seen_len < 55.0) return false;   // tiles of 64 reach twice as far
     const double unevenness = hint.seen_len * (double)m / (double)hint.nnz;
     if (unevenness > 3.0 || ((N == 128 || N == 256 || N == 512) && slices_fit_l2(k, N, 64) && !uneven_rows(m, hint))) return false;
     const bool uneven = unevenness >= 1.4;

@@ -36,3 +36,22 @@ def test_tiles_of_32_columns(m, k, even, N, narrow):
     names = kernels_of(lambda: da.da_spmm(m, k, N, *dev, C, da.DA_RB_RM_PR))
     assert np.array_equal(C.cpu().numpy(), want.astype(np.float32) + 0.0)
     assert any("rb_pr_kernel<4, 8," in n for n in names) == narrow, names
+
+
+# a launch holds 65 535 tiles of columns: beyond 32 columns each, tiles of 64
+@pytest.mark.parametrize("N,narrow", [(32 * 65535, True), (32 * 65536, False), (64 * 65535, False)])
+def test_more_columns_than_tiles_of_32_reach(N, narrow):
+    from paper_2202_08556_amd import binding as da
+    m, k = 9, 16
+    rowptr, colind, vals = matrix(m, k, False, seed=3)
+    B = torch.from_numpy(np.random.default_rng(1).integers(-4, 5, (k, N)).astype(np.float32))
+    a = torch.zeros((m, k), dtype=torch.float64)
+    a.index_put_((torch.from_numpy(np.repeat(np.arange(m), np.diff(rowptr))), torch.from_numpy(colind).long()),
+                 torch.from_numpy(vals).double(), accumulate=True)
+    dev = [torch.from_numpy(x).cuda() for x in (rowptr, colind, vals)]
+    print(f"tiles of 32 columns N={N}", flush=True)
+    da.da_spmm_features(m, N, dev[0])
+    C = torch.full((m, N), float("nan"), device="cuda")
+    names = kernels_of(lambda: da.da_spmm(m, k, N, *dev, B.cuda(), C, da.DA_RB_RM_PR))
+    assert torch.equal(C.cpu(), (a @ B.double()).float() + 0.0)
+    assert any("rb_pr_kernel<4, 8," in n for n in names) == narrow, names
