@@ -6,21 +6,24 @@
 // heavy_rows_kernel turns the loops round: a block owns a range of columns and heavy rows of similar length (up to 540).  It
 // brings its rows of B into LDS once, a band at a time in two buffers, and walks the stored entries of all its heavy
 // rows that lie in the band, with the rows' sums in registers from the first band to the last; they are added to C
-// atomically once per block.  The same matrix takes 294 us at N = 64, EB 445 (under
-// the profiler 232 here and 98 for the other rows), 129 and 172 at N = 8 (85 and 38).  What bounds it: latency.  The waves wait
-// in half of their cycles; LDS is busy in 38 % of them at N = 64, the vector units in about half (4 entries and 64 columns take two
-// operations with DPP, 4 cycles each, and four multiply-adds, 2 each; a batch of 64 entries some 20 operations).
+// atomically once per block.  The same matrix takes 294 us at N = 64, EB 458; 207 and 278 at N = 32, 166 and 228 at N = 16, 115 and 176
+// at N = 8.  What bounds it: latency.  The waves wait in half of their cycles; LDS is busy in 38 % of them at N = 64, the
+// vector units in about half (4 entries and 64 columns take two operations with DPP, 4 cycles each, and four multiply-adds, 2 each; a
+// batch of 64 entries some 20 operations).
 //
-// One wave, up to 8 columns two, does nothing but bring B, from memory to LDS directly.  While every wave brought a share through its
-// registers, in parts between its rows, each part's entries waited for B's latency, since loads come back in order (N = 64: 335 us; 303
-// with two waves that bring B, 294 with one and the ranges below).  Lanes in order of memory: with the columns of a lane
-// side by side in LDS, 64 bytes apart in memory, the kernel took 324 us with two such waves where it now takes 235.
+// One wave does nothing but bring B, 16 bytes a lane: from memory to LDS directly where rows of B are such pieces, through registers
+// where they are not (N = 41: 288 us; 492 directly, 4 bytes a lane).  While every wave brought a share through its registers, in parts
+// between its rows, each part's entries waited for B's latency, since loads come back in order (N = 64: 338 us, N = 41: 322, N = 8: 117); it
+// stays so where B is column-major or has less than four columns, see heavy_loader.  Two waves at N = 8: 110, one 108.  Lanes in order of
+// memory: with the columns of a lane side by side in LDS, 64 bytes apart in memory, the kernel took 324 us under the profiler where it
+// then took 235.
 //
 // Lane groups of 16 walk one row each, 16 entries at a time, one per lane; an entry's column and value reach the
 // lanes by DPP broadcasts, the column as an operand of the address addition (the value as an operand of the multiply-adds: DPP
 // halves their rate, no gain).  An entry takes the 16 lanes, or a quarter of them (GL = 4, up to 8 columns).  Lane j of them owns
-// V neighbouring columns, one read of 4 V bytes; before the additions to C the lanes exchange their sums through LDS, so that an
-// addition covers neighbouring elements.  Rows of similar length share a wave (in storage order: 318 us instead of 270 at N = 64).
+// V neighbouring columns, one read of 4 V bytes; before the additions to C the lanes exchange their sums, so that an
+// addition covers neighbouring elements (up to 8 columns all of them: 72 rows of 24 000, whose lines of C every block adds to, N = 2
+// 29 -> 20 us, N = 8 31 -> 24).  Rows of similar length share a wave (in storage order: 318 us instead of 270 at N = 64).
 // Two buffers of 64 KiB.  More requests for entries ahead (4 batches at V = 4, 8 at GL = 4) or two entries a lane: no gain.
 //
 // The plan (da_spmm_prepare) lists the heavy rows and, per row and cell of columns, the position at which the cell's
@@ -40,10 +43,11 @@
 namespace daspmm {
 
 constexpr int kHeavyBlock = 1024;
-constexpr int heavy_waves(int tile) { return kHeavyBlock / 64 - (tile <= 8 ? 2 : 1); }   // waves that walk rows; the others bring B
+// Waves of a block that walk rows.
+constexpr int heavy_waves(bool loader) { return kHeavyBlock / 64 - loader; }
 constexpr int kHeavyQuads = 9;                             // sets of 4 rows a wave holds
 template <int GL, int V> constexpr int kHeavyBand = 16384 / (GL * V);   // rows of B in a buffer of 64 KiB
-constexpr size_t kHeavyLds = 2 * 65536 + 256 + heavy_waves(64) * 1024;   // two buffers, a row of zeros, and a row's sums per lane group
+constexpr size_t kHeavyLds = 2 * 65536 + 256 + heavy_waves(false) * 1024;   // two buffers, a row of zeros, and a row's sums per lane group
 
 struct HeavyPlan {
     const int* rows;     // count row numbers, by length
@@ -172,7 +176,7 @@ __device__ __forceinline__ bool each_batch(BATCH& batch) {
     return true;
 }
 
-template <int GL, int V>
+template <int GL, int V, bool LOADER>
 __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     int m, int k, int N, Strides sd, const int* __restrict__ rowptr, const int* __restrict__ colind, const float* __restrict__ vals,
     const float* __restrict__ B, float* __restrict__ C, HeavyPlan plan, HeavyGroups groups)
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     char* const lds = heavy_lds;
     constexpr int kBand = kHeavyBand<GL, V>, kRow = 4 * GL * V;              // rows of a band; bytes of a row in LDS
     constexpr int kZero = 2 * 65536;                       // offset of the row of zeros
-    constexpr int kWaves = heavy_waves(GL * V), kLoaders = kHeavyBlock / 64 - kWaves;
+    constexpr int kWaves = heavy_waves(LOADER);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15, jc = lane & (GL - 1);
     int group = 0;
@@ -198,31 +202,79 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     const int col0 = cell0 * plan.cell;
     const int col1 = cell1 == plan.cells ? k : cell1 * plan.cell;
 
-    if (wave >= kWaves) {
-        // From memory to LDS, a wave's lanes one after another: 4 bytes a lane, 16 where rows of B and tiles are whole
-        // 16-byte pieces.
-        auto bring = [&](auto width) {
-            constexpr int W = decltype(width)::value, kLanes = GL * V / W, kPer = 64 / kLanes, kLoads = kBand / kPer;
-            const int col = min(tile0 + lane % kLanes * W, N - W), r = lane / kLanes;
-            const float* const mine = B + (long)col * sd.cb;
+    if constexpr (LOADER) {
+        if (wave == kWaves) {
+            // Lanes one after another, 16 bytes each: from memory to LDS where rows of B are whole 16-byte pieces, through
+            // registers where they are not.
+            typedef float four __attribute__((ext_vector_type(4), aligned(4)));
+            typedef float four_in_lds __attribute__((ext_vector_type(4)));
+            constexpr int kLanes = GL * V / 4, kPer = 64 / kLanes, kLoads = kBand / kPer, kAtOnce = 16;
+            static_assert(kLoads == 64, "1 KB each");
+            const int col = tile0 + lane % kLanes * 4, r = lane / kLanes;
+            const int past = col + 4 - N;                  // the four numbers come from column N - 4 on where they would end behind N - 1
+            const float* const mine = B + min(col, N - 4);
+            const bool whole = ((unsigned long long)B % 16 | N % 4 | sd.rb % 4) == 0;
+            auto from = [&](int first, int i) { return mine + (long)min(first + i * kPer + r, col1 - 1) * sd.rb; };
+            reinterpret_cast<float*>(lds + kZero)[lane] = 0.f;
             int buffer = 0;
             for (int first = col0; first < col1; first += kBand, buffer ^= 1) {
-                for (int i = wave - kWaves; i < kLoads; i += kLoaders) {
-                    const int row = min(first + i * kPer + r, col1 - 1);
-                    const auto from = (const __attribute__((address_space(1))) void*)(mine + (long)row * sd.rb);
-                    const auto to = (__attribute__((address_space(3))) void*)(lds + buffer * 65536 + i * 256 * W);
-                    if constexpr (W == 4) __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
-                    else __builtin_amdgcn_global_load_lds(from, to, 4, 0, 0);
+                char* const to = lds + buffer * 65536;
+                if (whole) {
+#pragma unroll 1    // 294 us, 298 in loops of 4 and more (N = 64)
+                    for (int i = 0; i < kLoads; ++i)
+                        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from(first, i),
+                                                         (__attribute__((address_space(3))) void*)(to + i * 1024), 16, 0, 0);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                } else {
+                    for (int i = 0; i < kLoads; i += kAtOnce) {
+                        four x[kAtOnce];
+#pragma unroll
+                        for (int q = 0; q < kAtOnce; ++q) x[q] = *reinterpret_cast<const four*>(from(first, i + q));
+#pragma unroll
+                        for (int q = 0; q < kAtOnce; ++q) {
+                            four y = x[q];                 // columns from N on are never read out
+                            if (past > 0 && past & 1) y = four{y[1], y[2], y[3], y[3]};
+                            if (past > 0 && past & 2) y = four{y[2], y[3], y[3], y[3]};
+                            *reinterpret_cast<four_in_lds*>(to + (i + q) * 1024 + lane * 16) = four_in_lds{y[0], y[1], y[2], y[3]};
+                        }
+                    }
                 }
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
+                lds_barrier();
             }
-        };
-        if (wave == kWaves) reinterpret_cast<float*>(lds + kZero)[lane] = 0.f;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (sd.cb == 1 && ((unsigned long long)B % 16 | N % 4 | sd.rb % 4) == 0) bring(Count<4>{});
-        else bring(Count<1>{});
-        return;
+            return;
+        }
+    }
+    // Without a loader a band's rows of B come through registers, in four parts of four numbers a thread; GL lanes on a row.
+    constexpr int kParts = 4, kEach = 4;
+    static_assert(kParts * kEach * kHeavyBlock == 16384, "a band");
+    float stage[kEach];
+    auto place = [&](int n, unsigned t, int* row, int* col) {
+        *row = t / GL + kHeavyBlock / GL * (n / V);
+        *col = t % GL + GL * (n % V);
+    };
+    auto fetch = [&](int first, int part) {
+        unsigned t = threadIdx.x;
+        asm volatile("" : "+v"(t));                        // nothing of this is worth registers from part to part
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) {
+            int row, col;
+            place(part * kEach + q, t, &row, &col);
+            stage[q] = B[(long)min(first + row, col1 - 1) * sd.rb + (long)min(tile0 + col, N - 1) * sd.cb];
+        }
+    };
+    auto put = [&](int buffer, int part) {
+        unsigned t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+#pragma unroll
+        for (int q = 0; q < kEach; ++q) {
+            int row, col;
+            place(part * kEach + q, t, &row, &col);
+            reinterpret_cast<float*>(lds + buffer * 65536)[row * GL * V + col] = stage[q];
+        }
+    };
+    if constexpr (!LOADER) {
+        if (wave == 0) reinterpret_cast<float*>(lds + kZero)[lane] = 0.f;
+        fetch(col0, 0);
     }
     int bcol[V];                                           // the lane's columns
 #pragma unroll
@@ -257,26 +309,34 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
         stop[i] = (unsigned)to * 4u;
     }
     struct Entry { int c; float v; };
-    // entries at byte offset p; past the last one of the matrix zeros
+    // The entry at byte offset p + ahead; past the last one of the matrix zeros.  From the row's end on, which is at `end`, any: the one
+    // there, which all lanes share, saves bytes (8000 rows of 700, N = 4: 51 -> 41 us, N = 8: 50 -> 39); with four columns a lane the
+    // operation costs more on long rows (524 of 20 000 to 100 000, N = 64: 298 -> 305) than it saves.
     const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(colind), 0, plan.nnz * 4, 0x00027000);
     const __amdgpu_buffer_rsrc_t numbers = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vals), 0, plan.nnz * 4, 0x00027000);
-    auto request = [&](unsigned p) {
+    auto request = [&](unsigned p, unsigned ahead, unsigned end) {
         Entry e;
+        p = (V < 4 ? min(p, end - ahead) : p) + ahead;
         e.c = (int)__builtin_amdgcn_raw_buffer_load_b32(cols, (int)p, 0, 0);
         e.v = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(numbers, (int)p, 0, 0));
         return e;
     };
     constexpr int D = V == 4 ? 2 : 4, L = 4;               // batches in flight; entries read together
     Entry next[D];
-    auto request_first = [&](unsigned p) {
+    auto request_first = [&](unsigned p, unsigned end) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) next[d] = request(p + 64 * d);
+        for (int d = 0; d < D; ++d) next[d] = request(p, 64 * d, end);
     };
-    request_first(pos[0]);
+    if constexpr (!LOADER) {
+#pragma unroll
+        for (int q = 0; q < kParts; ++q) { put(0, q); if (q + 1 < kParts) fetch(col0, q + 1); }
+    }
+    request_first(pos[0], stop[0]);
     int buffer = 0;
     for (int first = col0; first < col1; first += kBand) {
         const bool last = first + kBand >= col1;           // the last band takes what is left
         lds_barrier();                                     // the band is here
+        if (!LOADER && !last) fetch(first + kBand, 0);
         const unsigned here = (unsigned)min(kBand, col1 - first);              // rows of the band
         const int base = buffer * 65536, lane_off = jc * 4 * V;
 #pragma unroll
@@ -289,12 +349,12 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
                 const unsigned end = stop[i];
                 unsigned long long alive = ~0ull;          // lanes of groups that are not done with the band
                 // the next set's first batches are on their way while this one is worked on
-                if (i + 1 < kHeavyQuads && i + 1 < quads) request_first(pos[(i + 1) % kHeavyQuads]);
+                if (i + 1 < kHeavyQuads && i + 1 < quads) request_first(pos[(i + 1) % kHeavyQuads], stop[(i + 1) % kHeavyQuads]);
                 const int limit = last ? 0x7fffffff : first + kBand;
                 auto batch = [&](auto which) {
                     constexpr int d = decltype(which)::value;
                     const Entry now = e[d];
-                    e[d] = request(p + 64 * D);
+                    e[d] = request(p, 64 * D, end);
                     asm volatile("; batch %0" ::"n"(d));   // one loop over batches of changing registers would wait for each request
                     // leading entries of the batch that lie in the band or before it
                     unsigned long long bits = alive & __builtin_amdgcn_ballot_w64(p < end) & __builtin_amdgcn_ballot_w64(now.c < limit);
@@ -342,9 +402,21 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
                 };
                 while (each_batch<D>(batch)) {}
                 pos[i] = p;
+                // the next band's parts follow one another, two sets of rows apart
+                if (!LOADER && !last && i % 2 == 1 && i / 2 + 1 < kParts) { put(buffer ^ 1, i / 2); fetch(first + kBand, i / 2 + 1); }
             }
         }
-        if (!last) request_first(pos[0]);
+        if (!last) {
+            request_first(pos[0], stop[0]);
+            if constexpr (!LOADER) {
+#pragma unroll
+                for (int q = 0; q < kParts; ++q) {
+                    if (q < quads / 2 && q + 1 < kParts) continue;             // done above
+                    put(buffer ^ 1, q);
+                    if (q + 1 < kParts) fetch(first + kBand, q + 1);
+                }
+            }
+        }
         buffer ^= 1;
     }
     if (strayed && lane == 0) *plan.stale = 1;
@@ -364,14 +436,19 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
             if (h < row1) {
                 const int r = plan.rows[h];
                 if (rowptr[r + 1] - rowptr[r] >= plan.min_len) {
+                    if constexpr (GL == 4) {               // the four groups of 4 lanes have a quarter of the entries each
+                        static_assert(V == 2, "columns of lanes 0 ... 7");
+                        const int from = (lane & 48) + (j >> 1 & 3);
+                        const float even = __shfl(dpp_add<0x124>(dpp_add<0x128>(acc[i][0])), from);
+                        const float odd = __shfl(dpp_add<0x124>(dpp_add<0x128>(acc[i][1])), from);
+                        const float sum = j % 2 == 0 ? even : odd;
+                        if (j < 8 && tile0 + j < N) unsafeAtomicAdd(C + (long)r * sd.rc + (long)(tile0 + j) * sd.cc, sum);
+                    } else {
 #pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        if constexpr (GL == 4) {           // the four groups of 4 lanes have a quarter of the entries each
-                            acc[i][v] = dpp_add<0x128>(acc[i][v]);
-                            acc[i][v] = dpp_add<0x124>(acc[i][v]);
+                        for (int v = 0; v < V; ++v) {
+                            const int n = tile0 + j + GL * v;
+                            if (n < N) unsafeAtomicAdd(C + (long)r * sd.rc + (long)n * sd.cc, acc[i][v]);
                         }
-                        const int n = tile0 + (GL == 16 ? j + GL * v : jc * V + v);
-                        if (n < N && j < GL) unsafeAtomicAdd(C + (long)r * sd.rc + (long)n * sd.cc, acc[i][v]);
                     }
                 }
             }

@@ -663,6 +663,11 @@ constexpr double kHeavyVisit = 12.0;
 
 constexpr int heavy_tile(int64_t N) { return N <= 8 ? 8 : (N <= 16 ? 16 : (N <= 32 ? 32 : 64)); }
 
+// Whether a wave of each block brings B, 16 bytes a lane.  Rows of B that are column-major or have less than 16 bytes all
+// waves bring together (524 rows of 20 000 to 100 000, N = 41: 492 us with 4 bytes a lane by one wave, 322 by all waves, 302 by one wave with
+// 16 bytes a lane; N = 8: 117 by all waves, 110 by two, 108 by one).
+bool heavy_loader(int64_t N, const Strides& sd) { return sd.cb == 1 && N >= 4; }
+
 // Entries of a heavy row of n entries that a block has to add up, at least, for a sum as exact as EB's in chunks of c: as
 // one_sign_error, with sums of 16 entries that are added one after another inside a part.
 double heavy_part(double n, double c) {
@@ -672,10 +677,10 @@ double heavy_part(double n, double c) {
     return part;
 }
 
-HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sums, int64_t k, int64_t N, int chunk) {
+HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sums, int64_t k, int64_t N, int chunk, bool loader) {
     const int tile = heavy_tile(N), band = 16384 / tile;
     const int64_t tiles = (N + tile - 1) / tile;
-    const int waves = heavy_waves(tile), quads = (pl.count + 3) / 4, most = waves * kHeavyQuads, least = (quads + most - 1) / most;
+    const int waves = heavy_waves(loader), quads = (pl.count + 3) / 4, most = waves * kHeavyQuads, least = (quads + most - 1) / most;
     HeavyLaunch best{};
     auto deal = [&](int n, int unit) {                      // n groups of whole units of 4 * unit rows
         HeavyLaunch x{};
@@ -742,17 +747,22 @@ bool heavy_rows_pay(int64_t m, int64_t N, bool row_major, int count, int64_t nnz
 // Lanes: 4 of two columns up to 8 columns (N = 8: 90 us, 16 lanes of one column 114), 16 beyond (N = 16, 1.6 M entries: 16 us,
 // 4 lanes of four columns, whose random 64-byte reads meet in the banks of LDS, 33).
 int launch_heavy(const Problem& p, const HeavyPlan& pl, const HeavyGroups& groups) {
+    const int tile = heavy_tile(p.N);
     auto go = [&](auto kernel) {
-        const int tile = heavy_tile(p.N);
         hipLaunchKernelGGL(kernel, dim3((unsigned)groups.block[groups.count], (unsigned)((p.N + tile - 1) / tile)), dim3(kHeavyBlock), kHeavyLds,
                            p.stream, p.m, (int)p.k, p.N, p.sd, p.rowptr, p.colind, p.vals, p.B, p.C, pl, groups);
     };
-    switch (heavy_tile(p.N)) {
-    case 8: go(heavy_rows_kernel<4, 2>); break;
-    case 16: go(heavy_rows_kernel<16, 1>); break;
-    case 32: go(heavy_rows_kernel<16, 2>); break;
-    default: go(heavy_rows_kernel<16, 4>);
-    }
+    auto by_tile = [&](auto loader) {
+        constexpr bool LOADER = decltype(loader)::value;
+        switch (tile) {
+        case 8: go(heavy_rows_kernel<4, 2, LOADER>); break;
+        case 16: go(heavy_rows_kernel<16, 1, LOADER>); break;
+        case 32: go(heavy_rows_kernel<16, 2, LOADER>); break;
+        default: go(heavy_rows_kernel<16, 4, LOADER>);
+        }
+    };
+    if (heavy_loader(p.N, p.sd)) by_tile(Truth<true>{});
+    else by_tile(Truth<false>{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return DA_OK;
@@ -1085,7 +1095,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
         const HeavyLookup heavy = lookup_heavy(rowptr, colind, m, k, p.stream);
         const int64_t known = lookup_matrix(rowptr, m).nnz;              // the features may have been taken of another matrix since
         if (heavy.plan.count > 0 && heavy.rest_longest <= g.chunk && (known < 0 || known == heavy.plan.nnz)) {
-            const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk);
+            const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk, heavy_loader(N, sd));
             if (heavy_rows_pay(m, N, sd.cb == 1, heavy.plan.count, heavy.plan.nnz, dealt.load * cu_count() / heavy.plan.nnz)) {
                 Problem q = p;
                 q.layer = nullptr;

@@ -301,7 +301,9 @@ def test_sums_are_as_exact_as_in_chunks(N, longest_other, monkeypatch):
 @pytest.mark.parametrize("offset, more", [(0, 4), (0, 3), (1, 4), (4, 0), (2, 1)])
 def test_rows_of_b_at_any_alignment(prepared, N, offset, more):
     from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
     host, dev = prepared
+    da.da_spmm_prepare(M, K, host[1].size, dev[0], dev[1])         # plans of other tests may have taken its place
     print("heavy rows N", N, "offset", offset, "pitch", N + more, flush=True)
     B = dense(N)
     want, _ = orc.spmm(*host, B)
@@ -309,11 +311,39 @@ def test_rows_of_b_at_any_alignment(prepared, N, offset, more):
     inner = room[offset:].view(K, N + more)
     inner[:, :N] = torch.from_numpy(B).cuda()
     C = torch.full((M, N), float("nan"), device="cuda")
-    da.da_spmm_ex(M, K, N, *dev, inner, N + more, da.DA_ROW_MAJOR, C, N, da.DA_ROW_MAJOR, da.DA_EB_RM_SR)
+    names = kernels_of(lambda: da.da_spmm_ex(M, K, N, *dev, inner, N + more, da.DA_ROW_MAJOR, C, N, da.DA_ROW_MAJOR, da.DA_EB_RM_SR))
     assert np.array_equal(C.cpu().numpy(), want.astype(np.float32) + 0.0)
+    assert any("heavy_rows_kernel" in n for n in names), names
 
 
 # as many rows as the waves of a block hold, and one more: 504 up to 8 columns, 540 beyond
 @pytest.mark.parametrize("heavy, N", [(504, 8), (505, 8), (540, 16), (541, 64)])
 def test_rows_that_fill_a_block(heavy, N):
     test_groups_of_rows(heavy, N)
+
+
+# a wave of its own brings rows of B of four and more numbers, whatever they are aligned to; all waves bring others
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 6, 7, 9, 13, 15, 18, 19, 31, 33, 41, 62, 130])
+@pytest.mark.parametrize("order, offset, more", [("row", 0, 0), ("row", 1, 0), ("row", 3, 2), ("col", 0, 0)])
+def test_who_brings_rows_of_b(prepared, N, order, offset, more):
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    host, dev = prepared
+    da.da_spmm_prepare(M, K, host[1].size, dev[0], dev[1])         # plans of other tests may have taken its place
+    print("heavy rows N", N, order, "offset", offset, "pitch", N + more, flush=True)
+    B = dense(N)
+    want, _ = orc.spmm(*host, B)
+    room = torch.full((offset + (K - 1) * (N + more) + N,), float("nan"), device="cuda")
+    if order == "row":
+        Bd = room[offset:].as_strided((K, N), (N + more, 1))
+        Bd.copy_(torch.from_numpy(B))
+        ldb, C = N + more, torch.full((M, N), float("nan"), device="cuda")
+        call = lambda: da.da_spmm_ex(M, K, N, *dev, Bd, ldb, da.DA_ROW_MAJOR, C, N, da.DA_ROW_MAJOR, da.DA_EB_RM_SR)  # noqa: E731
+    else:
+        Bd, C = torch.from_numpy(np.ascontiguousarray(B.T)).cuda(), torch.full((N, M), float("nan"), device="cuda")
+        call = lambda: da.da_spmm_ex(M, K, N, *dev, Bd, K, da.DA_COL_MAJOR, C, M, da.DA_COL_MAJOR, da.DA_EB_RM_SR)  # noqa: E731
+    names = kernels_of(call)
+    got = C if order == "row" else C.t()
+    assert np.array_equal(got.cpu().numpy(), want.astype(np.float32) + 0.0)
+    by_one = order == "row" and N >= 4
+    assert any("heavy_rows_kernel" in n and ("true" if by_one else "false") in n for n in names), names
