@@ -724,23 +724,36 @@ HeavyLaunch deal_heavy_rows(const HeavyPlan& pl, const std::vector<int64_t>& sum
 
 // Whether the heavy rows' kernel beats EB, which has all rows in one kernel and as many blocks as it likes.  share: the load of
 // the block that has most, in shares of a CU of all entries.  EB's additions to the same few lines of C are what costs it
-// most, so that few rows of many entries always gain up to 32 columns (72 rows of 24 000, N = 32: 72 us in EB, 27 here; 300
-// of 2300, N = 8: 19.4 and 14.7, N = 24: 21.5 and 17.8; 800 of 6000, N = 24: 50.5 and 50.1).  Many short rows are EB's unless they
-// fill the CUs evenly (2000 of 3300, 6.8 M entries, N = 16: 43.5 and 46.1; 5000 of 3000, 15 M, N = 16, share 1.3: 79 and 89; 1500 of
-// 17 000, 25 M, share 1.13: 117 and 110).  Up to four columns EB has 16 and more workers to a wave and waits for them (4000 rows
-// of 1000, N = 4: 44 and 35).  Beyond 32 columns LDS is the bound, and the rows that are not heavy cost a kernel of their
-// own (12 M entries, 300 000 rows, N = 64: 142 and 149; 33 M, 524 000: 445 and 326; 800 rows of 6000, share 2.2: 69 and 71; 8000 of
-// 3000, share 1.4: 231 and 171); beyond 64 the entries are read for every tile (N = 96: 5 M 88 and 88, 12 M 240 and 242, 25 M
-// 385 and 284), beyond 128 in EB, too (N = 130: 12 M 520 and 390, 33 M 1543 and 880).  Column-major B gathers every element from a
-// line of its own in EB (300 heavy rows, N = 32: 65 and 52; 5000: 1224 and 392).
-bool heavy_rows_pay(int64_t m, int64_t N, bool row_major, int count, int64_t nnz, double share) {
+// most, so that few rows of many entries always gain up to 32 columns (72 rows of 24 000, N = 32: 72 us in EB, 34 here; 300
+// of 2300, N = 8: 20.3 and 15.3, N = 24: 27.6 and 24.3; 1000 of 20 000, share 1.34, N = 32: 123 and 131, the most that is lost).
+// Up to four columns EB has 16 and more workers to a wave and waits for them (4000 rows of 1000, N = 4: 47 and 39).  Beyond 128 the
+// entries are read for every tile in EB, too (N = 130: 12 M 520 and 390, 33 M 1540 and 833).  Column-major B gathers every element
+// from a line of its own in EB (300 heavy rows, N = 32: 92 and 76; 5000 of 8000: 2756 and 451).
+// Between, many rows are EB's unless they fill the CUs evenly, and EB's time for an entry grows with their number (N = 64: 10.4 us a
+// million at 12 M, 12.7 at 50 M): the share that still pays grows with it.  Fitted over 70 matrices of 72 to 8000 heavy rows, 0.8 to 50 M
+// entries; on either side of the line, EB and here:
+//   N <= 8           1500 of 8000, 12.3 M, share 1.14: 58 and 50; 6000 of 6000, 36 M, 1.26: 163 and 131; 8000 of 700, 5.8 M, 1.25: 36 and 39
+//   N <= 16          1500 of 17 000, 26 M, 1.30: 128 and 118; 5000 of 3000, 15 M, 1.33: 85 and 95; 3500 of 5000, 18 M, 1.32: 98 and 104
+//   N < 32           2000 of 6000, 12 M, 1.31, N = 24: 109 and 89; 1500 of 17 000, 1.47: 175 and 180; 8000 of 1300, 11 M, 1.80: 89 and 134
+//   N = 32           5000 of 4000 to 12 000, 41 M, 1.43: 314 and 281; 4000 of 4000, 16 M, 1.33: 98 and 118
+//   N <= 64          8000 of 3000, 24 M, 1.67, N = 64: 239 and 199; 1500 of 17 000, 1.84: 313 and 254; 1500 of 8000, 12 M, 1.84: 128 and
+//                    147; 5000 of 5000, 26 M, 2.32: 277 and 324; 3000 of 10 000, 31 M, 2.29: 391 and 360
+//   the same, rows of B not whole 16-byte pieces, which EB gathers in twice the time
+//                    1500 of 5000, 7.6 M, 1.99, N = 41: 112 and 87; 3500 of 5000, 18 M, 2.03: 196 and 216
+// Beyond 64 the entries are read for every tile (N = 96: 5 M 88 and 88, 12 M 286 and 216, 25 M 512 and 412), and beyond 32
+// the rows that are not heavy cost more in a kernel of their own (12 M entries, 300 000 rows, N = 64: 142 and 149).
+bool heavy_rows_pay(int64_t m, int64_t N, bool row_major, bool whole, int count, int64_t nnz, double share) {
     const bool many = nnz >= 10000000;
     if (!row_major) return (N > 8 || count <= 2048 || many) && (N <= 32 || count >= 256);
     if (N <= 4) return true;
-    if (N <= 32) return count <= 1024 || (many && share <= 1.25);
+    const double millions = (double)nnz * 1e-6;
+    if (N <= 8) return count <= 1024 || share <= 1.1 + millions / 20.0;
+    if (N <= 16) return count <= 1024 || share <= 1.0 + millions / 60.0;
+    if (N <= 32) return count <= 1024 || share <= (N < 32 ? 1.5 + millions / 120.0 : 1.05 + millions / 70.0);
     if (count < 256) return false;
     if (N > 128) return true;
-    return nnz / 48 >= m && (N <= 64 ? count <= 640 || share <= 1.6 : many);
+    if (nnz / 48 < m) return false;
+    return N <= 64 ? count <= 640 || share <= std::max(1.45 + millions / 34.0, whole ? 0.0 : 2.0) : many;
 }
 
 // The heavy rows' part of a product whose other rows are on the stream already.
@@ -1096,7 +1109,7 @@ int product(int64_t m, int64_t k, int64_t N, const int32_t* rowptr, const int32_
         const int64_t known = lookup_matrix(rowptr, m).nnz;              // the features may have been taken of another matrix since
         if (heavy.plan.count > 0 && heavy.rest_longest <= g.chunk && (known < 0 || known == heavy.plan.nnz)) {
             const HeavyLaunch dealt = deal_heavy_rows(heavy.plan, *heavy.sums, k, N, g.chunk, heavy_loader(N, sd));
-            if (heavy_rows_pay(m, N, sd.cb == 1, heavy.plan.count, heavy.plan.nnz, dealt.load * cu_count() / heavy.plan.nnz)) {
+            if (heavy_rows_pay(m, N, sd.cb == 1, ends % 16 == 0 && N % 4 == 0, heavy.plan.count, heavy.plan.nnz, dealt.load * cu_count() / heavy.plan.nnz)) {
                 Problem q = p;
                 q.layer = nullptr;
                 Geometry rest;

@@ -347,3 +347,35 @@ def test_who_brings_rows_of_b(prepared, N, order, offset, more):
     assert np.array_equal(got.cpu().numpy(), want.astype(np.float32) + 0.0)
     by_one = order == "row" and N >= 4
     assert any("heavy_rows_kernel" in n and ("true" if by_one else "false") in n for n in names), names
+
+
+# matrices on either side of the line between the two: many rows of one length, whose blocks have more than their share of the work
+@pytest.mark.parametrize("heavy, each, k, N, taken", [
+    (900, 9000, 100_000, 48, True), (900, 9000, 100_000, 41, True), (2000, 6000, 65_536, 24, True), (8000, 1300, 40_000, 24, False),
+    (8000, 1300, 40_000, 48, False), (1500, 8000, 130_000, 64, False), (1300, 3000, 50_000, 41, True), (3500, 5000, 100_000, 16, False),
+])
+def test_which_matrices_take_the_kernel(heavy, each, k, N, taken):
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    m, step, dev = heavy + 20_000, k // each, "cuda"
+    lens = torch.full((m,), 3, dtype=torch.int64, device=dev)
+    rows = torch.arange(heavy, device=dev) * (m // heavy)
+    lens[rows] = each
+    rowptr = torch.zeros(m + 1, dtype=torch.int32, device=dev)
+    torch.cumsum(lens, 0, out=rowptr[1:])
+    row = torch.repeat_interleave(torch.arange(m, device=dev), lens)
+    at = torch.arange(row.numel(), device=dev) - rowptr[row].long()
+    colind = (at * step + row % step).to(torch.int32)         # heavy rows with the same remainder are alike but for a factor
+    vals = (at % 3 - 1 + (row % 2) * 4).float()
+    B = (torch.arange(k * N, device=dev) * 7919 % 9 - 4).float().view(k, N)
+    da.da_spmm_prepare(m, k, colind.numel(), rowptr, colind)
+    C = torch.full((m, N), float("nan"), device=dev)
+    print("heavy", heavy, "each", each, "N", N, flush=True)
+    names = kernels_of(lambda: da.da_spmm(m, k, N, rowptr, colind, vals, B, C, da.DA_EB_RM_SR))
+    da.da_spmm_release(rowptr)
+    assert any("heavy_rows_kernel" in n for n in names) == taken, names
+    some = torch.cat([rows[:60], rows[-60:], rows[:60] + 1, torch.tensor([0, m - 1], device=dev)]).clamp(max=m - 1)
+    for r in some.tolist():
+        part = slice(int(rowptr[r]), int(rowptr[r + 1]))
+        assert torch.equal(C[r], (vals[part, None] * B[colind[part].long()]).sum(0))
+    assert not torch.isnan(C.sum(1)).any()
