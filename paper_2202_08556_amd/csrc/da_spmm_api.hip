@@ -252,25 +252,28 @@ bool uneven_rows(int64_t m, const MatrixHint& hint) { return hint.nnz >= 2000000
 // RB tiles of tile_cols columns on XCDs of their own, see launch_w.
 bool slices_fit_l2(int64_t k, int64_t N, int64_t tile_cols) { return k * tile_cols * 4 <= 12 << 20 && k * N * 4 > 9 << 19; }
 
-// RB+PR with whole 128-byte pieces of B: whether tiles of 32 columns beat tiles of 64.  They give a row 8 slots instead of
-// 4, which long rows fill, but read the entries twice as often.  Rows of more than a hundred entries gain where they are uneven
-// (lognormal, coefficient 0.9, mean 60: k = 3000, N = 64 11.5 -> 8.4 us, N = 128 13.6 -> 10.0; 60 000: 115 -> 86 and 212 -> 161) or B is
-// larger than an L2 (rows of 120 +- 11: k = 60 000, N = 64 191 -> 144, N = 128 380 -> 286, 20 000: 33.2 -> 31.4 and, N = 192,
-// 114 -> 91; 8000: N = 64 13.5 and 14.8, N = 128 23.6 and 26.5).  From 55 on it takes more of that: uneven rows (mean 23, seen as 62:
-// k = 4000, N = 64 9.2 -> 6.9, N = 128 12.9 -> 8.9; 20 000, N = 64 23.6 -> 19.9; 61 417, N = 64 59.0 -> 56.1, N = 96 82 -> 77;
-// 150 000, N = 128 240 and 251; mean 30, seen as 60: 61 417, N = 128 116 -> 105, 20 000, N = 96 26.9 and 27.9), even ones of a very wide B
-// (rows of 60: 61 417, N = 64 103 -> 81, N = 128 201 -> 159; 20 000, N = 64 19.9 and 21.8).  Shorter ones lose (mean 12, seen as 36: 61 417, N = 64
-// 36 and 45).  Not where tiles of 64 have XCDs of their own (mean 60, k = 8000, N = 256: 30 and 36), and not where rows are very
-// uneven: most are then short or empty (20 000 rows of 180 among a million: N = 64 168 and 316), and in graphs popular columns
-// go with that (power-law, N = 64: 104 and 115, N = 128 175 and 205).
+// RB+PR with whole 128-byte pieces of B: whether tiles of 32 columns beat tiles of 64.  They give a row 8 slots instead of 4, and an L2
+// slices of B half as wide, but a row of A twice the waves.  Measured over 1300 products, tiles of 64 and of 32 as they run now, in us;
+// (23, 61) are lognormal rows of 23 with coefficient 1.3, in which an average entry sees 61; so (28, 62), (50, 90), (90, 180).
+// - Rows of n entries and more columns than 1.25 M / n: the slices decide, however many rows there are.  60 000 rows, N = 64: (23, 61),
+//   k = 26 000 41.7 and 43.3, 80 000 56.4 -> 49.1; (50, 90), 18 000 51.6 and 50.9, 26 000 63.7 -> 52.3, 40 000 83.5 -> 58.4; rows of 60, 18 000
+//   46.2 and 51.4, 26 000 61.5 -> 51.8.  120 000 rows, N = 128: (50, 90), 26 000 206 -> 185.  They end where slices of 32 columns do not
+//   fit either: rows of 45, N = 64, k = 150 000 228 -> 208, 210 000 313 -> 304, 260 000 314 and 318; N = 96, whose second tile of 64 is half empty,
+//   150 000 330 -> 326, 180 000 403 and 415.
+// - Fewer columns: only while a few rows per wave of the chip are left, whose longest sets the time, and rows are uneven.  k = 14 000, N = 64: (23,
+//   61), 10 000 rows 17.3 -> 9.7, 28 000 21.3 and 22.5, 100 000 47.1 and 61.2; (90, 180), 40 000 rows 58.4 -> 55.1, 100 000 112 and 117; N = 96, (28, 62),
+//   28 000 rows 30.4 and 30.5, (90, 180), 100 000 186 and 166.  More columns, more rows: (35, 98), k = 31 000, 31 000 rows, N = 64 49.0 -> 32.9.
+// - Not while tiles of 64 have XCDs of their own and slices of up to 6 MB (rows of 45, k = 22 000, N = 128 34.2 and 36.1; 11 000, N = 256 27.7
+//   and 34.5), and not where rows are very uneven: most are then short or empty (20 000 rows of 180 among a million: N = 64 168 and 316), and in
+//   graphs popular columns go with that (power-law, N = 64: 104 and 115, N = 128 175 and 205).
 bool narrow_tiles_pay(int64_t m, int64_t k, int64_t N, const MatrixHint& hint) {
     if (N % 32 != 0 || N > 32L * kMaxGridY || hint.nnz <= 0 || hint.seen_len < 55.0) return false;   // tiles of 64 reach twice as far
-    const double unevenness = hint.seen_len * (double)m / (double)hint.nnz;
-    if (unevenness > 3.0 || ((N == 128 || N == 256 || N == 512) && slices_fit_l2(k, N, 64) && !uneven_rows(m, hint))) return false;
-    const bool uneven = unevenness >= 1.4;
-    if (hint.seen_len >= 100.0) return k > 16384 || uneven;
-    if (N > 128) return false;
-    return uneven ? k <= 16384 || N == 64 || (k > 40000 && (N < 128 || hint.nnz >= 28 * m)) : k > 40000;
+    const double mean = (double)hint.nnz / (double)m, unevenness = hint.seen_len / mean;
+    if (unevenness > 3.0 || k * 128 > (N % 64 == 0 ? 28 << 20 : 20 << 20)) return false;
+    if ((N == 128 || N == 256 || N == 512) && slices_fit_l2(k, N, 64) && !uneven_rows(m, hint) && k * 256 <= 6 << 20) return false;
+    if (k * 256 > 4 << 20 && (double)k * mean > 1.25e6) return true;
+    const double most = 1.3e6 * std::max(1.0, hint.seen_len / 60.0) * (N % 64 == 0 ? 1.0 : 2.0) * std::max(1.0, (double)k / 16384.0);
+    return unevenness >= 1.4 && (double)m * (double)N <= most;
 }
 
 // Rounding error of a row of n entries that is summed in chunks of c entries, relative to n: every chunk is summed
@@ -430,13 +433,14 @@ int launch_w(Family fam, const Problem& p, const Geometry& geo) {
     // 5000 11.3 -> 9.3, 24 000 62.2 -> 60.9, 27-point stencil of 28^3 28.6 -> 24.2.  4096 columns, N = 256, 4.2 MB: 6.1 and 6.2).
     // Not where many entries lie in rows of uneven length, whose XCDs then wait for each other (50 000 lognormal rows of 60,
     // PR, N = 256: k = 6000 133 and 140, 49 152 331 and 345; 5000 such rows, 12 000: 37 and 20).
-    // Tiles of 32 columns (narrow_tiles_pay): up to 6 MB, and then uneven rows gain, too (lognormal rows of 100, coefficient 0.7: N = 64,
-    // k = 15 000 27.4 -> 24.9, 40 000 70.9 -> 66.6, 61 417 132 and 131, 150 000 449 and 459).
+    // Tiles of 32 columns (narrow_tiles_pay): slices of up to 6 MB and not of a very small B (lognormal rows of 50, coefficient 0.9: N = 64,
+    // k = 5000, 10 000 rows 11.7 -> 10.1, 11 000 15.5 -> 13.2, 44 000 47.2 -> 45.6, 75 000 97 and 95; N = 128, 2500 8.9 and 9.1, 6000 15.5 -> 13.9), uneven
+    // rows too but for eight tiles (rows of 90, coefficient 1, 31 000: N = 64 53.1 -> 49.5, N = 128 90.7 -> 88.5, N = 256 166 and 195).
     const bool narrow = G == 8 && fam == RB_PR;
     const bool slices_fit = V == 4 && (G >= 16 || narrow) && (fam == RB_SR || fam == RB_PR) && p.sd.cb == 1 &&
                             tiles_l * tile_cols - p.N <= tile_cols / 8 &&
-                            (narrow ? tiles_l > 1 && p.k * tile_cols * 4 <= 6 << 20
-                                    : slices_fit_l2(p.k, p.N, tile_cols) && !uneven_rows(p.m, lookup_matrix(p.rowptr, p.m)));
+                            (narrow ? p.k * tile_cols * 4 <= 6 << 20 && (p.k > 3072 || (long)p.k * p.N * 4 > 2 << 20) : slices_fit_l2(p.k, p.N, tile_cols)) &&
+                            !((!narrow || tiles == 8) && uneven_rows(p.m, lookup_matrix(p.rowptr, p.m)));
     const int pin = ((geo.pin < 0 ? slices_fit : geo.pin != 0) && (tiles == 2 || tiles == 4 || tiles == 8)) ? (int)tiles : 0;
     // grid for `bx` blocks per column tile
     auto grid_for = [&](long bx) {
