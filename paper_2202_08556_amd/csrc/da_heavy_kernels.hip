@@ -312,8 +312,9 @@ __global__ __launch_bounds__(kHeavyBlock) void heavy_rows_kernel(
     // The entry at byte offset p + ahead; past the last one of the matrix zeros.  From the row's end on, which is at `end`, any: the one
     // there, which all lanes share, saves bytes (8000 rows of 700, N = 4: 51 -> 41 us, N = 8: 50 -> 39); with four columns a lane the
     // operation costs more on long rows (524 of 20 000 to 100 000, N = 64: 298 -> 305) than it saves.
-    const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(colind), 0, plan.nnz * 4, 0x00027000);
-    const __amdgpu_buffer_rsrc_t numbers = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vals), 0, plan.nnz * 4, 0x00027000);
+    const unsigned bytes = (unsigned)plan.nnz * 4u;        // plans end at 2^30 entries, 32 bits of bytes
+    const __amdgpu_buffer_rsrc_t cols = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(colind), 0, bytes, 0x00027000);
+    const __amdgpu_buffer_rsrc_t numbers = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vals), 0, bytes, 0x00027000);
     auto request = [&](unsigned p, unsigned ahead, unsigned end) {
         Entry e;
         p = (V < 4 ? min(p, end - ahead) : p) + ahead;

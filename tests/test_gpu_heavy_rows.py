@@ -63,7 +63,7 @@ def test_every_width(prepared, N):
     assert any("eb_sr_kernel" in n for n in names) == (65 <= N <= 128), names
 
 
-# rows around a wave's 4 and a block's 64 and 576, groups of rows of other lengths, with ranges of their own
+# rows around sets of 64, groups of rows of other lengths, with ranges of their own
 @pytest.mark.parametrize("heavy", [21, 64, 65, 127, 129, 576, 577, 1030])
 @pytest.mark.parametrize("N", [4, 8, 20, 64, 130])
 def test_groups_of_rows(heavy, N):
@@ -316,10 +316,64 @@ def test_rows_of_b_at_any_alignment(prepared, N, offset, more):
     assert any("heavy_rows_kernel" in n for n in names), names
 
 
-# as many rows as the waves of a block hold, and one more: 504 up to 8 columns, 540 beyond
-@pytest.mark.parametrize("heavy, N", [(504, 8), (505, 8), (540, 16), (541, 64)])
-def test_rows_that_fill_a_block(heavy, N):
-    test_groups_of_rows(heavy, N)
+# Sets of 4 rows a wave: a block has 15 waves that walk rows, 16 where all bring B, and up to nine sets in each.  A launch has at
+# most 17 groups of rows: beyond 17 * 8 * 60 = 8160 rows one of them has nine sets.  8192 are as many as a plan takes.
+@pytest.mark.parametrize("heavy, each, N, order", [
+    (60, 7000, 8, "row"), (61, 7000, 8, "row"), (64, 7000, 3, "row"), (65, 7000, 3, "row"), (540, 2000, 16, "row"), (541, 2000, 64, "row"),
+    (8161, 640, 4, "row"), (8192, 640, 4, "row"), (8161, 3000, 16, "row"), (8161, 3000, 24, "row"), (8192, 3000, 64, "row"),
+    (8161, 640, 130, "row"), (8192, 640, 2, "row"), (8192, 640, 12, "col"),
+])
+def test_rows_that_fill_a_block(heavy, each, N, order):
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    dev, m = "cuda", heavy + 41
+    lens = torch.full((m,), 3, dtype=torch.int64, device=dev)
+    lens[torch.arange(heavy, device=dev) * m // heavy] = each
+    rowptr = torch.zeros(m + 1, dtype=torch.int32, device=dev)
+    torch.cumsum(lens, 0, out=rowptr[1:])
+    row = torch.repeat_interleave(torch.arange(m, device=dev), lens)
+    at = torch.arange(row.numel(), device=dev) - rowptr[row].long()
+    step = (K - 1) // each
+    colind = (at * step + row * 7919 % (K - (each - 1) * step)).to(torch.int32)
+    vals = ((at + row) % 5 - 2).float()
+    B = (torch.arange(K * N, device=dev) * 7919 % 9 - 4).float().view(K, N)
+    a = torch.zeros((m, K), device=dev)
+    a[row, colind.long()] = vals
+    want = a @ B                                              # whole numbers below 2^24: exact in any order
+    da.da_spmm_prepare(m, K, colind.numel(), rowptr, colind)
+    print("heavy", heavy, "each", each, "N", N, order, flush=True)
+    if order == "row":
+        C = torch.full((m, N), float("nan"), device=dev)
+        names = kernels_of(lambda: da.da_spmm(m, K, N, rowptr, colind, vals, B, C, da.DA_EB_RM_SR))
+    else:
+        Bt, Ct = B.t().contiguous(), torch.full((N, m), float("nan"), device=dev)
+        names = kernels_of(lambda: da.da_spmm_ex(m, K, N, rowptr, colind, vals, Bt, K, da.DA_COL_MAJOR, Ct, m, da.DA_COL_MAJOR, da.DA_EB_RM_SR))
+        C = Ct.t()
+    da.da_spmm_release(rowptr)
+    assert any("heavy_rows_kernel" in n for n in names), names
+    assert torch.equal(C, want)
+
+
+# from 2^29 entries on their bytes are more than an int holds; a plan has less than 2^30 entries
+@pytest.mark.parametrize("rows, N", [(513, 8), (513, 64), (1024, 8), (1024, 64)])
+def test_plans_of_very_many_entries(rows, N):
+    from paper_2202_08556_amd import binding as da
+    from tests.gpu_util import kernels_of
+    dev, k = "cuda", 1 << 20
+    nnz = rows * k - 1                                        # every column in every row, but the last one of the last row
+    print("rows", rows, "entries", nnz, "N", N, flush=True)
+    rowptr = (torch.arange(rows + 1, device=dev) * k).clamp(max=nnz).to(torch.int32)
+    colind = torch.arange(k, dtype=torch.int32, device=dev).repeat(rows)
+    vals = torch.arange(rows * k, dtype=torch.int32, device=dev).remainder_(5).sub_(2).float()
+    vals[nnz] = 0.0
+    B = (torch.arange(k * N, device=dev) * 7919 % 9 - 4).float().view(k, N)
+    want = vals.view(rows, k) @ B                             # whole numbers below 2^24: exact in any order
+    da.da_spmm_prepare(rows, k, nnz, rowptr, colind)
+    C = torch.full((rows, N), float("nan"), device=dev)
+    names = kernels_of(lambda: da.da_spmm(rows, k, N, rowptr, colind, vals, B, C, da.DA_EB_RM_SR))
+    da.da_spmm_release(rowptr)
+    assert any("heavy_rows_kernel" in n for n in names), names
+    assert torch.equal(C, want)
 
 
 # a wave of its own brings rows of B of four and more numbers, whatever they are aligned to; all waves bring others
