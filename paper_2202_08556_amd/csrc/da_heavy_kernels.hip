@@ -3,7 +3,7 @@
 // them, but the EB kernels fetch it anew for every stored entry, and that rate, 64 bytes a clock and CU from the
 // vector L1, is what bounds them (33 M entries, N = 64: 460 us).
 //
-// heavy_rows_kernel turns the loops round: a block owns a range of columns and heavy rows of similar length (up to 540).  It
+// heavy_rows_kernel turns the loops round: a block owns a range of columns and heavy rows of similar length (up to 576).  It
 // brings its rows of B into LDS once, a band at a time in two buffers, and walks the stored entries of all its heavy
 // rows that lie in the band, with the rows' sums in registers from the first band to the last; they are added to C
 // atomically once per block.  The same matrix takes 294 us at N = 64, EB 458; 207 and 278 at N = 32, 166 and 228 at N = 16, 115 and 176

@@ -546,8 +546,10 @@ __global__ __launch_bounds__(kBlock) void rb_sr_kernel(
         // The last entries of a row in one block, whose gathers behind the end fetch row 0 and give way to zeros, or exactly, in
         // blocks of 4, 2 and 1, each a round trip that the wave's other rows wait for.  Lanes of one column gain from one block
         // (27-point stencil of 64 x 128 x 128, N = 8 91 -> 87 us, N = 16 145 -> 138; 2 entries a row, 300 000 rows, N = 16 24.1 -> 21.4;
-        // lognormal rows of 10, N = 16 17.2 -> 16.4), but for groups of four (the stencil, N = 4: 86 and 88); four columns a lane lose by
-        // the gathers (the stencil, N = 32: 168 and 172), also where only waves of short rows take it.
+        // lognormal rows of 10, N = 16 17.2 -> 16.4; groups of 32 and 64 little: lognormal rows of 40, N = 17 61.1 -> 59.8, N = 33 90.8 -> 89.8;
+        // rows of 60, N = 24 11.7 -> 11.5; 0.99 to 1.005 elsewhere over 8 matrices and N = 17 ... 130), but for groups of four (the stencil,
+        // N = 4: 86 and 88); four columns a lane lose by the gathers (the stencil, N = 32: 168 and 172), also where only waves of
+        // short rows take it.
         constexpr bool kInOne = V == 1 && G >= 8;
         for (int p0 = start; p0 < end; p0 += SB) {
             next.put(st, j);

@@ -663,10 +663,10 @@ __device__ __forceinline__ unsigned wave_inclusive_max(unsigned v) {
 // spans very many rows without entries searches after all.
 //
 // What bounds a pass: memory (8 bytes in and out per entry) and, close behind, the vector instructions of the ranking;
-// small tiles keep enough waves resident to overlap the two (13 M entries, k = 262 144: 76 and 46 us; with a branch around every
-// vote 79 and 51).  The tiles that an XCD has in hand at a time are
-// neighbours: blocks that stay and take several neighbouring tiles one after another, the next one's entries on their
-// way, took 125 and 80 us instead of 74 and 49, since their runs meet in L2 only when many lines have left it half full.
+// small tiles keep enough waves resident to overlap the two (13 M entries, k = 262 144: 68 and 46 us; with the row
+// pointers behind the ranking 76, with a branch around every vote 79 and 51 before that).  The tiles that an XCD has in hand at a
+// time are neighbours: blocks that stay and take several neighbouring tiles one after another, the next one's entries on their
+// way, took 125 and 80 us where the kernel then took 74 and 49, since their runs meet in L2 only when many lines have left it half full.
 template <int ROUNDS, bool FIRST, bool LAST, int BITS, bool WIDE>
 __global__ __launch_bounds__(kSortBlock) void transpose_scatter_kernel(TransposePass P)
 {
